@@ -1,0 +1,408 @@
+// Float matrix products on the CDNA4 matrix cores (v_mfma_f32_16x16x4_f32: float operands, float sums, 1/16 of the
+// bf16 rate), any shape and alignment.  They carry the float mode.
+//
+//   op 0  C[M,N]  = A[M,K] B[N,K]^T (+R)   A, B k-contiguous
+//   op 1  C[M,N]  = A[M,K] B[K,N]          B k-strided
+//   op 2  C[M,N] += A[K,M]^T B[K,N]        both k-strided; added atomically
+//
+// The instruction's k-slots may stand for any four k, so lane group kg = lane / 16 holds k = 4 kg .. 4 kg + 3 of a
+// group of 16 and four instructions take one element each: a fragment of 16 rows x 16 k of a k-contiguous operand
+// is one 16-byte read.  For ops 0 and 1 the tile of B is the instruction's row operand, so a lane ends with four
+// consecutive output columns of one row (16-byte stores, and whole rotary pairs for the epilogue); for op 2 the
+// tile of A is, so that a wavefront's atomics cover 64 contiguous bytes of four rows.
+//
+// Two kernels:
+//   k_gemm_f32        tiles of 128 x 128 or 64 x 64, four wavefronts, operands staged through LDS (global -> registers
+//                     one step ahead -> the other of two LDS buffers, one barrier per step of 32 k).  The matrix
+//                     instruction needs 32 cycles for 2 x 64 floats of operands, so LDS and memory keep up easily and
+//                     the kernel is bound by the matrix cores.
+//   k_gemm_f32_small  tiles of 32 x 32, eight wavefronts that divide the reduction between them, every wavefront
+//                     reading its fragments straight from memory (no LDS staging, no barrier until the eight partial
+//                     tiles meet): for products too small to fill the chip, where the time is one chain of latencies.
+// Measured against the vector-unit kernel they replaced (64 x 64 tiles, products and sums one lane at a time), us per
+// launch: op 0 3072 x 3072 x 1024 424 -> 191 (101 TFLOP/s of the 157 the cores peak at), op 1 2048 x 1024 x 5632 1109 ->
+// 235, op 2 864 x 288 x 4096 893 -> 30, and of the small ones op 0 128 x 288 x 768 95 -> 9.5, op 1 128 x 288 x 1536
+// 191 -> 14, most others at 8 (the launch).
+#include <algorithm>
+
+#include "devutil.h"
+#include "internal.h"
+
+namespace sp {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+constexpr int BK = 32;
+constexpr int kThreads = 256;
+constexpr int kSmallWaves = 8;   // wavefronts of the small kernel (the reduction is cut into as many shares)
+
+enum { kEpiPlain = 0, kEpiRope = 1, kEpiSwiglu = 2, kEpiSwigluBwd = 3 };   // as in the bf16 kernels
+
+struct Args {
+  const float *A, *B, *R;
+  float *C, *aux;
+  int M, N, K, tiles_m, tiles_n, split_k;   // split_k: k of one share (op 2), a multiple of BK
+  RopeArgs rope;
+};
+
+// element t of a fragment quad; VEC: the four are one aligned 16-byte access and all inside or all outside
+template <bool VEC>
+__device__ __forceinline__ f32x4 load4(const float* p, int valid) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (VEC) {
+    if (valid > 0) v = *reinterpret_cast<const f32x4*>(p);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < valid) v[e] = p[e];
+  }
+  return v;
+}
+
+template <bool VEC>
+__device__ __forceinline__ void store4(float* p, const f32x4& v, int valid) {
+  if (VEC) {
+    if (valid > 0) *reinterpret_cast<f32x4*>(p) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < valid) p[e] = v[e];
+  }
+}
+
+// Memory row of B that belongs at row t of a SwiGLU tile of TN rows made of shares of WN: the first half of a share
+// holds gate rows, the second half the up rows of the same features (h = N / 2 features).  -1: past the end.
+template <int TN, int WN>
+__device__ __forceinline__ int swiglu_row(int tn, int t, int h) {
+  const int w = t / WN, in = t % WN, f = tn * (TN / 2) + w * (WN / 2) + in % (WN / 2);
+  return f < h ? (in < WN / 2 ? f : h + f) : -1;
+}
+
+// Four consecutive output columns n .. n+3 of row m leave for memory (ops 0 and 1).
+template <int OP, int EPI, bool VEC>
+__device__ __forceinline__ void emit(const Args& g, int m, int n, f32x4 v) {
+  const int left = g.N - n;
+  const int64_t at = (int64_t)m * g.N + n;
+  if (EPI == kEpiSwigluBwd) {   // v = d(act); R = gate | up (rows of 2 N), C = d(gate) | d(up)
+    const int64_t a2 = (int64_t)m * 2 * g.N + n;
+    const f32x4 gt = load4<VEC>(g.R + a2, left), up = load4<VEC>(g.R + a2 + g.N, left);
+    f32x4 og, ou;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float sg = 1.0f / (1.0f + expf(-gt[e]));
+      og[e] = v[e] * up[e] * sg * (1.0f + gt[e] * (1.0f - sg));
+      ou[e] = v[e] * gt[e] * sg;
+    }
+    store4<VEC>(g.C + a2, og, left);
+    store4<VEC>(g.C + a2 + g.N, ou, left);
+    return;
+  }
+  if (EPI == kEpiRope) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {   // a pair never straddles the end of the rotated columns: their number is even
+      const int c = n + 2 * p;
+      if (c < g.rope.rot_cols) {
+        const float2 cs = reinterpret_cast<const float2*>(g.rope.table)[(int64_t)(m % g.rope.T) * (g.rope.hd / 2) + (c % g.rope.hd) / 2];
+        const float a = v[2 * p], b = v[2 * p + 1];
+        v[2 * p] = a * cs.x - b * cs.y;
+        v[2 * p + 1] = a * cs.y + b * cs.x;
+      }
+    }
+  }
+  if (OP == 0 && EPI == kEpiPlain && g.R) v += load4<VEC>(g.R + at, left);
+  store4<VEC>(g.C + at, v, left);
+}
+
+// gate and up of four consecutive features f .. f+3 of row m
+template <bool VEC>
+__device__ __forceinline__ void emit_swiglu(const Args& g, int m, int f, const f32x4& gt, const f32x4& up) {
+  const int h = g.N / 2, left = h - f;
+  f32x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = gt[e] / (1.0f + expf(-gt[e])) * up[e];
+  store4<VEC>(g.C + (int64_t)m * g.N + f, gt, left);
+  store4<VEC>(g.C + (int64_t)m * g.N + h + f, up, left);
+  store4<VEC>(g.aux + (int64_t)m * h + f, o, left);
+}
+
+// Ids that land on one XCD (id mod 8) get neighbouring tiles; tiles run down M inside bands of 8 tile columns.
+__device__ __forceinline__ void tile_of(const Args& g, int id, int& tm, int& tn) {
+  constexpr int kBand = 8;
+  const int band = id / (kBand * g.tiles_m), band_w = min(kBand, g.tiles_n - band * kBand), in = id - band * kBand * g.tiles_m;
+  tm = in / band_w;
+  tn = band * kBand + in % band_w;
+}
+__device__ __forceinline__ int xcd_major(int id, int n) {
+  const int per = n / 8, rem = n % 8, x = id % 8;
+  return x * per + min(x, rem) + id / 8;
+}
+
+// One operand's tile of T rows (or columns) x BK: memory -> registers -> LDS -> fragments.  LDS rows are padded by
+// four floats: [T][BK + 4] k-contiguous (16-byte fragment reads of 16 rows fall in different banks), [BK][T + 4]
+// k-strided (the four k rows a read touches start 16 banks apart).
+template <bool KS, int T, bool VEC>
+struct Tile {
+  static constexpr int N4 = T * BK / 4 / kThreads;
+  static constexpr int kFloats = KS ? BK * (T + 4) : T * (BK + 4);
+  f32x4 r[N4];
+  // rows: extent of the tile's own dimension in memory; row_of maps a tile row to a memory row or -1 (k-contiguous)
+  template <class RowOf>
+  __device__ __forceinline__ void load(const float* X, int rows, int ld, int x0, int k0, int kend, int tid, RowOf row_of) {
+#pragma unroll
+    for (int j = 0; j < N4; ++j) {
+      const int i = tid + kThreads * j;
+      if (KS) {
+        const int k = k0 + i / (T / 4), x = x0 + i % (T / 4) * 4;
+        r[j] = load4<VEC>(X + (int64_t)k * ld + x, k < kend ? rows - x : 0);
+      } else {
+        const int row = row_of(i / (BK / 4)), k = k0 + i % (BK / 4) * 4;
+        r[j] = load4<VEC>(X + (int64_t)row * ld + k, row >= 0 ? kend - k : 0);
+      }
+    }
+  }
+  __device__ __forceinline__ void store(float* lds, int tid) const {
+#pragma unroll
+    for (int j = 0; j < N4; ++j) {
+      const int i = tid + kThreads * j;
+      const int at = KS ? i / (T / 4) * (T + 4) + i % (T / 4) * 4 : i / (BK / 4) * (BK + 4) + i % (BK / 4) * 4;
+      *reinterpret_cast<f32x4*>(lds + at) = r[j];
+    }
+  }
+  // rows base .. base+15, k 16 s + 4 kg + {0..3}
+  static __device__ __forceinline__ f32x4 frag(const float* lds, int base, int s, int lr, int kg) {
+    if (!KS) return *reinterpret_cast<const f32x4*>(lds + (base + lr) * (BK + 4) + s * 16 + kg * 4);
+    const float* p = lds + (s * 16 + kg * 4) * (T + 4) + base + lr;
+    return f32x4{p[0], p[T + 4], p[2 * (T + 4)], p[3 * (T + 4)]};
+  }
+};
+
+template <int OP, int EPI, int T, bool VEC>
+__global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
+  constexpr bool AS = OP == 2, BS = OP != 0;
+  typedef Tile<AS, T, VEC> TA;
+  typedef Tile<BS, T, VEC> TB;
+  constexpr int W = T / 2, NB = W / 16;   // a wavefront's share (2 x 2 wavefronts), in blocks of 16 each way
+  __shared__ __attribute__((aligned(16))) float smem[2 * (TA::kFloats + TB::kFloats)];
+  constexpr int kStage = TA::kFloats + TB::kFloats;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const int tiles = g.tiles_m * g.tiles_n, id = xcd_major(blockIdx.x, gridDim.x);
+  int tm, tn;
+  tile_of(g, id % tiles, tm, tn);
+  const int m0 = tm * T, n0 = tn * T;
+  const int kb = id / tiles * g.split_k, kend = min(g.K, kb + g.split_k), steps = (kend - kb + BK - 1) / BK;
+
+  f32x4 acc[NB][NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto a_row = [&](int t) { return m0 + t < g.M ? m0 + t : -1; };
+  auto b_row = [&](int t) {
+    if (EPI == kEpiSwiglu) return swiglu_row<T, W>(tn, t, g.N / 2);
+    return n0 + t < g.N ? n0 + t : -1;
+  };
+  TA ta;
+  TB tb;
+  auto fetch = [&](int s) {
+    ta.load(g.A, g.M, AS ? g.M : g.K, m0, kb + s * BK, kend, tid, a_row);
+    tb.load(g.B, g.N, BS ? g.N : g.K, n0, kb + s * BK, kend, tid, b_row);
+  };
+  auto put = [&](int s) {
+    float* st = smem + (s & 1) * kStage;
+    ta.store(st, tid);
+    tb.store(st + TA::kFloats, tid);
+  };
+  fetch(0);
+  put(0);
+  __syncthreads();
+  for (int s = 0; s < steps; ++s) {
+    if (s + 1 < steps) fetch(s + 1);
+    const float* la = smem + (s & 1) * kStage;
+    const float* lb = la + TA::kFloats;
+#pragma unroll
+    for (int q = 0; q < BK / 16; ++q) {
+      f32x4 fa[NB], fb[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) fa[j] = TA::frag(la, wm * W + j * 16, q, lr, kg);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) fb[i] = TB::frag(lb, wn * W + i * 16, q, lr, kg);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+            acc[j][i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j][e], fb[i][e], acc[j][i], 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_16x16x4f32(fb[i][e], fa[j][e], acc[j][i], 0, 0, 0);
+    }
+    if (s + 1 < steps) put(s + 1);   // into the buffer that every wavefront left before the last barrier
+    __syncthreads();
+  }
+  if (OP == 2) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int n = n0 + wn * W + i * 16 + lr;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + wm * W + j * 16 + kg * 4 + r;
+          if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, acc[j][i][r]);
+        }
+      }
+  } else if (EPI == kEpiSwiglu) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int m = m0 + wm * W + j * 16 + lr;
+      if (m < g.M) {
+#pragma unroll
+        for (int i = 0; i < NB / 2; ++i)
+          emit_swiglu<VEC>(g, m, tn * (T / 2) + wn * (W / 2) + i * 16 + kg * 4, acc[j][i], acc[j][i + NB / 2]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int m = m0 + wm * W + j * 16 + lr;
+      if (m < g.M) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) emit<OP, EPI, VEC>(g, m, n0 + wn * W + i * 16 + kg * 4, acc[j][i]);
+      }
+    }
+  }
+}
+
+template <int OP, int EPI, bool VEC>
+__global__ __launch_bounds__(64 * kSmallWaves) void k_gemm_f32_small(Args g) {
+  constexpr bool AS = OP == 2, BS = OP != 0;
+  constexpr int T = 32, LD = T + 4, U = 3;   // U groups of 16 k per wavefront in flight
+  __shared__ __attribute__((aligned(16))) float part[kSmallWaves][T * LD];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles = g.tiles_m * g.tiles_n, id = xcd_major(blockIdx.x, gridDim.x);
+  int tm, tn;
+  tile_of(g, id % tiles, tm, tn);
+  const int m0 = tm * T, n0 = tn * T;
+  const int kb = id / tiles * g.split_k, kend = min(g.K, kb + g.split_k), groups = (kend - kb + 15) / 16;
+
+  int arow[2], brow[2];   // memory rows (k-contiguous) or columns (k-strided) of this lane's two fragments, -1: none
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int m = m0 + j * 16 + lr, n = n0 + j * 16 + lr;
+    arow[j] = m < g.M ? m : -1;
+    brow[j] = EPI == kEpiSwiglu ? swiglu_row<T, T>(tn, j * 16 + lr, g.N / 2) : (n < g.N ? n : -1);
+  }
+  auto frag_k = [&](const float* X, int row, int ld, int k) { return load4<VEC>(X + (int64_t)row * ld + k, row >= 0 ? kend - k : 0); };
+  auto frag_s = [&](const float* X, int col, int ld, int k) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col >= 0 && k + e < kend) v[e] = X[(int64_t)(k + e) * ld + col];
+    return v;
+  };
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int q0 = wave; q0 < groups; q0 += U * kSmallWaves) {
+    f32x4 fa[U][2], fb[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {   // a group past the end reads nothing and adds zeros
+      const int k = kb + (q0 + u * kSmallWaves) * 16 + kg * 4;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        fa[u][j] = AS ? frag_s(g.A, arow[j], g.M, k) : frag_k(g.A, arow[j], g.K, k);
+        fb[u][j] = BS ? frag_s(g.B, brow[j], g.N, k) : frag_k(g.B, brow[j], g.K, k);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[u][i][e], fa[u][j][e], acc[j][i], 0, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4*>(&part[wave][(j * 16 + lr) * LD + i * 16 + kg * 4]) = acc[j][i];
+  __syncthreads();
+  if (tid >= T * T / 4) return;
+  auto total = [&](int at) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(&part[0][at]);
+#pragma unroll
+    for (int w = 1; w < kSmallWaves; ++w) v += *reinterpret_cast<const f32x4*>(&part[w][at]);
+    return v;
+  };
+  const int m = m0 + tid / (T / 4), nq = tid % (T / 4) * 4;
+  if (m >= g.M) return;
+  const int at = tid / (T / 4) * LD + nq;
+  if (EPI == kEpiSwiglu) {
+    if (nq < T / 2) emit_swiglu<VEC>(g, m, tn * (T / 2) + nq, total(at), total(at + T / 2));
+  } else if (OP == 2) {
+    const f32x4 v = total(at);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n0 + nq + e < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n0 + nq + e, v[e]);
+  } else {
+    emit<OP, EPI, VEC>(g, m, n0 + nq, total(at));
+  }
+}
+
+inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
+}  // namespace
+
+// epi as in gemm_mfma: 0 plain (R optional), 1 rotary, 2 SwiGLU (N = 2h, aux = act), 3 SwiGLU backward (N = h, R =
+// gate|up, C = d(gate)|d(up)).
+void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R,
+              const RopeArgs* rope, int epi, void* aux) {
+  Args g{(const float*)A, (const float*)B, (const float*)R, (float*)C, (float*)aux, (int)M, (int)N, (int)K, 0, 0, 0,
+         rope ? *rope : RopeArgs{nullptr, 1, 2, 0}};
+  if (rope) epi = kEpiRope;
+  const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
+  const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0);
+  auto tiles = [&](int t) {
+    g.tiles_m = (int)((M + t - 1) / t);
+    g.tiles_n = (int)(epi == kEpiSwiglu ? (out + t / 2 - 1) / (t / 2) : (N + t - 1) / t);
+    return (int64_t)g.tiles_m * g.tiles_n;
+  };
+  // Every CU runs its tiles at the rate of its matrix cores, so a product takes as long as the CU with the most
+  // output: ceil(tiles / 256) tiles.  Tiles of 64 divide the work more evenly; tiles of 128 read half as much per flop
+  // and win where both come out alike (measured within 5 % of each other there).
+  const int64_t cus = 256, t128 = tiles(128), t64 = tiles(64);
+  const int64_t load128 = (t128 + cus - 1) / cus * 4, load64 = (t64 + cus - 1) / cus;
+  const int tile = load128 * 100 <= load64 * 105 ? 128 : (t64 >= 128 || (op == 2 && K >= 2048) ? 64 : 32);
+  const int64_t n = tiles(tile);
+  // a weight gradient (few tiles, long reduction) is cut along k until two workgroups per CU are busy
+  int64_t runs = 1;
+  if (op == 2) runs = std::max<int64_t>(1, std::min<int64_t>(512 / n, K / 128));
+  g.split_k = (int)((K + runs - 1) / runs + BK - 1) / BK * BK;
+  if (g.split_k < BK) g.split_k = BK;
+  runs = std::max<int64_t>(1, (K + g.split_k - 1) / g.split_k);
+  const dim3 grid((unsigned)(n * runs));
+#define SP_GO(OP, EPI, VEC)                                                                                             \
+  do {                                                                                                                  \
+    if (tile == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, VEC>), grid, dim3(kThreads), 0, s, g);                \
+    else if (tile == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, VEC>), grid, dim3(kThreads), 0, s, g);             \
+    else hipLaunchKernelGGL((k_gemm_f32_small<OP, EPI, VEC>), grid, dim3(64 * kSmallWaves), 0, s, g);                   \
+  } while (0)
+#define SP_GO_V(OP, EPI) do { if (vec) SP_GO(OP, EPI, true); else SP_GO(OP, EPI, false); } while (0)
+  if (op == 0 && epi == kEpiRope) SP_GO_V(0, kEpiRope);
+  else if (op == 0 && epi == kEpiSwiglu) SP_GO_V(0, kEpiSwiglu);
+  else if (op == 0) SP_GO_V(0, kEpiPlain);
+  else if (op == 1 && epi == kEpiSwigluBwd) SP_GO_V(1, kEpiSwigluBwd);
+  else if (op == 1) SP_GO_V(1, kEpiPlain);
+  else SP_GO_V(2, kEpiPlain);
+#undef SP_GO_V
+#undef SP_GO
+}
+
+}  // namespace sp

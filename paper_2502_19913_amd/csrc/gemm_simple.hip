@@ -1,5 +1,5 @@
-// Plain LDS-tiled matrix product with float accumulation for any shape, stride and element type.
-// It carries the float mode and every shape the MFMA kernels do not take; it is not the fast path.
+// Plain LDS-tiled bf16 matrix product with float accumulation for any shape and alignment, for what the matrix-core
+// kernel (gemm_mfma.hip) does not take; and the dispatch of products and feed-forward steps over the kernels.
 #include "devutil.h"
 #include "internal.h"
 
@@ -10,10 +10,10 @@ namespace {
 constexpr int TM = 64, TN = 64, TK = 16;
 
 // C(m,n) = sum_k A(m,k) * B(k,n), A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn].
-// ACC: C is float and is added to.  Otherwise C is T and R (same shape, may be null) is added.
-template <class T, bool ACC>
-__global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, const T* __restrict__ B, void* Cv,
-                                                     const T* __restrict__ Rr, int64_t M, int64_t N, int64_t K,
+// ACC: C is float and is added to.  Otherwise C is bf16 and R (same shape, may be null) is added.
+template <bool ACC>
+__global__ __launch_bounds__(256) void k_gemm_simple(const bf16* __restrict__ A, const bf16* __restrict__ B, void* Cv,
+                                                     const bf16* __restrict__ Rr, int64_t M, int64_t N, int64_t K,
                                                      int64_t sam, int64_t sak, int64_t sbk, int64_t sbn) {
   __shared__ float As[TK][TM + 1];
   __shared__ float Bs[TK][TN + 1];
@@ -57,37 +57,27 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, co
           float* C = (float*)Cv;
           C[m * N + n] += acc[i][j];
         } else {
-          T* C = (T*)Cv;
+          bf16* C = (bf16*)Cv;
           float v = acc[i][j];
           if (Rr) v += to_float(Rr[m * N + n]);
-          C[m * N + n] = from_float<T>(v);
+          C[m * N + n] = from_float<bf16>(v);
         }
       }
     }
 }
 
-template <class T>
-void launch(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
-            const void* R) {
-  dim3 grid((unsigned)((N + TN - 1) / TN), (unsigned)((M + TM - 1) / TM));
-  if (op == 0)
-    hipLaunchKernelGGL((k_gemm_simple<T, false>), grid, dim3(256), 0, s, (const T*)A, (const T*)B, C, (const T*)R, M,
-                       N, K, K, (int64_t)1, (int64_t)1, K);
-  else if (op == 1)
-    hipLaunchKernelGGL((k_gemm_simple<T, false>), grid, dim3(256), 0, s, (const T*)A, (const T*)B, C, (const T*)nullptr,
-                       M, N, K, K, (int64_t)1, N, (int64_t)1);
-  else
-    hipLaunchKernelGGL((k_gemm_simple<T, true>), grid, dim3(256), 0, s, (const T*)A, (const T*)B, C, (const T*)nullptr,
-                       M, N, K, (int64_t)1, M, N, (int64_t)1);
-}
-
 }  // namespace
 
-void gemm_simple(hipStream_t s, int dtype, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B,
-                 void* C, const void* R) {
+void gemm_simple(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R) {
   if (M <= 0 || N <= 0) return;
-  if (dtype == SP_BF16) launch<bf16>(s, op, M, N, K, A, B, C, R);
-  else launch<float>(s, op, M, N, K, A, B, C, R);
+  dim3 grid((unsigned)((N + TN - 1) / TN), (unsigned)((M + TM - 1) / TM));
+  const bf16 *a = (const bf16*)A, *b = (const bf16*)B, *r = (const bf16*)R;
+  if (op == 0)
+    hipLaunchKernelGGL(k_gemm_simple<false>, grid, dim3(256), 0, s, a, b, C, r, M, N, K, K, (int64_t)1, (int64_t)1, K);
+  else if (op == 1)
+    hipLaunchKernelGGL(k_gemm_simple<false>, grid, dim3(256), 0, s, a, b, C, (const bf16*)nullptr, M, N, K, K, (int64_t)1, N, (int64_t)1);
+  else
+    hipLaunchKernelGGL(k_gemm_simple<true>, grid, dim3(256), 0, s, a, b, C, (const bf16*)nullptr, M, N, K, (int64_t)1, M, N, (int64_t)1);
 }
 
 int gemm(hipStream_t s, int dtype, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
@@ -98,7 +88,8 @@ int gemm(hipStream_t s, int dtype, int op, int64_t M, int64_t N, int64_t K, cons
   const bool fast = dtype == SP_BF16 && gemm_mfma_supported(op, M, N, K, A, B, C, R);
   const int pi = prof_start(fast ? op : PROF_GEMM_PLAIN, s);
   if (fast) gemm_mfma(s, op, M, N, K, A, B, C, R);
-  else gemm_simple(s, dtype, op, M, N, K, A, B, C, R);
+  else if (dtype == SP_F32) gemm_f32(s, op, M, N, K, A, B, C, op == 0 ? R : nullptr, nullptr, 0, nullptr);
+  else gemm_simple(s, op, M, N, K, A, B, C, R);
   prof_stop(pi, s, 2.0 * (double)M * (double)N * (double)K);
   return SP_OK;
 }
@@ -109,6 +100,12 @@ int gemm_rope(hipStream_t s, int dtype, int64_t M, int64_t N, int64_t K, const v
     return fail(SP_EINVAL, "gemm_rope: bad shape");
   if ((M > 0 && N > 0) && (!C || (K > 0 && (!A || !B)))) return fail(SP_EINVAL, "gemm_rope: null operand");
   if (M == 0 || N == 0) return SP_OK;
+  if (dtype == SP_F32 && ra.table) {
+    const int pi = prof_start(PROF_GEMM_PLAIN, s);
+    gemm_f32(s, 0, M, N, K, A, B, C, nullptr, &ra, 0, nullptr);
+    prof_stop(pi, s, 2.0 * (double)M * (double)N * (double)K);
+    return SP_OK;
+  }
   // fused when the matrix-core path takes the product and a 16-byte output chunk never straddles a head
   const bool fast = dtype == SP_BF16 && ra.table && ra.hd % 8 == 0 && gemm_mfma_supported(0, M, N, K, A, B, C, nullptr);
   if (!fast) {
@@ -133,6 +130,12 @@ int ffn_up_fwd(hipStream_t s, int dtype, int64_t R, int64_t h, int64_t d, const 
     prof_stop(pi, s, 4.0 * (double)R * (double)h * (double)d);
     return SP_OK;
   }
+  if (dtype == SP_F32) {
+    const int pi = prof_start(PROF_GEMM_PLAIN, s);
+    gemm_f32(s, 0, R, 2 * h, d, hn, wgu, gu, nullptr, nullptr, 2, act);
+    prof_stop(pi, s, 4.0 * (double)R * (double)h * (double)d);
+    return SP_OK;
+  }
   int rc = gemm(s, dtype, 0, R, 2 * h, d, hn, wgu, gu, nullptr);
   if (rc) return rc;
   swiglu_fwd(s, dtype, gu, R, (int)h, act);
@@ -147,6 +150,12 @@ int ffn_down_bwd(hipStream_t s, int dtype, int64_t R, int64_t h, int64_t d, cons
   if (dtype == SP_BF16 && gemm_swiglu_supported(true, R, h, d, dy, wd, gu, dgu)) {
     const int pi = prof_start(1, s);
     gemm_mfma_swiglu_bwd(s, R, h, d, dy, wd, gu, dgu);
+    prof_stop(pi, s, 2.0 * (double)R * (double)h * (double)d);
+    return SP_OK;
+  }
+  if (dtype == SP_F32) {
+    const int pi = prof_start(PROF_GEMM_PLAIN, s);
+    gemm_f32(s, 1, R, h, d, dy, wd, dgu, gu, nullptr, 3, nullptr);
     prof_stop(pi, s, 2.0 * (double)R * (double)h * (double)d);
     return SP_OK;
   }

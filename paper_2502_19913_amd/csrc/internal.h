@@ -88,8 +88,10 @@ int gemm_rope(hipStream_t s, int dtype, int64_t M, int64_t N, int64_t K, const v
               const RopeArgs& ra, float rope_theta);
 
 // building blocks the dispatchers choose between
-void gemm_simple(hipStream_t s, int dtype, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B,
-                 void* C, const void* R);
+void gemm_simple(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R);
+// float, any shape; rope / epi / aux as for gemm_mfma
+void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R,
+              const RopeArgs* rope, int epi, void* aux);
 bool gemm_mfma_supported(int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, const void* C,
                          const void* R);
 void gemm_mfma(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
