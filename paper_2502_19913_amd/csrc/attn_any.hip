@@ -1,0 +1,456 @@
+// Causal attention for any element type and even head dimension up to 256, on the float matrix instruction
+// (v_mfma_f32_16x16x4_f32): the float mode, and bf16 with head dimensions the bf16 kernels (attn_flash.hip) do not
+// take.  Values are float from LDS on, whatever their storage type.  Also the dispatch over the two families.
+//
+// Same plan as the bf16 kernels: a workgroup of four wavefronts owns 64 queries (16 per wavefront; 64 keys in the
+// dK/dV kernel) of one head and walks the other side in tiles of 32 rows through LDS, two buffers, loaded into
+// registers one tile ahead, one barrier per tile.  Scores are formed transposed, S^T[key][query] = K Q^T, so a lane
+// (query lane % 16) ends with the scores of keys 4 kg .. 4 kg + 3 (kg = lane / 16), and its row statistics are
+// per-lane scalars; the instruction's four k-slots may stand for any keys, so accumulator r of all lanes is directly
+// the operand of the r-th instruction of the next product (O^T += V^T P^T).  The dK/dV kernel is the mirror image.
+//
+// The row-wise operand of a product is one 16-byte LDS read per four instructions, the transposed one a 4-byte read
+// per instruction; LDS rows are padded by 16 bytes, which keeps both free of bank conflicts.  With one LDS read per
+// 32-cycle instruction the kernels are bound by the matrix cores; at short sequences by the latency of the few tiles
+// a workgroup walks.  HD is the head dimension rounded up to a compiled size; columns past the real one are zeros.
+// One wavefront per row of scores (the kernels these replaced) left the matrix cores idle and re-read K and V for
+// every query.  Measured, forward | backward (dQ and dK/dV), us: 6 sequences x 512 x 16 heads of 64 in float 542 -> 90
+// (36 TFLOP/s of the causal half) | 7825 -> 269; 16 x 256 x 6 heads of 48 129 -> 33 | 1522 -> 82; 2 x 64 x 6 heads of 48,
+// where launches are most of it, 8 | 30 -> 18 (the delta pass rides in the dQ kernel).
+//
+// Layout: qkv rows of (H + 2*Hkv)*hd elements = query heads | key heads | value heads; rows are B sequences of T
+// positions; o rows of H*hd; lse[b][a][i] = log sum_j exp(q_i.k_j/sqrt(hd)).
+#include "devutil.h"
+#include "internal.h"
+
+namespace sp {
+
+namespace {
+
+constexpr int kMaxHd = 256;
+constexpr int kThreads = 256;
+constexpr int KT = 32;    // rows of a tile of the walked side
+constexpr int BQ = 64;    // rows a workgroup owns
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+__device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// columns c .. c+3 of a row of hd; vec: every row starts 4-element aligned and hd is a multiple of 4
+__device__ __forceinline__ f32x4 row4(const float* row, int c, int hd, bool vec) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (vec) {
+    if (c < hd) v = *reinterpret_cast<const f32x4*>(row + c);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c + e < hd) v[e] = row[c + e];
+  }
+  return v;
+}
+__device__ __forceinline__ f32x4 row4(const bf16* row, int c, int hd, bool vec) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (vec) {
+    if (c < hd) {
+      const uint2 q = *reinterpret_cast<const uint2*>(row + c);
+      v = f32x4{bf16_bits_to_float(q.x & 0xffffu), bf16_bits_to_float(q.x >> 16), bf16_bits_to_float(q.y & 0xffffu), bf16_bits_to_float(q.y >> 16)};
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c + e < hd) v[e] = (float)row[c + e];
+  }
+  return v;
+}
+template <class T>
+__device__ __forceinline__ void put4(T* row, int c, int hd, bool vec, const f32x4& v) {
+  if (vec) {
+    if (c < hd) {
+      if constexpr (sizeof(T) == 4) *reinterpret_cast<f32x4*>(row + c) = v;
+      else *reinterpret_cast<uint2*>(row + c) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c + e < hd) row[c + e] = from_float<T>(v[e]);
+  }
+}
+// gradient of a rotated vector -> gradient before the rotation, columns c .. c+3 at position pos
+__device__ __forceinline__ void unrotate4(f32x4& v, const float* tab, int pos, int c, int hd) {
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+    if (c + 2 * p < hd) {
+      const float2 cs = reinterpret_cast<const float2*>(tab)[(int64_t)pos * (hd / 2) + c / 2 + p];
+      const float a = v[2 * p], b = v[2 * p + 1];
+      v[2 * p] = a * cs.x + b * cs.y;
+      v[2 * p + 1] = b * cs.x - a * cs.y;
+    }
+}
+// over the four lanes that hold one query's (key's) values
+__device__ __forceinline__ float sum4(float v) { v += __shfl_xor(v, 16); return v + __shfl_xor(v, 32); }
+__device__ __forceinline__ float max4(float v) { v = fmaxf(v, __shfl_xor(v, 16)); return fmaxf(v, __shfl_xor(v, 32)); }
+
+// Two matrices' tiles of KT rows on their way from memory to LDS: [KT][HD + 4] floats each.
+template <class T, int HD>
+struct Pair {
+  static constexpr int LD = HD + 4, N4 = (KT * HD / 4 + kThreads - 1) / kThreads;
+  f32x4 x[N4], y[N4];
+  // rows r0 .. of X (row stride ldx) and Y (ldy); rows at or past `rows` are zeros
+  __device__ __forceinline__ void load(const T* X, int64_t ldx, const T* Y, int64_t ldy, int r0, int rows, int hd, bool vec, int tid) {
+#pragma unroll
+    for (int j = 0; j < N4; ++j) {
+      const int i = tid + kThreads * j, r = r0 + i / (HD / 4), c = i % (HD / 4) * 4;
+      x[j] = y[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (r < rows && i < KT * HD / 4) {
+        x[j] = row4(X + r * ldx, c, hd, vec);
+        y[j] = row4(Y + r * ldy, c, hd, vec);
+      }
+    }
+  }
+  __device__ __forceinline__ void store(float* lx, float* ly, int tid) const {
+#pragma unroll
+    for (int j = 0; j < N4; ++j) {
+      const int i = tid + kThreads * j, at = i / (HD / 4) * LD + i % (HD / 4) * 4;
+      if (i < KT * HD / 4) {
+        *reinterpret_cast<f32x4*>(lx + at) = x[j];
+        *reinterpret_cast<f32x4*>(ly + at) = y[j];
+      }
+    }
+  }
+};
+
+template <class T, int HD>
+__global__ __launch_bounds__(kThreads) void k_attn_fwd(const T* __restrict__ qkv, int T_, int H, int Hkv, int hd, bool vec, float scale,
+                                                       T* __restrict__ o, float* __restrict__ lse) {
+  constexpr int LD = HD + 4, NS = HD / 16;
+  __shared__ __attribute__((aligned(16))) float smem[2][2][KT * LD];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int a = blockIdx.y, b = blockIdx.z, kvh = a / (H / Hkv);
+  const int q0 = (int)(gridDim.x - 1 - blockIdx.x) * BQ;   // the longest blocks of a head first
+  const int qw0 = q0 + wave * 16, q = qw0 + lr;
+  const int64_t ld = (int64_t)(H + 2 * Hkv) * hd;
+  const T* base = qkv + (int64_t)b * T_ * ld;
+  const T *kp = base + (H + kvh) * hd, *vp = base + (H + Hkv + kvh) * hd;
+  f32x4 qf[NS], oacc[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    qf[s] = row4(base + (int64_t)min(q, T_ - 1) * ld + a * hd, s * 16 + kg * 4, hd, vec);
+    oacc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  float m_i = -INFINITY, l_i = 0.f;
+  const int tiles = (min(T_, q0 + BQ) + KT - 1) / KT;
+  Pair<T, HD> in;
+  in.load(kp, ld, vp, ld, 0, T_, hd, vec, tid);
+  in.store(smem[0][0], smem[0][1], tid);
+  __syncthreads();
+  for (int kt = 0; kt < tiles; ++kt) {
+    const int k0 = kt * KT;
+    if (kt + 1 < tiles) in.load(kp, ld, vp, ld, k0 + KT, T_, hd, vec, tid);
+    const float *lk = smem[kt & 1][0], *lv = smem[kt & 1][1];
+    if (k0 <= qw0 + 15) {   // some key of the tile is visible to this wavefront
+      f32x4 st[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const f32x4 f0 = *reinterpret_cast<const f32x4*>(lk + lr * LD + s * 16 + kg * 4);
+        const f32x4 f1 = *reinterpret_cast<const f32x4*>(lk + (16 + lr) * LD + s * 16 + kg * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          st[0] = mfma(f0[e], qf[s][e], st[0]);
+          st[1] = mfma(f1[e], qf[s][e], st[1]);
+        }
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (k0 + t * 16 + kg * 4 + r > q) st[t][r] = -INFINITY;
+          mx = fmaxf(mx, st[t][r]);
+        }
+      const float m_new = fmaxf(m_i, max4(mx) * scale);   // finite from the first tile on: key 0 is visible to all
+      const float alpha = expf(m_i - m_new);
+      float rs = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          st[t][r] = expf(st[t][r] * scale - m_new);
+          rs += st[t][r];
+        }
+      l_i = l_i * alpha + rs;
+      m_i = m_new;
+#pragma unroll
+      for (int c = 0; c < NS; ++c) oacc[c] *= alpha;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float* p = lv + (t * 16 + kg * 4 + e) * LD + lr;
+#pragma unroll
+          for (int c = 0; c < NS; ++c) oacc[c] = mfma(p[c * 16], st[t][e], oacc[c]);
+        }
+    }
+    if (kt + 1 < tiles) in.store(smem[(kt + 1) & 1][0], smem[(kt + 1) & 1][1], tid);
+    __syncthreads();
+  }
+  const float l = sum4(l_i);
+  if (q < T_) {
+    T* row = o + ((int64_t)b * T_ + q) * H * hd + a * hd;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) put4(row, c * 16 + kg * 4, hd, vec, oacc[c] / l);
+    if (kg == 0) lse[((int64_t)b * H + a) * T_ + q] = m_i + logf(l);
+  }
+}
+
+// dq_i = sum_{j<=i} ds_ij k_j,  ds_ij = p_ij (dO_i.v_j - delta_i) / sqrt(hd),  p_ij = exp(s_ij - lse_i), and on the way
+// delta_i = dO_i.o_i for the dK/dV kernel, which runs after this one
+template <class T, int HD>
+__global__ __launch_bounds__(kThreads) void k_attn_bwd_dq(const T* __restrict__ qkv, const T* __restrict__ o, const float* __restrict__ lse,
+                                                          float* __restrict__ delta, const T* __restrict__ dO, int T_, int H, int Hkv,
+                                                          int hd, bool vec, float scale, const float* __restrict__ rope_tab,
+                                                          T* __restrict__ dqkv) {
+  constexpr int LD = HD + 4, NS = HD / 16;
+  __shared__ __attribute__((aligned(16))) float smem[2][2][KT * LD];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int a = blockIdx.y, b = blockIdx.z, kvh = a / (H / Hkv);
+  const int q0 = (int)(gridDim.x - 1 - blockIdx.x) * BQ;
+  const int qw0 = q0 + wave * 16, q = qw0 + lr, qc = min(q, T_ - 1);
+  const int64_t ld = (int64_t)(H + 2 * Hkv) * hd, row = (int64_t)b * T_ + qc, stat = ((int64_t)b * H + a) * T_ + qc;
+  const T* base = qkv + (int64_t)b * T_ * ld;
+  const T *kp = base + (H + kvh) * hd, *vp = base + (H + Hkv + kvh) * hd;
+  f32x4 qf[NS], dof[NS], dq[NS];
+  float dlt = 0.f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int c = s * 16 + kg * 4;
+    qf[s] = row4(base + qc * ld + a * hd, c, hd, vec);
+    dof[s] = row4(dO + row * H * hd + a * hd, c, hd, vec);
+    const f32x4 of = row4(o + row * H * hd + a * hd, c, hd, vec);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dlt += dof[s][e] * of[e];
+    dq[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  dlt = sum4(dlt);
+  if (q < T_ && kg == 0) delta[stat] = dlt;
+  const float L = lse[stat];
+  const int tiles = (min(T_, q0 + BQ) + KT - 1) / KT;
+  Pair<T, HD> in;
+  in.load(kp, ld, vp, ld, 0, T_, hd, vec, tid);
+  in.store(smem[0][0], smem[0][1], tid);
+  __syncthreads();
+  for (int kt = 0; kt < tiles; ++kt) {
+    const int k0 = kt * KT;
+    if (kt + 1 < tiles) in.load(kp, ld, vp, ld, k0 + KT, T_, hd, vec, tid);
+    const float *lk = smem[kt & 1][0], *lv = smem[kt & 1][1];
+    if (k0 <= qw0 + 15) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const int at = (t * 16 + lr) * LD + s * 16 + kg * 4;
+          const f32x4 fk = *reinterpret_cast<const f32x4*>(lk + at), fv = *reinterpret_cast<const f32x4*>(lv + at);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            st = mfma(fk[e], qf[s][e], st);
+            dp = mfma(fv[e], dof[s][e], dp);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float p = k0 + t * 16 + kg * 4 + r > q ? 0.f : expf(st[r] * scale - L);
+          st[r] = p * (dp[r] - dlt) * scale;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float* p = lk + (t * 16 + kg * 4 + e) * LD + lr;
+#pragma unroll
+          for (int c = 0; c < NS; ++c) dq[c] = mfma(p[c * 16], st[e], dq[c]);
+        }
+      }
+    }
+    if (kt + 1 < tiles) in.store(smem[(kt + 1) & 1][0], smem[(kt + 1) & 1][1], tid);
+    __syncthreads();
+  }
+  if (q < T_) {
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      if (rope_tab) unrotate4(dq[c], rope_tab, q, c * 16 + kg * 4, hd);
+      put4(dqkv + row * ld + a * hd, c * 16 + kg * 4, hd, vec, dq[c]);
+    }
+  }
+}
+
+// dk_j = sum_a sum_{i>=j} ds_ij q_i ; dv_j = sum_a sum_{i>=j} p_ij dO_i   (a over the q heads of this kv head)
+template <class T, int HD>
+__global__ __launch_bounds__(kThreads) void k_attn_bwd_dkv(const T* __restrict__ qkv, const float* __restrict__ lse,
+                                                           const float* __restrict__ delta, const T* __restrict__ dO, int T_, int H,
+                                                           int Hkv, int hd, bool vec, float scale, const float* __restrict__ rope_tab,
+                                                           T* __restrict__ dqkv) {
+  constexpr int LD = HD + 4, NS = HD / 16;
+  __shared__ __attribute__((aligned(16))) float smem[2][2][KT * LD];
+  __shared__ __attribute__((aligned(16))) float s_lse[2][KT], s_dlt[2][KT];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kvh = blockIdx.y, b = blockIdx.z, rep = H / Hkv;
+  const int k0 = blockIdx.x * BQ, kw0 = k0 + wave * 16, key = kw0 + lr, kc = min(key, T_ - 1);
+  const int64_t ld = (int64_t)(H + 2 * Hkv) * hd, ldo = (int64_t)H * hd;
+  const T* base = qkv + (int64_t)b * T_ * ld;
+  f32x4 kf[NS], vf[NS], dk[NS], dv[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    kf[s] = row4(base + kc * ld + (H + kvh) * hd, s * 16 + kg * 4, hd, vec);
+    vf[s] = row4(base + kc * ld + (H + Hkv + kvh) * hd, s * 16 + kg * 4, hd, vec);
+    dk[s] = dv[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // the walk: for every query head of this kv head, the query tiles from the workgroup's first key on
+  const int t0 = k0 / KT, nt = (T_ + KT - 1) / KT - t0, steps = nt * rep;
+  Pair<T, HD> in;
+  float in_lse = 0.f, in_dlt = 0.f;
+  auto fetch = [&](int step) {
+    const int a = kvh * rep + step / nt, r0 = (t0 + step % nt) * KT;
+    in.load(base + a * hd, ld, dO + (int64_t)b * T_ * ldo + a * hd, ldo, r0, T_, hd, vec, tid);
+    if (tid < KT && r0 + tid < T_) {
+      const int64_t at = ((int64_t)b * H + a) * T_ + r0 + tid;
+      in_lse = lse[at];
+      in_dlt = delta[at];
+    }
+  };
+  auto put = [&](int step) {
+    in.store(smem[step & 1][0], smem[step & 1][1], tid);
+    if (tid < KT) { s_lse[step & 1][tid] = in_lse; s_dlt[step & 1][tid] = in_dlt; }
+  };
+  fetch(0);
+  put(0);
+  __syncthreads();
+  for (int step = 0; step < steps; ++step) {
+    if (step + 1 < steps) fetch(step + 1);
+    const int qs = (t0 + step % nt) * KT;
+    const float *lq = smem[step & 1][0], *lo = smem[step & 1][1];
+    if (qs + KT - 1 >= kw0) {   // some query of the tile sees a key of this wavefront
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const int at = (t * 16 + lr) * LD + s * 16 + kg * 4;
+          const f32x4 fq = *reinterpret_cast<const f32x4*>(lq + at), fo = *reinterpret_cast<const f32x4*>(lo + at);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            st = mfma(fq[e], kf[s][e], st);
+            dp = mfma(fo[e], vf[s][e], dp);
+          }
+        }
+        const f32x4 L = *reinterpret_cast<const f32x4*>(&s_lse[step & 1][t * 16 + kg * 4]);
+        const f32x4 D = *reinterpret_cast<const f32x4*>(&s_dlt[step & 1][t * 16 + kg * 4]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int q = qs + t * 16 + kg * 4 + r;
+          const float p = q >= key && q < T_ ? expf(st[r] * scale - L[r]) : 0.f;
+          st[r] = p;
+          dp[r] = p * (dp[r] - D[r]) * scale;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int at = (t * 16 + kg * 4 + e) * LD + lr;
+#pragma unroll
+          for (int c = 0; c < NS; ++c) {
+            dv[c] = mfma(lo[at + c * 16], st[e], dv[c]);
+            dk[c] = mfma(lq[at + c * 16], dp[e], dk[c]);
+          }
+        }
+      }
+    }
+    if (step + 1 < steps) put(step + 1);
+    __syncthreads();
+  }
+  if (key < T_) {
+    T* row = dqkv + ((int64_t)b * T_ + key) * ld;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      if (rope_tab) unrotate4(dk[c], rope_tab, key, c * 16 + kg * 4, hd);
+      put4(row + (H + kvh) * hd, c * 16 + kg * 4, hd, vec, dk[c]);
+      put4(row + (H + Hkv + kvh) * hd, c * 16 + kg * 4, hd, vec, dv[c]);
+    }
+  }
+}
+
+// every row and head starts on a four-element boundary
+template <class T>
+bool rows_of_four(int hd, const void* a, const void* b, const void* c, const void* d) {
+  return hd % 4 == 0 && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d) & (4 * sizeof(T) - 1)) == 0;
+}
+
+#define SP_BY_HD(GO)                                                                                        \
+  do {                                                                                                      \
+    if (hd <= 32) GO(32); else if (hd <= 48) GO(48); else if (hd <= 64) GO(64); else if (hd <= 96) GO(96);  \
+    else if (hd <= 128) GO(128); else GO(256);                                                              \
+  } while (0)
+
+template <class T>
+void fwd_t(hipStream_t s, int B, int T_, int H, int Hkv, int hd, const void* qkv, void* o, float* lse) {
+  const bool vec = rows_of_four<T>(hd, qkv, o, nullptr, nullptr);
+  const float scale = 1.0f / sqrtf((float)hd);
+#define SP_GO(HD) hipLaunchKernelGGL((k_attn_fwd<T, HD>), dim3((T_ + BQ - 1) / BQ, H, B), dim3(kThreads), 0, s, (const T*)qkv, T_, H, Hkv, hd, vec, scale, (T*)o, lse)
+  SP_BY_HD(SP_GO);
+#undef SP_GO
+}
+
+template <class T>
+void bwd_t(hipStream_t s, int B, int T_, int H, int Hkv, int hd, const void* qkv, const void* o, const float* lse, const void* dO,
+           void* dqkv, float* delta, const float* rope_tab) {
+  const bool vec = rows_of_four<T>(hd, qkv, o, dO, dqkv);
+  const float scale = 1.0f / sqrtf((float)hd);
+  const int nb = (T_ + BQ - 1) / BQ;
+#define SP_GO(HD)                                                                                                              \
+  do {                                                                                                                         \
+    hipLaunchKernelGGL((k_attn_bwd_dq<T, HD>), dim3(nb, H, B), dim3(kThreads), 0, s, (const T*)qkv, (const T*)o, lse, delta,    \
+                       (const T*)dO, T_, H, Hkv, hd, vec, scale, rope_tab, (T*)dqkv);                                          \
+    hipLaunchKernelGGL((k_attn_bwd_dkv<T, HD>), dim3(nb, Hkv, B), dim3(kThreads), 0, s, (const T*)qkv, lse, delta, (const T*)dO, \
+                       T_, H, Hkv, hd, vec, scale, rope_tab, (T*)dqkv);                                                        \
+  } while (0)
+  SP_BY_HD(SP_GO);
+#undef SP_GO
+}
+
+int check_attn(int B, int T, int H, int Hkv, int hd) {
+  if (B <= 0 || T <= 0 || H <= 0 || Hkv <= 0 || hd <= 0 || H % Hkv) return fail(SP_EINVAL, "attention: bad shape");
+  if (hd > kMaxHd) return fail(SP_EINVAL, "attention: head dimension above 256");
+  if (B > 65535 || H > 65535) return fail(SP_EINVAL, "attention: batch or head count above 65535");
+  return SP_OK;
+}
+
+}  // namespace
+
+int attention_fwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd, const void* qkv, void* o, float* lse) {
+  int rc = check_attn(B, T, H, Hkv, hd);
+  if (rc) return rc;
+  if (!qkv || !o || !lse) return fail(SP_EINVAL, "attention: null operand");
+  const bool fast = dtype == SP_BF16 && attention_flash_supported(B, T, H, Hkv, hd);
+  const int pi = prof_start(fast ? PROF_ATTN_FWD : PROF_ATTN_PLAIN, s);
+  if (fast) attention_flash_fwd(s, B, T, H, Hkv, hd, qkv, o, lse);
+  else if (dtype == SP_BF16) fwd_t<bf16>(s, B, T, H, Hkv, hd, qkv, o, lse);
+  else fwd_t<float>(s, B, T, H, Hkv, hd, qkv, o, lse);
+  prof_stop(pi, s, 2.0 * (double)B * H * (double)T * (T + 1) * hd);   // QK^T and PV over the causal half
+  return SP_OK;
+}
+
+int attention_bwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd, const void* qkv, const void* o,
+                  const float* lse, const void* do_, void* dqkv, float* delta, const float* rope_tab) {
+  int rc = check_attn(B, T, H, Hkv, hd);
+  if (rc) return rc;
+  if (!qkv || !o || !lse || !do_ || !dqkv || !delta) return fail(SP_EINVAL, "attention: null operand");
+  if (dtype == SP_BF16 && attention_flash_supported(B, T, H, Hkv, hd)) {
+    attention_flash_bwd(s, B, T, H, Hkv, hd, qkv, o, lse, do_, dqkv, delta, rope_tab);
+    return SP_OK;
+  }
+  const int pi = prof_start(PROF_ATTN_PLAIN, s);
+  if (dtype == SP_BF16) bwd_t<bf16>(s, B, T, H, Hkv, hd, qkv, o, lse, do_, dqkv, delta, rope_tab);
+  else bwd_t<float>(s, B, T, H, Hkv, hd, qkv, o, lse, do_, dqkv, delta, rope_tab);
+  prof_stop(pi, s, 4.0 * (double)B * H * (double)T * (T + 1) * hd);
+  return SP_OK;
+}
+
+}  // namespace sp

@@ -455,7 +455,7 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
     if ((rc = gemm(s, dt, 1, R, D.d, D.d, dh, P(ctx, params, w.wo), t, nullptr))) return rc;
     if ((rc = wait_done(3, par))) return rc;
     if ((rc = attention_bwd(s, dt, Bg, (int)D.T, (int)D.H, (int)D.Hkv, (int)D.hd, ls.qkv, ls.o, ls.lse, t, dqkv, delta,
-                            ctx->rope_tab, cfg.rope_theta)))
+                            ctx->rope_tab)))
       return rc;
     if ((rc = side_dw(3, par, D.nq, D.d, dqkv, ls.xn, grads + w.wqkv))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, D.nq, dqkv, P(ctx, params, w.wqkv), t, nullptr))) return rc;

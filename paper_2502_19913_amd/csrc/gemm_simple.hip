@@ -111,7 +111,7 @@ int gemm_rope(hipStream_t s, int dtype, int64_t M, int64_t N, int64_t K, const v
   if (!fast) {
     int rc = gemm(s, dtype, 0, M, N, K, A, B, C, nullptr);
     if (rc) return rc;
-    rope(s, dtype, C, M, ra.T, ra.rot_cols / ra.hd, ra.hd, (int)N, rope_theta, +1);
+    rope(s, dtype, C, M, ra.T, ra.rot_cols / ra.hd, ra.hd, (int)N, rope_theta);
     return SP_OK;
   }
   const int pi = prof_start(0, s);

@@ -55,7 +55,7 @@ constexpr int kRmsPartRows = 1024;
 void rmsnorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const void* g, const float* rstd,
                  const void* dres, int64_t R, int d, void* dx, float* dg, float* part = nullptr, int64_t part_floats = 0);
 // rotates the first nheads*hd columns of every row (row_stride elements apart); position = row % T
-void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta, int sign);
+void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta);
 // table[(p * hd/2 + i) * 2 + {0, 1}] = cos, sin of p * theta^(-2i/hd), the angles rope() uses, for p < T
 void rope_table(hipStream_t s, int T, int hd, float theta, float* table);
 // Rotation fused into a producer: the leading rot_cols columns of a row are heads of hd columns whose pairs
@@ -79,10 +79,9 @@ int gemm(hipStream_t s, int dtype, int op, int64_t M, int64_t N, int64_t K, cons
 
 int attention_fwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd, const void* qkv, void* o, float* lse);
 // rope_tab (may be null): if given, q and k in qkv are rotated vectors and dqkv is returned with respect to
-// the vectors before the rotation (theta is only used when the rotation runs as a pass of its own)
+// the vectors before the rotation
 int attention_bwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd, const void* qkv, const void* o,
-                  const float* lse, const void* do_, void* dqkv, float* delta, const float* rope_tab = nullptr,
-                  float rope_theta = 0.f);
+                  const float* lse, const void* do_, void* dqkv, float* delta, const float* rope_tab = nullptr);
 // C = A*B^T with the rotation applied to C on the way out (same result as gemm op 0 followed by rope)
 int gemm_rope(hipStream_t s, int dtype, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
               const RopeArgs& ra, float rope_theta);
@@ -108,10 +107,6 @@ void gemm_mfma_swiglu_bwd(hipStream_t s, int64_t R, int64_t h, int64_t d, const 
 int ffn_up_fwd(hipStream_t s, int dtype, int64_t R, int64_t h, int64_t d, const void* hn, const void* wgu, void* gu, void* act);
 int ffn_down_bwd(hipStream_t s, int dtype, int64_t R, int64_t h, int64_t d, const void* dy, const void* wd, const void* gu,
                  void* dgu, void* da_tmp);
-void attention_simple_fwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd, const void* qkv, void* o,
-                          float* lse);
-void attention_simple_bwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd, const void* qkv,
-                          const void* o, const float* lse, const void* do_, void* dqkv, float* delta);
 bool attention_flash_supported(int B, int T, int H, int Hkv, int hd);
 void attention_flash_fwd(hipStream_t s, int B, int T, int H, int Hkv, int hd, const void* qkv, void* o, float* lse);
 void attention_flash_bwd(hipStream_t s, int B, int T, int H, int Hkv, int hd, const void* qkv, const void* o,

@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_scalar(const T* __restri
 // One thread turns one pair.  pairs_per_row = nheads*hd/2; angle = (row % T) * theta^(-2i/hd).
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_rope(T* __restrict__ qk, int64_t R, int T_, int pairs_per_row, int hd,
-                                                 int row_stride, float log2_theta, float sign) {
+                                                 int row_stride, float log2_theta) {
   const int64_t total = R * pairs_per_row;
   const int half = hd / 2;
   for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * kBlock) {
@@ -382,7 +382,6 @@ __global__ __launch_bounds__(kBlock) void k_rope(T* __restrict__ qk, int64_t R, 
     float inv = exp2f(-(float)(2 * i) / (float)hd * log2_theta);
     float sn, cs;
     sincosf((float)p * inv, &sn, &cs);
-    sn *= sign;
     T* v = qk + r * row_stride + 2 * pr;
     float a = to_float(v[0]), b = to_float(v[1]);
     v[0] = from_float<T>(a * cs - b * sn);
@@ -769,16 +768,15 @@ void rmsnorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const 
   prof_stop(pi, s, (dres ? 4.0 : 3.0) * R * d * elt_size(dtype));   // dy, x (, dres) read, dx written
 }
 
-void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta,
-          int sign) {
+void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta) {
   if (R <= 0) return;
   int pairs = nheads * hd / 2;
   int grid = grid_for_rows(R * pairs, kBlock * 2, 16384);
   float l2 = log2f(theta);
   if (dtype == SP_BF16)
-    hipLaunchKernelGGL(k_rope<bf16>, dim3(grid), dim3(kBlock), 0, s, (bf16*)qk, R, T, pairs, hd, row_stride, l2, (float)sign);
+    hipLaunchKernelGGL(k_rope<bf16>, dim3(grid), dim3(kBlock), 0, s, (bf16*)qk, R, T, pairs, hd, row_stride, l2);
   else
-    hipLaunchKernelGGL(k_rope<float>, dim3(grid), dim3(kBlock), 0, s, (float*)qk, R, T, pairs, hd, row_stride, l2, (float)sign);
+    hipLaunchKernelGGL(k_rope<float>, dim3(grid), dim3(kBlock), 0, s, (float*)qk, R, T, pairs, hd, row_stride, l2);
 }
 
 void rope_table(hipStream_t s, int T, int hd, float theta, float* table) {

@@ -3,9 +3,10 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import skippipe_oracle as orc
 from paper_2502_19913_amd import binding as sp
 from paper_2502_19913_amd import synth
-from tests.gpuharness import maxerr, relerr
+from tests.gpuharness import maxerr, relerr, round_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +42,36 @@ def test_float_products(M, N, K):
         got = c.cpu().numpy()
         assert relerr(got, want) < 2e-5 and maxerr(got, want) < 2e-5, (op, relerr(got, want), maxerr(got, want))
         assert torch.all(buf[M * N:] == 7.0), op
+
+
+ATTENTION = [  # B, T, H, Hkv, hd: every compiled head dimension, at it and below it (zero columns, odd and unaligned
+    # widths); sequences of one row, one tile of 32 short of, at and past a row, one block of 64 likewise, several
+    (1, 1, 1, 1, 2), (2, 31, 2, 1, 32), (1, 33, 3, 3, 10), (2, 64, 2, 2, 48), (1, 65, 4, 2, 40), (1, 129, 2, 1, 64),
+    (2, 63, 2, 2, 80), (1, 130, 6, 2, 96), (1, 97, 2, 1, 128), (1, 66, 2, 2, 113), (1, 100, 2, 1, 200), (1, 70, 2, 2, 256),
+]
+
+
+@pytest.mark.parametrize("B,T,H,Hkv,hd", ATTENTION)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_attention_of_any_head_dimension(B, T, H, Hkv, hd, dtype):
+    # Float: sums of up to hd or T products, exponentials of arguments below 30 in magnitude (relative error about
+    # 30 * 2^-24): 2e-5 leaves a factor of ten.  bf16 storage: one rounding (2^-9) of o, and dO.o formed from that
+    # rounded o; the head dimensions 64 and 128 also round probabilities.  Entries near zero carry their neighbours' errors.
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    rnd = (lambda a: a) if dtype == "f32" else round_bf16
+    nq = (H + 2 * Hkv) * hd
+    qkv = rnd(synth.normal(51, f"q{B}{T}{H}{hd}", (B * T, nq))); do = rnd(synth.normal(52, f"o{B}{T}{H}{hd}", (B * T, H * hd)))
+    part = lambda lo, n: np.ascontiguousarray(qkv[:, lo * hd:(lo + n) * hd]).reshape(B * T, n, hd).astype(np.float64)
+    q, k, v = part(0, H), part(H, Hkv), part(H + Hkv, Hkv)
+    o_ref = orc.attention_fwd(q, k, v, B, T).reshape(B * T, -1)
+    grads = orc.attention_bwd(do.reshape(B * T, H, hd).astype(np.float64), q, k, v, B, T)
+    ref = np.concatenate([g.reshape(B * T, -1) for g in grads], axis=1)
+    x = dev(qkv).to(dt)
+    o = torch.empty((B * T, H * hd), dtype=dt, device="cuda"); lse = torch.empty((B, H, T), device="cuda")
+    sp.attention_fwd(x, o, lse, B, T, H, Hkv, hd)
+    dx = torch.empty_like(x); delta = torch.empty(B * H * T, device="cuda")
+    sp.attention_bwd(x, o, lse, dev(do).to(dt), dx, delta, B, T, H, Hkv, hd)
+    tol, worst = (2e-5, 5e-5) if dtype == "f32" else (2e-2, 4e-2)
+    assert relerr(o.float().cpu().numpy(), o_ref) < tol and maxerr(o.float().cpu().numpy(), o_ref) < worst
+    got = dx.float().cpu().numpy()
+    assert relerr(got, ref) < tol and maxerr(got, ref) < worst, (relerr(got, ref), maxerr(got, ref))
