@@ -1,15 +1,14 @@
-// bf16 matrix products on the CDNA4 matrix cores, float accumulation.  Ops 0 and 1 use
-// v_mfma_f32_16x16x32_bf16, which on random data sustains more flops per watt than the 32x32x16 form (the chip
-// is power-limited here); op 2 keeps v_mfma_f32_32x32x16_bf16, whose accumulator layout gives wider atomics.
+// bf16 matrix products on the CDNA4 matrix cores, float accumulation.  v_mfma_f32_16x16x32_bf16 sustains more flops
+// per watt on random data than the 32x32x16 form (the chip is power-limited here); op 2 in 256-tiles keeps
+// v_mfma_f32_32x32x16_bf16, whose accumulator layout gives wider atomics.
 //
-// One workgroup of 8 wavefronts owns a 256x256 tile of the output (128x128 when the product has too few
-// 256-tiles to occupy the CUs) and walks the reduction dimension in steps of 64.  Operand tiles go from
-// memory straight into LDS (buffer loads with the LDS modifier: no staging registers, no LDS stores; the
+// One workgroup of 8 wavefronts owns a 256x256 tile of the output (k_gemm_mfma), or a 128x128 or 64x64 tile where those
+// occupy the CUs better (k_gemm_ring; choose_shape decides), and walks the reduction dimension in steps of 64.  Operand
+// tiles go from memory straight into LDS (buffer loads with the LDS modifier: no staging registers, no LDS stores; the
 // hardware range check returns zero past the end of an operand, so ragged edges need no branches).  The
-// small tile keeps two stages of A and B, loaded one step ahead, with one barrier per step (two workgroups per
-// CU overlap each other).  The large tile fills the CU's 160 KB of LDS alone (two tiles of A, three of B) and
+// 256-tile fills the CU's 160 KB of LDS alone (two tiles of A, three of B) and
 // runs the alternating-phase loop described where it stands: the two wavefronts of a SIMD take turns between
-// reading fragments and issuing MFMAs, half a step apart.
+// reading fragments and issuing MFMAs, half a step apart.  The small tiles go through a ring of four or five steps.
 //
 // LDS layouts.  A load instruction fills 1 KiB of LDS in lane order, so tiles are unpadded and the
 // 16-byte chunks of a row are permuted by an XOR with bits of the row number (see Operand), which
@@ -37,6 +36,8 @@
 #include "devutil.h"
 #include "internal.h"
 
+#include <type_traits>
+
 namespace sp {
 
 namespace {
@@ -50,20 +51,30 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 constexpr int BK = 64;
 constexpr int kThreads = 512;
-// Geometry of a TILE x TILE output tile (TILE = 256, or 128 for products with few tiles)
+// Geometry of a TILE x TILE output tile: 256 (k_gemm_mfma), 128 or 64 (k_gemm_ring)
 template <int TILE>
 struct Geo {
   static constexpr int kTileBytes = TILE * BK * 2;        // one operand tile, either layout, unpadded
-  static constexpr int kStageBytes = 2 * kTileBytes;      // A and B
+  static constexpr int kStageBytes = 2 * kTileBytes;      // A and B of one step
   static constexpr int kCRowBytes = TILE * 2 + 16;        // output staging row: TILE bf16 + 16 bytes
-  static constexpr int kLdsBytes = TILE * kCRowBytes > 2 * kStageBytes ? TILE * kCRowBytes : 2 * kStageBytes;
   static constexpr int kLdsBytesPP = 5 * kTileBytes;     // alternating-phase loop: two tiles of A, three of B
-  static constexpr int NJ = kTileBytes / 1024 / 8;        // load instructions per wavefront and operand tile
   static constexpr int XCH = TILE / 8;                    // 16-byte chunks per k row of a k-strided tile
-  static constexpr int WM = TILE / 2, WN = TILE / 4;      // a wavefront's share of the tile (2 x 4 wavefronts)
 };
 
 constexpr uint32_t kPastEnd = 0x80000000u;      // no descriptor is this large
+
+// Permutation of a k-strided tile's 16-byte chunks: position p of k row k holds chunk p ^ kkey(k).
+//   16-wide fragments: the 8 k rows x 32 bytes that 32 lanes of a transpose read touch (rows k0 .. k0+3 and
+//     k0+8 .. k0+11) fall in 8 different 32-byte bank groups; two rows of a 64-wide tile fill the banks together, so
+//     there the parity of k separates them already and the key has the other two bits.
+//   32-wide fragments (W32, the 256-tile of the weight-gradient product): the 4 k rows x 4 chunks that 32 lanes
+//     touch fall in 16 different bank groups.
+template <bool W32, int TILE>
+__device__ __forceinline__ int kkey(int k) {
+  if (W32) return (k & 3) << 2;
+  if (TILE == 64) return (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1;
+  return ((k & 3) | (((k >> 3) & 1) << 2)) << 1;
+}
 
 // Byte offset, from the tile's first row (k-contiguous) or first x (k-strided) at the step's first k, of the
 // 16-byte chunk that belongs at position q of the tile in LDS (layouts above); kc8: for k-contiguous tiles, the
@@ -75,59 +86,13 @@ __device__ __forceinline__ uint32_t chunk_offset(int q, int ld, int& kc8, int sp
   constexpr int XCH = Geo<TILE>::XCH;
   if (KSTRIDED) {
     const int krow = q / XCH, pos = q % XCH;
-    const int c = pos ^ (W32 ? (krow & 3) << 2 : ((krow & 3) | (((krow >> 3) & 1) << 2)) << 1);
+    const int c = pos ^ kkey<W32, TILE>(krow);
     return ((uint32_t)krow * ld + c * 8) * 2u;
   }
   const int row = q >> 3, pos = q & 7, c = pos ^ ((row >> 1) & 7);
   kc8 = c * 8;
   return ((uint32_t)(row + (row >= TILE / 2 ? split : 0)) * ld + c * 8) * 2u;
 }
-
-// One operand's share of the tile loads for one wavefront: TILE / 64 instructions of 1 KiB per step.
-// Instruction j fills the tile's 16-byte chunks (8j + wave) * 64 + lane.
-//   k-contiguous tile: [TILE rows][64 k], 8 chunks per row; the chunk at position p of a row holds the row's
-//     chunk p ^ ((row >> 1) & 7): the 16 rows a ds_read_b128 touches then fall in 16 different bank groups.
-//   k-strided tile: [64 k][TILE x], TILE / 8 chunks per k row; position p of k row k holds chunk p ^ kkey(k).
-//     For 16-wide fragments kkey(k) = ((k & 3) | ((k >> 3) & 1) << 2) << 1: the 8 k rows x 32 bytes that 32
-//     lanes of a transpose read touch (rows k0..k0+3 and k0+8..k0+11) fall in 8 different 32-byte bank groups.
-//     For 32-wide fragments (W32, the weight-gradient product) kkey(k) = (k & 3) << 2: the 4 k rows x 4 chunks
-//     that 32 lanes touch fall in 16 different bank groups.
-// The permutation is applied on the memory side: a lane fetches the chunk that belongs at its position.
-template <bool KSTRIDED, bool W32, int TILE>
-struct Operand {
-  static constexpr int NJ = Geo<TILE>::NJ, XCH = Geo<TILE>::XCH;
-  const char* base;    // first byte of the tile's rows (k-contiguous) or of its first x (k-strided), at k = 0
-  int64_t left;        // bytes from base to the end of the operand
-  uint32_t voff[NJ];   // byte offset of the lane's chunk from base, per instruction
-  uint32_t k_step;     // byte distance of one k element
-  int kc8;             // k-contiguous: first k of the lane's chunk inside a step
-  // rows x ld elements in memory; origin: first tile row (k-contiguous) or first x (k-strided).
-  // Offsets stay below 2^31 for ld < 2^21 (checked by the caller); the operand itself may be larger.
-  __device__ __forceinline__ void init(const bf16* X, int64_t rows, int ld, int origin, int wave, int lane, int split = 0) {
-    const int64_t first = KSTRIDED ? (int64_t)origin : (int64_t)origin * ld;
-    base = reinterpret_cast<const char*>(X + first);
-    left = (rows * ld - first) * 2;
-    kc8 = 0;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int q = (8 * j + wave) * 64 + lane;
-      voff[j] = chunk_offset<KSTRIDED, W32, TILE>(q, ld, kc8, split);   // kc8: the same for every j (lane and wave & 1 only)
-    }
-    k_step = KSTRIDED ? (uint32_t)ld * 2u : 2u;
-  }
-  // The step's descriptor starts at the step's first k, so offsets never grow with the operand; its size
-  // is what is left of the operand, capped below kPastEnd.
-  // KMASK (k-contiguous only): chunks whose k is at or past kend read as zero
-  template <bool KMASK>
-  __device__ __forceinline__ void load(int k0, int kend, char* tile, int wave) const {
-    const bool dead = KMASK && !KSTRIDED && (k0 + kc8 >= kend);
-    const int64_t skip = (int64_t)k0 * k_step;
-    const int64_t rest = left - skip;
-    const u32x4 desc = make_desc(base + skip, (uint32_t)(rest < 0 ? 0 : (rest > 0x7fffffff ? 0x7fffffff : rest)));
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) load_to_lds16(desc, (lds_ptr)(tile + (8 * j + wave) * 1024), dead ? kPastEnd : voff[j]);
-  }
-};
 
 // The loads of one wavefront when a workgroup's halves divide the operands between them (the alternating-phase
 // loop): wavefronts 0-3 load the tiles of A, wavefronts 4-7 those of B, so a wavefront issues a quarter of one
@@ -151,14 +116,21 @@ struct HalfLoader {
     base = reinterpret_cast<const char*>(X + first);
     left = (rows * ld - first) * 2;
     kc8 = 0;
+    // two instructions further on: 64 rows (k-contiguous) or 16 k rows (k-strided) on, under the same permutation
+    const uint32_t two_on = (uint32_t)ld * (strided ? 16 * 2u : 64 * 2u);
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int q = (4 * j + w4) * 64 + lane;
-      int kc_a = 0, kc_b = 0;
-      const uint32_t oa = chunk_offset<AS, W32, TILE>(q, ld, kc_a);
-      const uint32_t ob = (AS == BS && b_split == 0) ? oa : chunk_offset<BS, W32, TILE>(q, ld, kc_b, b_split);
-      voff[j] = late ? ob : oa;
-      kc8 = late ? ((AS == BS && b_split == 0) ? kc_a : kc_b) : kc_a;
+      if (j < 2) {
+        const int q = (4 * j + w4) * 64 + lane;
+        int kc_a = 0, kc_b = 0;
+        const uint32_t oa = chunk_offset<AS, W32, TILE>(q, ld, kc_a);
+        const uint32_t ob = AS == BS ? oa : chunk_offset<BS, W32, TILE>(q, ld, kc_b);
+        voff[j] = late ? ob : oa;
+        kc8 = late && AS != BS ? kc_b : kc_a;
+      } else {
+        voff[j] = voff[j - 2] + two_on;
+        if (!BS && j / 2 == NJ / 4 && late) voff[j] += (uint32_t)b_split * ld * 2u;   // second half of the rows
+      }
     }
     k_step = strided ? (uint32_t)ld * 2u : 2u;
   }
@@ -186,9 +158,9 @@ __device__ __forceinline__ bf16x8 read_frag(const char* tile, int row_base, int 
   } else {
     // Two transpose reads.  Within a group of 16 lanes, lane s addresses k row s/4 and the 8-byte piece s%4 of
     // the group's 32 bytes (16 x), and receives x = s, 4 consecutive k.  Group g = lane/16 takes k rows
-    // 8g .. 8g+3, then 8g+4 .. 8g+7; both have the same kkey: (s/4) | (g & 1) << 2, shifted left by one.
+    // 8g .. 8g+3, then 8g+4 .. 8g+7; both have the same kkey.
     const int g = lane >> 4, s = lane & 15;
-    const int key = ((s >> 2) | ((g & 1) << 2)) << 1;
+    const int key = TILE == 64 ? kkey<false, TILE>((s >> 2) + (g & 1) * 8) : ((s >> 2) | ((g & 1) << 2)) << 1;
     const int lane_off = (g * 8 + (s >> 2)) * KR + (key << 4) + (((s & 3) >> 1) << 4) + (s & 1) * 8;
     const char* p = tile + k32 * 32 * KR + (lane_off ^ (row_base * 2));   // row_base * 2: a multiple of 32 bytes
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -236,26 +208,119 @@ __device__ __forceinline__ bf16x8 read_frag32(const char* tile, int row_base, in
 //                  d(gate) | d(up); d(act) itself is not stored
 enum { kEpiPlain = 0, kEpiRope = 1, kEpiSwiglu = 2, kEpiSwigluBwd = 3 };
 
-template <int OP, bool KMASK, int EPI, int TILE, bool PP = false>
+// A finished bf16 tile from its LDS staging area ([TILE][TILE], rows of kCRowBytes) to memory; all 512 threads.
+// m0, n0: the tile's first output row and column; the rest as in k_gemm_mfma.
+template <int OP, int EPI, int TILE>
+__device__ __forceinline__ void store_tile(const char* smem, bf16* C, const bf16* Rr, bf16* aux, const RopeArgs& rope, int M, int N,
+                                           int m0, int n0, int tid) {
+  constexpr bool ROPE = EPI == kEpiRope;
+  constexpr int kCRowBytes = Geo<TILE>::kCRowBytes;
+  const int hN = N / 2;
+  asm volatile("" : "+v"(tid));   // keeps what follows from tid out of the registers of the loop over tiles (30 spills)
+  const bool add = OP == 0 && Rr != nullptr;
+  if (EPI == kEpiSwiglu) {
+    // chunk nc < TILE/16 of a staged row is 8 gate values, chunk nc + TILE/16 the up values of the same features
+#pragma unroll 4
+    for (int c = tid; c < TILE * TILE / 16; c += kThreads) {
+      const int row = c / (TILE / 16), nc = c % (TILE / 16);
+      const int grow = m0 + row, gcol = n0 + nc * 8;
+      if (grow < M) {
+        const uint4 vg = *reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16);
+        const uint4 vu = *reinterpret_cast<const uint4*>(smem + row * kCRowBytes + (nc + TILE / 16) * 16);
+        float g[8], u[8], o[8];
+        unpack8(vg, g);
+        unpack8(vu, u);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
+        store16_stream(C + (int64_t)grow * N + gcol, vg);
+        store16_stream(C + (int64_t)grow * N + hN + gcol, vu);
+        store8_stream(aux + (int64_t)grow * hN + gcol, o);
+      }
+    }
+  } else if (EPI == kEpiSwigluBwd) {
+#pragma unroll 4
+    for (int it = 0; it < TILE * TILE / 8 / kThreads; ++it) {
+      const int c = tid + kThreads * it;
+      const int row = c / (TILE / 8), nc = c % (TILE / 8);
+      const int grow = m0 + row, gcol = n0 + nc * 8;
+      if (grow < M && gcol < N) {
+        float d[8], g[8], u[8], og[8], ou[8];
+        unpack8(*reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16), d);
+        const int64_t at = (int64_t)grow * 2 * N + gcol;
+        load8(Rr + at, g);
+        load8(Rr + at + N, u);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float sg = 1.0f / (1.0f + expf(-g[e]));
+          og[e] = d[e] * u[e] * sg * (1.0f + g[e] * (1.0f - sg));
+          ou[e] = d[e] * g[e] * sg;
+        }
+        store8_stream(C + at, og);
+        store8_stream(C + at + N, ou);
+      }
+    }
+  } else
+#pragma unroll 4
+  for (int it = 0; it < TILE * TILE / 8 / kThreads; ++it) {
+    const int c = tid + kThreads * it;
+    const int row = c / (TILE / 8), nc = c % (TILE / 8);
+    const int grow = m0 + row, gcol = n0 + nc * 8;
+    if (grow < M && gcol < N) {   // N is a multiple of 8: a chunk is inside or outside as a whole
+      uint4 v = *reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16);
+      const int64_t at = (int64_t)grow * N + gcol;
+      if (ROPE && gcol < rope.rot_cols) {
+        // 8 columns = 4 pairs of one head (hd is a multiple of 8); their cos, sin are 32 contiguous bytes
+        float x[8];
+        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[2 * e] = bf16_bits_to_float(wv[e] & 0xffffu); x[2 * e + 1] = bf16_bits_to_float(wv[e] >> 16); }
+        const float4* cs = reinterpret_cast<const float4*>(rope.table) + ((int64_t)(grow % rope.T) * (rope.hd / 2) + (gcol % rope.hd) / 2) / 2;
+        const float4 c01 = cs[0], c23 = cs[1];
+        const float c[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = x[2 * e], b = x[2 * e + 1];
+          x[2 * e] = a * c[e] - b * sn[e];
+          x[2 * e + 1] = a * sn[e] + b * c[e];
+        }
+        store8_stream(C + at, x);
+      } else if (add) {
+        // the sum is formed in float from the accumulator's bf16 rounding; one more rounding on the way out
+        float x[8], y[8];
+        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[2 * e] = bf16_bits_to_float(wv[e] & 0xffffu); x[2 * e + 1] = bf16_bits_to_float(wv[e] >> 16); }
+        load8(Rr + at, y);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] += y[e];
+        store8_stream(C + at, x);
+      } else {
+        store16_stream(C + at, v);
+      }
+    }
+  }
+}
+
+template <int OP, bool KMASK, int EPI>
 __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__ A, const bf16* __restrict__ B,
                                                         void* __restrict__ Cv, const bf16* __restrict__ Rr, int M,
                                                         int N, int K, int tiles_m, int tiles_n, RopeArgs rope,
                                                         bf16* __restrict__ aux) {
-  constexpr bool ROPE = EPI == kEpiRope;
+  constexpr int TILE = 256;
   static_assert(EPI == kEpiPlain || (EPI == kEpiSwigluBwd ? OP == 1 : OP == 0), "epilogue and product do not match");
   constexpr bool AS = OP == 2, BS = OP != 0;   // which operands are k-strided
   typedef Geo<TILE> G;
-  constexpr int kTileBytes = G::kTileBytes, kStageBytes = G::kStageBytes, kCRowBytes = G::kCRowBytes;
-  constexpr int WM = G::WM, WN = G::WN, BM = TILE, BN = TILE;
-  __shared__ __attribute__((aligned(1024))) char smem[PP ? G::kLdsBytesPP : G::kLdsBytes];
+  constexpr int kTileBytes = G::kTileBytes, kCRowBytes = G::kCRowBytes;
+  constexpr int WM = TILE / 2, WN = TILE / 4, BM = TILE, BN = TILE;   // a wavefront's share: 2 x 4 wavefronts
+  __shared__ __attribute__((aligned(1024))) char smem[G::kLdsBytesPP];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
 
-  // ---- the work of this workgroup: a sequence of pieces, each a range of k-steps of one output tile.
+  // ---- the work of this workgroup: tiles of the output, or a range of the k-steps of one.
   // OP 0/1: whole tiles id, id + gridDim.x, ...: the launch has as many workgroups as make its rounds of
-  // tiles equally full.  OP 2: the k-steps of all tiles form one sequence (tile-major), cut into gridDim.x
-  // equal runs (normally a whole number of runs per tile); every piece is added to the output atomically.
+  // tiles equally full.  OP 2: one of gridDim.x / tiles equal runs of the k-steps of one tile, added to the output
+  // atomically.
   // Ids that share an XCD (id mod 8) get consecutive tiles (runs); tiles run down M first inside bands
   // of 8 tile columns so that neighbours share B panels and reuse A panels.
   const int tiles = tiles_m * tiles_n;
@@ -269,12 +334,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
   // contiguous range) work on neighbouring tiles over the same k range and share their operand panels
   const int s_runs = OP == 2 ? (int)gridDim.x / tiles : 1;
   const int run = OP == 2 ? id / tiles : 0;
-  int64_t u = OP == 2 ? (int64_t)(id % tiles) * ksteps + (int64_t)run * ksteps / s_runs : (int64_t)id * ksteps;
-  const int64_t u_end = OP == 2 ? (int64_t)(id % tiles) * ksteps + (int64_t)(run + 1) * ksteps / s_runs : (int64_t)tiles * ksteps;
-  while (u < u_end) {
-  const int tile = (int)(u / ksteps), ks0 = (int)(u - (int64_t)tile * ksteps);
-  const int ks1 = OP == 2 ? (int)min((int64_t)ksteps, ks0 + (u_end - u)) : ksteps;
-  u += OP == 2 ? (int64_t)(ks1 - ks0) : (int64_t)gridDim.x * ksteps;
+  const int ks0 = OP == 2 ? (int)((int64_t)run * ksteps / s_runs) : 0;
+  const int ks1 = OP == 2 ? (int)((int64_t)(run + 1) * ksteps / s_runs) : ksteps;
+  for (int tile = OP == 2 ? id % tiles : id; tile < tiles; tile += OP == 2 ? tiles : (int)gridDim.x) {
   constexpr int kBand = 8;
   const int band = tile / (kBand * tiles_m);
   const int band_w = min(kBand, tiles_n - band * kBand);
@@ -288,10 +350,6 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
   const int nk = ks1 - ks0;
 
   constexpr bool W32 = OP == 2;   // which MFMA form (see read_frag32)
-  Operand<AS, W32, TILE> opa;
-  Operand<BS, W32, TILE> opb;
-  opa.init(A, AS ? K : M, AS ? M : K, m0, wave, lane);
-  opb.init(B, BS ? K : N, BS ? N : K, n0, wave, lane, b_split);
 
   // OP 0/1: acc[j][i] = 16 output rows m x 16 output columns n of the wavefront's WM x WN share.
   // OP 2: acc32[j][i] = 32 rows x 32 columns of it.
@@ -314,62 +372,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
         for (int r = 0; r < 4; ++r) acc[W32 ? 0 : j][W32 ? 0 : i][r] = 0.f;
   }
 
-  auto compute = [&](const char* base) {
-    const char* ta = base;
-    const char* tb = base + kTileBytes;
-    if (W32) {
-#pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks) {
-        bf16x8 fa[NJ32], fb[NI32];
-#pragma unroll
-        for (int j = 0; j < NJ32; ++j) fa[j] = read_frag32<AS, TILE>(ta, wm * WM + j * 32, ks, lane);
-#pragma unroll
-        for (int i = 0; i < NI32; ++i) fb[i] = read_frag32<BS, TILE>(tb, wn * WN + i * 32, ks, lane);
-#pragma unroll
-        for (int j = 0; j < NJ32; ++j)
-#pragma unroll
-          for (int i = 0; i < NI32; ++i)
-            acc32[W32 ? j : 0][W32 ? i : 0] =
-                __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[j], fb[i], acc32[W32 ? j : 0][W32 ? i : 0], 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int k32 = 0; k32 < BK / 32; ++k32) {
-        bf16x8 fa[NJ16], fb[NI16];
-#pragma unroll
-        for (int j = 0; j < NJ16; ++j) fa[j] = read_frag<AS, TILE>(ta, wm * WM + j * 16, k32, lane);
-#pragma unroll
-        for (int i = 0; i < NI16; ++i) fb[i] = read_frag<BS, TILE>(tb, wn * WN + i * 16, k32, lane);
-#pragma unroll
-        for (int j = 0; j < NJ16; ++j)
-#pragma unroll
-          for (int i = 0; i < NI16; ++i)
-            acc[W32 ? 0 : j][W32 ? 0 : i] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[i], fa[j], acc[W32 ? 0 : j][W32 ? 0 : i], 0, 0, 0);
-      }
-    }
-  };
-  // step t of the reduction goes to stage t & 1
-  auto issue = [&](int t) {
-    char* st = smem + (t & 1) * kStageBytes;
-    opa.template load<KMASK>(kb + t * BK, kend, st, wave);
-    opb.template load<KMASK>(kb + t * BK, kend, st + kTileBytes, wave);
-  };
-  // this wavefront's loads have landed and its LDS reads are done; then the same for the others
-  auto landed_barrier = [&]() {
-    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8));   // vmcnt(0) lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-  };
-
-  if (!PP) {
-    issue(0);
-    landed_barrier();
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 1 < nk) issue(kt + 1);   // into the stage every wavefront left before the last barrier
-      compute(smem + (kt & 1) * kStageBytes);
-      landed_barrier();
-    }
-  } else {
+  {
     // Two wavefronts share a SIMD (w and w + 4).  They alternate between a memory phase (all fragments of one
     // k-step from LDS into registers, loads of a later step issued) and a compute phase (the step's MFMAs, back
     // to back from registers), half a step apart, so that a SIMD's matrix core always has one wavefront
@@ -384,7 +387,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
     char* const a_ring = smem;                       // 2 tiles
     char* const b_ring = smem + 2 * kTileBytes;      // 3 tiles
     HalfLoader<AS, BS, W32, TILE> mine;
-    mine.init(late, A, AS ? K : M, AS ? M : K, m0, B, BS ? K : N, BS ? N : K, n0, w4, lane, b_split);
+    int at = lane;
+    asm volatile("" : "+v"(at));   // as in store_tile
+    mine.init(late, A, AS ? K : M, AS ? M : K, m0, B, BS ? K : N, BS ? N : K, n0, w4, at, b_split);
     auto issue_a = [&](int t) { mine.template load<KMASK>(kb + t * BK, kend, a_ring + (t & 1) * kTileBytes, w4); };
     auto issue_b = [&](int t, int slot) { mine.template load<KMASK>(kb + t * BK, kend, b_ring + slot * kTileBytes, w4); };
     if (!late) issue_a(0);
@@ -490,93 +495,227 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
         *reinterpret_cast<uint2*>(smem + (wm * WM + j * 16 + lm) * kCRowBytes + (wn * WN + i * 16 + kg * 4) * 2) = w;
       }
     __syncthreads();
-    bf16* C = reinterpret_cast<bf16*>(Cv);
-    const bool add = OP == 0 && Rr != nullptr;
-    if (EPI == kEpiSwiglu) {
-      // chunk nc < TILE/16 of a staged row is 8 gate values, chunk nc + TILE/16 the up values of the same features
-#pragma unroll 4
-      for (int it = 0; it < TILE * TILE / 16 / kThreads; ++it) {
-        const int c = tid + kThreads * it;
-        const int row = c / (TILE / 16), nc = c % (TILE / 16);
-        const int grow = m0 + row, gcol = n0 + nc * 8;
-        if (grow < M) {
-          const uint4 vg = *reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16);
-          const uint4 vu = *reinterpret_cast<const uint4*>(smem + row * kCRowBytes + (nc + TILE / 16) * 16);
-          float g[8], u[8], o[8];
-          unpack8(vg, g);
-          unpack8(vu, u);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
-          store16_stream(C + (int64_t)grow * N + gcol, vg);
-          store16_stream(C + (int64_t)grow * N + hN + gcol, vu);
-          store8_stream(aux + (int64_t)grow * hN + gcol, o);
-        }
-      }
-    } else if (EPI == kEpiSwigluBwd) {
-#pragma unroll 4
-      for (int it = 0; it < TILE * TILE / 8 / kThreads; ++it) {
-        const int c = tid + kThreads * it;
-        const int row = c / (TILE / 8), nc = c % (TILE / 8);
-        const int grow = m0 + row, gcol = n0 + nc * 8;
-        if (grow < M && gcol < N) {
-          float d[8], g[8], u[8], og[8], ou[8];
-          unpack8(*reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16), d);
-          const int64_t at = (int64_t)grow * 2 * N + gcol;
-          load8(Rr + at, g);
-          load8(Rr + at + N, u);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float sg = 1.0f / (1.0f + expf(-g[e]));
-            og[e] = d[e] * u[e] * sg * (1.0f + g[e] * (1.0f - sg));
-            ou[e] = d[e] * g[e] * sg;
-          }
-          store8_stream(C + at, og);
-          store8_stream(C + at + N, ou);
-        }
-      }
-    } else
-#pragma unroll 4
-    for (int it = 0; it < TILE * TILE / 8 / kThreads; ++it) {
-      const int c = tid + kThreads * it;
-      const int row = c / (TILE / 8), nc = c % (TILE / 8);
-      const int grow = m0 + row, gcol = n0 + nc * 8;
-      if (grow < M && gcol < N) {   // N is a multiple of 8: a chunk is inside or outside as a whole
-        uint4 v = *reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16);
-        const int64_t at = (int64_t)grow * N + gcol;
-        if (ROPE && gcol < rope.rot_cols) {
-          // 8 columns = 4 pairs of one head (hd is a multiple of 8); their cos, sin are 32 contiguous bytes
-          float x[8];
-          const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { x[2 * e] = bf16_bits_to_float(wv[e] & 0xffffu); x[2 * e + 1] = bf16_bits_to_float(wv[e] >> 16); }
-          const float4* cs = reinterpret_cast<const float4*>(rope.table) + ((int64_t)(grow % rope.T) * (rope.hd / 2) + (gcol % rope.hd) / 2) / 2;
-          const float4 c01 = cs[0], c23 = cs[1];
-          const float c[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float a = x[2 * e], b = x[2 * e + 1];
-            x[2 * e] = a * c[e] - b * sn[e];
-            x[2 * e + 1] = a * sn[e] + b * c[e];
-          }
-          store8_stream(C + at, x);
-        } else if (add) {
-          // the sum is formed in float from the accumulator's bf16 rounding; one more rounding on the way out
-          float x[8], y[8];
-          const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { x[2 * e] = bf16_bits_to_float(wv[e] & 0xffffu); x[2 * e + 1] = bf16_bits_to_float(wv[e] >> 16); }
-          load8(Rr + at, y);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] += y[e];
-          store8_stream(C + at, x);
-        } else {
-          store16_stream(C + at, v);
-        }
-      }
-    }
-    __syncthreads();   // the staging area becomes the next piece's operand stages
+    store_tile<OP, EPI, TILE>(smem, reinterpret_cast<bf16*>(Cv), Rr, aux, rope, M, N, m0, n0, tid);
+    __syncthreads();   // the staging area becomes the next tile's operand ring
   }
-  }  // next piece
+  }  // next tile
+}
+
+// ---- tiles of 128 or 64 for products that leave the chip partly idle in 256-tiles (a single microbatch, narrow
+// layers, the weight gradient of a small matrix).
+//
+// One workgroup per CU is then the rule, so nothing but its own loads in flight hides the memory's latency: operand
+// tiles go through a ring of S steps in LDS, a slot is loaded again as soon as its fragments are in registers, S - 1
+// steps before it is waited for, and the fragments of step t + 1 are read while the MFMAs of step t run.  One
+// barrier per step.  The eight wavefronts are a 2 x 2 grid over the tile twice: wavefronts 0-3 take the first 32 k of
+// every step, 4-7 the other 32 (a wavefront's share is as square as the tile, so LDS reads stay level with the MFMAs:
+// 64 KB against 512 matrix cycles a step at TILE = 128), and the two halves' accumulators meet in LDS at the end.
+// A step of a 128-tile takes 0.5 us; 0.36 with the loads delivering zeros (LDS: 96 KB a step at 128 bytes a cycle), the
+// rest is the way from the L2s.  Against the two-slot loop of 128-tiles with one wait per step that stood here before:
+// NT 4096 x 1024 x 2816 34 -> 25 us, NN 1777 x 2048 x 11264 127 -> 96 us; TN (256-tiles before) 1024 x 1024 x 4096
+// 37 -> 25 us, 288 x 768 x 999 19 -> 9 us.
+template <int TILE>
+struct RingGeo {
+  static constexpr int S = TILE == 128 ? 4 : 5;            // 128 KB; 80 KB, so that two workgroups of 64-tiles share a CU
+  static constexpr int kLdsBytes = S * Geo<TILE>::kStageBytes;
+  static constexpr int NL = Geo<TILE>::kTileBytes / 1024 / 8;   // load instructions per wavefront and operand tile
+  static constexpr int W = TILE / 2, NF = W / 16;          // a wavefront's share of the tile: NF x NF blocks of 16 x 16
+  static constexpr int kRowFloats = TILE + 4;              // float staging row (weight gradients)
+};
+
+// One operand's share of the loads of one wavefront: instruction j fills chunks (8 j + wave) * 64 + lane of the tile.
+template <bool KSTRIDED, int TILE>
+struct RingOperand {
+  static constexpr int NL = RingGeo<TILE>::NL;
+  const char* base;    // first byte of the tile's rows (k-contiguous) or of its first x (k-strided), at k = 0
+  int64_t left;        // bytes from base to the end of the operand
+  uint32_t voff[NL];
+  uint32_t k_step;     // byte distance of one k element
+  int kc8;             // k-contiguous: first k of the lane's chunk inside a step
+  __device__ __forceinline__ void init(const bf16* X, int64_t rows, int ld, int origin, int wave, int lane, int split = 0) {
+    const int64_t first = KSTRIDED ? (int64_t)origin : (int64_t)origin * ld;
+    base = reinterpret_cast<const char*>(X + first);
+    left = (rows * ld - first) * 2;
+    kc8 = 0;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) voff[j] = chunk_offset<KSTRIDED, false, TILE>((8 * j + wave) * 64 + lane, ld, kc8, split);
+    k_step = KSTRIDED ? (uint32_t)ld * 2u : 2u;
+  }
+  // live = false: zeros, without touching memory
+  __device__ __forceinline__ u32x4 desc(bool live, int k0) const {
+    const int64_t skip = (int64_t)k0 * k_step;
+    const int64_t rest = live ? left - skip : 0;
+    return make_desc(base + skip, (uint32_t)(rest < 0 ? 0 : (rest > 0x7fffffff ? 0x7fffffff : rest)));
+  }
+  template <bool KMASK>
+  __device__ __forceinline__ void load(int j, const u32x4& desc, int k0, int kend, char* tile, int wave) const {
+    const bool dead = KMASK && !KSTRIDED && (k0 + kc8 >= kend);
+    load_to_lds16(desc, (lds_ptr)(tile + (8 * j + wave) * 1024), dead ? kPastEnd : voff[j]);
+  }
+};
+
+template <int OP, bool KMASK, int EPI, int TILE>
+__global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__ A, const bf16* __restrict__ B,
+                                                        void* __restrict__ Cv, const bf16* __restrict__ Rr, int M,
+                                                        int N, int K, int tiles_m, int tiles_n, RopeArgs rope,
+                                                        bf16* __restrict__ aux) {
+  static_assert(EPI == kEpiPlain || (EPI == kEpiSwigluBwd ? OP == 1 : OP == 0), "epilogue and product do not match");
+  constexpr bool AS = OP == 2, BS = OP != 0;
+  typedef Geo<TILE> G;
+  typedef RingGeo<TILE> RG;
+  constexpr int S = RG::S, NF = RG::NF, W = RG::W;
+  __shared__ __attribute__((aligned(1024))) char smem[RG::kLdsBytes];
+  static_assert(TILE * RG::kRowFloats * 4 <= RG::kLdsBytes && TILE * G::kCRowBytes <= RG::kLdsBytes, "staging fits");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hh = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+
+  // the tiles of this workgroup, numbered as in k_gemm_mfma
+  const int tiles = tiles_m * tiles_n;
+  int id = blockIdx.x;
+  {
+    const int n_ids = gridDim.x, per = n_ids / 8, rem = n_ids % 8, x = id % 8;
+    id = x * per + min(x, rem) + id / 8;
+  }
+  const int ksteps = (K + BK - 1) / BK;
+  const int s_runs = OP == 2 ? (int)gridDim.x / tiles : 1;
+  const int run = OP == 2 ? id / tiles : 0;
+  const int ks0 = OP == 2 ? (int)((int64_t)run * ksteps / s_runs) : 0;
+  const int ks1 = OP == 2 ? (int)((int64_t)(run + 1) * ksteps / s_runs) : ksteps;
+  const int kb = ks0 * BK, kend = min(K, ks1 * BK), nk = ks1 - ks0;
+  for (int tile = OP == 2 ? id % tiles : id; tile < tiles; tile += OP == 2 ? tiles : (int)gridDim.x) {
+    constexpr int kBand = 8;
+    const int band = tile / (kBand * tiles_m);
+    const int band_w = min(kBand, tiles_n - band * kBand);
+    const int in_band = tile - band * kBand * tiles_m;
+    const int tm = in_band / band_w, tn = band * kBand + in_band % band_w;
+    const int hN = N / 2;
+    const int m0 = tm * TILE, n0 = EPI == kEpiSwiglu ? tn * (TILE / 2) : tn * TILE;
+    const int b_split = EPI == kEpiSwiglu ? hN - TILE / 2 : 0;
+
+    RingOperand<AS, TILE> opa;
+    RingOperand<BS, TILE> opb;
+    opa.init(A, AS ? K : M, AS ? M : K, m0, wave, lane);
+    opb.init(B, BS ? K : N, BS ? N : K, n0, wave, lane, b_split);
+    // every step issues 2 NL loads per wavefront, past the last one too (they deliver zeros), so that one wait fits all
+    auto issue = [&](int p, const u32x4& da, const u32x4& db, int t, int slot) {   // load p of the step's 2 NL
+      char* st = smem + slot * G::kStageBytes;
+      if (p < RG::NL) opa.template load<KMASK>(p, da, kb + t * BK, kend, st, wave);
+      else opb.template load<KMASK>(p - RG::NL, db, kb + t * BK, kend, st + G::kTileBytes, wave);
+    };
+    // this wavefront's LDS reads are done and all but its newest n loads have landed
+    auto wait = [](auto n) {
+      constexpr int v = decltype(n)::value;
+      __builtin_amdgcn_s_waitcnt((v & 15) | (7 << 4) | (0 << 8) | ((v >> 4) << 14));
+    };
+    struct Frags { bf16x8 a[NF], b[NF]; };
+    auto read = [&](int j, int slot, Frags& f) {
+      const char* ta = smem + slot * G::kStageBytes;
+      f.a[j] = read_frag<AS, TILE>(ta, wm * W + j * 16, hh, lane);
+      f.b[j] = read_frag<BS, TILE>(ta + G::kTileBytes, wn * W + j * 16, hh, lane);
+    };
+
+    f32x4 acc[NF][NF];
+#pragma unroll
+    for (int j = 0; j < NF; ++j)
+#pragma unroll
+      for (int i = 0; i < NF; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[j][i][r] = 0.f;
+
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+      const u32x4 da = opa.desc(t < nk, kb + t * BK), db = opb.desc(t < nk, kb + t * BK);
+#pragma unroll
+      for (int p = 0; p < 2 * RG::NL; ++p) issue(p, da, db, t, t);
+    }
+    wait(std::integral_constant<int, (S - 1) * 2 * RG::NL>());
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    Frags f0, f1;
+#pragma unroll
+    for (int j = 0; j < NF; ++j) read(j, 0, f0);
+    int slot = 0;   // kt mod S
+    auto step = [&](int kt, Frags& now, Frags& next) {
+      wait(std::integral_constant<int, (S - 2) * 2 * RG::NL>());   // `now` is in registers, step kt + 1 in LDS
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();                                // the same for every wavefront: the slot is free
+      __builtin_amdgcn_sched_barrier(0);
+      const int after = slot + 1 == S ? 0 : slot + 1;
+      const u32x4 da = opa.desc(kt + S < nk, kb + (kt + S) * BK), db = opb.desc(kt + S < nk, kb + (kt + S) * BK);
+      static_assert(2 * RG::NL == NF, "one load per row of blocks");
+      // the matrix core starts at once; reads and loads are issued behind each row of blocks
+#pragma unroll
+      for (int j = 0; j < NF; ++j) {
+#pragma unroll
+        for (int i = 0; i < NF; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.b[i], now.a[j], acc[j][i], 0, 0, 0);
+        read(j, after, next);
+        issue(j, da, db, kt + S, slot);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      slot = after;
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+      step(kt, f0, f1);
+      if (kt + 1 < nk) step(kt + 1, f1, f0);
+    }
+
+    // ---- the two halves' sums meet: a wavefront gives its partner (wave ^ 4) the row blocks the partner finishes and
+    // finishes the others, blocks hh * NF / 2 .. of the share
+    wait(std::integral_constant<int, 0>());
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4* const swap = reinterpret_cast<f32x4*>(smem);
+    f32x4 sum[NF / 2][NF];
+#pragma unroll
+    for (int j = 0; j < NF / 2; ++j)
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        swap[((wave * (NF / 2) + j) * NF + i) * 64 + lane] = hh ? acc[j][i] : acc[j + NF / 2][i];
+        sum[j][i] = hh ? acc[j + NF / 2][i] : acc[j][i];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NF / 2; ++j)
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        const f32x4 o = swap[(((wave ^ 4) * (NF / 2) + j) * NF + i) * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[j][i][r] += o[r];
+      }
+    __syncthreads();
+    // lane: row lane % 16 of a block, columns (lane / 16) * 4 .. + 3
+    const int lm = lane & 15, kg = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < NF / 2; ++j)
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        const int row = wm * W + (hh * (NF / 2) + j) * 16 + lm, col = wn * W + i * 16 + kg * 4;
+        if (OP == 2) {
+          *reinterpret_cast<f32x4*>(smem + (row * RG::kRowFloats + col) * 4) = sum[j][i];
+        } else {
+          uint2 w;
+          w.x = pack_bf16(sum[j][i][0], sum[j][i][1]);
+          w.y = pack_bf16(sum[j][i][2], sum[j][i][3]);
+          *reinterpret_cast<uint2*>(smem + row * G::kCRowBytes + col * 2) = w;
+        }
+      }
+    __syncthreads();
+    if (OP == 2) {
+      // a wavefront's atomics cover 256 contiguous bytes of one row
+      float* C = reinterpret_cast<float*>(Cv);
+#pragma unroll 8
+      for (int it = 0; it < TILE * TILE / kThreads; ++it) {
+        const int c = tid + kThreads * it, row = c / TILE, col = c % TILE;
+        if (m0 + row < M && n0 + col < N)
+          unsafeAtomicAdd(C + (int64_t)(m0 + row) * N + n0 + col, reinterpret_cast<const float*>(smem)[row * RG::kRowFloats + col]);
+      }
+    } else {
+      store_tile<OP, EPI, TILE>(smem, reinterpret_cast<bf16*>(Cv), Rr, aux, rope, M, N, m0, n0, tid);
+    }
+    __syncthreads();   // the staging area becomes the next tile's ring
+  }
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -589,6 +728,47 @@ int cu_count() {
     else n = 256;
   }
   return n;
+}
+
+// Tile, tile grid and workgroups of a launch: the least of what each choice is expected to take, in microseconds,
+//   rounds of workgroups x (k-steps x step + ends)  +  op 2: runs x output bytes / atomics rate
+// step and ends are fits to measured products of 4 to 344 steps over grids of 24 to 1400 tiles: a 256-tile takes 0.9 to
+// 1.3 us a step (the clock falls as CUs fill), a 128-tile 0.5 (its operand traffic per flop is twice as large), a
+// 64-tile 0.3 alone on its CU and 0.37 beside another.  Float atomics reach 1.4 TB/s over the whole chip whatever the
+// tile, so that further runs per tile cost most where the reduction is short.  Examples, us, 256- / 128-tile:
+// NT 4096 x 1024 x 2816 46 / 26, NT 1777 x 6144 x 2048 44 / 54, NN 8192 x 1024 x 1024 25 / 26, NT 8192 x 6144 x 2048
+// 145 / 213, TN 1024 x 1024 x 4096 37 / 25, TN 2048 x 2048 x 8192 91 / 78, TN 5632 x 1024 x 8192 108 / 130.
+struct Shape { int tile, tm, tn, wgs; };
+Shape choose_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
+  const int64_t cus = cu_count(), ksteps = (K + BK - 1) / BK;
+  Shape best{};
+  double best_us = 0;
+  for (int t : {256, 128, 64}) {
+    if (epi == kEpiSwiglu && (N / 2) % (t / 2)) continue;   // a tile covers t/2 gate and the matching t/2 up columns
+    const int64_t tm = (M + t - 1) / t, tn = (N + t - 1) / t, tiles = tm * tn;
+    // op 2, 256-tiles: the smallest number of runs whose last round is at least 0.65 full; another number has to
+    // promise 7 %, which is as good as the fits are
+    int usual = 0;
+    for (int runs = 1; op == 2 && t == 256 && runs <= 8 && (runs == 1 || ksteps / runs >= 8); ++runs) {
+      usual = runs;
+      const int64_t wgs = tiles * runs, last = wgs % cus;
+      if (last == 0 || last * 100 >= cus * 65 || wgs >= 6 * cus) break;
+    }
+    // an op 2 run of fewer than 4 steps would be mostly start and end
+    for (int runs = 1; runs <= (op == 2 ? 16 : 1) && (runs == 1 || ksteps / runs >= 4); ++runs) {
+      const int64_t wgs = tiles * runs, slots = t == 64 && wgs > cus ? 2 * cus : cus, rounds = (wgs + slots - 1) / slots;
+      const double step = t == 256 ? 0.85 + 0.45 * (double)wgs / (double)(rounds * cus) : t == 128 ? 0.5 : slots > cus ? 0.37 : 0.3;
+      const double ends = t == 256 ? 5 : t == 128 ? 4 : 3;
+      double us = (double)rounds * ((double)((ksteps + runs - 1) / runs) * step + ends) +
+                  (op == 2 ? runs * 4.0 * (double)M * (double)N / 1.4e6 : 0.0);
+      if (runs == usual) us *= 0.93;
+      if (best.tile && us >= best_us) continue;
+      best_us = us;
+      // op 0/1: equally full rounds, every workgroup taking every wgs-th tile
+      best = {t, (int)tm, (int)tn, (int)(op == 2 ? wgs : (tiles + rounds - 1) / rounds)};
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -614,54 +794,30 @@ bool gemm_mfma_supported(int op, int64_t M, int64_t N, int64_t K, const void* A,
 void gemm_mfma(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
                const void* R, const RopeArgs* rope, int epi, void* aux) {
   if (rope) epi = kEpiRope;
-  // The chip delivers about the same aggregate rate with two thirds of its CUs busy as with all of them
-  // (the kernel is bound by what the L2s and the power budget give), but a nearly empty round is lost time.
-  const int cus = cu_count();
-  // 256 x 256 tiles move the fewest bytes per flop; a product with too few of them to occupy the CUs
-  // (a single microbatch through a narrow layer) takes 128 x 128 tiles instead
-  const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-  int tile = (op != 2 && big * 4 < (int64_t)cus * 3) ? 128 : 256;
-  if (epi == kEpiSwiglu && (N / 2) % 128) tile = 128;   // the caller has checked (N/2) % 64 == 0
-  const int tm = (int)((M + tile - 1) / tile);
-  // kEpiSwiglu: a tile covers tile/2 gate and the matching tile/2 up columns
-  const int tn = epi == kEpiSwiglu ? (int)(N / tile) : (int)((N + tile - 1) / tile);
-  const int tiles = tm * tn;
-  int wgs;
-  if (op == 2) {
-    // a whole number s of runs per tile, so that the runs of neighbouring tiles walk the same k range
-    // together: the smallest s whose last round of s * tiles workgroups is at least 0.65 full
-    const int ksteps = (int)((K + BK - 1) / BK);
-    int s_best = 1;
-    for (int sp = 1; sp <= 8 && ksteps / sp >= 8; ++sp) {
-      const int64_t w = (int64_t)tiles * sp;
-      const int64_t last = w % cus;
-      s_best = sp;
-      if (last == 0 || last * 100 >= (int64_t)cus * 65 || w >= 6 * (int64_t)cus) break;
-    }
-    wgs = tiles * s_best;
-  } else {
-    // equally full rounds: ceil(tiles / rounds) workgroups, each taking every wgs-th tile
-    const int rounds = (tiles + cus - 1) / cus;
-    wgs = (tiles + rounds - 1) / rounds;
-  }
+  const Shape sh = choose_shape(op, M, N, K, epi);
+  const int tile = sh.tile, tm = sh.tm, tn = sh.tn, wgs = sh.wgs;
   dim3 grid(wgs);
   const bf16* a = (const bf16*)A;
   const bf16* b = (const bf16*)B;
   const bf16* r = (const bf16*)R;
   const bool kmask = K % BK != 0;
   const RopeArgs ra = rope ? *rope : RopeArgs{nullptr, 1, 8, 0};
-#define SP_LAUNCH(OP, KM, EP, TL) \
-  hipLaunchKernelGGL((k_gemm_mfma<OP, KM, EP, TL, TL == 256>), grid, dim3(kThreads), 0, s, a, b, C, r, (int)M, (int)N, (int)K, tm, tn, ra, (bf16*)aux)
-#define SP_LAUNCH_K(OP, EP, TL) \
-  do { if (kmask) SP_LAUNCH(OP, true, EP, TL); else SP_LAUNCH(OP, false, EP, TL); } while (0)
+#define SP_LAUNCH(KERNEL) \
+  hipLaunchKernelGGL(KERNEL, grid, dim3(kThreads), 0, s, a, b, C, r, (int)M, (int)N, (int)K, tm, tn, ra, (bf16*)aux)
+#define SP_LAUNCH_K(OP, KM, EP)                            \
+  do {                                                     \
+    if (tile == 256) SP_LAUNCH((k_gemm_mfma<OP, KM, EP>)); \
+    else if (tile == 128) SP_LAUNCH((k_gemm_ring<OP, KM, EP, 128>)); \
+    else SP_LAUNCH((k_gemm_ring<OP, KM, EP, 64>));         \
+  } while (0)
 #define SP_LAUNCH_T(OP, EP) \
-  do { if (tile == 128) SP_LAUNCH_K(OP, EP, 128); else SP_LAUNCH_K(OP, EP, 256); } while (0)
+  do { if (kmask) SP_LAUNCH_K(OP, true, EP); else SP_LAUNCH_K(OP, false, EP); } while (0)
   if (op == 0 && epi == kEpiRope) SP_LAUNCH_T(0, kEpiRope);
   else if (op == 0 && epi == kEpiSwiglu) SP_LAUNCH_T(0, kEpiSwiglu);
   else if (op == 0) SP_LAUNCH_T(0, kEpiPlain);
   else if (op == 1 && epi == kEpiSwigluBwd) SP_LAUNCH_T(1, kEpiSwigluBwd);
   else if (op == 1) SP_LAUNCH_T(1, kEpiPlain);
-  else SP_LAUNCH(2, false, kEpiPlain, 256);
+  else SP_LAUNCH_K(2, false, kEpiPlain);
 #undef SP_LAUNCH_T
 #undef SP_LAUNCH_K
 #undef SP_LAUNCH
@@ -669,7 +825,7 @@ void gemm_mfma(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const voi
 
 bool gemm_swiglu_supported(bool bwd, int64_t R, int64_t h, int64_t d, const void* X, const void* W, const void* gu,
                            const void* other) {
-  if (h % 64) return false;   // forward: a tile of 128 or 256 columns holds whole halves of gate and up
+  if (h % 64) return false;   // forward: a tile of 64, 128 or 256 columns holds whole halves of gate and up
   if (bwd) return gemm_mfma_supported(1, R, h, d, X, W, other, gu);
   return gemm_mfma_supported(0, R, 2 * h, d, X, W, gu, other);
 }
