@@ -98,7 +98,8 @@ Carve carve(const sp_cfg& c, int n_mb_max, int n_visits_max) {
   w.t_da = take(Rmax * D.h * D.E);
   w.t_delta = take(Rmax * D.H * sizeof(float));
   w.rope = take((size_t)D.T * (D.hd / 2) * 2 * sizeof(float));   // cos, sin per (position, pair)
-  w.dgpart = take((size_t)kRmsPartRows * D.d * sizeof(float));   // per-block partial sums of a norm's gain gradient
+  // per-block partial sums of the gain gradients of the norms that one launch folds
+  w.dgpart = take((size_t)std::min(kRmsFoldMax, 2 * c.layers_per_stage) * kRmsPartRows * D.d * sizeof(float));
   w.bad = take(sizeof(int32_t));   // raised by a kernel that meets a token id or target outside the vocabulary
   if (c.has_head) {
     const int64_t ch = head_chunk_rows(D, Rmax);
@@ -405,8 +406,14 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
   char* t = at(ctx, ctx->w.t_d2);
   char* da = at(ctx, ctx->w.t_da);
   float* delta = (float*)at(ctx, ctx->w.t_delta);
-  float* dgpart = (float*)at(ctx, ctx->w.dgpart);
+  // gain gradients wait as partial sums, one place each, for one launch at the end (or when the places are taken)
+  RmsFold fold{};
   const int64_t dgpart_n = (int64_t)kRmsPartRows * D.d;
+  auto norm_bwd = [&](const void* x, int64_t gain, const float* rstd, const void* dres, void* dx) {
+    if (fold.n == kRmsFoldMax) rmsnorm_bwd_fold(s, &fold, (int)D.d);
+    rmsnorm_bwd(s, dt, t, x, P(ctx, params, gain), rstd, dres, R, (int)D.d, dx, grads + gain,
+                (float*)at(ctx, ctx->w.dgpart) + fold.n * dgpart_n, dgpart_n, &fold);
+  };
   // A second stream pays while the layer's products are short: their partly filled last rounds of tiles take in
   // work of the other stream.  Products of many rounds only get in each other's way (workgroups of two kernels
   // interleave on the CUs and the tiles an XCD holds no longer share panels): measured 3 - 7 % slower from about
@@ -449,7 +456,7 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
     if ((rc = side_dw(1, par, 2 * D.h, D.d, dgu, ls.hn, grads + w.wgu))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, 2 * D.h, dgu, P(ctx, params, w.wgu), t, nullptr))) return rc;
     if ((rc = wait_done(2, par))) return rc;
-    rmsnorm_bwd(s, dt, t, ls.h, P(ctx, params, w.g2), ls.rstd2, dy, R, (int)D.d, dh, grads + w.g2, dgpart, dgpart_n);
+    norm_bwd(ls.h, w.g2, ls.rstd2, dy, dh);
     // attention: h = x + o Wo^T
     if ((rc = side_dw(2, par, D.d, D.d, dh, ls.o, grads + w.wo))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, D.d, dh, P(ctx, params, w.wo), t, nullptr))) return rc;
@@ -460,9 +467,10 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
     if ((rc = side_dw(3, par, D.nq, D.d, dqkv, ls.xn, grads + w.wqkv))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, D.nq, dqkv, P(ctx, params, w.wqkv), t, nullptr))) return rc;
     if ((rc = wait_done(0, par ^ 1))) return rc;   // the layer above may still read its dy
-    rmsnorm_bwd(s, dt, t, ls.x, P(ctx, params, w.g1), ls.rstd1, dh, R, (int)D.d, dy_next, grads + w.g1, dgpart, dgpart_n);
+    norm_bwd(ls.x, w.g1, ls.rstd1, dh, dy_next);
   }
   char* dy = at(ctx, ctx->w.t_dy[par]);
+  rmsnorm_bwd_fold(s, &fold, (int)D.d);
   // the caller's stream continues only after every weight gradient has landed
   SP_HIP(hipEventRecord(ctx->joined, side));
   SP_HIP(hipStreamWaitEvent(s, ctx->joined, 0));
@@ -506,8 +514,10 @@ static int head_impl(sp_ctx* ctx, const void* params, const void* act_pool, cons
     if (!backward) continue;
     if ((rc = gemm(s, dt, 2, D.V, D.d, R, logits, xn, grads + ctx->L.whead, nullptr))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, D.V, logits, P(ctx, params, ctx->L.whead), dxn, nullptr))) return rc;
+    RmsFold fold{};
     rmsnorm_bwd(s, dt, dxn, x, P(ctx, params, ctx->L.gf), rstd, nullptr, R, (int)D.d, dx, grads + ctx->L.gf,
-                (float*)at(ctx, ctx->w.dgpart), (int64_t)kRmsPartRows * D.d);
+                (float*)at(ctx, ctx->w.dgpart), (int64_t)kRmsPartRows * D.d, &fold);
+    rmsnorm_bwd_fold(s, &fold, (int)D.d);
   }
   SP_HIP(hipGetLastError());
   return SP_OK;

@@ -50,10 +50,20 @@ void fill_zero(hipStream_t s, void* p, int64_t bytes);
 void rmsnorm_fwd(hipStream_t s, int dtype, const void* x, const void* g, int64_t R, int d, float eps, void* y, float* rstd);
 // dx = (dres ? dres : 0) + rmsnorm'(dy) ; dg += sum_rows dy * x * rstd
 // part (may be null): scratch of part_floats floats for the per-block partial sums of dg (kRmsPartRows x d is
-// enough), which a second kernel adds up
+// enough); where the call leaves sums there it notes them in *fold, and dg is complete after rmsnorm_bwd_fold, which
+// adds up all that is noted (norms of the same width d) and empties the list
 constexpr int kRmsPartRows = 1024;
+constexpr int kRmsFoldMax = 8;   // two norms of each layer of a four-layer stage
+struct RmsFold {
+  const float* part[kRmsFoldMax];
+  float* dg[kRmsFoldMax];
+  int rows[kRmsFoldMax];
+  int n;
+  void add(const float* p, float* g, int r) { part[n] = p; dg[n] = g; rows[n++] = r; }
+};
+void rmsnorm_bwd_fold(hipStream_t s, RmsFold* fold, int d);
 void rmsnorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const void* g, const float* rstd,
-                 const void* dres, int64_t R, int d, void* dx, float* dg, float* part = nullptr, int64_t part_floats = 0);
+                 const void* dres, int64_t R, int d, void* dx, float* dg, float* part, int64_t part_floats, RmsFold* fold);
 // rotates the first nheads*hd columns of every row (row_stride elements apart); position = row % T
 void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta);
 // table[(p * hd/2 + i) * 2 + {0, 1}] = cos, sin of p * theta^(-2i/hd), the angles rope() uses, for p < T

@@ -222,27 +222,33 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd(const T* __restrict__ dy
   }
 }
 
-// The same for bf16, columns instead of rows divided among the wavefronts: the block's four wavefronts share
-// each row (wavefront w takes the 512-column pieces w, w + 4, ..), so a lane's gain and its gain-gradient sums
-// are NVW x 8 values for the whole kernel and nothing has to be folded across wavefronts at the end.  RPI rows are
-// in flight together (dy, x and the added gradient all loaded before the first is used); the four partial sums
-// of a row's mean meet in LDS, one barrier per RPI rows (two sets of slots, alternating, so that the next
-// round's sums never overwrite one still being read).
-template <int NVW, int RPI, bool HAS_RES>
+// The same for bf16, columns instead of rows divided among the wavefronts: WPR of the block's four wavefronts share
+// each row (wavefront w takes the 512-column pieces w, w + WPR, ..), so a lane's gain and its gain-gradient sums
+// are NVW x 8 values for the whole kernel.  RPI rows of each of the 4 / WPR row groups are
+// in flight together (dy, x and the added gradient all loaded before the first is used); the partial sums
+// of a row's mean meet in LDS, one barrier per round (two sets of slots, alternating, so that the next
+// round's sums never overwrite one still being read).  Where a row takes fewer than four pieces the other wavefronts
+// take rows of their own (with all four on one row, three of four idled at d <= 512 and two at d <= 1024), and the
+// groups' gain-gradient sums are folded through LDS at the end.
+// With that and one fold per stage, 50M shape in bf16 (d = 288) 4.58 -> 4.39 ms a pass, 500M shape (d = 1024) 65.9 -> 64.0 ms.
+template <int NVW, int RPI, int WPR, bool HAS_RES>
 __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restrict__ dy, const bf16* __restrict__ x,
                                                              const bf16* __restrict__ g, const float* __restrict__ rstd,
                                                              const bf16* __restrict__ dres, int64_t R, int d,
                                                              bf16* __restrict__ dx, float* __restrict__ dg,
                                                              float* __restrict__ part_out) {
+  constexpr int G = kWavesPerBlock / WPR;   // row groups
+  static_assert(G == 1 || NVW == 1, "several row groups only where a row is at most WPR pieces");
   __shared__ float s_m[2][RPI][kWavesPerBlock];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ __attribute__((aligned(16))) float s_fold[G > 1 ? (G - 1) * WPR * 512 : 4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = wave / WPR, piece = wave % WPR;
   int col[NVW];
   uint32_t coff[NVW];   // byte offset of the piece in a row; 0 for a lane past the end of the row (loads stay in bounds, the
                         // lane's gain is zero and nothing of it is stored)
   float gv[NVW][8], acc[NVW][8];
 #pragma unroll
   for (int i = 0; i < NVW; ++i) {
-    col[i] = ((i * kWavesPerBlock + wave) * 64 + lane) * 8;
+    col[i] = ((i * WPR + piece) * 64 + lane) * 8;
     coff[i] = col[i] < d ? (uint32_t)col[i] * 2u : 0u;
 #pragma unroll
     for (int j = 0; j < 8; ++j) { acc[i][j] = 0.f; gv[i][j] = 0.f; }
@@ -256,7 +262,8 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restr
   char* const dxb = reinterpret_cast<char*>(dx);
   int par = 0;
 #pragma nounroll
-  for (int64_t r0 = (int64_t)blockIdx.x * RPI; r0 < R; r0 += (int64_t)gridDim.x * RPI, par ^= 1) {
+  for (int64_t rb0 = (int64_t)blockIdx.x * (RPI * G); rb0 < R; rb0 += (int64_t)gridDim.x * (RPI * G), par ^= 1) {
+    const int64_t r0 = rb0 + grp * RPI;
     // all loads of the round first, unconditionally: a row past the end reads the last row again and counts
     // for nothing (its rstd is taken as zero)
     uint4 qdy[RPI][NVW], qx[RPI][NVW], qres[HAS_RES ? RPI : 1][NVW];
@@ -270,7 +277,7 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restr
         if (HAS_RES) qres[rr][i] = *reinterpret_cast<const uint4*>(resb + rb + coff[i]);
       }
     }
-    float dxh[RPI][NVW][8], xh[RPI][NVW][8], rs[RPI];
+    float dxh[RPI][NVW][8], xh[RPI][NVW][8], rs[RPI], mrow[RPI];
 #pragma unroll
     for (int rr = 0; rr < RPI; ++rr) {
       rs[rr] = r0 + rr < R ? rstd[r0 + rr] : 0.f;
@@ -288,13 +295,16 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restr
         }
       }
       m = wave_sum(m);
-      if (lane == 0) s_m[par][rr][wave] = m;
+      if (WPR == 1) mrow[rr] = m;
+      else if (lane == 0) s_m[par][rr][wave] = m;
     }
-    __syncthreads();
+    if (WPR > 1) __syncthreads();
 #pragma unroll
     for (int rr = 0; rr < RPI; ++rr) {
       const bool row_in = r0 + rr < R;
-      const float m = ((s_m[par][rr][0] + s_m[par][rr][1]) + (s_m[par][rr][2] + s_m[par][rr][3])) * inv_d;
+      if (WPR == 4) mrow[rr] = (s_m[par][rr][0] + s_m[par][rr][1]) + (s_m[par][rr][2] + s_m[par][rr][3]);
+      if (WPR == 2) mrow[rr] = s_m[par][rr][2 * grp] + s_m[par][rr][2 * grp + 1];
+      const float m = mrow[rr] * inv_d;
       const size_t rb = (size_t)(row_in ? r0 + rr : R - 1) * d * 2;
 #pragma unroll
       for (int i = 0; i < NVW; ++i) {
@@ -311,6 +321,15 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restr
       }
     }
   }
+  if (G > 1) {
+    if (grp > 0) store8(&s_fold[((grp - 1) * WPR + piece) * 512 + lane * 8], acc[0]);
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int o = 0; o < G - 1; ++o)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[0][j] += s_fold[(o * WPR + piece) * 512 + lane * 8 + j];
+  }
 #pragma unroll
   for (int i = 0; i < NVW; ++i) {
     if (col[i] < d) {
@@ -323,10 +342,15 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restr
   }
 }
 
-// dg[c] += sum over n rows of part[row][c].  A block takes 64 columns and one of gridDim.y runs of rows: its four
-// wavefronts stride the run's rows, fold in LDS, and add one value per column atomically (gridDim.y adds per
-// address in all).
-__global__ __launch_bounds__(kBlock) void k_colsum_add(const float* __restrict__ part, int n, int d, float* __restrict__ dg) {
+// dg[c] += sum over n rows of part[row][c], for every norm of the list (blockIdx.z).  A block takes 64 columns and one
+// of gridDim.y runs of rows: its four wavefronts stride the run's rows, fold in LDS, and add one value per column
+// atomically (gridDim.y adds per address in all).  One launch folds the norms of a whole stage backward: a launch
+// after every norm (4 us alone, 9 to 38 us beside the weight-gradient products whose workgroups fill the CUs) held
+// up the chain that carries the activation gradient.
+__global__ __launch_bounds__(kBlock) void k_colsum_add(RmsFold list, int d) {
+  const float* __restrict__ part = list.part[blockIdx.z];
+  float* __restrict__ dg = list.dg[blockIdx.z];
+  const int n = list.rows[blockIdx.z];
   __shared__ float s_part[kWavesPerBlock][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = blockIdx.x * 64 + lane;
   const int per = (n + gridDim.y - 1) / gridDim.y, r0 = blockIdx.y * per, r1 = min(n, r0 + per);
@@ -719,53 +743,61 @@ void rmsnorm_fwd(hipStream_t s, int dtype, const void* x, const void* g, int64_t
   prof_stop(pi, s, 2.0 * R * d * elt_size(dtype));   // x read, y written
 }
 
+// Returns the number of partial rows of dg left in `part` (0: dg is complete).
 template <class T>
-static void rmsnorm_bwd_t(hipStream_t s, const T* dy, const T* x, const T* g, const float* rstd, const T* dres,
-                          int64_t R, int d, T* dx, float* dg, float* part, int64_t part_floats) {
-  if (R <= 0) return;
+static int rmsnorm_bwd_t(hipStream_t s, const T* dy, const T* x, const T* g, const float* rstd, const T* dres,
+                         int64_t R, int d, T* dx, float* dg, float* part, int64_t part_floats) {
+  if (R <= 0) return 0;
   // the gain-gradient fold keeps one row of d floats per wavefront in LDS: 64 KB at d = 4096
   bool vec = d % 8 == 0 && d <= 4096 && aligned16<T>(x) && aligned16<T>(g) && aligned16<T>(dy) && aligned16<T>(dx) &&
              (!dres || aligned16<T>(dres));
   if (!vec) {
     int grid = grid_for_rows(R, kWavesPerBlock, 16384);
     hipLaunchKernelGGL(k_rmsnorm_bwd_scalar<T>, dim3(grid), dim3(kBlock), 0, s, dy, x, g, rstd, dres, R, d, dx, dg);
-    return;
+    return 0;
   }
   int grid = grid_for_rows(R, kWavesPerBlock * 4, 1024);  // >= 4 rows per wavefront amortise the dg fold
   size_t lds = (size_t)d * sizeof(float) * kWavesPerBlock;
   int nv = (d + 511) / 512;
   float* pp = (part && (int64_t)grid * d <= part_floats && grid > 8) ? part : nullptr;
   if constexpr (std::is_same<T, bf16>::value) {
-    // d <= 2048: one piece per lane, 4 rows in flight; d <= 4096: two pieces, 2 rows
-    const int rpi = d <= 2048 ? 4 : 2;
+    // pieces of 512 columns: one, two or four wavefronts per row, 4 rows in flight each; d > 2048: two pieces, 2 rows
+    const int rows = d <= 512 ? 16 : d <= 1024 ? 8 : d <= 2048 ? 4 : 2;   // a workgroup's round
     // three workgroups fit a CU (registers): one round of 256 x 3 resident workgroups that stride the rows
-    int gridc = (int)std::min<int64_t>((R + rpi - 1) / rpi, 768);
+    int gridc = (int)std::min<int64_t>((R + rows - 1) / rows, 768);
     static_assert(768 <= kRmsPartRows, "one partial row per workgroup");
     float* ppc = (part && (int64_t)gridc * d <= part_floats && gridc > 8) ? part : nullptr;
-#define SP_COLS(NVW, RPI)                                                                                              \
+#define SP_COLS(NVW, RPI, WPR)                                                                                         \
   do {                                                                                                                 \
-    if (dres) hipLaunchKernelGGL((k_rmsnorm_bwd_cols<NVW, RPI, true>), dim3(gridc), dim3(kBlock), 0, s, dy, x, g, rstd, dres, R, d, dx, dg, ppc); \
-    else hipLaunchKernelGGL((k_rmsnorm_bwd_cols<NVW, RPI, false>), dim3(gridc), dim3(kBlock), 0, s, dy, x, g, rstd, dres, R, d, dx, dg, ppc);   \
+    if (dres) hipLaunchKernelGGL((k_rmsnorm_bwd_cols<NVW, RPI, WPR, true>), dim3(gridc), dim3(kBlock), 0, s, dy, x, g, rstd, dres, R, d, dx, dg, ppc); \
+    else hipLaunchKernelGGL((k_rmsnorm_bwd_cols<NVW, RPI, WPR, false>), dim3(gridc), dim3(kBlock), 0, s, dy, x, g, rstd, dres, R, d, dx, dg, ppc);   \
   } while (0)
-    if (d <= 2048) SP_COLS(1, 4); else SP_COLS(2, 2);
+    if (d <= 512) SP_COLS(1, 4, 1); else if (d <= 1024) SP_COLS(1, 4, 2); else if (d <= 2048) SP_COLS(1, 4, 4); else SP_COLS(2, 2, 4);
 #undef SP_COLS
-    if (ppc) hipLaunchKernelGGL(k_colsum_add, dim3((d + 63) / 64, 8), dim3(kBlock), 0, s, ppc, gridc, d, dg);
-    return;
+    return ppc ? gridc : 0;
   }
 #define SP_CASE(N) hipLaunchKernelGGL((k_rmsnorm_bwd<T, N>), dim3(grid), dim3(kBlock), lds, s, dy, x, g, rstd, dres, R, d, dx, dg, pp)
   if (nv <= 1) SP_CASE(1); else if (nv <= 2) SP_CASE(2); else if (nv <= 4) SP_CASE(4); else if (nv <= 8) SP_CASE(8); else SP_CASE(16);
 #undef SP_CASE
-  if (pp) hipLaunchKernelGGL(k_colsum_add, dim3((d + 63) / 64, 8), dim3(kBlock), 0, s, pp, grid, d, dg);
+  return pp ? grid : 0;
 }
 
 void rmsnorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const void* g, const float* rstd,
-                 const void* dres, int64_t R, int d, void* dx, float* dg, float* part, int64_t part_floats) {
+                 const void* dres, int64_t R, int d, void* dx, float* dg, float* part, int64_t part_floats, RmsFold* fold) {
   const int pi = prof_start(PROF_RMSNORM_BWD, s);
+  int rows;
   if (dtype == SP_BF16)
-    rmsnorm_bwd_t<bf16>(s, (const bf16*)dy, (const bf16*)x, (const bf16*)g, rstd, (const bf16*)dres, R, d, (bf16*)dx, dg, part, part_floats);
+    rows = rmsnorm_bwd_t<bf16>(s, (const bf16*)dy, (const bf16*)x, (const bf16*)g, rstd, (const bf16*)dres, R, d, (bf16*)dx, dg, part, part_floats);
   else
-    rmsnorm_bwd_t<float>(s, (const float*)dy, (const float*)x, (const float*)g, rstd, (const float*)dres, R, d, (float*)dx, dg, part, part_floats);
+    rows = rmsnorm_bwd_t<float>(s, (const float*)dy, (const float*)x, (const float*)g, rstd, (const float*)dres, R, d, (float*)dx, dg, part, part_floats);
   prof_stop(pi, s, (dres ? 4.0 : 3.0) * R * d * elt_size(dtype));   // dy, x (, dres) read, dx written
+  if (rows) fold->add(part, dg, rows);
+}
+
+void rmsnorm_bwd_fold(hipStream_t s, RmsFold* fold, int d) {
+  if (!fold->n) return;
+  hipLaunchKernelGGL(k_colsum_add, dim3((d + 63) / 64, 8, fold->n), dim3(kBlock), 0, s, *fold, d);
+  fold->n = 0;
 }
 
 void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta) {
