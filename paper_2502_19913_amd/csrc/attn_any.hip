@@ -31,6 +31,13 @@ constexpr int kMaxHd = 256;
 constexpr int kThreads = 256;
 constexpr int KT = 32;    // rows of a tile of the walked side
 constexpr int BQ = 64;    // rows a workgroup owns
+// Sets of four wavefronts that take the tiles of the walked side in turn.  A workgroup's time is the chain of its tiles
+// (score products, exponentials, second products, LDS round trips: three to four times the matrix instructions alone),
+// and small models have one or two wavefronts per SIMD to overlap it.  Two sets up to a head dimension of 48: heads of
+// 48, 50M shape in bf16 on 3 x 333 tokens 4.40 -> 3.89 ms, in float on 4 x 256 tokens 6.14 -> 5.81 ms, on 64 tokens
+// 2.02 -> 1.96 ms a pass.  At 64 the stage of 2 x 512 tokens was 0.5 % slower with two sets, and from 96 on their
+// buffers take the room of a CU's second workgroup.
+template <int HD> constexpr int kSets = HD <= 48 ? 2 : 1;
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
@@ -97,13 +104,14 @@ struct Pair {
   f32x4 x[N4], y[N4];
   // rows r0 .. of X (row stride ldx) and Y (ldy); rows at or past `rows` are zeros
   __device__ __forceinline__ void load(const T* X, int64_t ldx, const T* Y, int64_t ldy, int r0, int rows, int hd, bool vec, int tid) {
+    const T *xt = X + (int64_t)r0 * ldx, *yt = Y + (int64_t)r0 * ldy;
 #pragma unroll
     for (int j = 0; j < N4; ++j) {
-      const int i = tid + kThreads * j, r = r0 + i / (HD / 4), c = i % (HD / 4) * 4;
+      const int i = tid + kThreads * j, in = i / (HD / 4), c = i % (HD / 4) * 4;
       x[j] = y[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (r < rows && i < KT * HD / 4) {
-        x[j] = row4(X + r * ldx, c, hd, vec);
-        y[j] = row4(Y + r * ldy, c, hd, vec);
+      if (r0 + in < rows && i < KT * HD / 4) {   // 32 rows of at most 3 x 65535 heads of 256: offsets fit 32 bits
+        x[j] = row4(xt + (uint32_t)in * (uint32_t)ldx, c, hd, vec);
+        y[j] = row4(yt + (uint32_t)in * (uint32_t)ldy, c, hd, vec);
       }
     }
   }
@@ -119,13 +127,31 @@ struct Pair {
   }
 };
 
+// The second set's HD / 16 accumulators of every lane on their way to the first set, quad by quad; the place past them,
+// which both return, has room for two more floats of a lane (kThreads apart).  All of it fits a set's buffers:
+// kThreads * (HD / 4 + 2) <= 4 KT (HD + 4) floats (checked below).
+template <int HD>
+__device__ __forceinline__ float* give(float* at, const f32x4* v, int tid) {
+  static_assert(kThreads * (HD / 4 + 2) <= 4 * KT * (HD + 4), "two sets' exchange fits one set's buffers");
+#pragma unroll
+  for (int c = 0; c < HD / 16; ++c) reinterpret_cast<f32x4*>(at)[c * kThreads + tid] = v[c];
+  return at + HD / 16 * 4 * kThreads + tid;
+}
+template <int HD>
+__device__ __forceinline__ const float* take(const float* at, f32x4* v, int tid) {
+#pragma unroll
+  for (int c = 0; c < HD / 16; ++c) v[c] = reinterpret_cast<const f32x4*>(at)[c * kThreads + tid];
+  return at + HD / 16 * 4 * kThreads + tid;
+}
+
 template <class T, int HD>
-__global__ __launch_bounds__(kThreads) void k_attn_fwd(const T* __restrict__ qkv, int T_, int H, int Hkv, int hd, bool vec, float scale,
+__global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_fwd(const T* __restrict__ qkv, int T_, int H, int Hkv, int hd, bool vec, float scale,
                                                        T* __restrict__ o, float* __restrict__ lse) {
-  constexpr int LD = HD + 4, NS = HD / 16;
-  __shared__ __attribute__((aligned(16))) float smem[2][2][KT * LD];
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int LD = HD + 4, NS = HD / 16, SETS = kSets<HD>;
+  __shared__ __attribute__((aligned(16))) float smem_all[SETS][2][2][KT * LD];
+  const int set = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
+  const int lane = tid & 63, lr = lane & 15, kg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto& smem = smem_all[set];
   const int a = blockIdx.y, b = blockIdx.z, kvh = a / (H / Hkv);
   const int q0 = (int)(gridDim.x - 1 - blockIdx.x) * BQ;   // the longest blocks of a head first
   const int qw0 = q0 + wave * 16, q = qw0 + lr;
@@ -141,14 +167,14 @@ __global__ __launch_bounds__(kThreads) void k_attn_fwd(const T* __restrict__ qkv
   float m_i = -INFINITY, l_i = 0.f;
   const int tiles = (min(T_, q0 + BQ) + KT - 1) / KT;
   Pair<T, HD> in;
-  in.load(kp, ld, vp, ld, 0, T_, hd, vec, tid);
+  in.load(kp, ld, vp, ld, set * KT, T_, hd, vec, tid);   // a row past the end is zeros
   in.store(smem[0][0], smem[0][1], tid);
   __syncthreads();
-  for (int kt = 0; kt < tiles; ++kt) {
-    const int k0 = kt * KT;
-    if (kt + 1 < tiles) in.load(kp, ld, vp, ld, k0 + KT, T_, hd, vec, tid);
-    const float *lk = smem[kt & 1][0], *lv = smem[kt & 1][1];
-    if (k0 <= qw0 + 15) {   // some key of the tile is visible to this wavefront
+  for (int i = 0; i * SETS < tiles; ++i) {   // every wavefront the same number of rounds
+    const int kt = i * SETS + set, k0 = kt * KT;
+    if (kt + SETS < tiles) in.load(kp, ld, vp, ld, k0 + SETS * KT, T_, hd, vec, tid);
+    const float *lk = smem[i & 1][0], *lv = smem[i & 1][1];
+    if (kt < tiles && k0 <= qw0 + 15) {   // some key of the tile is visible to this wavefront
       f32x4 st[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
@@ -168,7 +194,7 @@ __global__ __launch_bounds__(kThreads) void k_attn_fwd(const T* __restrict__ qkv
           if (k0 + t * 16 + kg * 4 + r > q) st[t][r] = -INFINITY;
           mx = fmaxf(mx, st[t][r]);
         }
-      const float m_new = fmaxf(m_i, max4(mx) * scale);   // finite from the first tile on: key 0 is visible to all
+      const float m_new = fmaxf(m_i, max4(mx) * scale);   // finite from the first tile on: its first key is visible to all
       const float alpha = expf(m_i - m_new);
       float rs = 0.f;
 #pragma unroll
@@ -191,8 +217,24 @@ __global__ __launch_bounds__(kThreads) void k_attn_fwd(const T* __restrict__ qkv
           for (int c = 0; c < NS; ++c) oacc[c] = mfma(p[c * 16], st[t][e], oacc[c]);
         }
     }
-    if (kt + 1 < tiles) in.store(smem[(kt + 1) & 1][0], smem[(kt + 1) & 1][1], tid);
+    if (kt + SETS < tiles) in.store(smem[(i + 1) & 1][0], smem[(i + 1) & 1][1], tid);
     __syncthreads();
+  }
+  if (SETS == 2) {   // the other set's maximum, sum and outputs come over through LDS; it may have seen no key (-inf, 0, 0)
+    if (set == 1) {
+      float* p = give<HD>(&smem_all[0][0][0][0], oacc, tid);
+      p[0] = m_i;
+      p[kThreads] = l_i;
+    }
+    __syncthreads();
+    if (set == 1) return;
+    f32x4 o1[NS];
+    const float* p = take<HD>(&smem_all[0][0][0][0], o1, tid);
+    const float m1 = p[0], m_new = fmaxf(m_i, m1), a0 = expf(m_i - m_new), a1 = expf(m1 - m_new);
+    l_i = l_i * a0 + p[kThreads] * a1;
+    m_i = m_new;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) oacc[c] = oacc[c] * a0 + o1[c] * a1;
   }
   const float l = sum4(l_i);
   if (q < T_) {
@@ -206,14 +248,15 @@ __global__ __launch_bounds__(kThreads) void k_attn_fwd(const T* __restrict__ qkv
 // dq_i = sum_{j<=i} ds_ij k_j,  ds_ij = p_ij (dO_i.v_j - delta_i) / sqrt(hd),  p_ij = exp(s_ij - lse_i), and on the way
 // delta_i = dO_i.o_i for the dK/dV kernel, which runs after this one
 template <class T, int HD>
-__global__ __launch_bounds__(kThreads) void k_attn_bwd_dq(const T* __restrict__ qkv, const T* __restrict__ o, const float* __restrict__ lse,
+__global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* __restrict__ qkv, const T* __restrict__ o, const float* __restrict__ lse,
                                                           float* __restrict__ delta, const T* __restrict__ dO, int T_, int H, int Hkv,
                                                           int hd, bool vec, float scale, const float* __restrict__ rope_tab,
                                                           T* __restrict__ dqkv) {
-  constexpr int LD = HD + 4, NS = HD / 16;
-  __shared__ __attribute__((aligned(16))) float smem[2][2][KT * LD];
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int LD = HD + 4, NS = HD / 16, SETS = kSets<HD>;
+  __shared__ __attribute__((aligned(16))) float smem_all[SETS][2][2][KT * LD];
+  const int set = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
+  const int lane = tid & 63, lr = lane & 15, kg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto& smem = smem_all[set];
   const int a = blockIdx.y, b = blockIdx.z, kvh = a / (H / Hkv);
   const int q0 = (int)(gridDim.x - 1 - blockIdx.x) * BQ;
   const int qw0 = q0 + wave * 16, q = qw0 + lr, qc = min(q, T_ - 1);
@@ -233,18 +276,18 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_dq(const T* __restrict__ 
     dq[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   dlt = sum4(dlt);
-  if (q < T_ && kg == 0) delta[stat] = dlt;
+  if (q < T_ && kg == 0 && set == 0) delta[stat] = dlt;
   const float L = lse[stat];
   const int tiles = (min(T_, q0 + BQ) + KT - 1) / KT;
   Pair<T, HD> in;
-  in.load(kp, ld, vp, ld, 0, T_, hd, vec, tid);
+  in.load(kp, ld, vp, ld, set * KT, T_, hd, vec, tid);   // a row past the end is zeros
   in.store(smem[0][0], smem[0][1], tid);
   __syncthreads();
-  for (int kt = 0; kt < tiles; ++kt) {
-    const int k0 = kt * KT;
-    if (kt + 1 < tiles) in.load(kp, ld, vp, ld, k0 + KT, T_, hd, vec, tid);
-    const float *lk = smem[kt & 1][0], *lv = smem[kt & 1][1];
-    if (k0 <= qw0 + 15) {
+  for (int i = 0; i * SETS < tiles; ++i) {   // every wavefront the same number of rounds
+    const int kt = i * SETS + set, k0 = kt * KT;
+    if (kt + SETS < tiles) in.load(kp, ld, vp, ld, k0 + SETS * KT, T_, hd, vec, tid);
+    const float *lk = smem[i & 1][0], *lv = smem[i & 1][1];
+    if (kt < tiles && k0 <= qw0 + 15) {
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
@@ -271,8 +314,17 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_dq(const T* __restrict__ 
         }
       }
     }
-    if (kt + 1 < tiles) in.store(smem[(kt + 1) & 1][0], smem[(kt + 1) & 1][1], tid);
+    if (kt + SETS < tiles) in.store(smem[(i + 1) & 1][0], smem[(i + 1) & 1][1], tid);
     __syncthreads();
+  }
+  if (SETS == 2) {
+    if (set == 1) give<HD>(&smem_all[0][0][0][0], dq, tid);
+    __syncthreads();
+    if (set == 1) return;
+    f32x4 o1[NS];
+    take<HD>(&smem_all[0][0][0][0], o1, tid);
+#pragma unroll
+    for (int c = 0; c < NS; ++c) dq[c] += o1[c];
   }
   if (q < T_) {
 #pragma unroll
@@ -285,15 +337,17 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_dq(const T* __restrict__ 
 
 // dk_j = sum_a sum_{i>=j} ds_ij q_i ; dv_j = sum_a sum_{i>=j} p_ij dO_i   (a over the q heads of this kv head)
 template <class T, int HD>
-__global__ __launch_bounds__(kThreads) void k_attn_bwd_dkv(const T* __restrict__ qkv, const float* __restrict__ lse,
+__global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* __restrict__ qkv, const float* __restrict__ lse,
                                                            const float* __restrict__ delta, const T* __restrict__ dO, int T_, int H,
                                                            int Hkv, int hd, bool vec, float scale, const float* __restrict__ rope_tab,
                                                            T* __restrict__ dqkv) {
-  constexpr int LD = HD + 4, NS = HD / 16;
-  __shared__ __attribute__((aligned(16))) float smem[2][2][KT * LD];
-  __shared__ __attribute__((aligned(16))) float s_lse[2][KT], s_dlt[2][KT];
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int LD = HD + 4, NS = HD / 16, SETS = kSets<HD>;
+  __shared__ __attribute__((aligned(16))) float smem_all[SETS][2][2][KT * LD];
+  __shared__ __attribute__((aligned(16))) float s_lse_all[SETS][2][KT], s_dlt_all[SETS][2][KT];
+  const int set = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
+  const int lane = tid & 63, lr = lane & 15, kg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto& smem = smem_all[set];
+  auto &s_lse = s_lse_all[set], &s_dlt = s_dlt_all[set];
   const int kvh = blockIdx.y, b = blockIdx.z, rep = H / Hkv;
   const int k0 = blockIdx.x * BQ, kw0 = k0 + wave * 16, key = kw0 + lr, kc = min(key, T_ - 1);
   const int64_t ld = (int64_t)(H + 2 * Hkv) * hd, ldo = (int64_t)H * hd;
@@ -318,18 +372,18 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_dkv(const T* __restrict__
       in_dlt = delta[at];
     }
   };
-  auto put = [&](int step) {
-    in.store(smem[step & 1][0], smem[step & 1][1], tid);
-    if (tid < KT) { s_lse[step & 1][tid] = in_lse; s_dlt[step & 1][tid] = in_dlt; }
+  auto put = [&](int buf) {
+    in.store(smem[buf][0], smem[buf][1], tid);
+    if (tid < KT) { s_lse[buf][tid] = in_lse; s_dlt[buf][tid] = in_dlt; }
   };
-  fetch(0);
-  put(0);
+  if (set < steps) fetch(set), put(0);
   __syncthreads();
-  for (int step = 0; step < steps; ++step) {
-    if (step + 1 < steps) fetch(step + 1);
+  for (int i = 0; i * SETS < steps; ++i) {
+    const int step = i * SETS + set, buf = i & 1;
+    if (step + SETS < steps) fetch(step + SETS);
     const int qs = (t0 + step % nt) * KT;
-    const float *lq = smem[step & 1][0], *lo = smem[step & 1][1];
-    if (qs + KT - 1 >= kw0) {   // some query of the tile sees a key of this wavefront
+    const float *lq = smem[buf][0], *lo = smem[buf][1];
+    if (step < steps && qs + KT - 1 >= kw0) {   // some query of the tile sees a key of this wavefront
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
@@ -343,8 +397,8 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_dkv(const T* __restrict__
             dp = mfma(fo[e], vf[s][e], dp);
           }
         }
-        const f32x4 L = *reinterpret_cast<const f32x4*>(&s_lse[step & 1][t * 16 + kg * 4]);
-        const f32x4 D = *reinterpret_cast<const f32x4*>(&s_dlt[step & 1][t * 16 + kg * 4]);
+        const f32x4 L = *reinterpret_cast<const f32x4*>(&s_lse[buf][t * 16 + kg * 4]);
+        const f32x4 D = *reinterpret_cast<const f32x4*>(&s_dlt[buf][t * 16 + kg * 4]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int q = qs + t * 16 + kg * 4 + r;
@@ -363,8 +417,25 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_dkv(const T* __restrict__
         }
       }
     }
-    if (step + 1 < steps) put(step + 1);
+    if (step + SETS < steps) put(buf ^ 1);
     __syncthreads();
+  }
+  if (SETS == 2) {   // dk over in the first half of the buffers, dv in the second
+    float* half = &smem_all[SETS - 1][0][0][0];
+    if (set == 1) {
+      give<HD>(&smem_all[0][0][0][0], dk, tid);
+      give<HD>(half, dv, tid);
+    }
+    __syncthreads();
+    if (set == 1) return;
+    f32x4 o1[NS], o2[NS];
+    take<HD>(&smem_all[0][0][0][0], o1, tid);
+    take<HD>(half, o2, tid);
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      dk[c] += o1[c];
+      dv[c] += o2[c];
+    }
   }
   if (key < T_) {
     T* row = dqkv + ((int64_t)b * T_ + key) * ld;
@@ -393,7 +464,7 @@ template <class T>
 void fwd_t(hipStream_t s, int B, int T_, int H, int Hkv, int hd, const void* qkv, void* o, float* lse) {
   const bool vec = rows_of_four<T>(hd, qkv, o, nullptr, nullptr);
   const float scale = 1.0f / sqrtf((float)hd);
-#define SP_GO(HD) hipLaunchKernelGGL((k_attn_fwd<T, HD>), dim3((T_ + BQ - 1) / BQ, H, B), dim3(kThreads), 0, s, (const T*)qkv, T_, H, Hkv, hd, vec, scale, (T*)o, lse)
+#define SP_GO(HD) hipLaunchKernelGGL((k_attn_fwd<T, HD>), dim3((T_ + BQ - 1) / BQ, H, B), dim3(kThreads * kSets<HD>), 0, s, (const T*)qkv, T_, H, Hkv, hd, vec, scale, (T*)o, lse)
   SP_BY_HD(SP_GO);
 #undef SP_GO
 }
@@ -406,9 +477,9 @@ void bwd_t(hipStream_t s, int B, int T_, int H, int Hkv, int hd, const void* qkv
   const int nb = (T_ + BQ - 1) / BQ;
 #define SP_GO(HD)                                                                                                              \
   do {                                                                                                                         \
-    hipLaunchKernelGGL((k_attn_bwd_dq<T, HD>), dim3(nb, H, B), dim3(kThreads), 0, s, (const T*)qkv, (const T*)o, lse, delta,    \
+    hipLaunchKernelGGL((k_attn_bwd_dq<T, HD>), dim3(nb, H, B), dim3(kThreads * kSets<HD>), 0, s, (const T*)qkv, (const T*)o, lse, delta,    \
                        (const T*)dO, T_, H, Hkv, hd, vec, scale, rope_tab, (T*)dqkv);                                          \
-    hipLaunchKernelGGL((k_attn_bwd_dkv<T, HD>), dim3(nb, Hkv, B), dim3(kThreads), 0, s, (const T*)qkv, lse, delta, (const T*)dO, \
+    hipLaunchKernelGGL((k_attn_bwd_dkv<T, HD>), dim3(nb, Hkv, B), dim3(kThreads * kSets<HD>), 0, s, (const T*)qkv, lse, delta, (const T*)dO, \
                        T_, H, Hkv, hd, vec, scale, rope_tab, (T*)dqkv);                                                        \
   } while (0)
   SP_BY_HD(SP_GO);
