@@ -5,19 +5,21 @@
 //
 // Same plan as the bf16 kernels: a workgroup of four wavefronts (or two sets of four, below) owns 64 queries (16 per
 // wavefront; 64 keys in the dK/dV kernel) of one head and walks the other side in tiles of 32 rows through LDS, two
-// buffers, loaded into registers one tile ahead, one barrier per tile.  Scores are formed transposed, S^T[key][query] = K Q^T, so a lane
-// (query lane % 16) ends with the scores of keys 4 kg .. 4 kg + 3 (kg = lane / 16), and its row statistics are
-// per-lane scalars; the instruction's four k-slots may stand for any keys, so accumulator r of all lanes is directly
-// the operand of the r-th instruction of the next product (O^T += V^T P^T).  The dK/dV kernel is the mirror image.
+// buffers, loaded into registers one tile ahead, one barrier per tile.  Scores are formed transposed, S^T[key][query]
+// = K Q^T, so a lane (query lane % 16) ends with the scores of keys 4 kg .. 4 kg + 3 (kg = lane / 16), and its row
+// statistics are per-lane scalars; the instruction's four k-slots may stand for any keys, so accumulator r of all
+// lanes is directly the operand of the r-th instruction of the next product (O^T += V^T P^T).  The dK/dV kernel is
+// the mirror image.
 //
 // The row-wise operand of a product is one 16-byte LDS read per four instructions, the transposed one a 4-byte read
 // per instruction; LDS rows are padded by 16 bytes, which keeps both free of bank conflicts.  One LDS read per
-// 32-cycle instruction leaves LDS idle most of the time; what bounds a workgroup is the chain of its tiles.  HD is the head dimension rounded up to a compiled size; columns past the real one are zeros.
-// One wavefront per row of scores (the kernels these replaced) left the matrix cores idle and re-read K and V for
-// every query.  Measured, forward | backward (dQ and dK/dV), us: 6 sequences x 512 x 16 heads of 64 in float 542 -> 90
-// (36 TFLOP/s of the causal half) | 7825 -> 269; 16 x 256 x 6 heads of 48 129 -> 33 | 1522 -> 82; 2 x 64 x 6 heads of 48,
-// where launches are most of it, 8 | 30 -> 18 (the delta pass rides in the dQ kernel); the two sets took the heads of 48
-// on 256 positions from 27 | 75 to 21 | 63 beside the weight-gradient products.
+// 32-cycle instruction leaves LDS idle most of the time; what bounds a workgroup is the chain of its tiles.  HD is
+// the head dimension rounded up to a compiled size; columns past the real one are zeros. One wavefront per row of
+// scores (the kernels these replaced) left the matrix cores idle and re-read K and V for every query.  Measured,
+// forward | backward (dQ and dK/dV), us: 6 sequences x 512 x 16 heads of 64 in float 542 -> 90 (36 TFLOP/s of the
+// causal half) | 7825 -> 269; 16 x 256 x 6 heads of 48 129 -> 33 | 1522 -> 82; 2 x 64 x 6 heads of 48, where launches
+// are most of it, 8 | 30 -> 18 (the delta pass rides in the dQ kernel); the two sets took the heads of 48 on 256
+// positions from 27 | 75 to 21 | 63 beside the weight-gradient products.
 //
 // Layout: qkv rows of (H + 2*Hkv)*hd elements = query heads | key heads | value heads; rows are B sequences of T
 // positions; o rows of H*hd; lse[b][a][i] = log sum_j exp(q_i.k_j/sqrt(hd)).
