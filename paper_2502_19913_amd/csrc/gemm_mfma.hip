@@ -507,9 +507,12 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
 // One workgroup per CU is then the rule, so nothing but its own loads in flight hides the memory's latency: operand
 // tiles go through a ring of S steps in LDS, a slot is loaded again as soon as its fragments are in registers, S - 1
 // steps before it is waited for, and the fragments of step t + 1 are read while the MFMAs of step t run.  One
-// barrier per step.  The eight wavefronts are a 2 x 2 grid over the tile twice: wavefronts 0-3 take the first 32 k of
-// every step, 4-7 the other 32 (a wavefront's share is as square as the tile, so LDS reads stay level with the MFMAs:
-// 64 KB against 512 matrix cycles a step at TILE = 128), and the two halves' accumulators meet in LDS at the end.
+// barrier per step.  The eight wavefronts are a 2 x 2 grid over the tile twice.  Weight gradients: wavefronts 0-3 take
+// the first 32 k of every step, 4-7 the other 32 (a wavefront's share is as square as the tile, so LDS reads stay level
+// with the MFMAs: 64 KB against 512 matrix cycles a step at TILE = 128), and the two halves' accumulators meet in LDS at
+// the end.  Forward and input-gradient products: the two sets divide the rows of a share instead (96 KB of reads), so
+// that every output is summed in the order of k as in a 256-tile: their results are rounded to bf16, and a
+// microbatch's must not depend on the tile that the size of its group leads to.
 // A step of a 128-tile takes 0.5 us; 0.36 with the loads delivering zeros (LDS: 96 KB a step at 128 bytes a cycle), the
 // rest is the way from the L2s.  Against the two-slot loop of 128-tiles with one wait per step that stood here before:
 // NT 4096 x 1024 x 2816 34 -> 25 us, NN 1777 x 2048 x 11264 127 -> 96 us; TN (256-tiles before) 1024 x 1024 x 4096
@@ -564,6 +567,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__
   typedef Geo<TILE> G;
   typedef RingGeo<TILE> RG;
   constexpr int S = RG::S, NF = RG::NF, W = RG::W;
+  constexpr bool KH = OP == 2;                           // the sets divide k (else rows)
+  constexpr int Q = KH ? 1 : 2, NA = KH ? NF : NF / 2;   // k halves and row blocks of a wavefront
   __shared__ __attribute__((aligned(1024))) char smem[RG::kLdsBytes];
   static_assert(TILE * RG::kRowFloats * 4 <= RG::kLdsBytes && TILE * G::kCRowBytes <= RG::kLdsBytes, "staging fits");
   const int tid = threadIdx.x, lane = tid & 63;
@@ -608,16 +613,17 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__
       constexpr int v = decltype(n)::value;
       __builtin_amdgcn_s_waitcnt((v & 15) | (7 << 4) | (0 << 8) | ((v >> 4) << 14));
     };
-    struct Frags { bf16x8 a[NF], b[NF]; };
+    struct Frags { bf16x8 a[Q * NA], b[Q][NF]; };   // a: by k half, then row block; Q NA = NF
     auto read = [&](int j, int slot, Frags& f) {
       const char* ta = smem + slot * G::kStageBytes;
-      f.a[j] = read_frag<AS, TILE>(ta, wm * W + j * 16, hh, lane);
-      f.b[j] = read_frag<BS, TILE>(ta + G::kTileBytes, wn * W + j * 16, hh, lane);
+      f.a[j] = read_frag<AS, TILE>(ta, wm * W + (KH ? j : hh * NA + j % NA) * 16, KH ? hh : j / NA, lane);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) f.b[q][j] = read_frag<BS, TILE>(ta + G::kTileBytes, wn * W + j * 16, KH ? hh : q, lane);
     };
 
-    f32x4 acc[NF][NF];
+    f32x4 acc[NA][NF];
 #pragma unroll
-    for (int j = 0; j < NF; ++j)
+    for (int j = 0; j < NA; ++j)
 #pragma unroll
       for (int i = 0; i < NF; ++i)
 #pragma unroll
@@ -648,7 +654,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__
 #pragma unroll
       for (int j = 0; j < NF; ++j) {
 #pragma unroll
-        for (int i = 0; i < NF; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.b[i], now.a[j], acc[j][i], 0, 0, 0);
+        for (int i = 0; i < NF; ++i) acc[j % NA][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.b[j / NA][i], now.a[j], acc[j % NA][i], 0, 0, 0);
         read(j, after, next);
         issue(j, da, db, kt + S, slot);
         __builtin_amdgcn_sched_barrier(0);
@@ -660,31 +666,38 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__
       if (kt + 1 < nk) step(kt + 1, f1, f0);
     }
 
-    // ---- the two halves' sums meet: a wavefront gives its partner (wave ^ 4) the row blocks the partner finishes and
+    // ---- k halves: the two halves' sums meet: a wavefront gives its partner (wave ^ 4) the row blocks the partner finishes and
     // finishes the others, blocks hh * NF / 2 .. of the share
     wait(std::integral_constant<int, 0>());
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    f32x4* const swap = reinterpret_cast<f32x4*>(smem);
     f32x4 sum[NF / 2][NF];
+    if constexpr (KH) {
+      f32x4* const swap = reinterpret_cast<f32x4*>(smem);
 #pragma unroll
-    for (int j = 0; j < NF / 2; ++j)
+      for (int j = 0; j < NF / 2; ++j)
 #pragma unroll
-      for (int i = 0; i < NF; ++i) {
-        swap[((wave * (NF / 2) + j) * NF + i) * 64 + lane] = hh ? acc[j][i] : acc[j + NF / 2][i];
-        sum[j][i] = hh ? acc[j + NF / 2][i] : acc[j][i];
-      }
-    __syncthreads();
+        for (int i = 0; i < NF; ++i) {
+          swap[((wave * (NF / 2) + j) * NF + i) * 64 + lane] = hh ? acc[j][i] : acc[j + NF / 2][i];
+          sum[j][i] = hh ? acc[j + NF / 2][i] : acc[j][i];
+        }
+      __syncthreads();
 #pragma unroll
-    for (int j = 0; j < NF / 2; ++j)
+      for (int j = 0; j < NF / 2; ++j)
 #pragma unroll
-      for (int i = 0; i < NF; ++i) {
-        const f32x4 o = swap[(((wave ^ 4) * (NF / 2) + j) * NF + i) * 64 + lane];
+        for (int i = 0; i < NF; ++i) {
+          const f32x4 o = swap[(((wave ^ 4) * (NF / 2) + j) * NF + i) * 64 + lane];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sum[j][i][r] += o[r];
-      }
-    __syncthreads();
+          for (int r = 0; r < 4; ++r) sum[j][i][r] += o[r];
+        }
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int j = 0; j < NF / 2; ++j)
+#pragma unroll
+        for (int i = 0; i < NF; ++i) sum[j][i] = acc[j][i];
+    }
     // lane: row lane % 16 of a block, columns (lane / 16) * 4 .. + 3
     const int lm = lane & 15, kg = lane >> 4;
 #pragma unroll
