@@ -11,18 +11,22 @@
 // consecutive output columns of one row (16-byte stores, and whole rotary pairs for the epilogue); for op 2 the
 // tile of A is, so that a wavefront's atomics cover 64 contiguous bytes of four rows.
 //
-// Two kernels:
-//   k_gemm_f32        tiles of 128 x 128 or 64 x 64, four wavefronts, operands staged through LDS (global -> registers
-//                     one step ahead -> the other of two LDS buffers, one barrier per step of 32 k).  The matrix
-//                     instruction needs 32 cycles for 2 x 64 floats of operands, so LDS and memory keep up easily and
-//                     the kernel is bound by the matrix cores.
-//   k_gemm_f32_small  tiles of 32 x 32, eight wavefronts that divide the reduction between them, every wavefront
-//                     reading its fragments straight from memory (no LDS staging, no barrier until the eight partial
-//                     tiles meet): for products too small to fill the chip, where the time is one chain of latencies.
+// Kernels:
+//   k_gemm_f32           tiles of 128 x 128 or 64 x 64, four wavefronts, operands staged through LDS (global -> registers
+//                        one step ahead -> the other of two LDS buffers, one barrier per step of 32 k).  The matrix
+//                        instruction needs 32 cycles for 2 x 64 floats of operands, so LDS and memory keep up easily and
+//                        the kernel is bound by the matrix cores.
+//   k_gemm_f32_small     ops 0 and 1 too small to fill the chip with those: tiles of 32 x 32, four wavefronts with a block
+//                        of 16 x 16 each, eight steps in flight.  The time is one chain of latencies.
+//   k_gemm_f32_small_tn  op 2 likewise: tiles of 32 x 32, eight wavefronts that divide the reduction between them, every
+//                        wavefront reading its fragments straight from memory (no LDS staging, no barrier until the
+//                        eight partial tiles meet).
+// In ops 0 and 1 every entry is one sum in the order of k, with the same instructions, in all of them: the tile follows
+// the number of rows, and a microbatch's rows must not depend on how many microbatches share its group.
 // Measured against the vector-unit kernel they replaced (64 x 64 tiles, products and sums one lane at a time), us per
 // launch: op 0 3072 x 3072 x 1024 424 -> 191 (101 TFLOP/s of the 157 the cores peak at), op 1 2048 x 1024 x 5632 1109 ->
-// 235, op 2 864 x 288 x 4096 893 -> 30, and of the small ones op 0 128 x 288 x 768 95 -> 9.5, op 1 128 x 288 x 1536
-// 191 -> 14, most others at 8 (the launch).
+// 235, op 2 864 x 288 x 4096 893 -> 30, and of the small ones op 0 128 x 288 x 768 95 -> 8.8, op 1 128 x 288 x 1536
+// 191 -> 13, most others at 8 (the launch).
 #include <algorithm>
 
 #include "devutil.h"
@@ -275,9 +279,146 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
   }
 }
 
+// One thread's quad of a step's BK x T tile for the kernel below: T = 32 rows of 8 quads (k-contiguous) or 32 k of T / 4
+// quads (k-strided), on its way from memory to LDS.  A quad past an edge reads the last one inside again, so that loads
+// need no branches: past the end of k `masked` makes it zeros, past the last row or column nothing of it is stored.
+template <bool KS, bool VEC>
+struct Quad {
+  const float* p;   // start of the quad's row (k-contiguous) or of its first column (k-strided)
+  int kq, dx[3];    // its first k inside a step; k-strided and element-wise: where its other columns are
+  __device__ __forceinline__ void init(const float* X, int row, int ld, int k) { p = X + (int64_t)row * ld; kq = k; }
+  __device__ __forceinline__ void init_cols(const float* X, int col, int cols, int k) {
+    const int x = VEC ? min(col, cols - 4) : min(col, cols - 1);
+    p = X + x;
+    kq = k;
+#pragma unroll
+    for (int e = 1; e < 4; ++e) dx[e - 1] = min(col + e, cols - 1) - x;
+  }
+  __device__ __forceinline__ f32x4 load(int k0, int K, int ld) const {
+    const int k = k0 + kq;
+    if (KS) {
+      const float* q = p + (int64_t)min(k, K - 1) * ld;
+      if (VEC) return *reinterpret_cast<const f32x4*>(q);
+      return f32x4{q[0], q[dx[0]], q[dx[1]], q[dx[2]]};
+    }
+    if (VEC) return *reinterpret_cast<const f32x4*>(p + min(k, K - 4));
+    return f32x4{p[min(k, K - 1)], p[min(k + 1, K - 1)], p[min(k + 2, K - 1)], p[min(k + 3, K - 1)]};
+  }
+  __device__ __forceinline__ f32x4 masked(f32x4 v, int k0, int K) const {
+    const int left = K - (k0 + kq);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if ((KS || VEC ? 0 : e) >= left) v[e] = 0.f;
+    return v;
+  }
+};
+
+// Ops 0 and 1 in tiles of 32 x 32 (SwiGLU: 32 rows x 32 features): a wavefront owns a block of 16 x 16 (SwiGLU: of gate and
+// of up columns) over the whole reduction and sums it in the order of k, with the instructions of k_gemm_f32, so that a
+// row has the same bits whatever kernel the number of rows leads to.  That chain of K / 4 dependent matrix instructions
+// of 32 cycles (and the launch) bounds it: U steps of 32 k are in flight from memory (registers), one in LDS ahead of the
+// one whose fragments are read, and that one ahead of the one being multiplied; one barrier per step.  Through LDS because
+// fragments read straight from memory touch 16 half cache lines an instruction, about 60 cycles each: op 0, us, staged /
+// straight in the order of k / straight with k divided among eight wavefronts as it was before: 128 x 288 x 1536 15.0 /
+// 25.0 / 16.4, 1024 x 288 x 768 12.6 / 27.7 / 15.9, 64 x 1024 x 2816 24.9 / 40.2 / 28.2.
 template <int OP, int EPI, bool VEC>
-__global__ __launch_bounds__(64 * kSmallWaves) void k_gemm_f32_small(Args g) {
-  constexpr bool AS = OP == 2, BS = OP != 0;
+__global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
+  constexpr bool BS = OP == 1;
+  constexpr int T = 32, NB = EPI == kEpiSwiglu ? 2 : 1, U = 8;
+  typedef Tile<false, T, VEC> TA;
+  typedef Tile<BS, T, VEC> TB;
+  static_assert(TA::N4 == 1, "one quad of each tile per thread");
+  constexpr int kStage = TA::kFloats + NB * TB::kFloats;
+  __shared__ __attribute__((aligned(16))) float smem[2 * kStage];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  int tm, tn;
+  tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
+  const int m0 = tm * T, n0 = tn * T, K = g.K, steps = (K + BK - 1) / BK;
+  const int cols = EPI == kEpiSwiglu ? g.N / 2 : g.N, ldb = BS ? g.N : K;
+  f32x4 acc[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (steps > 0) {
+    Quad<false, VEC> qa;
+    Quad<BS, VEC> qb[NB];
+    qa.init(g.A, min(m0 + tid / 8, g.M - 1), K, tid % 8 * 4);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (BS) qb[i].init_cols(g.B, n0 + tid % 8 * 4, cols, tid / 8);
+      else qb[i].init(g.B, i * cols + min(n0 + tid / 8, cols - 1), K, tid % 8 * 4);
+    }
+    f32x4 ra[U], rb[U][NB];
+    auto fetch = [&](int s, int u) {   // past the last step: the last one again
+      const int k0 = min(s, steps - 1) * BK;
+      ra[u] = qa.load(k0, K, K);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) rb[u][i] = qb[i].load(k0, K, ldb);
+      __builtin_amdgcn_sched_barrier(0);   // loads stay in the order they are waited for
+    };
+    auto put = [&](int s, int u) {
+      float* st = smem + (s & 1) * kStage;
+      const int at = tid / 8 * (BK + 4) + tid % 8 * 4;   // BK = T: the same for either order
+      static_assert(BK == T, "tile rows of the two orders");
+      *reinterpret_cast<f32x4*>(st + at) = qa.masked(ra[u], s * BK, K);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x4*>(st + TA::kFloats + i * TB::kFloats + at) = qb[i].masked(rb[u][i], s * BK, K);
+    };
+    struct Frags { f32x4 a[BK / 16], b[BK / 16][NB]; };
+    auto read = [&](int s) {
+      const float* st = smem + (s & 1) * kStage;
+      Frags f;
+#pragma unroll
+      for (int q = 0; q < BK / 16; ++q) {
+        f.a[q] = TA::frag(st, wm * 16, q, lr, kg);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) f.b[q][i] = TB::frag(st + TA::kFloats + i * TB::kFloats, wn * 16, q, lr, kg);
+      }
+      return f;
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) fetch(u, u);
+    put(0, 0);
+    fetch(U, 0);
+    put(1, 1);
+    fetch(U + 1, 1);
+    __syncthreads();
+    Frags now = read(0);
+    __syncthreads();
+    // in LDS: step s + 1 and, from the middle of the step on, s + 2; on the way: the next U
+    auto step = [&](int s, int u, bool more) {   // u = (s + 2) % U
+      const Frags next = read(s + 1);
+#pragma unroll
+      for (int q = 0; q < BK / 16; ++q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(now.b[q][i][e], now.a[q][e], acc[i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (q == 0) {
+          put(s + 2, u);
+          if (more) fetch(s + 2 + U, u);
+        }
+      }
+      now = next;
+      __syncthreads();
+    };
+    int s = 0;
+    for (; s + U <= steps; s += U)
+#pragma unroll
+      for (int u = 0; u < U; ++u) step(s + u, (u + 2) % U, true);
+#pragma unroll
+    for (int u = 0; u < U - 1; ++u)   // the rest is on its way
+      if (s + u < steps) step(s + u, (u + 2) % U, false);
+  }
+  const int m = m0 + wm * 16 + lr, n = n0 + wn * 16 + kg * 4;
+  if (m >= g.M) return;
+  if (EPI == kEpiSwiglu) emit_swiglu<VEC>(g, m, n, acc[0], acc[NB - 1]);
+  else emit<OP, EPI, VEC>(g, m, n, acc[0]);
+}
+
+// Op 2 in tiles of 32 x 32: eight wavefronts divide the reduction between them.
+__global__ __launch_bounds__(64 * kSmallWaves) void k_gemm_f32_small_tn(Args g) {
   constexpr int T = 32, LD = T + 4, U = 3;   // U groups of 16 k per wavefront in flight
   __shared__ __attribute__((aligned(16))) float part[kSmallWaves][T * LD];
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
@@ -288,15 +429,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_gemm_f32_small(Args g) {
   const int m0 = tm * T, n0 = tn * T;
   const int kb = id / tiles * g.split_k, kend = min(g.K, kb + g.split_k), groups = (kend - kb + 15) / 16;
 
-  int arow[2], brow[2];   // memory rows (k-contiguous) or columns (k-strided) of this lane's two fragments, -1: none
+  int acol[2], bcol[2];   // memory columns of this lane's two fragments, -1: none
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int m = m0 + j * 16 + lr, n = n0 + j * 16 + lr;
-    arow[j] = m < g.M ? m : -1;
-    brow[j] = EPI == kEpiSwiglu ? swiglu_row<T, T>(tn, j * 16 + lr, g.N / 2) : (n < g.N ? n : -1);
+    acol[j] = m < g.M ? m : -1;
+    bcol[j] = n < g.N ? n : -1;
   }
-  auto frag_k = [&](const float* X, int row, int ld, int k) { return load4<VEC>(X + (int64_t)row * ld + k, row >= 0 ? kend - k : 0); };
-  auto frag_s = [&](const float* X, int col, int ld, int k) {
+  auto frag = [&](const float* X, int col, int ld, int k) {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -315,8 +455,8 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_gemm_f32_small(Args g) {
       const int k = kb + (q0 + u * kSmallWaves) * 16 + kg * 4;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        fa[u][j] = AS ? frag_s(g.A, arow[j], g.M, k) : frag_k(g.A, arow[j], g.K, k);
-        fb[u][j] = BS ? frag_s(g.B, brow[j], g.N, k) : frag_k(g.B, brow[j], g.K, k);
+        fa[u][j] = frag(g.A, acol[j], g.M, k);
+        fb[u][j] = frag(g.B, bcol[j], g.N, k);
       }
     }
 #pragma unroll
@@ -335,25 +475,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_gemm_f32_small(Args g) {
     for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4*>(&part[wave][(j * 16 + lr) * LD + i * 16 + kg * 4]) = acc[j][i];
   __syncthreads();
   if (tid >= T * T / 4) return;
-  auto total = [&](int at) {
-    f32x4 v = *reinterpret_cast<const f32x4*>(&part[0][at]);
-#pragma unroll
-    for (int w = 1; w < kSmallWaves; ++w) v += *reinterpret_cast<const f32x4*>(&part[w][at]);
-    return v;
-  };
   const int m = m0 + tid / (T / 4), nq = tid % (T / 4) * 4;
   if (m >= g.M) return;
-  const int at = tid / (T / 4) * LD + nq;
-  if (EPI == kEpiSwiglu) {
-    if (nq < T / 2) emit_swiglu<VEC>(g, m, tn * (T / 2) + nq, total(at), total(at + T / 2));
-  } else if (OP == 2) {
-    const f32x4 v = total(at);
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (n0 + nq + e < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n0 + nq + e, v[e]);
-  } else {
-    emit<OP, EPI, VEC>(g, m, n0 + nq, total(at));
-  }
+  for (int w = 0; w < kSmallWaves; ++w) v += *reinterpret_cast<const f32x4*>(&part[w][tid / (T / 4) * LD + nq]);
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (n0 + nq + e < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n0 + nq + e, v[e]);
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -371,7 +500,8 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0);
   auto tiles = [&](int t) {
     g.tiles_m = (int)((M + t - 1) / t);
-    g.tiles_n = (int)(epi == kEpiSwiglu ? (out + t / 2 - 1) / (t / 2) : (N + t - 1) / t);
+    const int w = epi == kEpiSwiglu && t != 32 ? t / 2 : t;   // stored columns a tile covers of one run
+    g.tiles_n = (int)((out + w - 1) / w);
     return (int64_t)g.tiles_m * g.tiles_n;
   };
   // Every CU runs its tiles at the rate of its matrix cores, so a product takes as long as the CU with the most
@@ -388,11 +518,16 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   if (g.split_k < BK) g.split_k = BK;
   runs = std::max<int64_t>(1, (K + g.split_k - 1) / g.split_k);
   const dim3 grid((unsigned)(n * runs));
+#define SP_GO_SMALL(OP, EPI, VEC)                                                                                       \
+  do {                                                                                                                  \
+    if constexpr (OP == 2) hipLaunchKernelGGL(k_gemm_f32_small_tn, grid, dim3(64 * kSmallWaves), 0, s, g);              \
+    else hipLaunchKernelGGL((k_gemm_f32_small<OP, EPI, VEC>), grid, dim3(kThreads), 0, s, g);                           \
+  } while (0)
 #define SP_GO(OP, EPI, VEC)                                                                                             \
   do {                                                                                                                  \
     if (tile == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, VEC>), grid, dim3(kThreads), 0, s, g);                \
     else if (tile == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, VEC>), grid, dim3(kThreads), 0, s, g);             \
-    else hipLaunchKernelGGL((k_gemm_f32_small<OP, EPI, VEC>), grid, dim3(64 * kSmallWaves), 0, s, g);                   \
+    else SP_GO_SMALL(OP, EPI, VEC);                                                                                     \
   } while (0)
 #define SP_GO_V(OP, EPI) do { if (vec) SP_GO(OP, EPI, true); else SP_GO(OP, EPI, false); } while (0)
   if (op == 0 && epi == kEpiRope) SP_GO_V(0, kEpiRope);
@@ -403,6 +538,7 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   else SP_GO_V(2, kEpiPlain);
 #undef SP_GO_V
 #undef SP_GO
+#undef SP_GO_SMALL
 }
 
 }  // namespace sp

@@ -6,7 +6,7 @@ import torch
 from oracle import skippipe_oracle as orc
 from paper_2502_19913_amd import binding as sp
 from paper_2502_19913_amd import synth
-from tests.gpuharness import maxerr, relerr, round_bf16
+from tests.gpuharness import maxerr, relerr, round_bf16, run
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +75,39 @@ def test_attention_of_any_head_dimension(B, T, H, Hkv, hd, dtype):
     assert relerr(o.float().cpu().numpy(), o_ref) < tol and maxerr(o.float().cpu().numpy(), o_ref) < worst
     got = dx.float().cpu().numpy()
     assert relerr(got, ref) < tol and maxerr(got, ref) < worst, (relerr(got, ref), maxerr(got, ref))
+
+# N, K: the 50M-shape products; widths and depths that are no multiple of 4 or 16; rows: some of them alone leave the chip
+# idle in tiles of 64 (fewer than 128 of those), all of them take tiles of 64 or (last) of 128
+@pytest.mark.parametrize("N,K,few,rows", [(288, 768, 1000, 2100), (768, 288, 65, 1100), (70, 35, 33, 6000), (288, 49, 17, 2100),
+                                          (512, 65, 300, 16384)])
+def test_float_rows_do_not_depend_on_their_number(N, K, few, rows):
+    # forward and input-gradient products are row-wise: a microbatch alone and in a group has the same bits
+    a = dev(synth.normal(44, f"ra{N}{K}", (rows, K))); b = dev(synth.normal(45, f"rb{N}{K}", (N, K))); r = dev(synth.normal(46, f"rr{N}{K}", (rows, N)))
+    gu = dev(synth.normal(47, f"rg{N}{K}", (rows, 2 * N)))
+    wgu = torch.cat([b, b.flip(0)])
+    bt = b.t().contiguous()
+    out = []
+    for n in (rows, few):
+        empty = lambda w: torch.empty((n, w), device="cuda")
+        c0, c1, up, act, dgu = empty(N), empty(N), empty(2 * N), empty(N), empty(2 * N)
+        sp.gemm(0, a[:n], b, c0, r[:n])
+        sp.gemm(1, a[:n], bt, c1)
+        sp.ffn_up_fwd(a[:n], wgu, up, act)
+        sp.ffn_down_bwd(a[:n], bt, gu[:n], dgu, empty(N))
+        out.append([x[:few].cpu().numpy() for x in (c0, c1, up, act, dgu)])
+    for name, x, y in zip(("op 0", "op 1", "gate|up", "act", "d(gate)|d(up)"), *out):
+        assert np.array_equal(x, y), (name, relerr(x, y))
+
+
+def test_float_stage_does_not_depend_on_grouping():
+    # 1024 rows alone leave the chip idle in tiles of 64, three microbatches together do not
+    cfg = dict(synth.CONFIGS["c1"], dim=288, n_heads=6, n_kv_heads=6, hidden=768, n_stages=2, layers_per_stage=1, seq_len=256, seqs_per_mb=4,
+               n_mb=3, local_stage_begin=1, local_stage_count=1, has_embed=0, has_head=0)
+    named = synth.make_params(cfg, 8, 0.1, 0.05)
+    x = synth.make_activations(cfg, 8); dy = synth.make_upstream_grad(cfg, 8)
+    paths, lens = np.array([[0, 1]] * 3, np.int32), np.array([2] * 3, np.int32)
+    a = run(cfg, named, paths, lens, x_in=x, dy_in=dy)
+    b = run(cfg, named, paths, lens, x_in=x, dy_in=dy, regroup=lambda plan: [(pos, st, [mb]) for pos, st, mbs in plan for mb in mbs])
+    assert np.array_equal(a["y"], b["y"]) and np.array_equal(a["dx"], b["dx"])
+    for k in a["grads"]:
+        assert relerr(a["grads"][k], b["grads"][k]) < 1e-5, k
