@@ -131,6 +131,110 @@ __device__ __forceinline__ void unrotate4(f32x4& v, const float* tab, int pos, i
 __device__ __forceinline__ float sum4(float v) { v += __shfl_xor(v, 16); return v + __shfl_xor(v, 32); }
 __device__ __forceinline__ float max4(float v) { v = fmaxf(v, __shfl_xor(v, 16)); return fmaxf(v, __shfl_xor(v, 32)); }
 
+// A masked probability (or score gradient) is zero, but zero times a value that is not finite is NaN, and the matrix
+// instruction takes every row of a tile for all of its columns: a NaN or an infinity would reach positions that do not see
+// its row.  So a wavefront whose sums come out as NaN forms those rows anew, each over the positions it sees (below): a
+// row that sees the value gets its NaN again, the others their results.  So do rows that met a whole tile of scores of
+// -inf first, whose running maximum is then no number to subtract.  A check of the sums once at the end costs nothing
+// that can be measured; looking through the one tile that a row sees in part cost 1 % of a pass (50M shape in bf16).
+
+// The rows (queries or keys, 16 a wavefront, bit lane % 16) with a NaN among a lane's sums.
+template <int NS>
+__device__ __forceinline__ uint32_t nan_rows(const f32x4 (&v)[NS]) {
+  f32x4 t = v[0];
+#pragma unroll
+  for (int c = 1; c < NS; ++c) t += v[c];   // infinities of both signs may add a row that has no NaN: no harm
+  const float u = (t[0] + t[1]) + (t[2] + t[3]);
+  const uint64_t m = __ballot(u != u);
+  return (uint32_t)(m | m >> 16 | m >> 32 | m >> 48) & 0xffffu;
+}
+
+// One wavefront: 64 positions at a time, then columns lane, lane + 64, ..
+template <class T>
+__device__ __forceinline__ float dot_rows(const T* a, const T* b, int hd) {
+  float d = 0.f;
+  for (int c = 0; c < hd; ++c) d += to_float(a[c]) * to_float(b[c]);
+  return d;
+}
+// acc[u] += sum over n rows, one per lane's w, of w * row[lane + 64 u]
+template <class T, int NU>
+__device__ __forceinline__ void add_rows(float (&acc)[NU], float w, const T* rows, int64_t ld, int n, int hd, int lane) {
+  for (int i = 0; i < n; ++i) {
+    const float x = __shfl(w, i);
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (lane + 64 * u < hd) acc[u] += x * to_float(rows[i * ld + lane + 64 * u]);
+  }
+}
+template <class T, int NU>
+__device__ __forceinline__ void put_row(T* row, const float (&v)[NU], int hd, int lane) {
+#pragma unroll
+  for (int u = 0; u < NU; ++u)
+    if (lane + 64 * u < hd) row[lane + 64 * u] = from_float<T>(v[u]);
+}
+// as unrotate4; the other value of a pair is the neighbouring lane's
+template <int NU>
+__device__ __forceinline__ void unrotate_row(float (&v)[NU], const float* tab, int pos, int hd, int lane) {
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int c = min(lane + 64 * u, hd - 1);
+    const float2 cs = reinterpret_cast<const float2*>(tab)[(int64_t)pos * (hd / 2) + c / 2];
+    const float other = __shfl_xor(v[u], 1);
+    v[u] = c & 1 ? v[u] * cs.x - other * cs.y : v[u] * cs.x + other * cs.y;
+  }
+}
+// a query over its n keys
+template <class T, int HD>
+__device__ void fwd_row(const T* q, const T* k, const T* v, int64_t ld, int n, int hd, float scale, T* o, float* lse, int lane) {
+  float m = -INFINITY, l = 0.f, acc[(HD + 63) / 64] = {};
+  for (int j = lane; j < n; j += 64) m = fmaxf(m, dot_rows(q, k + j * ld, hd) * scale);
+  m = wave_max(m);
+  for (int j0 = 0; j0 < n; j0 += 64) {
+    const float p = j0 + lane < n ? expf(dot_rows(q, k + (j0 + lane) * ld, hd) * scale - m) : 0.f;
+    l += p;
+    add_rows(acc, p, v + j0 * ld, ld, min(64, n - j0), hd, lane);
+  }
+  l = wave_sum(l);
+#pragma unroll
+  for (int u = 0; u < (HD + 63) / 64; ++u) acc[u] /= l;
+  put_row(o, acc, hd, lane);
+  if (lane == 0) *lse = m + logf(l);
+}
+template <class T, int HD>
+__device__ void dq_row(const T* q, const T* dO, const T* k, const T* v, int64_t ld, int n, int hd, float scale, float L, float dlt,
+                       const float* rope_tab, T* dq, int lane) {
+  float acc[(HD + 63) / 64] = {};
+  for (int j0 = 0; j0 < n; j0 += 64) {
+    float ds = 0.f;
+    if (j0 + lane < n) {
+      const int64_t at = (j0 + lane) * ld;
+      ds = expf(dot_rows(q, k + at, hd) * scale - L) * (dot_rows(dO, v + at, hd) - dlt) * scale;
+    }
+    add_rows(acc, ds, k + j0 * ld, ld, min(64, n - j0), hd, lane);
+  }
+  if (rope_tab) unrotate_row(acc, rope_tab, n - 1, hd, lane);
+  put_row(dq, acc, hd, lane);
+}
+// a key at position pos over the queries of `rep` heads from its position on; q, dO: the first of these heads at position 0
+template <class T, int HD>
+__device__ void dkv_row(const T* k, const T* v, const T* q, const T* dO, const float* lse, const float* delta, int64_t ld, int64_t ldo,
+                        int rep, int pos, int T_, int hd, float scale, const float* rope_tab, T* dk, T* dv, int lane) {
+  float ak[(HD + 63) / 64] = {}, av[(HD + 63) / 64] = {};
+  for (int a = 0; a < rep; ++a, q += hd, dO += hd, lse += T_, delta += T_)
+    for (int i0 = pos; i0 < T_; i0 += 64) {
+      float p = 0.f, ds = 0.f;
+      if (const int i = i0 + lane; i < T_) {
+        p = expf(dot_rows(q + i * ld, k, hd) * scale - lse[i]);
+        ds = p * (dot_rows(dO + i * ldo, v, hd) - delta[i]) * scale;
+      }
+      add_rows(ak, ds, q + i0 * ld, ld, min(64, T_ - i0), hd, lane);
+      add_rows(av, p, dO + i0 * ldo, ldo, min(64, T_ - i0), hd, lane);
+    }
+  if (rope_tab) unrotate_row(ak, rope_tab, pos, hd, lane);
+  put_row(dk, ak, hd, lane);
+  put_row(dv, av, hd, lane);
+}
+
 // Two matrices' tiles of KT rows on their way from memory to LDS: [KT][HD + 4] floats each.
 template <class T, int HD>
 struct Pair {
@@ -226,7 +330,7 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_fwd(const T* __re
           if (k0 + t * 16 + kg * 4 + r > q) st[t][r] = -INFINITY;
           mx = fmaxf(mx, st[t][r]);
         }
-      const float m_new = fmaxf(m_i, max4(mx) * scale);   // finite from the first tile on: its first key is visible to all
+      const float m_new = fmaxf(m_i, max4(mx) * scale);   // -inf while every score is: NaN, formed anew
       const float alpha = expf(m_i - m_new);
       float rs = 0.f;
 #pragma unroll
@@ -269,11 +373,18 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_fwd(const T* __re
     for (int c = 0; c < NS; ++c) oacc[c] = oacc[c] * a0 + o1[c] * a1;
   }
   const float l = sum4(l_i);
-  if (q < T_) {
+  uint32_t anew = nan_rows(oacc);
+  if (q < T_ && !(anew >> lr & 1)) {
     T* row = o + ((int64_t)b * T_ + q) * H * hd + a * hd;
 #pragma unroll
     for (int c = 0; c < NS; ++c) put4(row, c * 16 + kg * 4, hd, vec, oacc[c] / l);
     if (kg == 0) lse[((int64_t)b * H + a) * T_ + q] = m_i + logf(l);
+  }
+  for (; anew; anew &= anew - 1) {
+    const int r = qw0 + __builtin_ctz(anew);
+    if (r < T_)
+      fwd_row<T, HD>(base + r * ld + a * hd, kp, vp, ld, r + 1, hd, scale, o + ((int64_t)b * T_ + r) * H * hd + a * hd,
+                     lse + ((int64_t)b * H + a) * T_ + r, lane);
   }
 }
 
@@ -334,8 +445,8 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float p = k0 + t * 16 + kg * 4 + r > q ? 0.f : expf(st[r] * scale - L);
-          st[r] = p * (dp[r] - dlt) * scale;
+          const bool seen = k0 + t * 16 + kg * 4 + r <= q;
+          st[r] = seen ? expf(st[r] * scale - L) * (dp[r] - dlt) * scale : 0.f;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -357,12 +468,20 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
 #pragma unroll
     for (int c = 0; c < NS; ++c) dq[c] += o1[c];
   }
-  if (q < T_) {
+  uint32_t anew = nan_rows(dq);
+  if (q < T_ && !(anew >> lr & 1)) {
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
       if (rope_tab) unrotate4(dq[c], rope_tab, q, c * 16 + kg * 4, hd);
       put4(dqkv + row * ld + a * hd, c * 16 + kg * 4, hd, vec, dq[c]);
     }
+  }
+  for (; anew; anew &= anew - 1) {
+    const int i = __builtin_ctz(anew), r = qw0 + i;
+    const int64_t at = (int64_t)b * T_ + r;
+    if (r < T_)
+      dq_row<T, HD>(base + r * ld + a * hd, dO + at * H * hd + a * hd, kp, vp, ld, r + 1, hd, scale, __shfl(L, i), __shfl(dlt, i), rope_tab,
+                    dqkv + at * ld + a * hd, lane);
   }
 }
 
@@ -431,9 +550,9 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int q = qs + t * 16 + kg * 4 + r;
-          const float p = q >= key && q < T_ ? expf(st[r] * scale - L[r]) : 0.f;
-          st[r] = p;
-          dp[r] = p * (dp[r] - D[r]) * scale;
+          const bool seen = q >= key && q < T_;
+          st[r] = seen ? expf(st[r] * scale - L[r]) : 0.f;
+          dp[r] = seen ? st[r] * (dp[r] - D[r]) * scale : 0.f;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -466,7 +585,8 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
       dv[c] += o2[c];
     }
   }
-  if (key < T_) {
+  uint32_t anew = nan_rows(dk) | nan_rows(dv);
+  if (key < T_ && !(anew >> lr & 1)) {
     T* row = dqkv + ((int64_t)b * T_ + key) * ld;
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
@@ -474,6 +594,15 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
       put4(row + (H + kvh) * hd, c * 16 + kg * 4, hd, vec, dk[c]);
       put4(row + (H + Hkv + kvh) * hd, c * 16 + kg * 4, hd, vec, dv[c]);
     }
+  }
+  for (; anew; anew &= anew - 1) {
+    const int r = kw0 + __builtin_ctz(anew);
+    if (r >= T_) continue;
+    T* row = dqkv + ((int64_t)b * T_ + r) * ld;
+    const int64_t head = ((int64_t)b * H + kvh * rep) * T_;
+    dkv_row<T, HD>(base + r * ld + (H + kvh) * hd, base + r * ld + (H + Hkv + kvh) * hd, base + kvh * rep * hd,
+                   dO + (int64_t)b * T_ * ldo + kvh * rep * hd, lse + head, delta + head, ld, ldo, rep, r, T_, hd, scale, rope_tab,
+                   row + (H + kvh) * hd, row + (H + Hkv + kvh) * hd, lane);
   }
 }
 

@@ -111,3 +111,64 @@ def test_float_stage_does_not_depend_on_grouping():
     assert np.array_equal(a["y"], b["y"]) and np.array_equal(a["dx"], b["dx"])
     for k in a["grads"]:
         assert relerr(a["grads"][k], b["grads"][k]) < 1e-5, k
+
+def attention(qkv, do, dtype, B, T, H, Hkv, hd, o=None):
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    x = dev(qkv).to(dt)
+    out = torch.empty((B * T, H * hd), dtype=dt, device="cuda"); lse = torch.empty((B, H, T), device="cuda")
+    sp.attention_fwd(x, out, lse, B, T, H, Hkv, hd)
+    dx = torch.empty_like(x); delta = torch.empty(B * H * T, device="cuda")
+    sp.attention_bwd(x, out, lse, dev(do).to(dt), dx, delta, B, T, H, Hkv, hd)
+    return out.float().cpu().numpy(), dx.float().cpu().numpy().reshape(B * T, H + 2 * Hkv, hd)
+
+
+# two sets of wavefronts (hd <= 48) and one; a hidden dimension below its compiled size; a group of query heads
+@pytest.mark.parametrize("T,H,Hkv,hd", [(130, 2, 2, 48), (77, 2, 1, 10), (130, 2, 1, 96), (70, 2, 2, 200)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_attention_is_causal_for_non_finite_values(T, H, Hkv, hd, dtype, bad):
+    # a key or value that is not finite reaches the queries that see it and no earlier one; a query or upstream gradient
+    # that is not finite reaches the keys it sees and no later one
+    rnd = (lambda a: a) if dtype == "f32" else round_bf16
+    qkv = rnd(synth.normal(61, f"nq{T}{hd}", (T, (H + 2 * Hkv) * hd))); do = rnd(synth.normal(62, f"no{T}{hd}", (T, H * hd)))
+    o0, d0 = attention(qkv, do, dtype, 1, T, H, Hkv, hd)
+    # sums over the same values in another order where they are formed anew: the bounds of the test above
+    same = lambda got, want: np.isfinite(got).all() and relerr(got, want) < (2e-5 if dtype == "f32" else 2e-2)
+    at, col = 37, 3
+    other = np.arange(hd) != col
+    p = qkv.copy(); p[at, (H + Hkv) * hd + col] = bad            # v: one column of the outputs, from its position on
+    o, d = attention(p, do, dtype, 1, T, H, Hkv, hd)
+    assert same(o[:at], o0[:at]) and not np.isfinite(o[at:, col]).any() and same(o[at:, :hd][:, other], o0[at:, :hd][:, other])
+    assert same(d[:at, :H], d0[:at, :H])                         # dq
+    p = qkv.copy(); p[at, H * hd + col] = bad                    # k
+    o, d = attention(p, do, dtype, 1, T, H, Hkv, hd)
+    assert same(o[:at], o0[:at]) and same(d[:at, :H], d0[:at, :H])
+    p = qkv.copy(); p[at, col] = bad                             # q of head 0
+    o, d = attention(p, do, dtype, 1, T, H, Hkv, hd)
+    assert same(np.delete(o, at, 0), np.delete(o0, at, 0)) and not np.isfinite(o[at, :hd]).any()
+    assert same(np.delete(d, at, 0)[:, :H], np.delete(d0, at, 0)[:, :H]) and same(d[at + 1:, H:], d0[at + 1:, H:])
+    p = do.copy(); p[at, col] = bad                              # upstream gradient of head 0
+    o, d = attention(qkv, p, dtype, 1, T, H, Hkv, hd)
+    assert same(d[at + 1:, H:], d0[at + 1:, H:]) and not np.isfinite(d[:at + 1, H + Hkv, col]).any()
+    assert same(d[:at + 1, H + Hkv][:, other], d0[:at + 1, H + Hkv][:, other])   # dv's other columns
+
+# whole tiles of 32 keys that no query attends to: the first of a wavefront's walk (one set of wavefronts: keys 0 .. 31;
+# two sets: also keys 32 .. 63) and a later one
+@pytest.mark.parametrize("hd", [40, 96])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("lo", [0, 32, 64])
+def test_attention_over_keys_of_weight_zero(hd, dtype, lo):
+    T, H = 160, 2
+    rnd = (lambda a: a) if dtype == "f32" else round_bf16
+    qkv = rnd(synth.normal(63, f"iq{hd}", (T, 3, H, hd)).reshape(T, -1)).reshape(T, 3, H, hd)
+    qkv[:, 0, :, 0] = 1.0
+    qkv[lo:lo + 32, 1, :, 0] = -np.inf                            # their scores are -inf: weight 0
+    o, _ = attention(qkv.reshape(T, -1), np.zeros((T, H * hd), np.float32), dtype, 1, T, H, H, hd)
+    q, k, v = (qkv[:, i].astype(np.float64) for i in range(3))
+    s = np.stack([q[:, h] @ np.where(np.isinf(k[:, h]), 0, k[:, h]).T for h in range(H)]) / np.sqrt(hd)
+    s[:, :, lo:lo + 32] = -np.inf
+    s = np.where(np.tril(np.ones((T, T), bool)), s, -np.inf)
+    rows = np.arange(32 if lo == 0 else 0, T)                     # a row that sees no other key has no result
+    p = np.exp(s[:, rows] - s[:, rows].max(-1, keepdims=True)); p /= p.sum(-1, keepdims=True)
+    ref = np.stack([p[h] @ v[:, h] for h in range(H)], 1).reshape(len(rows), -1)
+    assert relerr(o[rows], ref) < (2e-5 if dtype == "f32" else 1e-2), relerr(o[rows], ref)
