@@ -16,16 +16,14 @@
 //                        one step ahead -> the other of two LDS buffers, one barrier per step of 32 k).  The matrix
 //                        instruction needs 32 cycles for 2 x 64 floats of operands, so LDS and memory keep up easily and
 //                        the kernel is bound by the matrix cores.
-//   k_gemm_f32_small     ops 0 and 1 too small to fill the chip with those: tiles of 32 x 32, four wavefronts with a block
+//   k_gemm_f32_small     for products too small to fill the chip with those: tiles of 32 x 32, four wavefronts with a block
 //                        of 16 x 16 each, eight steps in flight.  The time is one chain of latencies.
-//   k_gemm_f32_small_tn  op 2 likewise: tiles of 32 x 32, eight wavefronts that divide the reduction between them, every
-//                        wavefront reading its fragments straight from memory (no LDS staging, no barrier until the
-//                        eight partial tiles meet).
-// In ops 0 and 1 every entry is one sum in the order of k, with the same instructions, in all of them: the tile follows
-// the number of rows, and a microbatch's rows must not depend on how many microbatches share its group.
+// Every entry is one sum in the order of k, with the same instructions, in both: the tile of ops 0 and 1 follows the
+// number of rows, and a microbatch's rows must not depend on how many microbatches share its group; a weight gradient is
+// added with one atomic per entry and launch, so that it repeats to the bit.
 // Measured against the vector-unit kernel they replaced (64 x 64 tiles, products and sums one lane at a time), us per
 // launch: op 0 3072 x 3072 x 1024 424 -> 191 (101 TFLOP/s of the 157 the cores peak at), op 1 2048 x 1024 x 5632 1109 ->
-// 235, op 2 864 x 288 x 4096 893 -> 30, and of the small ones op 0 128 x 288 x 768 95 -> 8.8, op 1 128 x 288 x 1536
+// 235, op 2 864 x 288 x 4096 893 -> 31, and of the small ones op 0 128 x 288 x 768 95 -> 8.8, op 1 128 x 288 x 1536
 // 191 -> 13, most others at 8 (the launch).
 #include <algorithm>
 
@@ -40,14 +38,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int BK = 32;
 constexpr int kThreads = 256;
-constexpr int kSmallWaves = 8;   // wavefronts of the small kernel (the reduction is cut into as many shares)
 
 enum { kEpiPlain = 0, kEpiRope = 1, kEpiSwiglu = 2, kEpiSwigluBwd = 3 };   // as in the bf16 kernels
 
 struct Args {
   const float *A, *B, *R;
   float *C, *aux;
-  int M, N, K, tiles_m, tiles_n, split_k;   // split_k: k of one share (op 2), a multiple of BK
+  int M, N, K, tiles_m, tiles_n;
   RopeArgs rope;
 };
 
@@ -192,11 +189,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
   constexpr int kStage = TA::kFloats + TB::kFloats;
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-  const int tiles = g.tiles_m * g.tiles_n, id = xcd_major(blockIdx.x, gridDim.x);
   int tm, tn;
-  tile_of(g, id % tiles, tm, tn);
-  const int m0 = tm * T, n0 = tn * T;
-  const int kb = id / tiles * g.split_k, kend = min(g.K, kb + g.split_k), steps = (kend - kb + BK - 1) / BK;
+  tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
+  const int m0 = tm * T, n0 = tn * T, steps = (g.K + BK - 1) / BK;
 
   f32x4 acc[NB][NB];
 #pragma unroll
@@ -211,8 +206,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
   TA ta;
   TB tb;
   auto fetch = [&](int s) {
-    ta.load(g.A, g.M, AS ? g.M : g.K, m0, kb + s * BK, kend, tid, a_row);
-    tb.load(g.B, g.N, BS ? g.N : g.K, n0, kb + s * BK, kend, tid, b_row);
+    ta.load(g.A, g.M, AS ? g.M : g.K, m0, s * BK, g.K, tid, a_row);
+    tb.load(g.B, g.N, BS ? g.N : g.K, n0, s * BK, g.K, tid, b_row);
   };
   auto put = [&](int s) {
     float* st = smem + (s & 1) * kStage;
@@ -313,19 +308,21 @@ struct Quad {
   }
 };
 
-// Ops 0 and 1 in tiles of 32 x 32 (SwiGLU: 32 rows x 32 features): a wavefront owns a block of 16 x 16 (SwiGLU: of gate and
+// Tiles of 32 x 32 (SwiGLU: 32 rows x 32 features): a wavefront owns a block of 16 x 16 (SwiGLU: of gate and
 // of up columns) over the whole reduction and sums it in the order of k, with the instructions of k_gemm_f32, so that a
 // row has the same bits whatever kernel the number of rows leads to.  That chain of K / 4 dependent matrix instructions
 // of 32 cycles (and the launch) bounds it: U steps of 32 k are in flight from memory (registers), one in LDS ahead of the
 // one whose fragments are read, and that one ahead of the one being multiplied; one barrier per step.  Through LDS because
 // fragments read straight from memory touch 16 half cache lines an instruction, about 60 cycles each: op 0, us, staged /
 // straight in the order of k / straight with k divided among eight wavefronts as it was before: 128 x 288 x 1536 15.0 /
-// 25.0 / 16.4, 1024 x 288 x 768 12.6 / 27.7 / 15.9, 64 x 1024 x 2816 24.9 / 40.2 / 28.2.
+// 25.0 / 16.4, 1024 x 288 x 768 12.6 / 27.7 / 15.9, 64 x 1024 x 2816 24.9 / 40.2 / 28.2.  Op 2, one sum / the reduction cut
+// over workgroups and wavefronts and added in no fixed order as it was before: 864 x 288 x 512 7.8 / 12.3, x 2048 17.4 /
+// 18.0, x 4096 30.9 / 29.3, 1536 x 288 x 999 16.1 / 23.6, 4096 x 288 x 4096 112 / 165, but 288 x 288 x 4096 30.5 / 14.4.
 template <int OP, int EPI, bool VEC>
 __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
-  constexpr bool BS = OP == 1;
+  constexpr bool AS = OP == 2, BS = OP != 0;
   constexpr int T = 32, NB = EPI == kEpiSwiglu ? 2 : 1, U = 8;
-  typedef Tile<false, T, VEC> TA;
+  typedef Tile<AS, T, VEC> TA;
   typedef Tile<BS, T, VEC> TB;
   static_assert(TA::N4 == 1, "one quad of each tile per thread");
   constexpr int kStage = TA::kFloats + NB * TB::kFloats;
@@ -335,14 +332,15 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
   int tm, tn;
   tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
   const int m0 = tm * T, n0 = tn * T, K = g.K, steps = (K + BK - 1) / BK;
-  const int cols = EPI == kEpiSwiglu ? g.N / 2 : g.N, ldb = BS ? g.N : K;
+  const int cols = EPI == kEpiSwiglu ? g.N / 2 : g.N, lda = AS ? g.M : K, ldb = BS ? g.N : K;
   f32x4 acc[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (steps > 0) {
-    Quad<false, VEC> qa;
+    Quad<AS, VEC> qa;
     Quad<BS, VEC> qb[NB];
-    qa.init(g.A, min(m0 + tid / 8, g.M - 1), K, tid % 8 * 4);
+    if (AS) qa.init_cols(g.A, m0 + tid % 8 * 4, g.M, tid / 8);
+    else qa.init(g.A, min(m0 + tid / 8, g.M - 1), K, tid % 8 * 4);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       if (BS) qb[i].init_cols(g.B, n0 + tid % 8 * 4, cols, tid / 8);
@@ -351,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
     f32x4 ra[U], rb[U][NB];
     auto fetch = [&](int s, int u) {   // past the last step: the last one again
       const int k0 = min(s, steps - 1) * BK;
-      ra[u] = qa.load(k0, K, K);
+      ra[u] = qa.load(k0, K, lda);
 #pragma unroll
       for (int i = 0; i < NB; ++i) rb[u][i] = qb[i].load(k0, K, ldb);
       __builtin_amdgcn_sched_barrier(0);   // loads stay in the order they are waited for
@@ -393,7 +391,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(now.b[q][i][e], now.a[q][e], acc[i], 0, 0, 0);
+          for (int i = 0; i < NB; ++i)
+            acc[i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(now.a[q][e], now.b[q][i][e], acc[i], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_16x16x4f32(now.b[q][i][e], now.a[q][e], acc[i], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         if (q == 0) {
           put(s + 2, u);
@@ -411,78 +411,19 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
     for (int u = 0; u < U - 1; ++u)   // the rest is on its way
       if (s + u < steps) step(s + u, (u + 2) % U, false);
   }
+  if (OP == 2) {
+    const int n = n0 + wn * 16 + lr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + wm * 16 + kg * 4 + r;
+      if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, acc[0][r]);
+    }
+    return;
+  }
   const int m = m0 + wm * 16 + lr, n = n0 + wn * 16 + kg * 4;
   if (m >= g.M) return;
   if (EPI == kEpiSwiglu) emit_swiglu<VEC>(g, m, n, acc[0], acc[NB - 1]);
   else emit<OP, EPI, VEC>(g, m, n, acc[0]);
-}
-
-// Op 2 in tiles of 32 x 32: eight wavefronts divide the reduction between them.
-__global__ __launch_bounds__(64 * kSmallWaves) void k_gemm_f32_small_tn(Args g) {
-  constexpr int T = 32, LD = T + 4, U = 3;   // U groups of 16 k per wavefront in flight
-  __shared__ __attribute__((aligned(16))) float part[kSmallWaves][T * LD];
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tiles = g.tiles_m * g.tiles_n, id = xcd_major(blockIdx.x, gridDim.x);
-  int tm, tn;
-  tile_of(g, id % tiles, tm, tn);
-  const int m0 = tm * T, n0 = tn * T;
-  const int kb = id / tiles * g.split_k, kend = min(g.K, kb + g.split_k), groups = (kend - kb + 15) / 16;
-
-  int acol[2], bcol[2];   // memory columns of this lane's two fragments, -1: none
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int m = m0 + j * 16 + lr, n = n0 + j * 16 + lr;
-    acol[j] = m < g.M ? m : -1;
-    bcol[j] = n < g.N ? n : -1;
-  }
-  auto frag = [&](const float* X, int col, int ld, int k) {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (col >= 0 && k + e < kend) v[e] = X[(int64_t)(k + e) * ld + col];
-    return v;
-  };
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int q0 = wave; q0 < groups; q0 += U * kSmallWaves) {
-    f32x4 fa[U][2], fb[U][2];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {   // a group past the end reads nothing and adds zeros
-      const int k = kb + (q0 + u * kSmallWaves) * 16 + kg * 4;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        fa[u][j] = frag(g.A, acol[j], g.M, k);
-        fb[u][j] = frag(g.B, bcol[j], g.N, k);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[u][i][e], fa[u][j][e], acc[j][i], 0, 0, 0);
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4*>(&part[wave][(j * 16 + lr) * LD + i * 16 + kg * 4]) = acc[j][i];
-  __syncthreads();
-  if (tid >= T * T / 4) return;
-  const int m = m0 + tid / (T / 4), nq = tid % (T / 4) * 4;
-  if (m >= g.M) return;
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int w = 0; w < kSmallWaves; ++w) v += *reinterpret_cast<const f32x4*>(&part[w][tid / (T / 4) * LD + nq]);
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (n0 + nq + e < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n0 + nq + e, v[e]);
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -493,7 +434,7 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // gate|up, C = d(gate)|d(up)).
 void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R,
               const RopeArgs* rope, int epi, void* aux) {
-  Args g{(const float*)A, (const float*)B, (const float*)R, (float*)C, (float*)aux, (int)M, (int)N, (int)K, 0, 0, 0,
+  Args g{(const float*)A, (const float*)B, (const float*)R, (float*)C, (float*)aux, (int)M, (int)N, (int)K, 0, 0,
          rope ? *rope : RopeArgs{nullptr, 1, 2, 0}};
   if (rope) epi = kEpiRope;
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
@@ -509,25 +450,24 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   // and win where both come out alike (measured within 5 % of each other there).
   const int64_t cus = 256, t128 = tiles(128), t64 = tiles(64);
   const int64_t load128 = (t128 + cus - 1) / cus * 4, load64 = (t64 + cus - 1) / cus;
-  const int tile = load128 * 100 <= load64 * 105 ? 128 : (t64 >= 128 || (op == 2 && K >= 2048) ? 64 : 32);
-  const int64_t n = tiles(tile);
-  // a weight gradient (few tiles, long reduction) is cut along k until two workgroups per CU are busy
-  int64_t runs = 1;
-  if (op == 2) runs = std::max<int64_t>(1, std::min<int64_t>(512 / n, K / 128));
-  g.split_k = (int)((K + runs - 1) / runs + BK - 1) / BK * BK;
-  if (g.split_k < BK) g.split_k = BK;
-  runs = std::max<int64_t>(1, (K + g.split_k - 1) / g.split_k);
-  const dim3 grid((unsigned)(n * runs));
-#define SP_GO_SMALL(OP, EPI, VEC)                                                                                       \
-  do {                                                                                                                  \
-    if constexpr (OP == 2) hipLaunchKernelGGL(k_gemm_f32_small_tn, grid, dim3(64 * kSmallWaves), 0, s, g);              \
-    else hipLaunchKernelGGL((k_gemm_f32_small<OP, EPI, VEC>), grid, dim3(kThreads), 0, s, g);                           \
-  } while (0)
+  int tile = load128 * 100 <= load64 * 105 ? 128 : (t64 >= 128 ? 64 : 32);
+  if (op == 2) {
+    // A weight gradient is few tiles and a long reduction, and is not cut along k over workgroups: their sums would be added
+    // in the order in which they end, and no two passes of the mode that gradients are checked in would agree.  Tiles of 32
+    // keep their loads in flight and divide best, but read twice as much and take a tenth longer on a full chip: us, 32 / 64 /
+    // 128, 4096 x 288 x 2048 59 / 83 / 162, 1536 x 1024 x 1024 38 / 44 / 85, 2048 x 1024 x 3072 133 / 127 / 242, 3072 x 1024
+    // x 2048 133 / 120 / 167, 2048 x 2048 x 4096 342 / 308 / 325, 4096 x 4096 x 1024 369 / 308 / 294.  At one tile of 64 a CU
+    // (1024 x 1024 x 2048 47 / 60) the stage of the 500M shape is 0.4 % faster with 64, beside the other products.
+    const int64_t load32 = (tiles(32) + cus - 1) / cus;
+    if (tile == 128 && t128 < 2 * cus) tile = 64;
+    if (tile != 128) tile = load32 * 110 <= load64 * 400 ? 32 : 64;
+  }
+  const dim3 grid((unsigned)tiles(tile));
 #define SP_GO(OP, EPI, VEC)                                                                                             \
   do {                                                                                                                  \
     if (tile == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, VEC>), grid, dim3(kThreads), 0, s, g);                \
     else if (tile == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, VEC>), grid, dim3(kThreads), 0, s, g);             \
-    else SP_GO_SMALL(OP, EPI, VEC);                                                                                     \
+    else hipLaunchKernelGGL((k_gemm_f32_small<OP, EPI, VEC>), grid, dim3(kThreads), 0, s, g);                           \
   } while (0)
 #define SP_GO_V(OP, EPI) do { if (vec) SP_GO(OP, EPI, true); else SP_GO(OP, EPI, false); } while (0)
   if (op == 0 && epi == kEpiRope) SP_GO_V(0, kEpiRope);
@@ -538,7 +478,6 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   else SP_GO_V(2, kEpiPlain);
 #undef SP_GO_V
 #undef SP_GO
-#undef SP_GO_SMALL
 }
 
 }  // namespace sp

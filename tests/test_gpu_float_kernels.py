@@ -172,3 +172,17 @@ def test_attention_over_keys_of_weight_zero(hd, dtype, lo):
     p = np.exp(s[:, rows] - s[:, rows].max(-1, keepdims=True)); p /= p.sum(-1, keepdims=True)
     ref = np.stack([p[h] @ v[:, h] for h in range(H)], 1).reshape(len(rows), -1)
     assert relerr(o[rows], ref) < (2e-5 if dtype == "f32" else 1e-2), relerr(o[rows], ref)
+
+# few tiles and a long reduction: tiles of 64 and of 32, and ones that leave remainders
+@pytest.mark.parametrize("M,N,K", [(864, 288, 4096), (288, 288, 1000), (1024, 1024, 3072), (70, 66, 2049)])
+def test_float_weight_gradients_are_repeatable(M, N, K):
+    # in float every entry is summed in one order and added once: the same bits on every run
+    a = dev(synth.normal(48, f"pa{M}{K}", (K, M))); b = dev(synth.normal(49, f"pb{N}{K}", (K, N))); c0 = dev(synth.normal(50, f"pc{M}{N}", (M, N)))
+    got = []
+    for _ in range(6):
+        c = c0.clone()
+        sp.gemm(2, a, b, c)
+        got.append(c.cpu().numpy())
+    assert all(np.array_equal(g, got[0]) for g in got[1:])
+    want = a.cpu().numpy().astype(np.float64).T @ b.cpu().numpy().astype(np.float64) + c0.cpu().numpy()
+    assert relerr(got[0], want) < 2e-5 and maxerr(got[0], want) < 2e-5
