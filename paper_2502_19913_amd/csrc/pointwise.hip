@@ -796,7 +796,9 @@ void rmsnorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const 
 
 void rmsnorm_bwd_fold(hipStream_t s, RmsFold* fold, int d) {
   if (!fold->n) return;
+  const int pi = prof_start(PROF_RMSNORM_BWD, s);   // part of the norms' backward; their algorithmic bytes are counted there
   hipLaunchKernelGGL(k_colsum_add, dim3((d + 63) / 64, 8, fold->n), dim3(kBlock), 0, s, *fold, d);
+  prof_stop(pi, s, 0.0);
   fold->n = 0;
 }
 
