@@ -446,9 +446,9 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
     return (int64_t)g.tiles_m * g.tiles_n;
   };
   // Every CU runs its tiles at the rate of its matrix cores, so a product takes as long as the CU with the most
-  // output: ceil(tiles / 256) tiles.  Tiles of 64 divide the work more evenly; tiles of 128 read half as much per flop
+  // output: ceil(tiles / CUs) tiles.  Tiles of 64 divide the work more evenly; tiles of 128 read half as much per flop
   // and win where both come out alike (measured within 5 % of each other there).
-  const int64_t cus = 256, t128 = tiles(128), t64 = tiles(64);
+  const int64_t cus = cu_count(), t128 = tiles(128), t64 = tiles(64);
   const int64_t load128 = (t128 + cus - 1) / cus * 4, load64 = (t64 + cus - 1) / cus;
   int tile = load128 * 100 <= load64 * 105 ? 128 : (t64 >= 128 ? 64 : 32);
   if (op == 2) {

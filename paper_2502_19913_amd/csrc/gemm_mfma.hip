@@ -40,6 +40,16 @@
 
 namespace sp {
 
+int cu_count() {
+  static int n = 0;
+  if (!n) {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) n = v;
+    else n = 256;
+  }
+  return n;
+}
+
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -732,16 +742,6 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-
-int cu_count() {
-  static int n = 0;
-  if (!n) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) n = v;
-    else n = 256;
-  }
-  return n;
-}
 
 // Tile, tile grid and workgroups of a launch: the least of what each choice is expected to take, in microseconds,
 //   rounds of workgroups x (k-steps x step + ends)  +  op 2: runs x output bytes / atomics rate

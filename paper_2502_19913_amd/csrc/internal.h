@@ -96,6 +96,7 @@ int attention_bwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd
 int gemm_rope(hipStream_t s, int dtype, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
               const RopeArgs& ra, float rope_theta);
 
+int cu_count();   // compute units of the current device
 // building blocks the dispatchers choose between
 void gemm_simple(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R);
 // float, any shape; rope / epi / aux as for gemm_mfma
