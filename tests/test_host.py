@@ -166,3 +166,11 @@ def test_product_path_refuses_to_run_without_a_gpu():
             if f.endswith((".py", ".hip", ".cpp", ".h")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert not re.search(r"^\s*(from|import)\s+oracle|#include\s+\".*oracle", text, re.M), (dirpath, f)
+
+
+@pytest.mark.parametrize("dim,more", [(1024, True), (2048, False), (4096, False)])
+def test_gain_gradient_scratch_grows_with_the_layers_only_where_it_pays(dim, more):
+    # no saved visits: the scratch for the norms' partial sums is all that depends on the number of layers
+    cfg = dict(synth.CONFIGS["c1"], dim=dim, n_heads=16, n_kv_heads=16, hidden=256, dtype="bf16")
+    one, four = (sp.workspace_bytes(dict(cfg, layers_per_stage=n), 1, 0) for n in (1, 4))
+    assert four - one == (6 * 1024 * dim * 4 if more else 0)
