@@ -267,7 +267,7 @@ int sp_gemm(void* hip_stream, int dtype, int op, int M, int N, int K, const void
  * decoder layer: act = silu(gate) * up with [gate | up] = hn wgu^T, and its gradient), exposed for unit tests.
  *   sp_ffn_up_fwd:   gu[R, 2h] = hn[R, d] * wgu[2h, d]^T  and  act[R, h] = silu(gu[:, :h]) * gu[:, h:]
  *   sp_ffn_down_bwd: dgu[R, 2h] = d(gate) | d(up) for d(act) = dy[R, d] * wd[d, h] and the saved gu;
- *                    da_scratch [R, h] is used only where the fused kernel does not apply (float, odd shapes)
+ *                    da_scratch [R, h] is used only where the fused kernel does not apply (bfloat16 at odd shapes)
  * All tensors in dtype, row-major, dense. */
 int sp_ffn_up_fwd(void* hip_stream, int dtype, int R, int h, int d, const void* hn, const void* wgu, void* gu, void* act);
 int sp_ffn_down_bwd(void* hip_stream, int dtype, int R, int h, int d, const void* dy, const void* wd, const void* gu,
@@ -345,7 +345,7 @@ int sp_grad_reduce(void* hip_stream, const float* const* replica_grads, int n_re
  * product, 8 plain attention; and the bandwidth-bound kernels, whose "flops" entry holds algorithmic
  * BYTES instead: 4 attention delta (rows of o and dO read, one float per row and head written), 9 RMSNorm
  * forward, 10 RMSNorm backward (and, as launches of their own, the folds of its gain gradients), 11
- * cross-entropy, 12 slot gather / scatter, 13 SwiGLU as a pass of its own (float mode, odd shapes). */
+ * cross-entropy, 12 slot gather / scatter, 13 SwiGLU as a pass of its own (bfloat16 at odd shapes). */
 int sp_prof_begin(void);
 int sp_prof_end(int n_classes, double* ms, double* flops, int64_t* launches);
 

@@ -95,7 +95,7 @@ Carve carve(const sp_cfg& c, int n_mb_max, int n_visits_max) {
     w.t_dqkv[p] = take(Rmax * D.nq * D.E);
   }
   w.t_d2 = take(Rmax * D.d * D.E);
-  w.t_da = take(Rmax * D.h * D.E);
+  w.t_da = take(c.dtype == SP_F32 ? 0 : Rmax * D.h * D.E);   // d(act) where the product's epilogue does not take it
   w.t_delta = take(Rmax * D.H * sizeof(float));
   w.rope = take((size_t)D.T * (D.hd / 2) * 2 * sizeof(float));   // cos, sin per (position, pair)
   // per-block partial sums of the gain gradients of the norms that one launch folds

@@ -98,20 +98,20 @@ int gemm_rope(hipStream_t s, int dtype, int64_t M, int64_t N, int64_t K, const v
               const RopeArgs& ra, float rope_theta) {
   if (M < 0 || N < 0 || K < 0 || ra.hd < 2 || ra.hd % 2 || ra.rot_cols % ra.hd || ra.rot_cols > N || ra.T < 1)
     return fail(SP_EINVAL, "gemm_rope: bad shape");
-  if ((M > 0 && N > 0) && (!C || (K > 0 && (!A || !B)))) return fail(SP_EINVAL, "gemm_rope: null operand");
+  if ((M > 0 && N > 0) && (!C || !ra.table || (K > 0 && (!A || !B)))) return fail(SP_EINVAL, "gemm_rope: null operand");
   if (M == 0 || N == 0) return SP_OK;
-  if (dtype == SP_F32 && ra.table) {
+  if (dtype == SP_F32) {
     const int pi = prof_start(PROF_GEMM_PLAIN, s);
     gemm_f32(s, 0, M, N, K, A, B, C, nullptr, &ra, 0, nullptr);
     prof_stop(pi, s, 2.0 * (double)M * (double)N * (double)K);
     return SP_OK;
   }
   // fused when the matrix-core path takes the product and a 16-byte output chunk never straddles a head
-  const bool fast = dtype == SP_BF16 && ra.table && ra.hd % 8 == 0 && gemm_mfma_supported(0, M, N, K, A, B, C, nullptr);
+  const bool fast = ra.hd % 8 == 0 && gemm_mfma_supported(0, M, N, K, A, B, C, nullptr);
   if (!fast) {
     int rc = gemm(s, dtype, 0, M, N, K, A, B, C, nullptr);
     if (rc) return rc;
-    rope(s, dtype, C, M, ra.T, ra.rot_cols / ra.hd, ra.hd, (int)N, rope_theta);
+    rope(s, C, M, ra.T, ra.rot_cols / ra.hd, ra.hd, (int)N, rope_theta);
     return SP_OK;
   }
   const int pi = prof_start(0, s);
@@ -138,7 +138,7 @@ int ffn_up_fwd(hipStream_t s, int dtype, int64_t R, int64_t h, int64_t d, const 
   }
   int rc = gemm(s, dtype, 0, R, 2 * h, d, hn, wgu, gu, nullptr);
   if (rc) return rc;
-  swiglu_fwd(s, dtype, gu, R, (int)h, act);
+  swiglu_fwd(s, gu, R, (int)h, act);
   return SP_OK;
 }
 
@@ -161,7 +161,7 @@ int ffn_down_bwd(hipStream_t s, int dtype, int64_t R, int64_t h, int64_t d, cons
   }
   int rc = gemm(s, dtype, 1, R, h, d, dy, wd, da_tmp, nullptr);
   if (rc) return rc;
-  swiglu_bwd(s, dtype, da_tmp, gu, R, (int)h, dgu);
+  swiglu_bwd(s, da_tmp, gu, R, (int)h, dgu);
   return SP_OK;
 }
 

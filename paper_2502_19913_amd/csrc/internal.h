@@ -68,8 +68,8 @@ inline int rms_fold_places(int d, int norms) { return d <= 1024 ? (norms < kRmsF
 void rmsnorm_bwd_fold(hipStream_t s, RmsFold* fold, int d);
 void rmsnorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const void* g, const float* rstd,
                  const void* dres, int64_t R, int d, void* dx, float* dg, float* part, int64_t part_floats, RmsFold* fold);
-// rotates the first nheads*hd columns of every row (row_stride elements apart); position = row % T
-void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta);
+// bf16: rotates the first nheads*hd columns of every row (row_stride elements apart); position = row % T
+void rope(hipStream_t s, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta);
 // table[(p * hd/2 + i) * 2 + {0, 1}] = cos, sin of p * theta^(-2i/hd), the angles rope() uses, for p < T
 void rope_table(hipStream_t s, int T, int hd, float theta, float* table);
 // Rotation fused into a producer: the leading rot_cols columns of a row are heads of hd columns whose pairs
@@ -78,8 +78,9 @@ struct RopeArgs {
   const float* table;
   int T, hd, rot_cols;
 };
-void swiglu_fwd(hipStream_t s, int dtype, const void* gu, int64_t R, int h, void* a);
-void swiglu_bwd(hipStream_t s, int dtype, const void* da, const void* gu, int64_t R, int h, void* dgu);
+// bf16; a = silu(gate) * up and its gradient as passes of their own
+void swiglu_fwd(hipStream_t s, const void* gu, int64_t R, int h, void* a);
+void swiglu_bwd(hipStream_t s, const void* da, const void* gu, int64_t R, int h, void* dgu);
 // counts[mb] = number of targets in [0, V) among the rows of microbatch mb; a target below -1 or >= V sets *bad
 void count_targets(hipStream_t s, const int32_t* tgt, int n_mb, int64_t rows_per_mb, int V, int32_t* counts,
                    int32_t* bad);

@@ -393,9 +393,9 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_scalar(const T* __restri
 }
 
 // ------------------------------------------------------------------------------------------ rotary embedding
-// One thread turns one pair.  pairs_per_row = nheads*hd/2; angle = (row % T) * theta^(-2i/hd).
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_rope(T* __restrict__ qk, int64_t R, int T_, int pairs_per_row, int hd,
+// bf16 at shapes the products' rotary epilogue does not take.  One thread turns one pair.  pairs_per_row =
+// nheads*hd/2; angle = (row % T) * theta^(-2i/hd).
+__global__ __launch_bounds__(kBlock) void k_rope(bf16* __restrict__ qk, int64_t R, int T_, int pairs_per_row, int hd,
                                                  int row_stride, float log2_theta) {
   const int64_t total = R * pairs_per_row;
   const int half = hd / 2;
@@ -407,10 +407,10 @@ __global__ __launch_bounds__(kBlock) void k_rope(T* __restrict__ qk, int64_t R, 
     float inv = exp2f(-(float)(2 * i) / (float)hd * log2_theta);
     float sn, cs;
     sincosf((float)p * inv, &sn, &cs);
-    T* v = qk + r * row_stride + 2 * pr;
+    bf16* v = qk + r * row_stride + 2 * pr;
     float a = to_float(v[0]), b = to_float(v[1]);
-    v[0] = from_float<T>(a * cs - b * sn);
-    v[1] = from_float<T>(a * sn + b * cs);
+    v[0] = from_float<bf16>(a * cs - b * sn);
+    v[1] = from_float<bf16>(a * sn + b * cs);
   }
 }
 
@@ -427,8 +427,8 @@ __global__ __launch_bounds__(kBlock) void k_rope_table(float2* __restrict__ tabl
 }
 
 // ------------------------------------------------------------------------------------------ SwiGLU
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_swiglu_fwd(const T* __restrict__ gu, int64_t R, int h, T* __restrict__ a) {
+// bf16 at shapes the products' epilogues do not take (in float they take all)
+__global__ __launch_bounds__(kBlock) void k_swiglu_fwd(const bf16* __restrict__ gu, int64_t R, int h, bf16* __restrict__ a) {
   const int hv = h / 8;
   const int64_t total = R * hv;
   for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * kBlock) {
@@ -443,9 +443,8 @@ __global__ __launch_bounds__(kBlock) void k_swiglu_fwd(const T* __restrict__ gu,
   }
 }
 
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_swiglu_bwd(const T* __restrict__ da, const T* __restrict__ gu, int64_t R,
-                                                       int h, T* __restrict__ dgu) {
+__global__ __launch_bounds__(kBlock) void k_swiglu_bwd(const bf16* __restrict__ da, const bf16* __restrict__ gu, int64_t R,
+                                                       int h, bf16* __restrict__ dgu) {
   const int hv = h / 8;
   const int64_t total = R * hv;
   for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * kBlock) {
@@ -466,29 +465,27 @@ __global__ __launch_bounds__(kBlock) void k_swiglu_bwd(const T* __restrict__ da,
   }
 }
 
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_swiglu_fwd_scalar(const T* __restrict__ gu, int64_t R, int h,
-                                                              T* __restrict__ a) {
+__global__ __launch_bounds__(kBlock) void k_swiglu_fwd_scalar(const bf16* __restrict__ gu, int64_t R, int h,
+                                                              bf16* __restrict__ a) {
   const int64_t total = R * h;
   for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * kBlock) {
     int64_t r = idx / h;
     int c = (int)(idx - r * h);
     float g = to_float(gu[r * 2 * h + c]), u = to_float(gu[r * 2 * h + h + c]);
-    a[idx] = from_float<T>(g / (1.0f + expf(-g)) * u);
+    a[idx] = from_float<bf16>(g / (1.0f + expf(-g)) * u);
   }
 }
 
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_swiglu_bwd_scalar(const T* __restrict__ da, const T* __restrict__ gu,
-                                                              int64_t R, int h, T* __restrict__ dgu) {
+__global__ __launch_bounds__(kBlock) void k_swiglu_bwd_scalar(const bf16* __restrict__ da, const bf16* __restrict__ gu,
+                                                              int64_t R, int h, bf16* __restrict__ dgu) {
   const int64_t total = R * h;
   for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * kBlock) {
     int64_t r = idx / h;
     int c = (int)(idx - r * h);
     float g = to_float(gu[r * 2 * h + c]), u = to_float(gu[r * 2 * h + h + c]), d = to_float(da[idx]);
     float sg = 1.0f / (1.0f + expf(-g));
-    dgu[r * 2 * h + c] = from_float<T>(d * u * sg * (1.0f + g * (1.0f - sg)));
-    dgu[r * 2 * h + h + c] = from_float<T>(d * g * sg);
+    dgu[r * 2 * h + c] = from_float<bf16>(d * u * sg * (1.0f + g * (1.0f - sg)));
+    dgu[r * 2 * h + h + c] = from_float<bf16>(d * g * sg);
   }
 }
 
@@ -803,15 +800,11 @@ void rmsnorm_bwd_fold(hipStream_t s, RmsFold* fold, int d) {
   fold->n = 0;
 }
 
-void rope(hipStream_t s, int dtype, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta) {
+void rope(hipStream_t s, void* qk, int64_t R, int T, int nheads, int hd, int row_stride, float theta) {
   if (R <= 0) return;
   int pairs = nheads * hd / 2;
   int grid = grid_for_rows(R * pairs, kBlock * 2, 16384);
-  float l2 = log2f(theta);
-  if (dtype == SP_BF16)
-    hipLaunchKernelGGL(k_rope<bf16>, dim3(grid), dim3(kBlock), 0, s, (bf16*)qk, R, T, pairs, hd, row_stride, l2);
-  else
-    hipLaunchKernelGGL(k_rope<float>, dim3(grid), dim3(kBlock), 0, s, (float*)qk, R, T, pairs, hd, row_stride, l2);
+  hipLaunchKernelGGL(k_rope, dim3(grid), dim3(kBlock), 0, s, (bf16*)qk, R, T, pairs, hd, row_stride, log2f(theta));
 }
 
 void rope_table(hipStream_t s, int T, int hd, float theta, float* table) {
@@ -820,33 +813,24 @@ void rope_table(hipStream_t s, int T, int hd, float theta, float* table) {
   hipLaunchKernelGGL(k_rope_table, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (float2*)table, T, hd, log2f(theta));
 }
 
-template <class T>
-static void swiglu_t(hipStream_t s, bool bwd, const T* da, const T* gu, int64_t R, int h, T* out) {
+void swiglu_fwd(hipStream_t s, const void* gu, int64_t R, int h, void* a) {
   if (R <= 0) return;
-  bool vec = h % 8 == 0 && aligned16<T>(gu) && aligned16<T>(out) && (!bwd || aligned16<T>(da));
-  int64_t work = vec ? R * (h / 8) : R * (int64_t)h;
-  int grid = grid_for_rows(work, kBlock * 2, 16384);
-  if (vec) {
-    if (bwd) hipLaunchKernelGGL(k_swiglu_bwd<T>, dim3(grid), dim3(kBlock), 0, s, da, gu, R, h, out);
-    else hipLaunchKernelGGL(k_swiglu_fwd<T>, dim3(grid), dim3(kBlock), 0, s, gu, R, h, out);
-  } else {
-    if (bwd) hipLaunchKernelGGL(k_swiglu_bwd_scalar<T>, dim3(grid), dim3(kBlock), 0, s, da, gu, R, h, out);
-    else hipLaunchKernelGGL(k_swiglu_fwd_scalar<T>, dim3(grid), dim3(kBlock), 0, s, gu, R, h, out);
-  }
+  const int pi = prof_start(PROF_SWIGLU, s);
+  const bool vec = h % 8 == 0 && aligned16<bf16>((const bf16*)gu) && aligned16<bf16>((const bf16*)a);
+  const dim3 grid(grid_for_rows(vec ? R * (h / 8) : R * (int64_t)h, kBlock * 2, 16384));
+  if (vec) hipLaunchKernelGGL(k_swiglu_fwd, grid, dim3(kBlock), 0, s, (const bf16*)gu, R, h, (bf16*)a);
+  else hipLaunchKernelGGL(k_swiglu_fwd_scalar, grid, dim3(kBlock), 0, s, (const bf16*)gu, R, h, (bf16*)a);
+  prof_stop(pi, s, 3.0 * R * h * 2);
 }
 
-void swiglu_fwd(hipStream_t s, int dtype, const void* gu, int64_t R, int h, void* a) {
+void swiglu_bwd(hipStream_t s, const void* da, const void* gu, int64_t R, int h, void* dgu) {
+  if (R <= 0) return;
   const int pi = prof_start(PROF_SWIGLU, s);
-  struct Stop { int pi; hipStream_t s; double b; ~Stop() { prof_stop(pi, s, b); } } stop{pi, s, 3.0 * R * h * elt_size(dtype)};
-  if (dtype == SP_BF16) swiglu_t<bf16>(s, false, nullptr, (const bf16*)gu, R, h, (bf16*)a);
-  else swiglu_t<float>(s, false, nullptr, (const float*)gu, R, h, (float*)a);
-}
-
-void swiglu_bwd(hipStream_t s, int dtype, const void* da, const void* gu, int64_t R, int h, void* dgu) {
-  const int pi = prof_start(PROF_SWIGLU, s);
-  struct Stop { int pi; hipStream_t s; double b; ~Stop() { prof_stop(pi, s, b); } } stop{pi, s, 5.0 * R * h * elt_size(dtype)};
-  if (dtype == SP_BF16) swiglu_t<bf16>(s, true, (const bf16*)da, (const bf16*)gu, R, h, (bf16*)dgu);
-  else swiglu_t<float>(s, true, (const float*)da, (const float*)gu, R, h, (float*)dgu);
+  const bool vec = h % 8 == 0 && aligned16<bf16>((const bf16*)gu) && aligned16<bf16>((const bf16*)dgu) && aligned16<bf16>((const bf16*)da);
+  const dim3 grid(grid_for_rows(vec ? R * (h / 8) : R * (int64_t)h, kBlock * 2, 16384));
+  if (vec) hipLaunchKernelGGL(k_swiglu_bwd, grid, dim3(kBlock), 0, s, (const bf16*)da, (const bf16*)gu, R, h, (bf16*)dgu);
+  else hipLaunchKernelGGL(k_swiglu_bwd_scalar, grid, dim3(kBlock), 0, s, (const bf16*)da, (const bf16*)gu, R, h, (bf16*)dgu);
+  prof_stop(pi, s, 5.0 * R * h * 2);
 }
 
 void count_targets(hipStream_t s, const int32_t* tgt, int n_mb, int64_t rows_per_mb, int V, int32_t* counts,
