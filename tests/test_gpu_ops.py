@@ -56,6 +56,24 @@ def test_gemm_three_layouts(M, N, K, dtype):
     assert relerr(got2, ref2) < (2e-5 if dtype == "f32" else 2e-5), (relerr(got2, ref2))
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (65, 50, 36), (64, 64, 15), (130, 77, 100), (63, 129, 1001)])
+def test_gemm_of_odd_shapes_bf16(M, N, K):
+    # widths that are no multiple of 8: the plain kernel, at and past its 64 x 64 x 16 tiles
+    a = round_bf16(synth.normal(31, f"oa{M}{N}{K}", (M, K))); b = round_bf16(synth.normal(32, f"ob{M}{N}{K}", (N, K)))
+    r = round_bf16(synth.normal(33, f"or{M}{N}{K}", (M, N)))
+    ref = a.astype(np.float64) @ b.astype(np.float64).T
+    bf = torch.bfloat16
+    buf = torch.full((M * N + 64,), 7.0, dtype=bf, device="cuda"); c = buf[:M * N].view(M, N)
+    for op, args, want in ((0, (dev(a, bf), dev(b, bf), c, dev(r, bf)), ref + r), (1, (dev(a, bf), dev(b.T, bf), c), ref)):
+        sp.gemm(op, *args)
+        got = c.float().cpu().numpy()
+        assert relerr(got, want) < 2.0 ** -8 and maxerr(got, want) < 2.0 ** -8, op      # float sums, one rounding of 2^-9
+        assert torch.all(buf[M * N:] == 7.0)
+    c2 = torch.full((M, N), 7.0, device="cuda")
+    sp.gemm(2, dev(a.T, bf), dev(b.T, bf), c2)
+    assert relerr(c2.cpu().numpy(), ref + 7.0) < 2e-5
+
+
 def test_gemm_long_reduction_split():
     # the weight-gradient shape: reduction over tokens, few output tiles
     K, M, N = 8192, 512, 264
@@ -95,7 +113,7 @@ def test_gemm_operand_larger_than_2gib():
 
 FFN_SHAPES = [  # R, h, d: tiles of 256 (h % 128 == 0) and of 128 (h % 64 == 0), ragged rows, ragged reduction,
     (1000, 1280, 264),      # and shapes the fused kernels do not take (h % 64 != 0)
-    (4096, 2816, 1024), (300, 192, 72), (5000, 1152, 520), (77, 96, 40), (2560, 5632, 128), (3000, 5632, 200),
+    (4096, 2816, 1024), (300, 192, 72), (5000, 1152, 520), (77, 96, 40), (2560, 5632, 128), (3000, 5632, 200), (45, 50, 36),
 ]
 
 

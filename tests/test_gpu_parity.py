@@ -89,13 +89,23 @@ def test_small_f32_skip_swap_gqa(whole_call):
 
 
 def test_odd_shapes_take_the_scalar_kernels_f32():
-    # nothing divisible by 8: dim 36 (hd 6), hidden 50, vocab 77, T 13
+    # nothing divisible by 8: dim 36 (hd 6), hidden 50, vocab 77, T 13 (norms, loss, copies; products take any shape)
     cfg = dict(SMALL, dim=36, n_heads=6, n_kv_heads=3, hidden=50, vocab=77, seq_len=13, seqs_per_mb=3, layers_per_stage=1,
                path_flags=sp.SP_SWAP_ANY_GAP)
     named, tok, tgt = inputs(cfg, 4, std=0.1, jitter=0.1)
     ref = orc.run_paths(cfg, named, PATHS5, LENS5, tokens=tok, targets=tgt)
     got = run(cfg, named, PATHS5, LENS5, tokens=tok, targets=tgt)
     check_f32(got, ref, "odd")
+
+
+def test_odd_shapes_take_the_scalar_kernels_bf16():
+    # the same, and the rotation (hd 6) and SwiGLU (hidden 50) as scalar passes of their own, all products on the plain kernel
+    cfg = dict(SMALL, dim=36, n_heads=6, n_kv_heads=3, hidden=50, vocab=77, seq_len=13, seqs_per_mb=3, layers_per_stage=1,
+               path_flags=sp.SP_SWAP_ANY_GAP, dtype="bf16")
+    named, tok, tgt = inputs(cfg, 4, std=0.1, jitter=0.1, bf16=True)
+    ref = orc.run_paths(cfg, named, PATHS5, LENS5, tokens=tok, targets=tgt)
+    got = run(cfg, named, PATHS5, LENS5, tokens=tok, targets=tgt)
+    check_bf16(got, ref, "odd")
 
 
 def test_grouping_does_not_change_the_result_f32():
