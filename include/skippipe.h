@@ -263,6 +263,12 @@ int sp_run_paths(sp_ctx* ctx, const void* params, const int32_t* tokens, const i
 int sp_gemm(void* hip_stream, int dtype, int op, int M, int N, int K, const void* A, const void* B, void* C,
             const void* R);
 
+/* Measurement aid (host only): how a product of 16-byte aligned operands is divided on the current device.  epilogue: 0
+ * none, 1 rotation, 2 SwiGLU (op 0 with N = 2h), 3 SwiGLU gradient (op 1 with N = h).  shape (host int32[3]): edge of the
+ * square tiles (0: the plain kernel), their number, workgroups (fewer than tiles: each takes several in turn; op 2 more:
+ * runs of the reduction). */
+int sp_gemm_shape(int dtype, int op, int M, int N, int K, int epilogue, int32_t* shape);
+
 /* The two feed-forward steps whose pointwise part rides in a matrix product's epilogue (the SwiGLU block of the
  * decoder layer: act = silu(gate) * up with [gate | up] = hn wgu^T, and its gradient), exposed for unit tests.
  *   sp_ffn_up_fwd:   gu[R, 2h] = hn[R, d] * wgu[2h, d]^T  and  act[R, h] = silu(gu[:, :h]) * gu[:, h:]

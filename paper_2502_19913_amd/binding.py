@@ -23,7 +23,7 @@ EXPORTS = ["sp_param_count", "sp_param_layout", "sp_workspace_bytes", "sp_make_p
            "sp_route_plan", "sp_schedule_paths", "sp_stage_sizes", "sp_strerror", "sp_create", "sp_destroy", "sp_reset", "sp_set_side_stream", "sp_embed_fwd", "sp_embed_bwd",
            "sp_stage_fwd", "sp_stage_bwd", "sp_head_fwd_bwd", "sp_run_paths", "sp_eval_paths", "sp_gemm", "sp_attention_fwd",
            "sp_attention_bwd", "sp_optim_workspace_bytes", "sp_optim_step", "sp_prof_begin", "sp_prof_end", "sp_input_status",
-           "sp_grad_reduce", "sp_optim_step_noalloc", "sp_ffn_up_fwd", "sp_ffn_down_bwd", "sp_probe_mfma_rate"]
+           "sp_grad_reduce", "sp_optim_step_noalloc", "sp_ffn_up_fwd", "sp_ffn_down_bwd", "sp_probe_mfma_rate", "sp_gemm_shape"]
 
 
 class SpCfg(C.Structure):
@@ -290,6 +290,13 @@ def gemm(op: int, A, B, C_out, R=None, stream=None):
         K, M = A.shape; N = B.shape[1]
     _check(lib().sp_gemm(_stream_ptr(stream), C.c_int(_dt(A)), C.c_int(op), C.c_int(M), C.c_int(N), C.c_int(K),
                          _dptr(A), _dptr(B), _dptr(C_out), _dptr(R)))
+
+
+def gemm_shape(dtype: int, op: int, M: int, N: int, K: int, epilogue: int = 0):
+    """(edge of the tiles, tiles, workgroups) of a product; epilogue: 0 none, 1 rotation, 2 SwiGLU, 3 its gradient."""
+    out = np.zeros(3, np.int32)
+    _check(lib().sp_gemm_shape(C.c_int(dtype), C.c_int(op), C.c_int(M), C.c_int(N), C.c_int(K), C.c_int(epilogue), _iptr(out)))
+    return tuple(int(v) for v in out)
 
 
 def ffn_up_fwd(hn, wgu, gu, act, stream=None):

@@ -628,6 +628,23 @@ int sp_gemm(void* hip_stream, int dtype, int op, int M, int N, int K, const void
   return SP_OK;
 }
 
+int sp_gemm_shape(int dtype, int op, int M, int N, int K, int epilogue, int32_t* shape) {
+  if (dtype != SP_F32 && dtype != SP_BF16) return fail(SP_EINVAL, "gemm_shape: unknown dtype");
+  if (!shape || op < 0 || op > 2 || M < 1 || N < 1 || K < 1 || epilogue < 0 || epilogue > 3 ||
+      (epilogue && op != (epilogue == 3 ? 1 : 0)) || (epilogue == 2 && N % 2))
+    return fail(SP_EINVAL, "gemm_shape: bad op, shape or epilogue");
+  GemmShape s{0, 0, 0};
+  if (dtype == SP_F32) s = gemm_f32_shape(op, M, N, K, epilogue);
+  else if (epilogue >= 2 && gemm_swiglu_supported(epilogue == 3, M, epilogue == 3 ? N : N / 2, K, nullptr, nullptr, nullptr, nullptr))
+    s = gemm_mfma_shape(op, M, N, K, epilogue);
+  else if (gemm_mfma_supported(op, M, N, K, nullptr, nullptr, nullptr, nullptr)) s = gemm_mfma_shape(op, M, N, K, epilogue >= 2 ? 0 : epilogue);
+  if (!s.tile) s.tiles = s.workgroups = ((M + 63) / 64) * ((N + 63) / 64);
+  shape[0] = s.tile;
+  shape[1] = s.tiles;
+  shape[2] = s.workgroups;
+  return SP_OK;
+}
+
 int sp_ffn_up_fwd(void* hip_stream, int dtype, int R, int h, int d, const void* hn, const void* wgu, void* gu, void* act) {
   if (dtype != SP_F32 && dtype != SP_BF16) return fail(SP_EINVAL, "ffn: unknown dtype");
   int rc = ffn_up_fwd((hipStream_t)hip_stream, dtype, R, h, d, hn, wgu, gu, act);

@@ -430,21 +430,15 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 
-// epi as in gemm_mfma: 0 plain (R optional), 1 rotary, 2 SwiGLU (N = 2h, aux = act), 3 SwiGLU backward (N = h, R =
-// gate|up, C = d(gate)|d(up)).
-void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R,
-              const RopeArgs* rope, int epi, void* aux) {
-  Args g{(const float*)A, (const float*)B, (const float*)R, (float*)C, (float*)aux, (int)M, (int)N, (int)K, 0, 0,
-         rope ? *rope : RopeArgs{nullptr, 1, 2, 0}};
-  if (rope) epi = kEpiRope;
+// Tile and its grid for a product.
+struct F32Shape { int tile, tm, tn; };
+static F32Shape choose_f32(int op, int64_t M, int64_t N, int64_t K, int epi) {
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
-  const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0);
-  auto tiles = [&](int t) {
-    g.tiles_m = (int)((M + t - 1) / t);
+  auto at = [&](int t) {
     const int w = epi == kEpiSwiglu && t != 32 ? t / 2 : t;   // stored columns a tile covers of one run
-    g.tiles_n = (int)((out + w - 1) / w);
-    return (int64_t)g.tiles_m * g.tiles_n;
+    return F32Shape{t, (int)((M + t - 1) / t), (int)((out + w - 1) / w)};
   };
+  auto tiles = [&](int t) { return (int64_t)at(t).tm * at(t).tn; };
   // Every CU runs its tiles at the rate of its matrix cores, so a product takes as long as the CU with the most
   // output: ceil(tiles / CUs) tiles.  Tiles of 64 divide the work more evenly; tiles of 128 read half as much per flop
   // and win where both come out alike (measured within 5 % of each other there).
@@ -462,7 +456,28 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
     if (tile == 128 && t128 < 2 * cus) tile = 64;
     if (tile != 128) tile = load32 * 110 <= load64 * 400 ? 32 : 64;
   }
-  const dim3 grid((unsigned)tiles(tile));
+  return at(tile);
+}
+
+GemmShape gemm_f32_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
+  const F32Shape c = choose_f32(op, M, N, K, epi);
+  return {c.tile, c.tm * c.tn, c.tm * c.tn};
+}
+
+// epi as in gemm_mfma: 0 plain (R optional), 1 rotary, 2 SwiGLU (N = 2h, aux = act), 3 SwiGLU backward (N = h, R =
+// gate|up, C = d(gate)|d(up)).
+void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R,
+              const RopeArgs* rope, int epi, void* aux) {
+  Args g{(const float*)A, (const float*)B, (const float*)R, (float*)C, (float*)aux, (int)M, (int)N, (int)K, 0, 0,
+         rope ? *rope : RopeArgs{nullptr, 1, 2, 0}};
+  if (rope) epi = kEpiRope;
+  const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
+  const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0);
+  const F32Shape c = choose_f32(op, M, N, K, epi);
+  const int tile = c.tile;
+  g.tiles_m = c.tm;
+  g.tiles_n = c.tn;
+  const dim3 grid((unsigned)(c.tm * c.tn));
 #define SP_GO(OP, EPI, VEC)                                                                                             \
   do {                                                                                                                  \
     if (tile == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, VEC>), grid, dim3(kThreads), 0, s, g);                \

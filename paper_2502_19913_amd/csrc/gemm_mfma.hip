@@ -786,6 +786,11 @@ Shape choose_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
 
 }  // namespace
 
+GemmShape gemm_mfma_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
+  const Shape s = choose_shape(op, M, N, K, epi);
+  return {s.tile, s.tm * s.tn, s.wgs};
+}
+
 bool gemm_mfma_supported(int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, const void* C,
                          const void* R) {
   if (M < 1 || N < 1 || K < 1) return false;

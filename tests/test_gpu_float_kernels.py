@@ -18,10 +18,14 @@ def dev(a):
 # A float sum of K products of unit normals carries a relative rounding error of about sqrt(K) 2^-24 or less: 2e-6 at
 # K = 1100.  The bounds allow ten times that over the tensor, and over the largest entry.
 PRODUCTS = [  # M, N, K: 32-tiles and one entry; remainders in every dimension that are no multiple of 4 (element-wise
-    # access); 64-tiles; 128-tiles; a reduction of one step, of one group past a step, and of several shares (op 2)
+    # access); 64-tiles; a reduction of one step, of one group past a step, and of many
     (1, 1, 1), (33, 31, 17), (70, 50, 35), (130, 66, 300), (1100, 515, 33), (1030, 1100, 515), (2048, 2052, 36),
     (2049, 2047, 65), (516, 260, 1100), (36, 68, 4100),
 ]
+# 128-tiles (the last two: of op 2 as well), with and without remainders that are no multiple of 4; 64-tiles of op 2; the
+# small kernel one step short of, at and past its eight steps in flight.  tests/test_host.py checks this against the dispatch.
+PRODUCTS += [(2048, 2048, 36), (2183, 1351, 33), (2047, 2045, 67), (4096, 2048, 36), (4095, 2047, 33),
+             (40, 36, 224), (40, 36, 256), (39, 35, 287), (40, 36, 292), (40, 36, 321)]
 
 
 @pytest.mark.parametrize("M,N,K", PRODUCTS)

@@ -14,13 +14,20 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda().bfloat16()
 
 
-# M, N, K: one 16-byte chunk; one 64-tile less, exactly and one chunk more in every dimension; steps of the ring below,
-# at and past its five slots; 128-tiles with remainders, below, at and past four slots; 256-tiles with remainders;
-# several tiles per workgroup; a reduction cut into runs that are no multiple of the ring (op 2)
+# M, N, K: one 16-byte chunk; one 64-tile less, exactly and one chunk more in every dimension; 64-tiles with steps below,
+# at and past the ring's five slots; 128-tiles with remainders past its four slots; 256-tiles with remainders; a reduction
+# cut into runs that are no multiple of the ring (op 2, 64-tiles)
 PRODUCTS = [
     (8, 8, 8), (56, 56, 56), (64, 64, 64), (72, 72, 72), (72, 136, 320), (200, 72, 1032), (1000, 1032, 136), (1032, 1000, 256),
     (2056, 1160, 328), (4096, 2824, 72), (4000, 1032, 200), (520, 264, 2056),
 ]
+# 128-tiles of three, four and five steps; 64-, 128- and 256-tiles of which a workgroup takes several in turn; op 2 in
+# several runs of 128- and 256-tiles.  tests/test_host.py checks against the dispatch that the lists hold what they say.
+PRODUCTS += [(1288, 1544, 192), (1288, 1544, 200), (1288, 1544, 264), (6664, 520, 200), (20670, 272, 1472), (8200, 2312, 72),
+             (1032, 1032, 3080), (2056, 2056, 2056)]
+# R, h, d; the last four: several 64- and 128-tiles in turn, forward and backward
+FEED_FORWARD = [(1, 64, 64), (65, 64, 72), (999, 768, 288), (129, 192, 96), (2050, 1408, 512), (4100, 2816, 64),
+                (675, 2752, 64), (723, 2752, 64), (6657, 576, 200), (20489, 320, 1480)]
 
 
 @pytest.mark.parametrize("M,N,K", PRODUCTS)
@@ -47,7 +54,7 @@ def test_products_at_tile_edges(M, N, K):
         assert torch.all(buf[M * N:] == 7.0), op
 
 
-@pytest.mark.parametrize("R,h,d", [(1, 64, 64), (65, 64, 72), (999, 768, 288), (129, 192, 96), (2050, 1408, 512), (4100, 2816, 64)])
+@pytest.mark.parametrize("R,h,d", FEED_FORWARD)
 def test_feed_forward_epilogues_at_tile_edges(R, h, d):
     hn = round_bf16(synth.normal(54, f"th{R}{h}", (R, d))); w = round_bf16(synth.normal(55, f"tw{R}{h}", (2 * h, d)) / np.sqrt(d))
     dy = round_bf16(synth.normal(56, f"ty{R}{h}", (R, d))); wd = round_bf16(synth.normal(57, f"tv{R}{h}", (d, h)) / np.sqrt(d))

@@ -174,3 +174,28 @@ def test_gain_gradient_scratch_grows_with_the_layers_only_where_it_pays(dim, mor
     cfg = dict(synth.CONFIGS["c1"], dim=dim, n_heads=16, n_kv_heads=16, hidden=256, dtype="bf16")
     one, four = (sp.workspace_bytes(dict(cfg, layers_per_stage=n), 1, 0) for n in (1, 4))
     assert four - one == (6 * 1024 * dim * 4 if more else 0)
+
+
+def test_the_product_tests_reach_every_tile():
+    # the shapes of the GPU tests, against the dispatch they are meant to cover (256 compute units here and on an MI355X)
+    from tests import test_gpu_float_kernels as flt, test_gpu_ops as ops, test_gpu_tiles as tiles
+    got = {(op, 0) + sp.gemm_shape(sp.SP_BF16, op, *c) + ((c[2] + 63) // 64,) for c in tiles.PRODUCTS for op in (0, 1, 2)}
+    got |= {(0, 2) + sp.gemm_shape(sp.SP_BF16, 0, R, 2 * h, d, 2) + ((d + 63) // 64,) for R, h, d in tiles.FEED_FORWARD}
+    got |= {(1, 3) + sp.gemm_shape(sp.SP_BF16, 1, R, h, d, 3) + ((d + 63) // 64,) for R, h, d in tiles.FEED_FORWARD}
+    for tile in (64, 128, 256):
+        for op, epi in ((0, 0), (1, 0), (2, 0), (0, 2), (1, 3)):
+            mine = [g for g in got if g[:3] == (op, epi, tile)]
+            assert mine, (tile, op, epi)
+            if op == 2:
+                assert any(g[4] > g[3] for g in mine) and any(g[4] == g[3] for g in mine), ("runs", tile)
+            elif not (tile == 256 and epi == 3):
+                assert any(g[4] < g[3] for g in mine), ("several tiles in turn", tile, op, epi)
+    for op in (0, 1, 2):   # steps: around the slots of the rings
+        assert {1, 2, 4, 5, 17} <= {g[5] for g in got if g[:3] == (op, 0, 64)}
+    for op in (0, 1):
+        assert {3, 4, 5, 6} <= {g[5] for g in got if g[:3] == (op, 0, 128)}
+    f32 = {(op, sp.gemm_shape(sp.SP_F32, op, *c)[0], any(x % 4 for x in c)) for c in flt.PRODUCTS for op in (0, 1, 2)}
+    assert {(op, t, odd) for op in (0, 1, 2) for t in (32, 64, 128) for odd in (False, True)} <= f32, f32
+    ffn = {(op, sp.gemm_shape(sp.SP_F32, op, R, n * h, d, e)[0], h % 4 + d % 4 > 0) for R, h, d in ops.FFN_SHAPES for op, n, e in ((0, 2, 2), (1, 1, 3))}
+    assert {(op, t, odd) for op in (0, 1) for t in (32, 64, 128) for odd in (False, True)} <= ffn, ffn
+    assert any(sp.gemm_shape(sp.SP_BF16, op, 65, 50, 36)[0] == 0 for op in (0, 1))
