@@ -523,10 +523,11 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
 // the end.  Forward and input-gradient products: the two sets divide the rows of a share instead (96 KB of reads), so
 // that every output is summed in the order of k as in a 256-tile: their results are rounded to bf16, and a
 // microbatch's must not depend on the tile that the size of its group leads to.
-// A step of a 128-tile takes 0.5 us; 0.36 with the loads delivering zeros (LDS: 96 KB a step at 128 bytes a cycle), the
-// rest is the way from the L2s.  Against the two-slot loop of 128-tiles with one wait per step that stood here before:
-// NT 4096 x 1024 x 2816 34 -> 25 us, NN 1777 x 2048 x 11264 127 -> 96 us; TN (256-tiles before) 1024 x 1024 x 4096
-// 37 -> 25 us, 288 x 768 x 999 19 -> 9 us.
+// A step of a 128-tile takes 0.51 us (op 0), 0.54 (op 1), 0.46 (op 2) with every CU busy; with the loads delivering zeros
+// 0.32, 0.36 and 0.36: in ops 0 and 1 that is the fragment reads (96 KB at 128 bytes a cycle 0.32 us at 2.4 GHz), against
+// 0.21 of MFMAs, and the rest is the way from the L2s.  Against the two-slot loop of 128-tiles with one wait per step that
+// stood here before: NT 4096 x 1024 x 2816 34 -> 27 us, NN 1777 x 2048 x 11264 127 -> 92 us; TN (256-tiles before) 1024 x
+// 1024 x 4096 37 -> 26 us, 288 x 768 x 999 19 -> 8 us (64-tiles).
 template <int TILE>
 struct RingGeo {
   static constexpr int S = TILE == 128 ? 4 : 5;            // 128 KB; 80 KB, so that two workgroups of 64-tiles share a CU
@@ -747,10 +748,13 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 //   rounds of workgroups x (k-steps x step + ends)  +  op 2: runs x output bytes / atomics rate
 // step and ends are fits to measured products of 4 to 344 steps over grids of 24 to 1400 tiles: a 256-tile takes 0.9 to
 // 1.3 us a step (the clock falls as CUs fill), a 128-tile 0.5 (its operand traffic per flop is twice as large), a
-// 64-tile 0.3 alone on its CU and 0.37 beside another.  Float atomics reach 1.4 TB/s over the whole chip whatever the
-// tile, so that further runs per tile cost most where the reduction is short.  Examples, us, 256- / 128-tile:
-// NT 4096 x 1024 x 2816 46 / 26, NT 1777 x 6144 x 2048 44 / 54, NN 8192 x 1024 x 1024 25 / 26, NT 8192 x 6144 x 2048
-// 145 / 213, TN 1024 x 1024 x 4096 37 / 25, TN 2048 x 2048 x 8192 91 / 78, TN 5632 x 1024 x 8192 108 / 130.
+// 64-tile 0.3 alone on its CU and 0.37 beside another.  (Taken again over one full round: 256-tiles 1.30 / 1.33 / 1.44 for
+// ops 0 / 1 / 2, 128-tiles 0.51 / 0.54 / 0.46, 64-tiles 0.25 / 0.27 / 0.27 alone and 0.42 / 0.47 / 0.43 beside another; the
+// choices at the examples stay the faster ones or within 3 %.)  Float atomics reach 1.4 TB/s over the whole chip whatever the
+// tile, so that further runs per tile cost most where the reduction is short.  Examples, us, 256- / 128- / 64-tile:
+// NT 4096 x 1024 x 2816 47 / 27 / 46, NT 1777 x 6144 x 2048 42 / 53 / 91, NN 8192 x 1024 x 1024 24 / 23 / 41, NT 8192 x
+// 6144 x 2048 148 / 219 / 369, NN 1777 x 2048 x 11264 178 / 92 / 168, TN 1024 x 1024 x 4096 32 / 26 / 26, TN 2048 x 2048
+// x 8192 90 / 79 / 126, TN 5632 x 1024 x 8192 108 / 126 / 183, TN 288 x 768 x 999 15 / 9 / 8.
 struct Shape { int tile, tm, tn, wgs; };
 Shape choose_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
   const int64_t cus = cu_count(), ksteps = (K + BK - 1) / BK;
