@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd(const T* __restrict__ dy
 // Together with one fold for all norms of a stage (rms_fold_places: 1.3 and 0.3 % of it), 50M shape in bf16 (d = 288) 4.58 ->
 // 4.39 ms a pass, 500M shape (d = 1024) 65.9 -> 64.0 ms.
 template <int NVW, int RPI, int WPR, bool HAS_RES>
-__global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restrict__ dy, const bf16* __restrict__ x,
+__global__ __launch_bounds__(kBlock, 3) void k_rmsnorm_bwd_cols(const bf16* __restrict__ dy, const bf16* __restrict__ x,
                                                              const bf16* __restrict__ g, const float* __restrict__ rstd,
                                                              const bf16* __restrict__ dres, int64_t R, int d,
                                                              bf16* __restrict__ dx, float* __restrict__ dg,
@@ -242,7 +242,9 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd_cols(const bf16* __restr
   static_assert(G == 1 || NVW == 1, "several row groups only where a row is at most WPR pieces");
   __shared__ float s_m[2][RPI][kWavesPerBlock];
   __shared__ __attribute__((aligned(16))) float s_fold[G > 1 ? (G - 1) * WPR * 512 : 4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = wave / WPR, piece = wave % WPR;
+  // the wavefront's number as a scalar: with it in a vector register the row addresses are vectors too, and the kernel takes
+  // 174 registers instead of 154, one workgroup less on a CU
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = wave / WPR, piece = wave % WPR;
   int col[NVW];
   uint32_t coff[NVW];   // byte offset of the piece in a row; 0 for a lane past the end of the row (loads stay in bounds, the
                         // lane's gain is zero and nothing of it is stored)
