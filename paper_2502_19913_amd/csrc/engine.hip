@@ -411,9 +411,9 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
   const int64_t dgpart_n = (int64_t)kRmsPartRows * D.d;
   const int fold_places = rms_fold_places((int)D.d, 2 * cfg.layers_per_stage);
   auto norm_bwd = [&](const void* x, int64_t gain, const float* rstd, const void* dres, void* dx) {
-    if (fold.n == fold_places) rmsnorm_bwd_fold(s, &fold, (int)D.d);
     rmsnorm_bwd(s, dt, t, x, P(ctx, params, gain), rstd, dres, R, (int)D.d, dx, grads + gain,
                 (float*)at(ctx, ctx->w.dgpart) + fold.n * dgpart_n, dgpart_n, &fold);
+    if (fold.n == fold_places) rmsnorm_bwd_fold(s, &fold, (int)D.d);   // the sums are still in the L2s
   };
   // A second stream pays while the layer's products are short: their partly filled last rounds of tiles take in
   // work of the other stream.  Products of many rounds only get in each other's way (workgroups of two kernels
