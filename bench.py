@@ -21,11 +21,12 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA, published
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E, published
-# HBM-side bytes per launch of the weight-gradient product at the default workload, from rocprofv3 --pmc
-# FETCH_SIZE (x 1.998, the factor a plain copy of known size gives) + WRITE_SIZE (x 1.000); see
-# profiles/c3_stage_counters_pmc.txt.  Valid for the kernel as it was when the counters were taken: set to None
-# when k_gemm_mfma changes.
-GEMM_TN_C3_TRAFFIC_BYTES = 599.1e6
+# HBM-side bytes per launch of the weight-gradient products at the default workload, from rocprofv3 --pmc
+# FETCH_SIZE (x 1.997, the factor a plain copy of known size gives) + WRITE_SIZE (x 1.000), over the class's launches (11 in
+# 12 are k_gemm_mfma<2>'s, the 2048 x 2048 gradients of a group of two are k_gemm_ring<2>'s); see
+# profiles/c3_stage_counters_pmc.txt.  Valid for the kernels as they were when the counters were taken: set to None
+# when k_gemm_mfma, k_gemm_ring or the choice between them changes.
+GEMM_TN_C3_TRAFFIC_BYTES = 591.5e6
 
 
 def flops_per_token_layer(cfg):
@@ -389,7 +390,7 @@ def main():
         p = prof[dom]
         achieved = p["flops"] / (p["ms"] * 1e-3) / 1e12
         roof = dict(bound="mfma", kernel={"gemm_nt": "k_gemm_mfma<0>", "gemm_nn": "k_gemm_mfma<1>",
-                                          "gemm_tn": "k_gemm_mfma<2>"}[dom],
+                                          "gemm_tn": "k_gemm_mfma<2>, k_gemm_ring<2>"}[dom],
                     achieved=round(achieved, 1), peak=PEAK_BF16_TFLOPS, unit="TFLOP/s",
                     frac=round(achieved / PEAK_BF16_TFLOPS, 4),
                     traffic=(GEMM_TN_C3_TRAFFIC_BYTES if dom == "gemm_tn" and args.config == "c3" and not args.one_group

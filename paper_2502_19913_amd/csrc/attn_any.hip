@@ -38,10 +38,11 @@ constexpr int BQ = 64;    // rows a workgroup owns
 // (score products, exponentials, second products, LDS round trips: three to four times the matrix instructions alone),
 // and small models have one or two wavefronts per SIMD to overlap it.  Two sets up to a head dimension of 48: heads of
 // 48, 50M shape in bf16 on 3 x 333 tokens 4.40 -> 3.89 ms, in float on 4 x 256 tokens 6.14 -> 5.81 ms, on 64 tokens
-// 2.02 -> 1.96 ms a pass; heads of 32 alone, forward | backward us with one set -> two, 3 x 333 x 6 heads float 18 | 50 ->
-// 14 | 39, bf16 18 | 45 -> 13 | 32, 8 x 1024 x 16 heads float 219 | 615 -> 205 | 619, bf16 177 | 435 -> 167 | 396, and heads
-// of 16 the same (they run as 32 columns); only the bf16 forward of 8 x 1024 x 16 heads of 48 loses, 238 -> 262.  At 64 the stage of 2 x 512 tokens was 0.5 % slower with two sets, and from 96 on their
-// buffers take the room of a CU's second workgroup.
+// 2.02 -> 1.96 ms a pass; heads of 32 alone, forward | backward us with one set -> two, 3 x 333 x 6 heads in float 18 |
+// 50 -> 14 | 39, in bf16 18 | 45 -> 13 | 32, 8 x 1024 x 16 heads in float 219 | 615 -> 205 | 619, in bf16 177 | 435 -> 167 |
+// 396 (heads of 16, which run as 32 columns, the same); only the bf16 forward of 8 x 1024 x 16 heads of 48 loses, 238 ->
+// 262.  At 64 the stage of 2 x 512 tokens was 0.5 % slower with two sets, and from 96 on their buffers take the room of
+// a CU's second workgroup.
 template <int HD> constexpr int kSets = HD <= 48 ? 2 : 1;
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
