@@ -99,7 +99,7 @@ Carve carve(const sp_cfg& c, int n_mb_max, int n_visits_max) {
   w.t_delta = take(Rmax * D.H * sizeof(float));
   w.rope = take((size_t)D.T * (D.hd / 2) * 2 * sizeof(float));   // cos, sin per (position, pair)
   // per-block partial sums of the gain gradients of the norms that one launch folds
-  w.dgpart = take((size_t)rms_fold_places((int)D.d, 2 * c.layers_per_stage) * kRmsPartRows * D.d * sizeof(float));
+  w.dgpart = take((size_t)std::min(kRmsFoldMax, 2 * c.layers_per_stage) * kRmsPartRows * D.d * sizeof(float));
   w.bad = take(sizeof(int32_t));   // raised by a kernel that meets a token id or target outside the vocabulary
   if (c.has_head) {
     const int64_t ch = head_chunk_rows(D, Rmax);
@@ -406,14 +406,13 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
   char* t = at(ctx, ctx->w.t_d2);
   char* da = at(ctx, ctx->w.t_da);
   float* delta = (float*)at(ctx, ctx->w.t_delta);
-  // gain gradients wait as partial sums, one place each, for a launch when the places are taken or at the end
+  // gain gradients wait as partial sums, one place each, for one launch at the end (or when the places are taken)
   RmsFold fold{};
   const int64_t dgpart_n = (int64_t)kRmsPartRows * D.d;
-  const int fold_places = rms_fold_places((int)D.d, 2 * cfg.layers_per_stage);
   auto norm_bwd = [&](const void* x, int64_t gain, const float* rstd, const void* dres, void* dx) {
     rmsnorm_bwd(s, dt, t, x, P(ctx, params, gain), rstd, dres, R, (int)D.d, dx, grads + gain,
                 (float*)at(ctx, ctx->w.dgpart) + fold.n * dgpart_n, dgpart_n, &fold);
-    if (fold.n == fold_places) rmsnorm_bwd_fold(s, &fold, (int)D.d);   // the sums are still in the L2s
+    if (fold.n == kRmsFoldMax) rmsnorm_bwd_fold(s, &fold, (int)D.d);
   };
   // A second stream pays while the layer's products are short: their partly filled last rounds of tiles take in
   // work of the other stream.  Products of many rounds only get in each other's way (workgroups of two kernels

@@ -53,7 +53,11 @@ void rmsnorm_fwd(hipStream_t s, int dtype, const void* x, const void* g, int64_t
 // enough); where the call leaves sums there it notes them in *fold, and dg is complete after rmsnorm_bwd_fold, which
 // adds up all that is noted (norms of the same width d) and empties the list
 constexpr int kRmsPartRows = 1024;
-constexpr int kRmsFoldMax = 8;   // two norms of each layer of a four-layer stage (see rms_fold_places)
+// Two norms of each layer of a four-layer stage wait for one fold.  One launch instead of eight: 50M shapes (d = 288) 3.65 ->
+// 3.60 ms a pass in bf16, 5.72 -> 5.64 in float, 500M shape (d = 1024) 64.6 -> 64.4, 1.5B stage (d = 2048) on 300 to 2500
+// rows 0.2 to 1 % (2.65 -> 2.62 on 700), 7B stage (d = 4096) 6.30 -> 6.17 on 500 rows, 10.05 -> 10.0 on 1500; large groups
+// even.  It costs 8 x 1024 x d floats of workspace (128 MiB at d = 4096).
+constexpr int kRmsFoldMax = 8;
 struct RmsFold {
   const float* part[kRmsFoldMax];
   float* dg[kRmsFoldMax];
@@ -61,10 +65,6 @@ struct RmsFold {
   int n;
   void add(const float* p, float* g, int r) { part[n] = p; dg[n] = g; rows[n++] = r; }
 };
-// How many of a stage's norms wait for one fold.  One launch instead of eight: 50M shapes (d = 288) 3.65 -> 3.60 ms in bf16,
-// 5.72 -> 5.64 in float, 500M shape (d = 1024) 64.6 -> 64.4 ms a pass.  At d = 2048 and 4096 (1.5B and 7B stages) it gains
-// nothing, so there the scratch stays one norm's (16 MiB at d = 4096).
-inline int rms_fold_places(int d, int norms) { return d <= 1024 ? (norms < kRmsFoldMax ? norms : kRmsFoldMax) : 1; }
 void rmsnorm_bwd_fold(hipStream_t s, RmsFold* fold, int d);
 void rmsnorm_bwd(hipStream_t s, int dtype, const void* dy, const void* x, const void* g, const float* rstd,
                  const void* dres, int64_t R, int d, void* dx, float* dg, float* part, int64_t part_floats, RmsFold* fold);

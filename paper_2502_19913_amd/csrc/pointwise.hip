@@ -230,8 +230,8 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm_bwd(const T* __restrict__ dy
 // round's sums never overwrite one still being read).  Where a row takes fewer than four pieces the other wavefronts
 // take rows of their own (with all four on one row, three of four idled at d <= 512 and two at d <= 1024), and the
 // groups' gain-gradient sums are folded through LDS at the end.
-// Together with one fold for all norms of a stage (rms_fold_places: 1.3 and 0.3 % of it), 50M shape in bf16 (d = 288) 4.58 ->
-// 4.39 ms a pass, 500M shape (d = 1024) 65.9 -> 64.0 ms.
+// With that and one fold per stage (1.3 and 0.3 % of it), 50M shape in bf16 (d = 288) 4.58 -> 4.39 ms a pass, 500M shape (d =
+// 1024) 65.9 -> 64.0 ms.
 template <int NVW, int RPI, int WPR, bool HAS_RES>
 __global__ __launch_bounds__(kBlock, 3) void k_rmsnorm_bwd_cols(const bf16* __restrict__ dy, const bf16* __restrict__ x,
                                                              const bf16* __restrict__ g, const float* __restrict__ rstd,
@@ -347,9 +347,9 @@ __global__ __launch_bounds__(kBlock, 3) void k_rmsnorm_bwd_cols(const bf16* __re
 
 // dg[c] += sum over n rows of part[row][c], for every norm of the list (blockIdx.z).  A block takes 64 columns and one
 // of gridDim.y runs of rows: its four wavefronts stride the run's rows, fold in LDS, and add one value per column
-// atomically (gridDim.y adds per address in all).  Up to d = 1024 one launch folds the norms of a whole stage backward: a
-// launch after every norm (4 us alone, 9 to 38 us beside the weight-gradient products whose workgroups fill the CUs)
-// holds up the chain that carries the activation gradient (rms_fold_places).
+// atomically (gridDim.y adds per address in all).  One launch folds the norms of a whole stage backward: a launch
+// after every norm (4 us alone, 9 to 38 us beside the weight-gradient products whose workgroups fill the CUs) held
+// up the chain that carries the activation gradient.
 __global__ __launch_bounds__(kBlock) void k_colsum_add(RmsFold list, int d) {
   const float* __restrict__ part = list.part[blockIdx.z];
   float* __restrict__ dg = list.dg[blockIdx.z];
