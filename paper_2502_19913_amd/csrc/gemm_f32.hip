@@ -18,7 +18,7 @@
 //                        the kernel is bound by the matrix cores.
 //   k_gemm_f32_small     for products too small to fill the chip with those: tiles of 32 x 32, four wavefronts with a block
 //                        of 16 x 16 each, eight steps in flight.  The time is one chain of latencies.
-// Every entry is one sum in the order of k, with the same instructions, in both: the tile of ops 0 and 1 follows the
+// Every entry is summed in one order (runs of 64 k), with the same instructions, in both: the tile of ops 0 and 1 follows the
 // number of rows, and a microbatch's rows must not depend on how many microbatches share its group; a weight gradient is
 // added with one atomic per entry and launch, so that it repeats to the bit.
 // Measured against the vector-unit kernel they replaced (64 x 64 tiles, products and sums one lane at a time), us per
@@ -26,6 +26,7 @@
 // 235, op 2 864 x 288 x 4096 893 -> 31, and of the small ones op 0 128 x 288 x 768 95 -> 8.8, op 1 128 x 288 x 1536
 // 191 -> 13, most others at 8 (the launch).
 #include <algorithm>
+#include <type_traits>
 
 #include "devutil.h"
 #include "internal.h"
@@ -39,6 +40,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int BK = 32;
 constexpr int kThreads = 256;
 
+// Every kernel sums runs of 64 k and adds them up in turn: one chain of K / 4 instructions is off by 1.8e-8 sqrt(K) (2-norm,
+// unit normals), 5.0e-7 at K = 768 and 1.1e-6 at 4096, the runs by 1.6e-7 and 2.1e-7 (runs of 128 2.1e-7 and 2.3e-7, of 32
+// 1.4e-7 and 2.3e-7).  It takes one more set of accumulators.  With the loop written out over the two steps of a run, the first
+// of which starts from zero, it costs nothing: us, one chain / runs, op 0 2048 x 288 x 768 22.7 / 21.1, 3072 x 1024 x 2816
+// 168 / 161 (64-tiles), 4096 x 4096 x 1024 288 / 291, 2048 x 2048 x 2048 157 / 164 (128-tiles); 500M stage 7.18 / 7.17 ms
+// (7.25 with a loop over single steps).
+constexpr int kRun = 64 / BK;   // steps
 enum { kEpiPlain = 0, kEpiRope = 1, kEpiSwiglu = 2, kEpiSwigluBwd = 3 };   // as in the bf16 kernels
 
 struct Args {
@@ -79,6 +87,11 @@ template <int TN, int WN>
 __device__ __forceinline__ int swiglu_row(int tn, int t, int h) {
   const int w = t / WN, in = t % WN, f = tn * (TN / 2) + w * (WN / 2) + in % (WN / 2);
   return f < h ? (in < WN / 2 ? f : h + f) : -1;
+}
+
+__device__ __forceinline__ void end_run(f32x4& sum, f32x4& acc) {
+  sum += acc;
+  acc = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // Four consecutive output columns n .. n+3 of row m leave for memory (ops 0 and 1).
@@ -180,7 +193,7 @@ struct Tile {
 };
 
 template <int OP, int EPI, int T, bool VEC>
-__global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
+__global__ __launch_bounds__(kThreads, 2) void k_gemm_f32(Args g) {
   constexpr bool AS = OP == 2, BS = OP != 0;
   typedef Tile<AS, T, VEC> TA;
   typedef Tile<BS, T, VEC> TB;
@@ -193,11 +206,11 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
   tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
   const int m0 = tm * T, n0 = tn * T, steps = (g.K + BK - 1) / BK;
 
-  f32x4 acc[NB][NB];
+  f32x4 acc[NB][NB], sum[NB][NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j)
 #pragma unroll
-    for (int i = 0; i < NB; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < NB; ++i) sum[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto a_row = [&](int t) { return m0 + t < g.M ? m0 + t : -1; };
   auto b_row = [&](int t) {
     if (EPI == kEpiSwiglu) return swiglu_row<T, W>(tn, t, g.N / 2);
@@ -217,7 +230,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
   fetch(0);
   put(0);
   __syncthreads();
-  for (int s = 0; s < steps; ++s) {
+  auto step = [&](int s, auto begins) {   // begins: a run, whose first products need no sum to be added to
     if (s + 1 < steps) fetch(s + 1);
     const float* la = smem + (s & 1) * kStage;
     const float* lb = la + TA::kFloats;
@@ -233,12 +246,24 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
-          for (int i = 0; i < NB; ++i)
-            acc[j][i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j][e], fb[i][e], acc[j][i], 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_16x16x4f32(fb[i][e], fa[j][e], acc[j][i], 0, 0, 0);
+          for (int i = 0; i < NB; ++i) {
+            const f32x4 c = decltype(begins)::value && q == 0 && e == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[j][i];
+            acc[j][i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j][e], fb[i][e], c, 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_16x16x4f32(fb[i][e], fa[j][e], c, 0, 0, 0);
+          }
     }
     if (s + 1 < steps) put(s + 1);   // into the buffer that every wavefront left before the last barrier
+    if (!decltype(begins)::value || s + 1 == steps)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) sum[j][i] += acc[j][i];
     __syncthreads();
+  };
+  static_assert(kRun == 2, "a step that begins a run and one that ends it");
+  for (int s = 0; s < steps; s += 2) {
+    step(s, std::true_type());
+    if (s + 1 < steps) step(s + 1, std::false_type());
   }
   if (OP == 2) {
 #pragma unroll
@@ -249,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int m = m0 + wm * W + j * 16 + kg * 4 + r;
-          if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, acc[j][i][r]);
+          if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, sum[j][i][r]);
         }
       }
   } else if (EPI == kEpiSwiglu) {
@@ -259,7 +284,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
       if (m < g.M) {
 #pragma unroll
         for (int i = 0; i < NB / 2; ++i)
-          emit_swiglu<VEC>(g, m, tn * (T / 2) + wn * (W / 2) + i * 16 + kg * 4, acc[j][i], acc[j][i + NB / 2]);
+          emit_swiglu<VEC>(g, m, tn * (T / 2) + wn * (W / 2) + i * 16 + kg * 4, sum[j][i], sum[j][i + NB / 2]);
       }
     }
   } else {
@@ -268,7 +293,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32(Args g) {
       const int m = m0 + wm * W + j * 16 + lr;
       if (m < g.M) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) emit<OP, EPI, VEC>(g, m, n0 + wn * W + i * 16 + kg * 4, acc[j][i]);
+        for (int i = 0; i < NB; ++i) emit<OP, EPI, VEC>(g, m, n0 + wn * W + i * 16 + kg * 4, sum[j][i]);
       }
     }
   }
@@ -309,7 +334,7 @@ struct Quad {
 };
 
 // Tiles of 32 x 32 (SwiGLU: 32 rows x 32 features): a wavefront owns a block of 16 x 16 (SwiGLU: of gate and
-// of up columns) over the whole reduction and sums it in the order of k, with the instructions of k_gemm_f32, so that a
+// of up columns) over the whole reduction and sums it in the order and with the instructions of k_gemm_f32, so that a
 // row has the same bits whatever kernel the number of rows leads to.  That chain of K / 4 dependent matrix instructions
 // of 32 cycles (and the launch) bounds it: U steps of 32 k are in flight from memory (registers), one in LDS ahead of the
 // one whose fragments are read, and that one ahead of the one being multiplied; one barrier per step.  Through LDS because
@@ -333,9 +358,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
   tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
   const int m0 = tm * T, n0 = tn * T, K = g.K, steps = (K + BK - 1) / BK;
   const int cols = EPI == kEpiSwiglu ? g.N / 2 : g.N, lda = AS ? g.M : K, ldb = BS ? g.N : K;
-  f32x4 acc[NB];
+  f32x4 acc[NB], sum[NB];
 #pragma unroll
-  for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < NB; ++i) acc[i] = sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (steps > 0) {
     Quad<AS, VEC> qa;
     Quad<BS, VEC> qb[NB];
@@ -384,7 +409,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
     Frags now = read(0);
     __syncthreads();
     // in LDS: step s + 1 and, from the middle of the step on, s + 2; on the way: the next U
-    auto step = [&](int s, int u, bool more) {   // u = (s + 2) % U
+    static_assert(U % kRun == 0, "runs end at fixed places of a round of U steps");
+    auto step = [&](int s, int u, bool more, bool ends) {   // u = (s + 2) % U; ends: a run
       const Frags next = read(s + 1);
 #pragma unroll
       for (int q = 0; q < BK / 16; ++q) {
@@ -400,30 +426,35 @@ __global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
           if (more) fetch(s + 2 + U, u);
         }
       }
+      if (ends)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) end_run(sum[i], acc[i]);
       now = next;
       __syncthreads();
     };
     int s = 0;
     for (; s + U <= steps; s += U)
 #pragma unroll
-      for (int u = 0; u < U; ++u) step(s + u, (u + 2) % U, true);
+      for (int u = 0; u < U; ++u) step(s + u, (u + 2) % U, true, u % kRun == kRun - 1);
 #pragma unroll
     for (int u = 0; u < U - 1; ++u)   // the rest is on its way
-      if (s + u < steps) step(s + u, (u + 2) % U, false);
+      if (s + u < steps) step(s + u, (u + 2) % U, false, u % kRun == kRun - 1);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) sum[i] += acc[i];
   }
   if (OP == 2) {
     const int n = n0 + wn * 16 + lr;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = m0 + wm * 16 + kg * 4 + r;
-      if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, acc[0][r]);
+      if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, sum[0][r]);
     }
     return;
   }
   const int m = m0 + wm * 16 + lr, n = n0 + wn * 16 + kg * 4;
   if (m >= g.M) return;
-  if (EPI == kEpiSwiglu) emit_swiglu<VEC>(g, m, n, acc[0], acc[NB - 1]);
-  else emit<OP, EPI, VEC>(g, m, n, acc[0]);
+  if (EPI == kEpiSwiglu) emit_swiglu<VEC>(g, m, n, sum[0], sum[NB - 1]);
+  else emit<OP, EPI, VEC>(g, m, n, sum[0]);
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }

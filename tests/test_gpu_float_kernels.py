@@ -190,3 +190,15 @@ def test_float_weight_gradients_are_repeatable(M, N, K):
     assert all(np.array_equal(g, got[0]) for g in got[1:])
     want = a.cpu().numpy().astype(np.float64).T @ b.cpu().numpy().astype(np.float64) + c0.cpu().numpy()
     assert relerr(got[0], want) < 2e-5 and maxerr(got[0], want) < 2e-5
+
+
+@pytest.mark.parametrize("op,M,N,K", [(0, 128, 288, 768), (1, 1000, 288, 1536), (0, 2048, 288, 768), (0, 2048, 2048, 2048), (2, 864, 288, 4096),
+                                      (2, 1024, 1024, 3072), (2, 4096, 2048, 1024)])
+def test_float_products_lose_little_over_long_reductions(op, M, N, K):
+    # runs of 64 k (16 instructions), then K / 64 runs: about 3.6e-8 (16 + K / 64)^0.5 at most, 3.2e-7 at K = 4096; one
+    # chain over the whole reduction would be 5e-7 at K = 768 and 1.1e-6 at 4096
+    a = synth.normal(64, f"la{M}{K}", (M, K)); b = synth.normal(65, f"lb{N}{K}", (N, K))
+    c = torch.zeros((M, N), device="cuda")
+    sp.gemm(op, dev(a.T if op == 2 else a), dev(b if op == 0 else b.T), c)
+    err = relerr(c.cpu().numpy(), a.astype(np.float64) @ b.astype(np.float64).T)
+    assert err < 3.6e-8 * np.sqrt(16 + K / 64), err
