@@ -1,30 +1,36 @@
-// Float matrix products on the CDNA4 matrix cores (v_mfma_f32_16x16x4_f32: float operands, float sums, 1/16 of the
-// bf16 rate), any shape and alignment.  They carry the float mode.
+// Float matrix products on the CDNA4 matrix cores, any shape and alignment.  They carry the float mode.
 //
 //   op 0  C[M,N]  = A[M,K] B[N,K]^T (+R)   A, B k-contiguous
 //   op 1  C[M,N]  = A[M,K] B[K,N]          B k-strided
 //   op 2  C[M,N] += A[K,M]^T B[K,N]        both k-strided; added atomically
 //
-// The instruction's k-slots may stand for any four k, so lane group kg = lane / 16 holds k = 4 kg .. 4 kg + 3 of a
-// group of 16 and four instructions take one element each: a fragment of 16 rows x 16 k of a k-contiguous operand
-// is one 16-byte read.  For ops 0 and 1 the tile of B is the instruction's row operand, so a lane ends with four
-// consecutive output columns of one row (16-byte stores, and whole rotary pairs for the epilogue); for op 2 the
-// tile of A is, so that a wavefront's atomics cover 64 contiguous bytes of four rows.
+// On the bf16 instruction (v_mfma_f32_16x16x32_bf16, 16 times the rate of the float one): a float is the sum of three
+// bfloat16s, exactly (8 + 8 + 8 bits), and a product of two floats the sum of nine products of those, each exact.  Six are
+// formed; the three left out (middle x low, low x middle, low x low) are below 2^-24 of the product, less than its rounding
+// to a float.  Sums are floats as with the float instruction, and fewer: its error against 64 bits (2-norm, unit normals; the
+// float instruction over the same runs of 64 k / this) 1.45e-7 / 1.00e-7 at K = 288, 1.58 / 1.17 at 768, 1.73 / 1.36 at
+// 1536, 2.04 / 1.80 at 4096, 2.83 / 2.70 at 11264.  Leaving out nothing changes no digit of these.  Parts below the smallest
+// bfloat16 are lost: an operand below 2^-110 (8e-34) keeps an absolute error of up to 2^-134.
 //
-// Kernels:
-//   k_gemm_f32           tiles of 128 x 128 or 64 x 64, four wavefronts, operands staged through LDS (global -> registers
-//                        one step ahead -> the other of two LDS buffers, one barrier per step of 32 k).  The matrix
-//                        instruction needs 32 cycles for 2 x 64 floats of operands, so LDS and memory keep up easily and
-//                        the kernel is bound by the matrix cores.
-//   k_gemm_f32_small     for products too small to fill the chip with those: tiles of 32 x 32, four wavefronts with a block
-//                        of 16 x 16 each, eight steps in flight.  The time is one chain of latencies.
-// Every entry is summed in one order (runs of 64 k), with the same instructions, in both: the tile of ops 0 and 1 follows the
+// For ops 0 and 1 the tile of B is the instruction's row operand, so a lane ends with four consecutive output columns of
+// one row (16-byte stores, and whole rotary pairs for the epilogue); for op 2 the tile of A is, so that a wavefront's atomics
+// cover 64 contiguous bytes of four rows.
+//
+// What bounds it: the split.  A tile's operands are split once per tile, 5.5 vector instructions a value, and beside matrix
+// instructions that keep their core busy a SIMD issues another vector instruction every 6.5 cycles; LDS holds 6 bytes a value.
+// A step (32 k) of a 128-tile takes 2700 cycles: 1580 of matrix instructions on every SIMD, 1500 of the split's issue, 1570 of
+// LDS.  Tried for it and not better: every wavefront splitting and multiplying in turn (3800 cycles: a wavefront's own
+// matrix instruction hides 1.5 vector ones, another's 2.5), the leading part taken off by v_dot2_f32_bf16 (half the
+// instructions, each 9 cycles beside matrix instructions), the stages of several quads interleaved.
+// us per launch, float instruction (two thirds of its 157 TFLOP/s) -> this: op 0 2048 x 1024 x 1024 43 -> 30, 2048 x 3072 x 1024
+// 131 -> 74, 2048 x 1024 x 5632 220 -> 140, 4096 x 4096 x 4096 1135 -> 657 (209 TFLOP/s), op 1 2048 x 1024 x 5632 235 -> 145, op 2
+// 1024 x 1024 x 2048 61 -> 39, 3072 x 1024 x 2048 123 -> 81, 5632 x 1024 x 2048 237 -> 147; small ones even: op 0 1024 x 288 x 1536
+// 22 -> 20, 128 x 288 x 1536 15 -> 16.  The stage of the 500M shape on 2 x 2 x 512 tokens 7.18 -> 5.09 ms, the 50M shape on 4 x 4 x
+// 256 tokens 5.60 -> 4.93 ms a pass.
+//
+// Every entry is summed in one order (runs of 64 k), with the same instructions, whatever the tile: that follows the
 // number of rows, and a microbatch's rows must not depend on how many microbatches share its group; a weight gradient is
 // added with one atomic per entry and launch, so that it repeats to the bit.
-// Measured against the vector-unit kernel they replaced (64 x 64 tiles, products and sums one lane at a time), us per
-// launch: op 0 3072 x 3072 x 1024 424 -> 191 (101 TFLOP/s of the 157 the cores peak at), op 1 2048 x 1024 x 5632 1109 ->
-// 235, op 2 864 x 288 x 4096 893 -> 31, and of the small ones op 0 128 x 288 x 768 95 -> 8.8, op 1 128 x 288 x 1536
-// 191 -> 13, most others at 8 (the launch).
 #include <algorithm>
 #include <type_traits>
 
@@ -36,16 +42,18 @@ namespace sp {
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
 constexpr int BK = 32;
-constexpr int kThreads = 256;
+constexpr int kThreads = 512;
 
-// Every kernel sums runs of 64 k and adds them up in turn: one chain of K / 4 instructions is off by 1.8e-8 sqrt(K) (2-norm,
-// unit normals), 5.0e-7 at K = 768 and 1.1e-6 at 4096, the runs by 1.6e-7 and 2.1e-7 (runs of 128 2.1e-7 and 2.3e-7, of 32
-// 1.4e-7 and 2.3e-7).  It takes one more set of accumulators.  With the loop written out over the two steps of a run, the first
-// of which starts from zero, it costs nothing: us, one chain / runs, op 0 2048 x 288 x 768 22.7 / 21.1, 3072 x 1024 x 2816
-// 168 / 161 (64-tiles), 4096 x 4096 x 1024 288 / 291, 2048 x 2048 x 2048 157 / 164 (128-tiles); 500M stage 7.18 / 7.17 ms
-// (7.25 with a loop over single steps).
+// Runs of 64 k are summed from zero and added up in turn: with one chain over the whole reduction the error grows with its
+// length (4.2e-7 at K = 768, 1.0e-6 at 4096).  It takes one more set of accumulators.
+// The instruction rounds the sum of its products towards minus infinity, so that all entries are off in one direction (the mean
+// of the errors at K = 1536 is 3.5e-8 of an entry, four times what chance leaves; through a model's residual additions
+// such errors add up, not their squares).  So every second run is formed of the
+// negated A, and subtracted.  Gradients of whole models against 64 bits, float instruction / this / this without the negation:
+// 50M widths, 2 x 256 tokens 6.3e-7 / 5.8e-7 / 9.0e-7, 500M widths, 2 x 128 tokens 8.3e-7 / 7.0e-7 / 12.4e-7.
 constexpr int kRun = 64 / BK;   // steps
 enum { kEpiPlain = 0, kEpiRope = 1, kEpiSwiglu = 2, kEpiSwigluBwd = 3 };   // as in the bf16 kernels
 
@@ -81,18 +89,7 @@ __device__ __forceinline__ void store4(float* p, const f32x4& v, int valid) {
   }
 }
 
-// Memory row of B that belongs at row t of a SwiGLU tile of TN rows made of shares of WN: the first half of a share
-// holds gate rows, the second half the up rows of the same features (h = N / 2 features).  -1: past the end.
-template <int TN, int WN>
-__device__ __forceinline__ int swiglu_row(int tn, int t, int h) {
-  const int w = t / WN, in = t % WN, f = tn * (TN / 2) + w * (WN / 2) + in % (WN / 2);
-  return f < h ? (in < WN / 2 ? f : h + f) : -1;
-}
-
-__device__ __forceinline__ void end_run(f32x4& sum, f32x4& acc) {
-  sum += acc;
-  acc = f32x4{0.f, 0.f, 0.f, 0.f};
-}
+__device__ __forceinline__ bool finite(float v) { return fabsf(v) <= __FLT_MAX__; }
 
 // Four consecutive output columns n .. n+3 of row m leave for memory (ops 0 and 1).
 template <int OP, int EPI, bool VEC>
@@ -153,346 +150,409 @@ __device__ __forceinline__ int xcd_major(int id, int n) {
   return x * per + min(x, rem) + id / 8;
 }
 
-// One operand's tile of T rows (or columns) x BK: memory -> registers -> LDS -> fragments.  LDS rows are padded by
-// four floats: [T][BK + 4] k-contiguous (16-byte fragment reads of 16 rows fall in different banks), [BK][T + 4]
-// k-strided (the four k rows a read touches start 16 banks apart).
-template <bool KS, int T, bool VEC>
-struct Tile {
-  static constexpr int N4 = T * BK / 4 / kThreads;
-  static constexpr int kFloats = KS ? BK * (T + 4) : T * (BK + 4);
-  f32x4 r[N4];
-  // rows: extent of the tile's own dimension in memory; row_of maps a tile row to a memory row or -1 (k-contiguous)
-  template <class RowOf>
-  __device__ __forceinline__ void load(const float* X, int rows, int ld, int x0, int k0, int kend, int tid, RowOf row_of) {
-#pragma unroll
-    for (int j = 0; j < N4; ++j) {
-      const int i = tid + kThreads * j;
-      if (KS) {
-        const int k = k0 + i / (T / 4), x = x0 + i % (T / 4) * 4;
-        r[j] = load4<VEC>(X + (int64_t)k * ld + x, k < kend ? rows - x : 0);
-      } else {
-        const int row = row_of(i / (BK / 4)), k = k0 + i % (BK / 4) * 4;
-        r[j] = load4<VEC>(X + (int64_t)row * ld + k, row >= 0 ? kend - k : 0);
-      }
-    }
-  }
-  __device__ __forceinline__ void store(float* lds, int tid) const {
-#pragma unroll
-    for (int j = 0; j < N4; ++j) {
-      const int i = tid + kThreads * j;
-      const int at = KS ? i / (T / 4) * (T + 4) + i % (T / 4) * 4 : i / (BK / 4) * (BK + 4) + i % (BK / 4) * 4;
-      *reinterpret_cast<f32x4*>(lds + at) = r[j];
-    }
-  }
-  // rows base .. base+15, k 16 s + 4 kg + {0..3}
-  static __device__ __forceinline__ f32x4 frag(const float* lds, int base, int s, int lr, int kg) {
-    if (!KS) return *reinterpret_cast<const f32x4*>(lds + (base + lr) * (BK + 4) + s * 16 + kg * 4);
-    const float* p = lds + (s * 16 + kg * 4) * (T + 4) + base + lr;
-    return f32x4{p[0], p[T + 4], p[2 * (T + 4)], p[3 * (T + 4)]};
-  }
-};
-
-template <int OP, int EPI, int T, bool VEC>
-__global__ __launch_bounds__(kThreads, 2) void k_gemm_f32(Args g) {
-  constexpr bool AS = OP == 2, BS = OP != 0;
-  typedef Tile<AS, T, VEC> TA;
-  typedef Tile<BS, T, VEC> TB;
-  constexpr int W = T / 2, NB = W / 16;   // a wavefront's share (2 x 2 wavefronts), in blocks of 16 each way
-  __shared__ __attribute__((aligned(16))) float smem[2 * (TA::kFloats + TB::kFloats)];
-  constexpr int kStage = TA::kFloats + TB::kFloats;
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-  int tm, tn;
-  tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
-  const int m0 = tm * T, n0 = tn * T, steps = (g.K + BK - 1) / BK;
-
-  f32x4 acc[NB][NB], sum[NB][NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j)
-#pragma unroll
-    for (int i = 0; i < NB; ++i) sum[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto a_row = [&](int t) { return m0 + t < g.M ? m0 + t : -1; };
-  auto b_row = [&](int t) {
-    if (EPI == kEpiSwiglu) return swiglu_row<T, W>(tn, t, g.N / 2);
-    return n0 + t < g.N ? n0 + t : -1;
-  };
-  TA ta;
-  TB tb;
-  auto fetch = [&](int s) {
-    ta.load(g.A, g.M, AS ? g.M : g.K, m0, s * BK, g.K, tid, a_row);
-    tb.load(g.B, g.N, BS ? g.N : g.K, n0, s * BK, g.K, tid, b_row);
-  };
-  auto put = [&](int s) {
-    float* st = smem + (s & 1) * kStage;
-    ta.store(st, tid);
-    tb.store(st + TA::kFloats, tid);
-  };
-  fetch(0);
-  put(0);
-  __syncthreads();
-  auto step = [&](int s, auto begins) {   // begins: a run, whose first products need no sum to be added to
-    if (s + 1 < steps) fetch(s + 1);
-    const float* la = smem + (s & 1) * kStage;
-    const float* lb = la + TA::kFloats;
-#pragma unroll
-    for (int q = 0; q < BK / 16; ++q) {
-      f32x4 fa[NB], fb[NB];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) fa[j] = TA::frag(la, wm * W + j * 16, q, lr, kg);
-#pragma unroll
-      for (int i = 0; i < NB; ++i) fb[i] = TB::frag(lb, wn * W + i * 16, q, lr, kg);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-          for (int i = 0; i < NB; ++i) {
-            const f32x4 c = decltype(begins)::value && q == 0 && e == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[j][i];
-            acc[j][i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j][e], fb[i][e], c, 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_16x16x4f32(fb[i][e], fa[j][e], c, 0, 0, 0);
-          }
-    }
-    if (s + 1 < steps) put(s + 1);   // into the buffer that every wavefront left before the last barrier
-    if (!decltype(begins)::value || s + 1 == steps)
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int i = 0; i < NB; ++i) sum[j][i] += acc[j][i];
-    __syncthreads();
-  };
-  static_assert(kRun == 2, "a step that begins a run and one that ends it");
-  for (int s = 0; s < steps; s += 2) {
-    step(s, std::true_type());
-    if (s + 1 < steps) step(s + 1, std::false_type());
-  }
-  if (OP == 2) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int n = n0 + wn * W + i * 16 + lr;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = m0 + wm * W + j * 16 + kg * 4 + r;
-          if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, sum[j][i][r]);
-        }
-      }
-  } else if (EPI == kEpiSwiglu) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int m = m0 + wm * W + j * 16 + lr;
-      if (m < g.M) {
-#pragma unroll
-        for (int i = 0; i < NB / 2; ++i)
-          emit_swiglu<VEC>(g, m, tn * (T / 2) + wn * (W / 2) + i * 16 + kg * 4, sum[j][i], sum[j][i + NB / 2]);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int m = m0 + wm * W + j * 16 + lr;
-      if (m < g.M) {
-#pragma unroll
-        for (int i = 0; i < NB; ++i) emit<OP, EPI, VEC>(g, m, n0 + wn * W + i * 16 + kg * 4, sum[j][i]);
-      }
-    }
-  }
+// ---- three-way split, x = h + m + l
+__device__ __forceinline__ uint32_t lead2(float x0, float x1) {   // two values' nearest bfloat16s, one instruction
+  typedef __attribute__((ext_vector_type(2))) float f2;
+  typedef __attribute__((ext_vector_type(2))) __bf16 b2;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, b2));
+}
+struct Split { uint2 h, m, l; };   // four values' parts, in order
+__device__ __forceinline__ uint32_t rest2(float& x0, float& x1) {   // lead2, leaving what is left of the values
+  const uint32_t p = lead2(x0, x1);
+  x0 -= bf16_bits_to_float(p & 0xffffu);
+  x1 -= __uint_as_float(p & 0xffff0000u);
+  return p;
+}
+__device__ __forceinline__ Split split4(float a, float b, float c, float d) {
+  Split s;
+  s.h.x = rest2(a, b); s.h.y = rest2(c, d);
+  s.m.x = rest2(a, b); s.m.y = rest2(c, d);
+  s.l = make_uint2(lead2(a, b), lead2(c, d));
+  return s;
 }
 
-// One thread's quad of a step's BK x T tile for the kernel below: T = 32 rows of 8 quads (k-contiguous) or 32 k of T / 4
-// quads (k-strided), on its way from memory to LDS.  A quad past an edge reads the last one inside again, so that loads
-// need no branches: past the end of k `masked` makes it zeros, past the last row or column nothing of it is stored.
-template <bool KS, bool VEC>
-struct Quad {
-  const float* p;   // start of the quad's row (k-contiguous) or of its first column (k-strided)
-  int kq, dx[3];    // its first k inside a step; k-strided and element-wise: where its other columns are
-  __device__ __forceinline__ void init(const float* X, int row, int ld, int k) { p = X + (int64_t)row * ld; kq = k; }
-  __device__ __forceinline__ void init_cols(const float* X, int col, int cols, int k) {
-    const int x = VEC ? min(col, cols - 4) : min(col, cols - 1);
-    p = X + x;
-    kq = k;
+// An operand's tile of T rows (columns of a k-strided operand) x BK in LDS: three planes [T][BK] of parts, 64 bytes a row,
+// unpadded.  Row r lies at position r / 4 + (r % 4) T / 4 and its 16-byte chunks are permuted by r % 4, so that the 16 rows of
+// a fragment read, the 4 k x columns that half a wavefront of a k-strided operand writes, and the four rows of 32 k of half
+// a wavefront of the other kind each fall in all 64 banks.
+template <int T>
+struct Planes {
+  static constexpr int kPlane = T * BK * 2, kBytes = 3 * kPlane;
+  static __device__ __forceinline__ int at(int row, int chunk) { return ((row >> 2) + (row & 3) * (T / 4)) * 64 + ((chunk ^ (row & 3)) << 4); }
+};
+struct Frag { bf16x8 p[3]; };   // h, m, l of row base + lane % 16, k = (lane / 16) * 8 .. + 7; base a multiple of 16
+template <int T>
+__device__ __forceinline__ Frag frag(const char* lds, int base, int lane_at) {   // lane_at: of row lane % 16
+  Frag f;
 #pragma unroll
-    for (int e = 1; e < 4; ++e) dx[e - 1] = min(col + e, cols - 1) - x;
-  }
-  __device__ __forceinline__ f32x4 load(int k0, int K, int ld) const {
-    const int k = k0 + kq;
-    if (KS) {
-      const float* q = p + (int64_t)min(k, K - 1) * ld;
-      if (VEC) return *reinterpret_cast<const f32x4*>(q);
-      return f32x4{q[0], q[dx[0]], q[dx[1]], q[dx[2]]};
+  for (int i = 0; i < 3; ++i) f.p[i] = *reinterpret_cast<const bf16x8*>(lds + i * Planes<T>::kPlane + base * 16 + lane_at);
+  return f;
+}
+// acc += X Y without the three smallest products (below 2^-24 of a product), the smallest first
+constexpr int kTerms = 6;
+constexpr int kTermX[kTerms] = {2, 0, 1, 1, 0, 0}, kTermY[kTerms] = {0, 2, 1, 0, 1, 0};
+
+// The share of one of NW wavefronts in bringing an operand's tile from memory to LDS: units of a row's 4 consecutive k
+// (k-contiguous) or of 4 k of XW neighbouring columns (k-strided).
+// VEC: buffer loads from a descriptor that starts at the step, so that a lane's offsets are the same for all steps and k past
+// the end of a k-strided operand reads as zeros.  Otherwise element by element.  Rows (columns) past the edge are read as
+// the last one (VEC, k-strided: as what follows); nothing of them is stored.
+template <bool KS, int T, int NW, bool VEC>
+struct Share {
+  static constexpr int Q = T / (8 * NW);                          // quads of 4 k
+  static constexpr int XW = KS ? (Q < 4 ? Q : 4) : 1, NU = Q / XW;
+  const char* base;      // VEC: the first byte that the tile can reach, and how many follow it
+  int64_t left;
+  uint32_t off[NU];
+  const float* p[NU];    // not VEC: a unit's row or first column, and where its other columns are
+  int dx[NU][3], row[NU], lds[NU], k;
+  template <class RowOf>
+  __device__ __forceinline__ void init(const float* X, int ld, int x0, int cols, int K, int wave, int lane, RowOf row_of) {
+    const int64_t first = KS ? (int64_t)x0 : (int64_t)x0 * ld;
+    base = reinterpret_cast<const char*>(X + first);
+    left = ((int64_t)(KS ? K : cols) * ld - first) * 4;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      if (KS) {   // a wavefront: 8 x 4 k by 8 groups of XW columns
+        row[u] = ((wave + NW * u) * 8 + (XW == 4 ? (lane & 3) + (lane >> 5) * 4 : lane & 7)) * XW;
+        k = (XW == 4 ? (lane >> 2) & 7 : lane >> 3) * 4;
+        off[u] = ((uint32_t)k * (uint32_t)ld + row[u]) * 4u;
+        const int c = min(x0 + row[u], cols - 1);
+        p[u] = X + c;
+#pragma unroll
+        for (int e = 1; e < 4; ++e) dx[u][e - 1] = min(x0 + row[u] + e, cols - 1) - c;
+      } else {    // 8 rows of 32 k, four apart and neighbours; two wavefronts take 16 rows
+        row[u] = ((wave >> 1) + NW / 2 * u) * 16 + ((lane >> 3) & 3) * 4 + (wave & 1) * 2 + (lane >> 5);
+        k = (lane & 7) * 4;
+        const int r = row_of(row[u]);
+        off[u] = ((uint32_t)(r - x0) * (uint32_t)ld + k) * 4u;
+        p[u] = X + (int64_t)r * ld;
+      }
+      lds[u] = Planes<T>::at(row[u], k >> 3) + (k & 4) * 2;
     }
-    if (VEC) return *reinterpret_cast<const f32x4*>(p + min(k, K - 4));
-    return f32x4{p[min(k, K - 1)], p[min(k + 1, K - 1)], p[min(k + 2, K - 1)], p[min(k + 3, K - 1)]};
   }
-  __device__ __forceinline__ f32x4 masked(f32x4 v, int k0, int K) const {
-    const int left = K - (k0 + kq);
+  // v[q]: quad q = unit * XW + column; MASK: k past the end of a k-contiguous operand become zeros
+  template <bool MASK>
+  __device__ __forceinline__ void load(float (*v)[4], int k0, int K, int ld) const {
+    if constexpr (VEC) {
+      const int64_t skip = (int64_t)k0 * (KS ? ld : 1) * 4, rest = left - skip;
+      const rsrc_t rs = make_rsrc(base + skip, (uint32_t)(rest > 0x7fffffff ? 0x7fffffff : rest));
+      const uint32_t dead = MASK && !KS && k0 + k >= K ? 0x80000000u : 0u;   // a quad is inside or outside as a whole
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if ((KS || VEC ? 0 : e) >= left) v[e] = 0.f;
-    return v;
+      for (int u = 0; u < NU; ++u) {
+        if constexpr (KS) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int o = (int)(off[u] + (uint32_t)e * (uint32_t)ld * 4u);
+            if constexpr (XW == 4) {
+              const f32x4 x = __builtin_bit_cast(f32x4, buffer_load16(rs, o));
+#pragma unroll
+              for (int c = 0; c < 4; ++c) v[u * XW + c][e] = x[c];
+            } else if constexpr (XW == 2) {
+              const float2 x = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, o, 0, 0));
+              v[u * XW][e] = x.x; v[u * XW + 1][e] = x.y;
+            } else {
+              v[u][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0));
+            }
+          }
+        } else {
+          const f32x4 x = __builtin_bit_cast(f32x4, buffer_load16(rs, MASK ? off[u] | dead : off[u]));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[u][e] = x[e];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int c = 0; c < XW; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int at = min(k0 + k + e, K - 1);
+            const float x = KS ? p[u][(int64_t)at * ld + (c ? dx[u][c ? c - 1 : 0] : 0)] : p[u][at];
+            v[u * XW + c][e] = k0 + k + e < K ? x : 0.f;
+          }
+    }
+  }
+  template <bool NEG>   // negated (a modifier of the split's instructions)
+  __device__ __forceinline__ void put(char* tile, float (*v)[4]) const {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const Split s = NEG ? split4(-v[q][0], -v[q][1], -v[q][2], -v[q][3]) : split4(v[q][0], v[q][1], v[q][2], v[q][3]);
+      char* p = tile + (q % XW ? Planes<T>::at(row[q / XW] + q % XW, k >> 3) + (k & 4) * 2 : lds[q / XW]);
+      *reinterpret_cast<uint2*>(p) = s.h;
+      *reinterpret_cast<uint2*>(p + Planes<T>::kPlane) = s.m;
+      *reinterpret_cast<uint2*>(p + 2 * Planes<T>::kPlane) = s.l;
+    }
   }
 };
 
-// Tiles of 32 x 32 (SwiGLU: 32 rows x 32 features): a wavefront owns a block of 16 x 16 (SwiGLU: of gate and
-// of up columns) over the whole reduction and sums it in the order and with the instructions of k_gemm_f32, so that a
-// row has the same bits whatever kernel the number of rows leads to.  That chain of K / 4 dependent matrix instructions
-// of 32 cycles (and the launch) bounds it: U steps of 32 k are in flight from memory (registers), one in LDS ahead of the
-// one whose fragments are read, and that one ahead of the one being multiplied; one barrier per step.  Through LDS because
-// fragments read straight from memory touch 16 half cache lines an instruction, about 60 cycles each: op 0, us, staged /
-// straight in the order of k / straight with k divided among eight wavefronts as it was before: 128 x 288 x 1536 15.0 /
-// 25.0 / 16.4, 1024 x 288 x 768 12.6 / 27.7 / 15.9, 64 x 1024 x 2816 24.9 / 40.2 / 28.2.  Op 2, one sum / the reduction cut
-// over workgroups and wavefronts and added in no fixed order as it was before: 864 x 288 x 512 7.8 / 12.3, x 2048 17.4 /
-// 18.0, x 4096 30.9 / 29.3, 1536 x 288 x 999 16.1 / 23.6, 4096 x 288 x 4096 112 / 165, but 288 x 288 x 4096 30.5 / 14.4.
-template <int OP, int EPI, bool VEC>
-__global__ __launch_bounds__(kThreads) void k_gemm_f32_small(Args g) {
+// The feeding wavefronts' work: a step per barrier into the buffer that the multiplying ones have left; loads U steps ahead.
+// fetch(step, quads) and put(step, quads): all of the wavefront's quads of a step.
+template <int Q, class Fetch, class Put>
+__device__ __forceinline__ void feed(int steps, Fetch fetch, Put put) {
+  constexpr int U = Q > 6 ? 2 : Q > 4 ? 3 : Q > 3 ? 4 : 6;
+  float raw[U][Q][4];
+  auto load = [&](int s, int u) {   // past the last step the last one again
+    fetch(min(s, steps - 1), raw[u]);
+    __builtin_amdgcn_sched_barrier(0);   // loads stay in the order they are waited for
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) load(u, u);
+  int s = 0;
+  for (; s + U <= steps; s += U)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      put(s + u, raw[u]);
+      load(s + u + U, u);
+      __syncthreads();
+    }
+#pragma unroll
+  for (int u = 0; u < U - 1; ++u)   // the rest is on its way
+    if (s + u < steps) {
+      put(s + u, raw[u]);
+      __syncthreads();
+    }
+}
+
+// Tiles of TM x TN, eight wavefronts, a barrier per step.  The first four (a share of TM / 2 x TN / 2 each) only read fragments
+// and multiply, the others only bring the operands of the next step to LDS, split on the way, U steps of loads in flight: a
+// SIMD holds one of either, and beside the matrix instructions of one wavefront (16 cycles each) another can issue 2.5
+// others, where one that does both gets 1.5 for nothing.
+template <int OP, int EPI, int TM, int TN, bool VEC>
+__global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f32(Args g) {
   constexpr bool AS = OP == 2, BS = OP != 0;
-  constexpr int T = 32, NB = EPI == kEpiSwiglu ? 2 : 1, U = 8;
-  typedef Tile<AS, T, VEC> TA;
-  typedef Tile<BS, T, VEC> TB;
-  static_assert(TA::N4 == 1, "one quad of each tile per thread");
-  constexpr int kStage = TA::kFloats + NB * TB::kFloats;
-  __shared__ __attribute__((aligned(16))) float smem[2 * kStage];
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kg = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  // SwiGLU in 32-tiles: a wavefront holds 16 gate columns and the 16 up columns, so the tile of B has 64 rows
+  constexpr int NSEG = EPI == kEpiSwiglu && TN == 32 ? 2 : 1, TB = TN * NSEG;
+  constexpr int WM = TM / 2, WN = TN / 2, NA = WM / 16, NB = WN / 16 * NSEG;   // a wavefront's share, in blocks of 16
+  constexpr int kBuf = Planes<TM>::kBytes + Planes<TB>::kBytes;
+  __shared__ __attribute__((aligned(16))) char smem[2 * kBuf];
+  const int lane = threadIdx.x & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int tm, tn;
   tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
-  const int m0 = tm * T, n0 = tn * T, K = g.K, steps = (K + BK - 1) / BK;
-  const int cols = EPI == kEpiSwiglu ? g.N / 2 : g.N, lda = AS ? g.M : K, ldb = BS ? g.N : K;
-  f32x4 acc[NB], sum[NB];
-#pragma unroll
-  for (int i = 0; i < NB; ++i) acc[i] = sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (steps > 0) {
-    Quad<AS, VEC> qa;
-    Quad<BS, VEC> qb[NB];
-    if (AS) qa.init_cols(g.A, m0 + tid % 8 * 4, g.M, tid / 8);
-    else qa.init(g.A, min(m0 + tid / 8, g.M - 1), K, tid % 8 * 4);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      if (BS) qb[i].init_cols(g.B, n0 + tid % 8 * 4, cols, tid / 8);
-      else qb[i].init(g.B, i * cols + min(n0 + tid / 8, cols - 1), K, tid % 8 * 4);
-    }
-    f32x4 ra[U], rb[U][NB];
-    auto fetch = [&](int s, int u) {   // past the last step: the last one again
-      const int k0 = min(s, steps - 1) * BK;
-      ra[u] = qa.load(k0, K, lda);
-#pragma unroll
-      for (int i = 0; i < NB; ++i) rb[u][i] = qb[i].load(k0, K, ldb);
-      __builtin_amdgcn_sched_barrier(0);   // loads stay in the order they are waited for
+  const int m0 = tm * TM, n0 = tn * TN, K = g.K, steps = (K + BK - 1) / BK, lda = AS ? g.M : K, ldb = BS ? g.N : K;
+  const int b0 = EPI == kEpiSwiglu && NSEG == 1 ? n0 / 2 : n0;   // the tile's first row (column) of B
+  // memory row of the tile's row t of B (k-contiguous).  SwiGLU: a wavefront's share holds gate rows and the up rows of the
+  // same features (h = N / 2 of them)
+  auto b_row = [&](int t) {
+    if (EPI != kEpiSwiglu) return min(n0 + t, g.N - 1);
+    const int h = g.N / 2;
+    if (NSEG == 2) return (t & 16 ? h : 0) + min(b0 + (t >> 5) * 16 + (t & 15), h - 1);
+    const int w = t / WN, in = t % WN, f = b0 + w * (WN / 2) + in % (WN / 2);
+    return (in < WN / 2 ? 0 : h) + min(f, h - 1);
+  };
+  if (wave >= 4) {
+    if (steps == 0) return;
+    auto a_row = [&](int t) { return min(m0 + t, g.M - 1); };
+    auto buf = [&](int s) { return smem + (s & 1) * kBuf; };
+    auto put_a = [&](const auto& a, int s, float (*v)[4]) {   // every second run negated (kRun)
+      if (s & kRun) a.template put<true>(buf(s), v);
+      else a.template put<false>(buf(s), v);
     };
-    auto put = [&](int s, int u) {
-      float* st = smem + (s & 1) * kStage;
-      const int at = tid / 8 * (BK + 4) + tid % 8 * 4;   // BK = T: the same for either order
-      static_assert(BK == T, "tile rows of the two orders");
-      *reinterpret_cast<f32x4*>(st + at) = qa.masked(ra[u], s * BK, K);
-#pragma unroll
-      for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x4*>(st + TA::kFloats + i * TB::kFloats + at) = qb[i].masked(rb[u][i], s * BK, K);
-    };
-    struct Frags { f32x4 a[BK / 16], b[BK / 16][NB]; };
-    auto read = [&](int s) {
-      const float* st = smem + (s & 1) * kStage;
-      Frags f;
-#pragma unroll
-      for (int q = 0; q < BK / 16; ++q) {
-        f.a[q] = TA::frag(st, wm * 16, q, lr, kg);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) f.b[q][i] = TB::frag(st + TA::kFloats + i * TB::kFloats, wn * 16, q, lr, kg);
+    // Tiles of the same size: two wavefronts for each operand (wider loads); else all four for both.  In op 0 the operands'
+    // rows run on past the end of k: zeros in one of them do (where what the other meets there is not finite, entries are
+    // formed anew).
+    if constexpr (TM == TB) {
+      if (wave < 6) {
+        Share<AS, TM, 2, VEC> a;
+        a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
+        feed<a.Q>(steps, [&](int s, float (*v)[4]) { a.template load<false>(v, s * BK, K, lda); }, [&](int s, float (*v)[4]) { put_a(a, s, v); });
+      } else {
+        Share<BS, TB, 2, VEC> b;
+        b.init(g.B, ldb, b0, g.N, K, wave - 6, lane, b_row);
+        feed<b.Q>(steps, [&](int s, float (*v)[4]) { b.template load<true>(v, s * BK, K, ldb); },
+                  [&](int s, float (*v)[4]) { b.template put<false>(buf(s) + Planes<TM>::kBytes, v); });
       }
-      return f;
-    };
-#pragma unroll
-    for (int u = 0; u < U; ++u) fetch(u, u);
-    put(0, 0);
-    fetch(U, 0);
-    put(1, 1);
-    fetch(U + 1, 1);
-    __syncthreads();
-    Frags now = read(0);
-    __syncthreads();
-    // in LDS: step s + 1 and, from the middle of the step on, s + 2; on the way: the next U
-    static_assert(U % kRun == 0, "runs end at fixed places of a round of U steps");
-    auto step = [&](int s, int u, bool more, bool ends) {   // u = (s + 2) % U; ends: a run
-      const Frags next = read(s + 1);
-#pragma unroll
-      for (int q = 0; q < BK / 16; ++q) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < NB; ++i)
-            acc[i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(now.a[q][e], now.b[q][i][e], acc[i], 0, 0, 0)
-                             : __builtin_amdgcn_mfma_f32_16x16x4f32(now.b[q][i][e], now.a[q][e], acc[i], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (q == 0) {
-          put(s + 2, u);
-          if (more) fetch(s + 2 + U, u);
-        }
-      }
-      if (ends)
-#pragma unroll
-        for (int i = 0; i < NB; ++i) end_run(sum[i], acc[i]);
-      now = next;
-      __syncthreads();
-    };
-    int s = 0;
-    for (; s + U <= steps; s += U)
-#pragma unroll
-      for (int u = 0; u < U; ++u) step(s + u, (u + 2) % U, true, u % kRun == kRun - 1);
-#pragma unroll
-    for (int u = 0; u < U - 1; ++u)   // the rest is on its way
-      if (s + u < steps) step(s + u, (u + 2) % U, false, u % kRun == kRun - 1);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) sum[i] += acc[i];
-  }
-  if (OP == 2) {
-    const int n = n0 + wn * 16 + lr;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + wm * 16 + kg * 4 + r;
-      if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, sum[0][r]);
+    } else {
+      Share<AS, TM, 4, VEC> a;
+      Share<BS, TB, 4, VEC> b;
+      a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
+      b.init(g.B, ldb, b0, g.N, K, wave - 4, lane, b_row);
+      feed<a.Q + b.Q>(
+          steps,
+          [&](int s, float (*v)[4]) {
+            a.template load<false>(v, s * BK, K, lda);
+            b.template load<true>(v + a.Q, s * BK, K, ldb);
+          },
+          [&](int s, float (*v)[4]) {
+            put_a(a, s, v);
+            b.template put<false>(buf(s) + Planes<TM>::kBytes, v + a.Q);
+          });
     }
     return;
   }
-  const int m = m0 + wm * 16 + lr, n = n0 + wn * 16 + kg * 4;
-  if (m >= g.M) return;
-  if (EPI == kEpiSwiglu) emit_swiglu<VEC>(g, m, n, sum[0], sum[NB - 1]);
-  else emit<OP, EPI, VEC>(g, m, n, sum[0]);
+  const int wm = wave >> 1, wn = wave & 1, base_a = wm * WM, base_b = wn * WN * NSEG;
+  f32x4 acc[NA][NB], sum[NA][NB];
+#pragma unroll
+  for (int j = 0; j < NA; ++j)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) acc[j][i] = sum[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int at_a = Planes<TM>::at(lr, kg), at_b = Planes<TB>::at(lr, kg);
+  Frag fa[2], fb[NB];
+  auto read_a = [&](int s, int j) { return frag<TM>(smem + (s & 1) * kBuf, base_a + j * 16, at_a); };
+  auto read_b = [&](int s, int i) { return frag<TB>(smem + (s & 1) * kBuf + Planes<TM>::kBytes, base_b + i * 16, at_b); };
+  // blocks i0 .. i1 - 1 of row j of blocks
+  auto multiply = [&](int j, int i0, int i1, const Frag& a, auto begins) {
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t)
+#pragma unroll
+      for (int i = i0; i < i1; ++i) {
+        const f32x4 c = decltype(begins)::value && t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[j][i];
+        // ops 0 and 1: B is the instruction's row operand (X), A its column operand; op 2: the other way round
+        acc[j][i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[kTermX[t]], fb[i].p[kTermY[t]], c, 0, 0, 0)
+                            : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[i].p[kTermX[t]], a.p[kTermY[t]], c, 0, 0, 0);
+      }
+  };
+  if (steps > 0) {
+    __syncthreads();   // step 0 is in LDS
+#pragma unroll
+    for (int i = 0; i < NB; ++i) fb[i] = read_b(0, i);
+    fa[0] = read_a(0, 0);
+    // The fragments of a row of blocks are read while the row before it is multiplied.  All of a step's are read by its
+    // last row: there the barrier stands, and behind it the next step's are read as registers come free, half a row of
+    // blocks before they are used.  A row's sums of a run are added up while the next row is multiplied.
+    constexpr int H = NB == 1 ? 1 : NB / 2;   // blocks of half a row
+    auto add_up = [&](int j, float sign) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[j][i][r] = __builtin_fmaf(acc[j][i][r], sign, sum[j][i][r]);
+    };
+    auto step = [&](int s, auto begins, auto par) {   // par: which of fa holds the step's first row
+      constexpr int P = decltype(par)::value;
+      constexpr bool first = decltype(begins)::value;
+      const bool more = s + 1 < steps;
+      const float sign = s & kRun ? -1.f : 1.f;
+#pragma unroll
+      for (int j = 0; j < NA; ++j) {
+        if (j + 1 < NA) fa[(P + j + 1) & 1] = read_a(s, j + 1);
+        else if (more) {
+          __syncthreads();
+          fa[(P + NA) & 1] = read_a(s + 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NB; i += H) {
+          multiply(j, i, i + H, fa[(P + j) & 1], begins);
+          if (i == 0 && NA > 1) {
+            if (j > 0 && !first) add_up(j - 1, sign);
+            if (j == 0 && first) add_up(NA - 1, -sign);   // of the run before (zeros in the first)
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (j == NA - 1 && more)
+#pragma unroll
+            for (int e = 0; e < H; ++e) fb[i + e] = read_b(s + 1, i + e);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (NA == 1 && !first) add_up(0, sign);
+    };
+    static_assert(kRun == 2, "a step that begins a run and one that ends it");
+    constexpr int odd = NA & 1;   // an odd number of rows: the next step starts in the other of fa
+    for (int s = 0; s < steps; s += 2) {
+      step(s, std::true_type(), std::integral_constant<int, 0>());
+      if (s + 1 < steps) step(s + 1, std::false_type(), std::integral_constant<int, odd>());
+    }
+    // what the loop left: a run of one step, and the last row of one of two
+    if (steps & 1)
+#pragma unroll
+      for (int j = 0; j < NA; ++j) add_up(j, (steps - 1) & kRun ? -1.f : 1.f);
+    else if (NA > 1) add_up(NA - 1, (steps - 1) & kRun ? -1.f : 1.f);
+  }
+  // The parts of a value that is not finite, or rounds past the largest bfloat16, are infinities and NaN.  An entry that comes
+  // out as either is formed anew from the floats themselves, on the float instruction.
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < NA; ++j)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) bad |= !(finite(sum[j][i][0]) && finite(sum[j][i][1]) && finite(sum[j][i][2]) && finite(sum[j][i][3]));
+  if (__ballot(bad)) {
+    for (int j = 0; j < NA; ++j)
+      for (int i = 0; i < NB; ++i) {
+        const int m = min(m0 + base_a + j * 16 + lr, g.M - 1), n = BS ? min(n0 + base_b + i * 16 + lr, g.N - 1) : b_row(base_b + i * 16 + lr);
+        f32x4 c = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < K; k += 4) {
+          const bool in = k + kg < K;
+          const int kk = min(k + kg, K - 1);
+          const float a = in ? (AS ? g.A[(int64_t)kk * g.M + m] : g.A[(int64_t)m * K + kk]) : 0.f;
+          const float b = in ? (BS ? g.B[(int64_t)kk * g.N + n] : g.B[(int64_t)n * K + kk]) : 0.f;
+          c = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0);
+        }
+#pragma unroll
+        for (int jj = 0; jj < NA; ++jj)
+#pragma unroll
+          for (int ii = 0; ii < NB; ++ii)
+            if (jj == j && ii == i)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) sum[jj][ii][r] = finite(sum[jj][ii][r]) ? sum[jj][ii][r] : c[r];
+      }
+  }
+  if (OP == 2) {
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int n = n0 + base_b + i * 16 + lr;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + base_a + j * 16 + kg * 4 + r;
+          if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, sum[j][i][r]);
+        }
+      }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < NA; ++j) {
+    const int m = m0 + base_a + j * 16 + lr;
+    if (m >= g.M) continue;
+    if (EPI == kEpiSwiglu) {
+      const int f0 = b0 + wn * (NSEG == 2 ? 16 : WN / 2);   // the share's first feature
+#pragma unroll
+      for (int i = 0; i < NB / 2; ++i) emit_swiglu<VEC>(g, m, f0 + i * 16 + kg * 4, sum[j][i], sum[j][i + NB / 2]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) emit<OP, EPI, VEC>(g, m, n0 + base_b + i * 16 + kg * 4, sum[j][i]);
+    }
+  }
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 
-// Tile and its grid for a product.
-struct F32Shape { int tile, tm, tn; };
-static F32Shape choose_f32(int op, int64_t M, int64_t N, int64_t K, int epi) {
+// Tile and its grid for a product: the least of (steps + ends) x time of a step of the CU with the most tiles.  Times are fits
+// (us, op 0 to 2 within 5 %): a 128-tile 1.25; 128 x 64 0.78 alone on its CU, 0.72 each of several; a 64-tile 0.58 alone, 0.88
+// two, 0.44 each of more; a 32-tile 0.27, 0.36 two, 0.52 three, 0.18 each of more (SwiGLU, with its 64 rows of B, 1.6 x).
+// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps.  A product is not cut along k over workgroups: their sums would be
+// added in the order in which they end, and neither would a microbatch's rows have the same bits alone and in a group, nor two
+// passes of the mode that gradients are checked in agree.  us by tile, 128 / 128 x 64 / 64 / 32: op 0 1024 x 1024 x 1024 39 /
+// 29 / 22 / 28, 2048 x 1024 x 5632 188 / 143 / 157 / 236, 3072 x 1024 x 1024 42 / 46 / 46 / 66, 4096 x 768 x 288 17 / 18 / 17 / 23,
+// 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.
+struct F32Shape { int tile_m, tile_n, tm, tn; };
+static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi) {
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
-  auto at = [&](int t) {
-    const int w = epi == kEpiSwiglu && t != 32 ? t / 2 : t;   // stored columns a tile covers of one run
-    return F32Shape{t, (int)((M + t - 1) / t), (int)((out + w - 1) / w)};
-  };
-  auto tiles = [&](int t) { return (int64_t)at(t).tm * at(t).tn; };
-  // Every CU runs its tiles at the rate of its matrix cores, so a product takes as long as the CU with the most
-  // output: ceil(tiles / CUs) tiles.  Tiles of 64 divide the work more evenly; tiles of 128 read half as much per flop
-  // and win where both come out alike (measured within 5 % of each other there).
-  const int64_t cus = cu_count(), t128 = tiles(128), t64 = tiles(64);
-  const int64_t load128 = (t128 + cus - 1) / cus * 4, load64 = (t64 + cus - 1) / cus;
-  int tile = load128 * 100 <= load64 * 105 ? 128 : (t64 >= 128 ? 64 : 32);
-  if (op == 2) {
-    // A weight gradient is few tiles and a long reduction, and is not cut along k over workgroups: their sums would be added
-    // in the order in which they end, and no two passes of the mode that gradients are checked in would agree.  Tiles of 32
-    // keep their loads in flight and divide best, but read twice as much and take a tenth longer on a full chip: us, 32 / 64 /
-    // 128, 4096 x 288 x 2048 59 / 83 / 162, 1536 x 1024 x 1024 38 / 44 / 85, 2048 x 1024 x 3072 133 / 127 / 242, 3072 x 1024
-    // x 2048 133 / 120 / 167, 2048 x 2048 x 4096 342 / 308 / 325, 4096 x 4096 x 1024 369 / 308 / 294.  At one tile of 64 a CU
-    // (1024 x 1024 x 2048 47 / 60) the stage of the 500M shape is 0.4 % faster with 64, beside the other products.
-    const int64_t load32 = (tiles(32) + cus - 1) / cus;
-    if (tile == 128 && t128 < 2 * cus) tile = 64;
-    if (tile != 128) tile = load32 * 110 <= load64 * 400 ? 32 : 64;
+  const int64_t cus = cu_count(), steps = (K + BK - 1) / BK;
+  F32Shape best{};
+  double best_us = 0;
+  const int edges[4][2] = {{128, 128}, {128, 64}, {64, 64}, {32, 32}};
+  for (int t = 0; t < 4; ++t) {
+    const int m = edges[t][0], n = edges[t][1], w = epi == kEpiSwiglu && t < 3 ? n / 2 : n;   // w: stored columns of one run
+    const int64_t tm = (M + m - 1) / m, tn = (out + w - 1) / w, load = (tm * tn + cus - 1) / cus;
+    const double c = (double)load;
+    const double step = t == 0 ? 1.25 * c : t == 1 ? (load == 1 ? 0.78 : 0.72 * c) : t == 2 ? (load == 1 ? 0.58 : 0.44 * c)
+                        : (load == 1 ? 0.27 : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
+    const double us = step * ((double)steps + (t == 0 ? 4.8 : t == 3 ? 6.0 : 4.0));
+    if (t && us >= best_us) continue;
+    best_us = us;
+    best = {m, n, (int)tm, (int)tn};
   }
-  return at(tile);
+  return best;
 }
 
-GemmShape gemm_f32_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
-  const F32Shape c = choose_f32(op, M, N, K, epi);
-  return {c.tile, c.tm * c.tn, c.tm * c.tn};
+GemmShape gemm_f32_shape(int64_t M, int64_t N, int64_t K, int epi) {
+  const F32Shape c = choose_f32(M, N, K, epi);
+  return {c.tile_n, c.tm * c.tn, c.tm * c.tn};
 }
 
 // epi as in gemm_mfma: 0 plain (R optional), 1 rotary, 2 SwiGLU (N = 2h, aux = act), 3 SwiGLU backward (N = h, R =
@@ -503,17 +563,18 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
          rope ? *rope : RopeArgs{nullptr, 1, 2, 0}};
   if (rope) epi = kEpiRope;
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
-  const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0);
-  const F32Shape c = choose_f32(op, M, N, K, epi);
-  const int tile = c.tile;
+  const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0) &&
+                   std::max(std::max(M, N), K) <= 1 << 21 && (epi != kEpiSwiglu || (out + 128) * K < 1ll << 29);   // a tile's offsets fit 31 bits
+  const F32Shape c = choose_f32(M, N, K, epi);
   g.tiles_m = c.tm;
   g.tiles_n = c.tn;
   const dim3 grid((unsigned)(c.tm * c.tn));
 #define SP_GO(OP, EPI, VEC)                                                                                             \
   do {                                                                                                                  \
-    if (tile == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, VEC>), grid, dim3(kThreads), 0, s, g);                \
-    else if (tile == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, VEC>), grid, dim3(kThreads), 0, s, g);             \
-    else hipLaunchKernelGGL((k_gemm_f32_small<OP, EPI, VEC>), grid, dim3(kThreads), 0, s, g);                           \
+    if (c.tile_n == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 128, VEC>), grid, dim3(kThreads), 0, s, g);           \
+    else if (c.tile_m == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 64, VEC>), grid, dim3(kThreads), 0, s, g);       \
+    else if (c.tile_n == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, 64, VEC>), grid, dim3(kThreads), 0, s, g);         \
+    else hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 32, 32, VEC>), grid, dim3(kThreads), 0, s, g);                             \
   } while (0)
 #define SP_GO_V(OP, EPI) do { if (vec) SP_GO(OP, EPI, true); else SP_GO(OP, EPI, false); } while (0)
   if (op == 0 && epi == kEpiRope) SP_GO_V(0, kEpiRope);

@@ -202,3 +202,30 @@ def test_float_products_lose_little_over_long_reductions(op, M, N, K):
     sp.gemm(op, dev(a.T if op == 2 else a), dev(b if op == 0 else b.T), c)
     err = relerr(c.cpu().numpy(), a.astype(np.float64) @ b.astype(np.float64).T)
     assert err < 3.6e-8 * np.sqrt(16 + K / 64), err
+
+
+# 64-tiles alone on their CUs and 128 x 64-tiles, one step and a run and a half; with and without remainders; the smallest
+@pytest.mark.parametrize("M,N,K", [(1024, 1024, 96), (1023, 1021, 97), (2048, 1024, 32), (2048, 1024, 96), (2047, 1023, 95), (5, 3, 2), (36, 32, 33)])
+def test_float_products_of_values_at_the_ends_of_the_range(M, N, K):
+    # operands are split into bfloat16 parts: values that have none, that round past the largest one, and that are so
+    # small that products vanish give what float products of them give, and reach no other row or column
+    a = synth.normal(66, f"ea{M}{N}{K}", (M, K)); b = synth.normal(67, f"eb{M}{N}{K}", (N, K))
+    b[N // 2] *= 1e-30
+    # a value that rounds past the largest bfloat16; no partial sum may pass the largest float (its order would decide)
+    a[M // 3, K // 2] = 3.4028e38; b[:, K // 2] = 0; b[N // 2, K // 2] = 1e-3
+    a[M // 2, 0] = np.inf; a[M - 1, K - 1] = np.nan; b[0, K - 1] = -np.inf
+    a[0] *= 1e-25
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref = a.astype(np.float64) @ b.astype(np.float64).T
+        ref32 = ref.astype(np.float32)
+    for op in (0, 1, 2):
+        c = torch.zeros((M, N), device="cuda")
+        sp.gemm(op, dev(a.T if op == 2 else a), dev(b if op == 0 else b.T), c)
+        got = c.cpu().numpy()
+        fin = np.isfinite(ref32)
+        assert np.array_equal(np.isfinite(got), fin) and np.array_equal(np.isnan(got), np.isnan(ref32)), op
+        assert np.array_equal(got[~fin & ~np.isnan(ref32)], ref32[~fin & ~np.isnan(ref32)]), op
+        # rows have scales of their own: against the largest product of an entry, ten times sqrt(K) 2^-24
+        with np.errstate(over="ignore", invalid="ignore"):
+            size = np.sqrt((a.astype(np.float64) ** 2) @ (b.astype(np.float64) ** 2).T)
+        assert np.all(np.abs(got[fin] - ref[fin]) <= 6e-7 * np.sqrt(K) * size[fin] + 1e-37), op
