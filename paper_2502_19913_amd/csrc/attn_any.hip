@@ -80,6 +80,54 @@ template <> struct Stored<bf16> {
   }
 };
 
+// The products of probabilities (or score gradients) with the walked side, over the tile's 32 rows: lane group kg holds rows
+// 4 kg .. 4 kg + 3 of either half (p0, p1), `rows` is column lr of its first row in LDS, LD floats a row.  acc[c] gets
+// columns 16 c + lr.
+// bf16 storage: a float is the sum of three bfloat16s, exactly, and the other operand is one: three bf16 instructions over 32 rows
+// (48 cycles) form the same products as eight float ones (256 cycles).
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+template <class T> struct Weights {
+  f32x4 p[2];
+  __device__ __forceinline__ Weights(const f32x4& p0, const f32x4& p1) : p{p0, p1} {}
+  template <int LD, int NS>
+  __device__ __forceinline__ void times(const float* rows, f32x4 (&acc)[NS]) const {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int c = 0; c < NS; ++c) acc[c] = mfma(rows[(t * 16 + e) * LD + c * 16], p[t][e], acc[c]);
+  }
+};
+template <> struct Weights<bf16> {
+  bf16x8 part[3];
+  __device__ __forceinline__ Weights(const f32x4& p0, const f32x4& p1) {
+    float v[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        part[i][e] = (bf16)v[e];
+        v[e] -= (float)part[i][e];
+      }
+  }
+  template <int LD, int NS>
+  __device__ __forceinline__ void times(const float* rows, f32x4 (&acc)[NS]) const {
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      typedef __attribute__((ext_vector_type(4))) uint32_t U;
+      U q;   // LDS floats that are bfloat16s: their upper halves
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float* r = rows + ((w >> 1) * 16 + (w & 1) * 2) * LD + c * 16;
+        q[w] = __builtin_amdgcn_perm(__float_as_uint(r[LD]), __float_as_uint(r[0]), 0x07060302u);
+      }
+#pragma unroll
+      for (int i = 2; i >= 0; --i) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, q), part[i], acc[c], 0, 0, 0);
+    }
+  }
+};
+
 // columns c .. c+3 of a row of hd; vec: every row starts 4-element aligned and hd is a multiple of 4
 __device__ __forceinline__ f32x4 row4(const float* row, int c, int hd, bool vec) {
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -347,14 +395,7 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_fwd(const T* __re
       m_i = m_new;
 #pragma unroll
       for (int c = 0; c < NS; ++c) oacc[c] *= alpha;
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float* p = lv + (t * 16 + kg * 4 + e) * LD + lr;
-#pragma unroll
-          for (int c = 0; c < NS; ++c) oacc[c] = mfma(p[c * 16], st[t][e], oacc[c]);
-        }
+      Weights<T>(st[0], st[1]).template times<LD>(lv + kg * 4 * LD + lr, oacc);
     }
     if (kt + SETS < tiles) in.store(smem[(i + 1) & 1][0], smem[(i + 1) & 1][1], tid);
     __syncthreads();
@@ -437,6 +478,7 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
     if (kt + SETS < tiles) in.load(kp, ld, vp, ld, k0 + SETS * KT, T_, hd, vec, tid);
     const float *lk = smem[i & 1][0], *lv = smem[i & 1][1];
     if (kt < tiles && k0 <= qw0 + 15) {
+      f32x4 ds[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
@@ -449,15 +491,10 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const bool seen = k0 + t * 16 + kg * 4 + r <= q;
-          st[r] = seen ? expf(st[r] * scale - L) * (dp[r] - dlt) * scale : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float* p = lk + (t * 16 + kg * 4 + e) * LD + lr;
-#pragma unroll
-          for (int c = 0; c < NS; ++c) dq[c] = mfma(p[c * 16], st[e], dq[c]);
+          ds[t][r] = seen ? expf(st[r] * scale - L) * (dp[r] - dlt) * scale : 0.f;
         }
       }
+      Weights<T>(ds[0], ds[1]).template times<LD>(lk + kg * 4 * LD + lr, dq);
     }
     if (kt + SETS < tiles) in.store(smem[(i + 1) & 1][0], smem[(i + 1) & 1][1], tid);
     __syncthreads();
@@ -539,6 +576,7 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
     const int qs = (t0 + step % nt) * KT;
     const float *lq = smem[buf][0], *lo = smem[buf][1];
     if (step < steps && qs + KT - 1 >= kw0) {   // some query of the tile sees a key of this wavefront
+      f32x4 p[2], ds[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
@@ -554,19 +592,12 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
         for (int r = 0; r < 4; ++r) {
           const int q = qs + t * 16 + kg * 4 + r;
           const bool seen = q >= key && q < T_;
-          st[r] = seen ? expf(st[r] * scale - L[r]) : 0.f;
-          dp[r] = seen ? st[r] * (dp[r] - D[r]) * scale : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int at = (t * 16 + kg * 4 + e) * LD + lr;
-#pragma unroll
-          for (int c = 0; c < NS; ++c) {
-            dv[c] = mfma(lo[at + c * 16], st[e], dv[c]);
-            dk[c] = mfma(lq[at + c * 16], dp[e], dk[c]);
-          }
+          p[t][r] = seen ? expf(st[r] * scale - L[r]) : 0.f;
+          ds[t][r] = seen ? p[t][r] * (dp[r] - D[r]) * scale : 0.f;
         }
       }
+      Weights<T>(p[0], p[1]).template times<LD>(lo + kg * 4 * LD + lr, dv);
+      Weights<T>(ds[0], ds[1]).template times<LD>(lq + kg * 4 * LD + lr, dk);
     }
     if (step + SETS < steps) put(buf ^ 1);
     __syncthreads();

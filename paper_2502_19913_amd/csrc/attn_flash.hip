@@ -540,8 +540,10 @@ __global__ __launch_bounds__(256, 2) void k_flash_bwd_dq(const bf16* __restrict_
 // held negated so that delta enters unchanged), so phase 2 is a product, an exponential, a product and
 // the conversions per element.
 //
-// One wavefront per SIMD (the accumulators leave no room for two), so matrix work, arithmetic and
-// LDS latency overlap inside the wavefront, by software pipelining over the tiles:
+// One wavefront per SIMD (at head dimension 128 the accumulators leave no room for two), so matrix work, arithmetic and
+// LDS latency overlap inside the wavefront, by software pipelining over the tiles (at 64 two fit once the compiler is held to
+// 256 registers, which it meets without spills: the whole backward of 64 / 192 / 512 heads of 1024 positions 65 -> 57, 168 -> 133,
+// 488 -> 382 us; three, 168 registers, spill: 3 x slower):
 //   first half of an iteration   phase 1 of tile i+1 (operands already in registers), phase 2 of
 //                                tile i, LDS reads of tile i's phase 3 operands
 //   second half                  phase 3 of tile i, LDS reads of tile i+2's phase 1 operands and
@@ -561,7 +563,7 @@ __global__ __launch_bounds__(256, 2) void k_flash_bwd_dq(const bf16* __restrict_
 // the buffer descriptors), and zero rows of Q and dO contribute nothing to either gradient.
 
 template <int HD>
-__global__ __launch_bounds__(256) void k_flash_bwd_dkv(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
+__global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void k_flash_bwd_dkv(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
                                                        const float* __restrict__ lse, const float* __restrict__ delta,
                                                        bf16* __restrict__ dqkv, int T, int H, int Hkv, float scale,
                                                        const float* __restrict__ rope_tab) {
