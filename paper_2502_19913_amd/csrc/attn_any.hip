@@ -1,7 +1,6 @@
-// Causal attention for any element type and even head dimension up to 256, on the float matrix instruction
-// (v_mfma_f32_16x16x4_f32): the float mode, and bf16 with head dimensions the bf16 kernels (attn_flash.hip) do not
-// take.  Values are float from LDS on, whatever their storage type; only the products of two stored bf16 operands use
-// the bf16 instruction.  Also the dispatch over the two families.
+// Causal attention for any element type and even head dimension up to 256: the float mode, on the float matrix instruction
+// (v_mfma_f32_16x16x4_f32), and bf16 with head dimensions the bf16 kernels (attn_flash.hip) do not take, on the bf16 one, with
+// probabilities and score gradients still floats (Stored<bf16> below).  Also the dispatch over the two families.
 //
 // Same plan as the bf16 kernels: a workgroup of four wavefronts (or two sets of four, below) owns 64 queries (16 per
 // wavefront; 64 keys in the dK/dV kernel) of one head and walks the other side in tiles of 32 rows through LDS, two
@@ -11,10 +10,15 @@
 // lanes is directly the operand of the r-th instruction of the next product (O^T += V^T P^T).  The dK/dV kernel is
 // the mirror image.
 //
-// The row-wise operand of a product is one 16-byte LDS read per four instructions, the transposed one a 4-byte read
+// In float the row-wise operand of a product is one 16-byte LDS read per four instructions, the transposed one a 4-byte read
 // per instruction; LDS rows are padded by 16 bytes, which keeps both free of bank conflicts.  One LDS read per
-// 32-cycle instruction leaves LDS idle most of the time; what bounds a workgroup is the chain of its tiles.  HD is
-// the head dimension rounded up to a compiled size; columns past the real one are zeros. One wavefront per row of
+// 32-cycle instruction leaves LDS idle most of the time; what bounds a workgroup is the chain of its tiles.  In bf16 the
+// matrix instructions are a fifth of that and vector instructions bound it (four wavefronts a SIMD, 285 a tile and wavefront of
+// the forward kernel before, 190 now): tiles lie in LDS as stored, the transposed operand comes by the LDS transpose read,
+// exponentials take half of expf's instructions, masks only stand where some key is hidden.  Heads of 48, forward | backward us, float
+// instruction and float tiles -> this: 3 x 333 positions x 6 heads 17 | 43 -> 10 | 25, 16 x 256 x 6 22 | 53 -> 13 | 31, 8 x 1024 x 16
+// 263 | 646 -> 109 | 289; the 50M shape on 3 x 333 tokens 3.60 -> 2.96 ms a pass.  (Float, of the same exponentials and masks: 8 x
+// 1024 x 16 heads of 48 312 | 891 -> 284 | 856.)  HD is the head dimension rounded up to a compiled size; columns past the real one are zeros. One wavefront per row of
 // scores (the kernels these replaced) left the matrix cores idle and re-read K and V for every query.  Measured,
 // forward | backward (dQ and dK/dV), us: 6 sequences x 512 x 16 heads of 64 in float 542 -> 90 (36 TFLOP/s of the
 // causal half) | 7825 -> 269; 16 x 256 x 6 heads of 48 129 -> 33 | 1522 -> 82; 2 x 64 x 6 heads of 48, where launches
@@ -49,108 +53,105 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 __device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-// The two products whose operands both come from storage (scores, and dO V^T).  F: four columns of the side that stays
-// in registers; a0, a1: four columns of the walked side as they lie in LDS; c0, c1: two independent sums.  bf16 storage
-// takes the bf16 instruction: its operands are the stored values themselves (an LDS float's upper half), their
-// products are exact and the sums float, for an eighth of the cycles.  Probabilities and score gradients are
-// floats in either type, so the products that take them stay on the float instruction.
-// 50M shape in bf16 (heads of 48, 3 x 333 tokens): 3.91 -> 3.61 ms a pass.
+// exp(x) for x at most a few units above zero: x log2(e) in two parts, the second (the first's rounding and the constant's) at
+// first order, so that large arguments lose nothing; half the instructions of expf, which also looks after overflow.
+__device__ __forceinline__ float exp_(float x) {
+  constexpr float kL = 1.44269502f, kLl = 1.92596299e-8f, kLn2 = 0.693147182f;   // log2(e) and what is left of it; ln 2
+  const float hi = x * kL, lo = __builtin_fmaf(x, kLl, __builtin_fmaf(x, kL, -hi)), e = __builtin_amdgcn_exp2f(hi);
+  return hi > -__FLT_MAX__ ? __builtin_fmaf(e, lo * kLn2, e) : e;   // at -inf there is no second part
+}
+
+// What differs between the two storage types.  Quad: four values of a row as they travel and lie in LDS (LD values a row).
+//   dot2    the two products whose operands both come from storage (scores, and dO V^T): a0, a1 four columns of the walked
+//           side, b0, b1 of the side that stays in registers, c0, c1 two independent sums.
+//   times   acc[c] (columns 16 c + lr) += products of probabilities (or score gradients) with the tile's 32 rows: lane
+//           group kg holds those of rows 4 kg .. 4 kg + 3 of either half (p0, p1).
+// Probabilities and score gradients are floats in either type.  bf16 storage takes the bf16 instruction for both: stored
+// operands are used as they are, their products are exact and the sums float, and a probability is the sum of three
+// bfloat16s, exactly: three instructions over 32 rows (48 cycles) instead of eight float ones (256).
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
 template <class T> struct Stored {
-  typedef f32x4 F;
-  static __device__ __forceinline__ F keep(const f32x4& v) { return v; }
-  static __device__ __forceinline__ void dot2(const f32x4& a0, const F& b0, f32x4& c0, const f32x4& a1, const F& b1, f32x4& c1) {
+  typedef f32x4 Quad;
+  template <int HD> static constexpr int LD = HD + 4;
+  static __device__ __forceinline__ Quad of(float a, float b, float c, float d) { return Quad{a, b, c, d}; }
+  static __device__ __forceinline__ f32x4 floats(const Quad& q) { return q; }
+  static __device__ __forceinline__ void dot2(const Quad& a0, const Quad& b0, f32x4& c0, const Quad& a1, const Quad& b1, f32x4& c1) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       c0 = mfma(a0[e], b0[e], c0);
       c1 = mfma(a1[e], b1[e], c1);
     }
   }
-};
-template <> struct Stored<bf16> {
-  typedef __attribute__((ext_vector_type(4))) short F;
-  static __device__ __forceinline__ F keep(const f32x4& v) {
-    typedef __attribute__((ext_vector_type(2))) uint32_t U;
-    const U q = {__builtin_amdgcn_perm(__float_as_uint(v[1]), __float_as_uint(v[0]), 0x07060302u),
-                 __builtin_amdgcn_perm(__float_as_uint(v[3]), __float_as_uint(v[2]), 0x07060302u)};
-    return __builtin_bit_cast(F, q);
-  }
-  static __device__ __forceinline__ void dot2(const f32x4& a0, const F& b0, f32x4& c0, const f32x4& a1, const F& b1, f32x4& c1) {
-    c0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(keep(a0), b0, c0, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(keep(a1), b1, c1, 0, 0, 0);
-  }
-};
-
-// The products of probabilities (or score gradients) with the walked side, over the tile's 32 rows: lane group kg holds rows
-// 4 kg .. 4 kg + 3 of either half (p0, p1), `rows` is column lr of its first row in LDS, LD floats a row.  acc[c] gets
-// columns 16 c + lr.
-// bf16 storage: a float is the sum of three bfloat16s, exactly, and the other operand is one: three bf16 instructions over 32 rows
-// (48 cycles) form the same products as eight float ones (256 cycles).
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-template <class T> struct Weights {
-  f32x4 p[2];
-  __device__ __forceinline__ Weights(const f32x4& p0, const f32x4& p1) : p{p0, p1} {}
   template <int LD, int NS>
-  __device__ __forceinline__ void times(const float* rows, f32x4 (&acc)[NS]) const {
+  static __device__ __forceinline__ void times(const f32x4& p0, const f32x4& p1, const float* tile, int lr, int kg, f32x4 (&acc)[NS]) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e) {
+        const float* row = tile + (t * 16 + kg * 4 + e) * LD + lr;
 #pragma unroll
-        for (int c = 0; c < NS; ++c) acc[c] = mfma(rows[(t * 16 + e) * LD + c * 16], p[t][e], acc[c]);
+        for (int c = 0; c < NS; ++c) acc[c] = mfma(row[c * 16], t ? p1[e] : p0[e], acc[c]);
+      }
   }
 };
-template <> struct Weights<bf16> {
-  bf16x8 part[3];
-  __device__ __forceinline__ Weights(const f32x4& p0, const f32x4& p1) {
+template <> struct Stored<bf16> {
+  typedef s16x4 Quad;
+  template <int HD> static constexpr int LD = HD + 8;
+  static __device__ __forceinline__ Quad of(bf16 a, bf16 b, bf16 c, bf16 d) {
+    typedef __attribute__((ext_vector_type(4))) __bf16 B;
+    return __builtin_bit_cast(Quad, B{a, b, c, d});
+  }
+  static __device__ __forceinline__ f32x4 floats(const Quad& v) {
+    const uint2 q = __builtin_bit_cast(uint2, v);
+    return f32x4{bf16_bits_to_float(q.x & 0xffffu), __uint_as_float(q.x & 0xffff0000u), bf16_bits_to_float(q.y & 0xffffu), __uint_as_float(q.y & 0xffff0000u)};
+  }
+  static __device__ __forceinline__ void dot2(const Quad& a0, const Quad& b0, f32x4& c0, const Quad& a1, const Quad& b1, f32x4& c1) {
+    c0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b0, c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b1, c1, 0, 0, 0);
+  }
+  // The walked side column by column with the LDS transpose read (within 16 lanes, lane s addresses row s / 4 and columns
+  // 4 (s % 4) .. + 3 of a block of 4 rows x 16 columns and receives column s of the four rows).
+  template <int LD, int NS>
+  static __device__ __forceinline__ void times(const f32x4& p0, const f32x4& p1, const bf16* tile, int lr, int kg, f32x4 (&acc)[NS]) {
+    typedef __attribute__((ext_vector_type(2))) float f2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 b2;
+    typedef __attribute__((ext_vector_type(4))) uint32_t U;
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
     float v[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+    U part[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        part[i][e] = (bf16)v[e];
-        v[e] -= (float)part[i][e];
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t p = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{v[2 * w], v[2 * w + 1]}, b2));
+        part[i][w] = p;
+        v[2 * w] -= bf16_bits_to_float(p & 0xffffu);
+        v[2 * w + 1] -= __uint_as_float(p & 0xffff0000u);
       }
-  }
-  template <int LD, int NS>
-  __device__ __forceinline__ void times(const float* rows, f32x4 (&acc)[NS]) const {
+    const bf16* at = tile + (kg * 4 + (lr >> 2)) * LD + (lr & 3) * 4;
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
-      typedef __attribute__((ext_vector_type(4))) uint32_t U;
-      U q;   // LDS floats that are bfloat16s: their upper halves
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(at + c * 16));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(at + 16 * LD + c * 16));
+      typedef __attribute__((ext_vector_type(8))) short s16x8;
+      const bf16x8 x = __builtin_bit_cast(bf16x8, s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float* r = rows + ((w >> 1) * 16 + (w & 1) * 2) * LD + c * 16;
-        q[w] = __builtin_amdgcn_perm(__float_as_uint(r[LD]), __float_as_uint(r[0]), 0x07060302u);
-      }
-#pragma unroll
-      for (int i = 2; i >= 0; --i) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, q), part[i], acc[c], 0, 0, 0);
+      for (int i = 2; i >= 0; --i) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8, part[i]), acc[c], 0, 0, 0);
     }
   }
 };
 
-// columns c .. c+3 of a row of hd; vec: every row starts 4-element aligned and hd is a multiple of 4
-__device__ __forceinline__ f32x4 row4(const float* row, int c, int hd, bool vec) {
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+// columns c .. c+3 of a row of hd, zeros past it; vec: every row starts 4-element aligned and hd is a multiple of 4
+template <class T>
+__device__ __forceinline__ typename Stored<T>::Quad row4(const T* row, int c, int hd, bool vec) {
+  typedef typename Stored<T>::Quad Quad;
+  const T zero = from_float<T>(0.f);
+  Quad v = Stored<T>::of(zero, zero, zero, zero);
   if (vec) {
-    if (c < hd) v = *reinterpret_cast<const f32x4*>(row + c);
+    if (c < hd) v = *reinterpret_cast<const Quad*>(row + c);
   } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (c + e < hd) v[e] = row[c + e];
-  }
-  return v;
-}
-__device__ __forceinline__ f32x4 row4(const bf16* row, int c, int hd, bool vec) {
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  if (vec) {
-    if (c < hd) {
-      const uint2 q = *reinterpret_cast<const uint2*>(row + c);
-      v = f32x4{bf16_bits_to_float(q.x & 0xffffu), bf16_bits_to_float(q.x >> 16), bf16_bits_to_float(q.y & 0xffffu), bf16_bits_to_float(q.y >> 16)};
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (c + e < hd) v[e] = (float)row[c + e];
+    v = Stored<T>::of(c < hd ? row[c] : zero, c + 1 < hd ? row[c + 1] : zero, c + 2 < hd ? row[c + 2] : zero, c + 3 < hd ? row[c + 3] : zero);
   }
   return v;
 }
@@ -286,31 +287,34 @@ __device__ void dkv_row(const T* k, const T* v, const T* q, const T* dO, const f
   put_row(dv, av, hd, lane);
 }
 
-// Two matrices' tiles of KT rows on their way from memory to LDS: [KT][HD + 4] floats each.
+// Two matrices' tiles of KT rows on their way from memory to LDS: [KT][LD] values each.
 template <class T, int HD>
 struct Pair {
-  static constexpr int LD = HD + 4, N4 = (KT * HD / 4 + kThreads - 1) / kThreads;
-  f32x4 x[N4], y[N4];
+  typedef Stored<T> S;
+  typedef typename S::Quad Quad;
+  static constexpr int LD = S::template LD<HD>, N4 = (KT * HD / 4 + kThreads - 1) / kThreads;
+  Quad x[N4], y[N4];
   // rows r0 .. of X (row stride ldx) and Y (ldy); rows at or past `rows` are zeros
   __device__ __forceinline__ void load(const T* X, int64_t ldx, const T* Y, int64_t ldy, int r0, int rows, int hd, bool vec, int tid) {
     const T *xt = X + (int64_t)r0 * ldx, *yt = Y + (int64_t)r0 * ldy;
 #pragma unroll
     for (int j = 0; j < N4; ++j) {
       const int i = tid + kThreads * j, in = i / (HD / 4), c = i % (HD / 4) * 4;
-      x[j] = y[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const T zero = from_float<T>(0.f);
+      x[j] = y[j] = S::of(zero, zero, zero, zero);
       if (r0 + in < rows && i < KT * HD / 4) {   // 32 rows of at most 3 x 65535 heads of 256: offsets fit 32 bits
         x[j] = row4(xt + (uint32_t)in * (uint32_t)ldx, c, hd, vec);
         y[j] = row4(yt + (uint32_t)in * (uint32_t)ldy, c, hd, vec);
       }
     }
   }
-  __device__ __forceinline__ void store(float* lx, float* ly, int tid) const {
+  __device__ __forceinline__ void store(T* lx, T* ly, int tid) const {
 #pragma unroll
     for (int j = 0; j < N4; ++j) {
       const int i = tid + kThreads * j, at = i / (HD / 4) * LD + i % (HD / 4) * 4;
       if (i < KT * HD / 4) {
-        *reinterpret_cast<f32x4*>(lx + at) = x[j];
-        *reinterpret_cast<f32x4*>(ly + at) = y[j];
+        *reinterpret_cast<Quad*>(lx + at) = x[j];
+        *reinterpret_cast<Quad*>(ly + at) = y[j];
       }
     }
   }
@@ -318,10 +322,10 @@ struct Pair {
 
 // The second set's HD / 16 accumulators of every lane on their way to the first set, quad by quad; the place past them,
 // which both return, has room for two more floats of a lane (kThreads apart).  All of it fits a set's buffers:
-// kThreads * (HD / 4 + 2) <= 4 KT (HD + 4) floats (checked below).
+// kThreads * (HD / 4 + 2) floats <= 4 KT LD values (checked below).
 template <int HD>
 __device__ __forceinline__ float* give(float* at, const f32x4* v, int tid) {
-  static_assert(kThreads * (HD / 4 + 2) <= 4 * KT * (HD + 4), "two sets' exchange fits one set's buffers");
+  static_assert(kThreads * (HD / 4 + 2) * 4 <= 4 * KT * (HD + 8) * 2, "two sets' exchange fits one set's buffers (of the smaller type)");
 #pragma unroll
   for (int c = 0; c < HD / 16; ++c) reinterpret_cast<f32x4*>(at)[c * kThreads + tid] = v[c];
   return at + HD / 16 * 4 * kThreads + tid;
@@ -336,8 +340,10 @@ __device__ __forceinline__ const float* take(const float* at, f32x4* v, int tid)
 template <class T, int HD>
 __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_fwd(const T* __restrict__ qkv, int T_, int H, int Hkv, int hd, bool vec, float scale,
                                                        T* __restrict__ o, float* __restrict__ lse) {
-  constexpr int LD = HD + 4, NS = HD / 16, SETS = kSets<HD>;
-  __shared__ __attribute__((aligned(16))) float smem_all[SETS][2][2][KT * LD];
+  typedef Stored<T> S;
+  typedef typename S::Quad Quad;
+  constexpr int LD = S::template LD<HD>, NS = HD / 16, SETS = kSets<HD>;
+  __shared__ __attribute__((aligned(16))) T smem_all[SETS][2][2][KT * LD];
   const int set = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
   const int lane = tid & 63, lr = lane & 15, kg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto& smem = smem_all[set];
@@ -347,12 +353,11 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_fwd(const T* __re
   const int64_t ld = (int64_t)(H + 2 * Hkv) * hd;
   const T* base = qkv + (int64_t)b * T_ * ld;
   const T *kp = base + (H + kvh) * hd, *vp = base + (H + Hkv + kvh) * hd;
-  typedef Stored<T> S;
-  typename S::F qf[NS];
+  Quad qf[NS];
   f32x4 oacc[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    qf[s] = S::keep(row4(base + (int64_t)min(q, T_ - 1) * ld + a * hd, s * 16 + kg * 4, hd, vec));
+    qf[s] = row4(base + (int64_t)min(q, T_ - 1) * ld + a * hd, s * 16 + kg * 4, hd, vec);
     oacc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   float m_i = -INFINITY, l_i = 0.f;
@@ -364,52 +369,56 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_fwd(const T* __re
   for (int i = 0; i * SETS < tiles; ++i) {   // every wavefront the same number of rounds
     const int kt = i * SETS + set, k0 = kt * KT;
     if (kt + SETS < tiles) in.load(kp, ld, vp, ld, k0 + SETS * KT, T_, hd, vec, tid);
-    const float *lk = smem[i & 1][0], *lv = smem[i & 1][1];
+    const T *lk = smem[i & 1][0], *lv = smem[i & 1][1];
     if (kt < tiles && k0 <= qw0 + 15) {   // some key of the tile is visible to this wavefront
       f32x4 st[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const f32x4 f0 = *reinterpret_cast<const f32x4*>(lk + lr * LD + s * 16 + kg * 4);
-        const f32x4 f1 = *reinterpret_cast<const f32x4*>(lk + (16 + lr) * LD + s * 16 + kg * 4);
+        const Quad f0 = *reinterpret_cast<const Quad*>(lk + lr * LD + s * 16 + kg * 4);
+        const Quad f1 = *reinterpret_cast<const Quad*>(lk + (16 + lr) * LD + s * 16 + kg * 4);
         S::dot2(f0, qf[s], st[0], f1, qf[s], st[1]);
+      }
+      if (k0 + KT - 1 > qw0) {   // not every key is visible to every query
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (k0 + t * 16 + kg * 4 + r > q) st[t][r] = -INFINITY;
       }
       float mx = -INFINITY;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (k0 + t * 16 + kg * 4 + r > q) st[t][r] = -INFINITY;
-          mx = fmaxf(mx, st[t][r]);
-        }
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, st[t][r]);
       const float m_new = fmaxf(m_i, max4(mx) * scale);   // -inf while every score is: NaN, formed anew
-      const float alpha = expf(m_i - m_new);
+      const float alpha = exp_(m_i - m_new);
       float rs = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          st[t][r] = expf(st[t][r] * scale - m_new);
+          st[t][r] = exp_(st[t][r] * scale - m_new);
           rs += st[t][r];
         }
       l_i = l_i * alpha + rs;
       m_i = m_new;
 #pragma unroll
       for (int c = 0; c < NS; ++c) oacc[c] *= alpha;
-      Weights<T>(st[0], st[1]).template times<LD>(lv + kg * 4 * LD + lr, oacc);
+      S::template times<LD>(st[0], st[1], lv, lr, kg, oacc);
     }
     if (kt + SETS < tiles) in.store(smem[(i + 1) & 1][0], smem[(i + 1) & 1][1], tid);
     __syncthreads();
   }
   if (SETS == 2) {   // the other set's maximum, sum and outputs come over through LDS; it may have seen no key (-inf, 0, 0)
     if (set == 1) {
-      float* p = give<HD>(&smem_all[0][0][0][0], oacc, tid);
+      float* p = give<HD>(reinterpret_cast<float*>(&smem_all[0][0][0][0]), oacc, tid);
       p[0] = m_i;
       p[kThreads] = l_i;
     }
     __syncthreads();
     if (set == 1) return;
     f32x4 o1[NS];
-    const float* p = take<HD>(&smem_all[0][0][0][0], o1, tid);
+    const float* p = take<HD>(reinterpret_cast<const float*>(&smem_all[0][0][0][0]), o1, tid);
     const float m1 = p[0], m_new = fmaxf(m_i, m1), a0 = expf(m_i - m_new), a1 = expf(m1 - m_new);
     l_i = l_i * a0 + p[kThreads] * a1;
     m_i = m_new;
@@ -439,8 +448,10 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
                                                           float* __restrict__ delta, const T* __restrict__ dO, int T_, int H, int Hkv,
                                                           int hd, bool vec, float scale, const float* __restrict__ rope_tab,
                                                           T* __restrict__ dqkv) {
-  constexpr int LD = HD + 4, NS = HD / 16, SETS = kSets<HD>;
-  __shared__ __attribute__((aligned(16))) float smem_all[SETS][2][2][KT * LD];
+  typedef Stored<T> S;
+  typedef typename S::Quad Quad;
+  constexpr int LD = S::template LD<HD>, NS = HD / 16, SETS = kSets<HD>;
+  __shared__ __attribute__((aligned(16))) T smem_all[SETS][2][2][KT * LD];
   const int set = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
   const int lane = tid & 63, lr = lane & 15, kg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto& smem = smem_all[set];
@@ -450,17 +461,15 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
   const int64_t ld = (int64_t)(H + 2 * Hkv) * hd, row = (int64_t)b * T_ + qc, stat = ((int64_t)b * H + a) * T_ + qc;
   const T* base = qkv + (int64_t)b * T_ * ld;
   const T *kp = base + (H + kvh) * hd, *vp = base + (H + Hkv + kvh) * hd;
-  typedef Stored<T> S;
-  typename S::F qf[NS], dof[NS];
+  Quad qf[NS], dof[NS];
   f32x4 dq[NS];
   float dlt = 0.f;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const int c = s * 16 + kg * 4;
-    qf[s] = S::keep(row4(base + qc * ld + a * hd, c, hd, vec));
-    const f32x4 df = row4(dO + row * H * hd + a * hd, c, hd, vec);
-    dof[s] = S::keep(df);
-    const f32x4 of = row4(o + row * H * hd + a * hd, c, hd, vec);
+    qf[s] = row4(base + qc * ld + a * hd, c, hd, vec);
+    dof[s] = row4(dO + row * H * hd + a * hd, c, hd, vec);
+    const f32x4 df = S::floats(dof[s]), of = S::floats(row4(o + row * H * hd + a * hd, c, hd, vec));
 #pragma unroll
     for (int e = 0; e < 4; ++e) dlt += df[e] * of[e];
     dq[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -476,7 +485,7 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
   for (int i = 0; i * SETS < tiles; ++i) {   // every wavefront the same number of rounds
     const int kt = i * SETS + set, k0 = kt * KT;
     if (kt + SETS < tiles) in.load(kp, ld, vp, ld, k0 + SETS * KT, T_, hd, vec, tid);
-    const float *lk = smem[i & 1][0], *lv = smem[i & 1][1];
+    const T *lk = smem[i & 1][0], *lv = smem[i & 1][1];
     if (kt < tiles && k0 <= qw0 + 15) {
       f32x4 ds[2];
 #pragma unroll
@@ -485,26 +494,30 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dq(const T* _
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
           const int at = (t * 16 + lr) * LD + s * 16 + kg * 4;
-          const f32x4 fk = *reinterpret_cast<const f32x4*>(lk + at), fv = *reinterpret_cast<const f32x4*>(lv + at);
+          const Quad fk = *reinterpret_cast<const Quad*>(lk + at), fv = *reinterpret_cast<const Quad*>(lv + at);
           S::dot2(fk, qf[s], st, fv, dof[s], dp);
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const bool seen = k0 + t * 16 + kg * 4 + r <= q;
-          ds[t][r] = seen ? expf(st[r] * scale - L) * (dp[r] - dlt) * scale : 0.f;
-        }
+        for (int r = 0; r < 4; ++r) ds[t][r] = exp_(st[r] * scale - L) * (dp[r] - dlt) * scale;
       }
-      Weights<T>(ds[0], ds[1]).template times<LD>(lk + kg * 4 * LD + lr, dq);
+      if (k0 + KT - 1 > qw0) {   // not every key is visible to every query
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (k0 + t * 16 + kg * 4 + r > q) ds[t][r] = 0.f;
+      }
+      S::template times<LD>(ds[0], ds[1], lk, lr, kg, dq);
     }
     if (kt + SETS < tiles) in.store(smem[(i + 1) & 1][0], smem[(i + 1) & 1][1], tid);
     __syncthreads();
   }
   if (SETS == 2) {
-    if (set == 1) give<HD>(&smem_all[0][0][0][0], dq, tid);
+    if (set == 1) give<HD>(reinterpret_cast<float*>(&smem_all[0][0][0][0]), dq, tid);
     __syncthreads();
     if (set == 1) return;
     f32x4 o1[NS];
-    take<HD>(&smem_all[0][0][0][0], o1, tid);
+    take<HD>(reinterpret_cast<const float*>(&smem_all[0][0][0][0]), o1, tid);
 #pragma unroll
     for (int c = 0; c < NS; ++c) dq[c] += o1[c];
   }
@@ -531,8 +544,10 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
                                                            const float* __restrict__ delta, const T* __restrict__ dO, int T_, int H,
                                                            int Hkv, int hd, bool vec, float scale, const float* __restrict__ rope_tab,
                                                            T* __restrict__ dqkv) {
-  constexpr int LD = HD + 4, NS = HD / 16, SETS = kSets<HD>;
-  __shared__ __attribute__((aligned(16))) float smem_all[SETS][2][2][KT * LD];
+  typedef Stored<T> S;
+  typedef typename S::Quad Quad;
+  constexpr int LD = S::template LD<HD>, NS = HD / 16, SETS = kSets<HD>;
+  __shared__ __attribute__((aligned(16))) T smem_all[SETS][2][2][KT * LD];
   __shared__ __attribute__((aligned(16))) float s_lse_all[SETS][2][KT], s_dlt_all[SETS][2][KT];
   const int set = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
   const int lane = tid & 63, lr = lane & 15, kg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -542,13 +557,12 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
   const int k0 = blockIdx.x * BQ, kw0 = k0 + wave * 16, key = kw0 + lr, kc = min(key, T_ - 1);
   const int64_t ld = (int64_t)(H + 2 * Hkv) * hd, ldo = (int64_t)H * hd;
   const T* base = qkv + (int64_t)b * T_ * ld;
-  typedef Stored<T> S;
-  typename S::F kf[NS], vf[NS];
+  Quad kf[NS], vf[NS];
   f32x4 dk[NS], dv[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    kf[s] = S::keep(row4(base + kc * ld + (H + kvh) * hd, s * 16 + kg * 4, hd, vec));
-    vf[s] = S::keep(row4(base + kc * ld + (H + Hkv + kvh) * hd, s * 16 + kg * 4, hd, vec));
+    kf[s] = row4(base + kc * ld + (H + kvh) * hd, s * 16 + kg * 4, hd, vec);
+    vf[s] = row4(base + kc * ld + (H + Hkv + kvh) * hd, s * 16 + kg * 4, hd, vec);
     dk[s] = dv[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // the walk: for every query head of this kv head, the query tiles from the workgroup's first key on
@@ -574,7 +588,7 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
     const int step = i * SETS + set, buf = i & 1;
     if (step + SETS < steps) fetch(step + SETS);
     const int qs = (t0 + step % nt) * KT;
-    const float *lq = smem[buf][0], *lo = smem[buf][1];
+    const T *lq = smem[buf][0], *lo = smem[buf][1];
     if (step < steps && qs + KT - 1 >= kw0) {   // some query of the tile sees a key of this wavefront
       f32x4 p[2], ds[2];
 #pragma unroll
@@ -583,35 +597,42 @@ __global__ __launch_bounds__(kThreads * kSets<HD>) void k_attn_bwd_dkv(const T* 
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
           const int at = (t * 16 + lr) * LD + s * 16 + kg * 4;
-          const f32x4 fq = *reinterpret_cast<const f32x4*>(lq + at), fo = *reinterpret_cast<const f32x4*>(lo + at);
+          const Quad fq = *reinterpret_cast<const Quad*>(lq + at), fo = *reinterpret_cast<const Quad*>(lo + at);
           S::dot2(fq, kf[s], st, fo, vf[s], dp);
         }
         const f32x4 L = *reinterpret_cast<const f32x4*>(&s_lse[buf][t * 16 + kg * 4]);
         const f32x4 D = *reinterpret_cast<const f32x4*>(&s_dlt[buf][t * 16 + kg * 4]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int q = qs + t * 16 + kg * 4 + r;
-          const bool seen = q >= key && q < T_;
-          p[t][r] = seen ? expf(st[r] * scale - L[r]) : 0.f;
-          ds[t][r] = seen ? p[t][r] * (dp[r] - D[r]) * scale : 0.f;
+          p[t][r] = exp_(st[r] * scale - L[r]);
+          ds[t][r] = p[t][r] * (dp[r] - D[r]) * scale;
         }
       }
-      Weights<T>(p[0], p[1]).template times<LD>(lo + kg * 4 * LD + lr, dv);
-      Weights<T>(ds[0], ds[1]).template times<LD>(lq + kg * 4 * LD + lr, dk);
+      if (qs < kw0 + 15 || qs + KT > T_) {   // not every query sees every key, or there are none
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int q = qs + t * 16 + kg * 4 + r;
+            if (q < key || q >= T_) p[t][r] = ds[t][r] = 0.f;
+          }
+      }
+      S::template times<LD>(p[0], p[1], lo, lr, kg, dv);
+      S::template times<LD>(ds[0], ds[1], lq, lr, kg, dk);
     }
     if (step + SETS < steps) put(buf ^ 1);
     __syncthreads();
   }
   if (SETS == 2) {   // dk over in the first half of the buffers, dv in the second
-    float* half = &smem_all[SETS - 1][0][0][0];
+    float* half = reinterpret_cast<float*>(&smem_all[SETS - 1][0][0][0]);
     if (set == 1) {
-      give<HD>(&smem_all[0][0][0][0], dk, tid);
+      give<HD>(reinterpret_cast<float*>(&smem_all[0][0][0][0]), dk, tid);
       give<HD>(half, dv, tid);
     }
     __syncthreads();
     if (set == 1) return;
     f32x4 o1[NS], o2[NS];
-    take<HD>(&smem_all[0][0][0][0], o1, tid);
+    take<HD>(reinterpret_cast<const float*>(&smem_all[0][0][0][0]), o1, tid);
     take<HD>(half, o2, tid);
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
