@@ -25,7 +25,7 @@
 // us per launch, float instruction (two thirds of its 157 TFLOP/s) -> this: op 0 2048 x 1024 x 1024 43 -> 30, 2048 x 3072 x 1024
 // 131 -> 74, 2048 x 1024 x 5632 220 -> 140, 4096 x 4096 x 4096 1135 -> 657 (209 TFLOP/s), op 1 2048 x 1024 x 5632 235 -> 145, op 2
 // 1024 x 1024 x 2048 61 -> 39, 3072 x 1024 x 2048 123 -> 81, 5632 x 1024 x 2048 237 -> 147; small ones even: op 0 1024 x 288 x 1536
-// 22 -> 20, 128 x 288 x 1536 15 -> 16.  The stage of the 500M shape on 2 x 2 x 512 tokens 7.18 -> 5.09 ms, the 50M shape on 4 x 4 x
+// 22 -> 20.  The stage of the 500M shape on 2 x 2 x 512 tokens 7.18 -> 5.09 ms, the 50M shape on 4 x 4 x
 // 256 tokens 5.60 -> 4.93 ms a pass.
 //
 // Every entry is summed in one order (runs of 64 k), with the same instructions, whatever the tile: that follows the
@@ -192,6 +192,26 @@ __device__ __forceinline__ Frag frag(const char* lds, int base, int lane_at) {  
 constexpr int kTerms = 6;
 constexpr int kTermX[kTerms] = {2, 0, 1, 1, 0, 0}, kTermY[kTerms] = {0, 2, 1, 0, 1, 0};
 
+// The parts of a value that is not finite, or rounds past the largest bfloat16, are infinities and NaN.  Entries of a block of
+// 16 x 16 that come out as either are formed anew from the floats themselves, on the float instruction.  m, n: lane's row of A and
+// row (column) of B.
+template <int OP>
+__device__ __forceinline__ void mend(const Args& g, f32x4& v, int m, int n, int kg) {
+  constexpr bool AS = OP == 2, BS = OP != 0;
+  if (!__ballot(!(finite(v[0]) && finite(v[1]) && finite(v[2]) && finite(v[3])))) return;
+  const int K = g.K;
+  f32x4 c = {0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < K; k += 4) {
+    const bool in = k + kg < K;
+    const int kk = min(k + kg, K - 1);
+    const float a = in ? (AS ? g.A[(int64_t)kk * g.M + m] : g.A[(int64_t)m * K + kk]) : 0.f;
+    const float b = in ? (BS ? g.B[(int64_t)kk * g.N + n] : g.B[(int64_t)n * K + kk]) : 0.f;
+    c = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = finite(v[r]) ? v[r] : c[r];
+}
+
 // The share of one of NW wavefronts in bringing an operand's tile from memory to LDS: units of a row's 4 consecutive k
 // (k-contiguous) or of 4 k of XW neighbouring columns (k-strided).
 // VEC: buffer loads from a descriptor that starts at the step, so that a lane's offsets are the same for all steps and k past
@@ -222,7 +242,7 @@ struct Share {
 #pragma unroll
         for (int e = 1; e < 4; ++e) dx[u][e - 1] = min(x0 + row[u] + e, cols - 1) - c;
       } else {    // 8 rows of 32 k, four apart and neighbours; two wavefronts take 16 rows
-        row[u] = ((wave >> 1) + NW / 2 * u) * 16 + ((lane >> 3) & 3) * 4 + (wave & 1) * 2 + (lane >> 5);
+        row[u] = (NW == 1 ? 2 * u : ((wave >> 1) + NW / 2 * u) * 16 + (wave & 1) * 2) + ((lane >> 3) & 3) * 4 + (lane >> 5);
         k = (lane & 7) * 4;
         const int r = row_of(row[u]);
         off[u] = ((uint32_t)(r - x0) * (uint32_t)ld + k) * 4u;
@@ -460,34 +480,11 @@ __global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f3
       for (int j = 0; j < NA; ++j) add_up(j, (steps - 1) & kRun ? -1.f : 1.f);
     else if (NA > 1) add_up(NA - 1, (steps - 1) & kRun ? -1.f : 1.f);
   }
-  // The parts of a value that is not finite, or rounds past the largest bfloat16, are infinities and NaN.  An entry that comes
-  // out as either is formed anew from the floats themselves, on the float instruction.
-  bool bad = false;
 #pragma unroll
   for (int j = 0; j < NA; ++j)
 #pragma unroll
-    for (int i = 0; i < NB; ++i) bad |= !(finite(sum[j][i][0]) && finite(sum[j][i][1]) && finite(sum[j][i][2]) && finite(sum[j][i][3]));
-  if (__ballot(bad)) {
-    for (int j = 0; j < NA; ++j)
-      for (int i = 0; i < NB; ++i) {
-        const int m = min(m0 + base_a + j * 16 + lr, g.M - 1), n = BS ? min(n0 + base_b + i * 16 + lr, g.N - 1) : b_row(base_b + i * 16 + lr);
-        f32x4 c = {0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < K; k += 4) {
-          const bool in = k + kg < K;
-          const int kk = min(k + kg, K - 1);
-          const float a = in ? (AS ? g.A[(int64_t)kk * g.M + m] : g.A[(int64_t)m * K + kk]) : 0.f;
-          const float b = in ? (BS ? g.B[(int64_t)kk * g.N + n] : g.B[(int64_t)n * K + kk]) : 0.f;
-          c = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0);
-        }
-#pragma unroll
-        for (int jj = 0; jj < NA; ++jj)
-#pragma unroll
-          for (int ii = 0; ii < NB; ++ii)
-            if (jj == j && ii == i)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) sum[jj][ii][r] = finite(sum[jj][ii][r]) ? sum[jj][ii][r] : c[r];
-      }
-  }
+    for (int i = 0; i < NB; ++i)
+      mend<OP>(g, sum[j][i], min(m0 + base_a + j * 16 + lr, g.M - 1), BS ? min(n0 + base_b + i * 16 + lr, g.N - 1) : b_row(base_b + i * 16 + lr), kg);
   if (OP == 2) {
 #pragma unroll
     for (int j = 0; j < NA; ++j)
@@ -517,32 +514,139 @@ __global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f3
   }
 }
 
+// For products too small to fill the chip, where the time is one chain of latencies: tiles of 16 x 16 (SwiGLU: rows x
+// features), eight wavefronts that each form whole runs of 64 k, in turn, from loads and splits of their own (no barrier:
+// LDS operations of one wavefront are in order), the next run's loads on their way.  After every eight runs the first
+// wavefront adds them up in order, so that entries have the bits that the other tiles give them.
+template <int OP, int EPI, bool VEC>
+__global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) {
+  constexpr bool AS = OP == 2, BS = OP != 0;
+  constexpr int NB = EPI == kEpiSwiglu ? 2 : 1, NW = kThreads / 64;
+  typedef Share<AS, 16, 1, VEC> SA;
+  typedef Share<BS, 16, 1, VEC> SB;
+  constexpr int kTile = Planes<16>::kBytes;
+  __shared__ __attribute__((aligned(16))) char tiles[NW][(1 + NB) * kTile];
+  __shared__ __attribute__((aligned(16))) f32x4 found[2][NW][NB][64];
+  const int lane = threadIdx.x & 63, lr = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tm, tn;
+  tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
+  const int m0 = tm * 16, n0 = tn * 16, K = g.K, steps = (K + BK - 1) / BK, runs = (steps + kRun - 1) / kRun;
+  const int cols = NB == 2 ? g.N / 2 : g.N, lda = AS ? g.M : K, ldb = BS ? g.N : K;
+  f32x4 sum[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (runs > 0) {
+    SA a;
+    SB b[NB];
+    a.init(g.A, lda, m0, g.M, K, 0, lane, [&](int t) { return min(m0 + t, g.M - 1); });
+#pragma unroll
+    for (int i = 0; i < NB; ++i) b[i].init(g.B, ldb, i * cols + n0, NB == 2 ? 2 * cols : cols, K, 0, lane, [&](int t) { return i * cols + min(n0 + t, cols - 1); });
+    float ra[kRun][SA::Q][4], rb[kRun][NB][SB::Q][4];
+    auto load = [&](int run) {   // past the end: the last step again
+#pragma unroll
+      for (int e = 0; e < kRun; ++e) {
+        const int k0 = min(run * kRun + e, steps - 1) * BK;
+        a.template load<false>(ra[e], k0, K, lda);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) b[i].template load<true>(rb[e][i], k0, K, ldb);
+      }
+    };
+    char* const mine = tiles[wave];
+    const int at = Planes<16>::at(lr, kg);
+    load(wave);
+    for (int r0 = 0, par = 0; r0 < runs; r0 += NW, par ^= 1) {
+      const int run = r0 + wave;
+      if (run < runs) {
+        f32x4 acc[NB];
+#pragma unroll
+        for (int e = 0; e < kRun; ++e) {
+          if (run * kRun + e < steps) {
+            if (run & 1) a.template put<true>(mine, ra[e]);
+            else a.template put<false>(mine, ra[e]);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) b[i].template put<false>(mine + (1 + i) * kTile, rb[e][i]);
+            const Frag fa = frag<16>(mine, 0, at);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+              const Frag fb = frag<16>(mine + (1 + i) * kTile, 0, at);
+#pragma unroll
+              for (int t = 0; t < kTerms; ++t) {
+                const f32x4 c = e == 0 && t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i];
+                acc[i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.p[kTermX[t]], fb.p[kTermY[t]], c, 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb.p[kTermX[t]], fa.p[kTermY[t]], c, 0, 0, 0);
+              }
+            }
+          }
+        }
+        if (run + NW < runs) load(run + NW);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) found[par][wave][i][lane] = acc[i];
+      }
+      __syncthreads();   // the other half of `found` is free: the first wavefront read it before it came here
+      if (wave == 0) {
+        const int n = min(NW, runs - r0);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+          if (w < n)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+              const f32x4 v = found[par][w][i][lane];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) sum[i][e] = __builtin_fmaf(v[e], w & 1 ? -1.f : 1.f, sum[i][e]);
+            }
+      }
+    }
+  }
+  if (wave) return;
+  static_assert(NW % 2 == 0, "a wavefront's runs are all odd or all even");
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    mend<OP>(g, sum[i], min(m0 + lr, g.M - 1), i * cols + min(n0 + lr, cols - 1), kg);
+  if (OP == 2) {
+    const int n = n0 + lr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + kg * 4 + r;
+      if (m < g.M && n < g.N) unsafeAtomicAdd(g.C + (int64_t)m * g.N + n, sum[0][r]);
+    }
+    return;
+  }
+  const int m = m0 + lr, n = n0 + kg * 4;
+  if (m >= g.M) return;
+  if (EPI == kEpiSwiglu) emit_swiglu<VEC>(g, m, n, sum[0], sum[NB - 1]);
+  else emit<OP, EPI, VEC>(g, m, n, sum[0]);
+}
+
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 
 // Tile and its grid for a product: the least of (steps + ends) x time of a step of the CU with the most tiles.  Times are fits
 // (us, op 0 to 2 within 5 %): a 128-tile 1.25; 128 x 64 0.78 alone on its CU, 0.72 each of several; a 64-tile 0.58 alone, 0.88
-// two, 0.44 each of more; a 32-tile 0.27, 0.36 two, 0.52 three, 0.18 each of more (SwiGLU, with its 64 rows of B, 1.6 x).
-// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps.  A product is not cut along k over workgroups: their sums would be
+// two, 0.44 each of more; a 32-tile 0.29, 0.36 two, 0.52 three, 0.18 each of more (SwiGLU, with its 64 rows of B, 1.6 x).
+// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps.  A 16-tile of k_gemm_f32_few: 0.17 a run and 0.45 (SwiGLU 1.85 x), 1 once.  A product is not cut along k over workgroups: their sums would be
 // added in the order in which they end, and neither would a microbatch's rows have the same bits alone and in a group, nor two
 // passes of the mode that gradients are checked in agree.  us by tile, 128 / 128 x 64 / 64 / 32: op 0 1024 x 1024 x 1024 39 /
 // 29 / 22 / 28, 2048 x 1024 x 5632 188 / 143 / 157 / 236, 3072 x 1024 x 1024 42 / 46 / 46 / 66, 4096 x 768 x 288 17 / 18 / 17 / 23,
-// 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.
+// 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.  32 / 16: op 0
+// 128 x 288 x 1536 16.6 / below 7.5 (the launch), 512 x 288 x 1536 16.9 / 14.2, 1024 x 288 x 1536 21 / 22, 64 x 1024 x 5632 53 / 21,
+// 512 x 768 x 288 7.7 / 8.9.
 struct F32Shape { int tile_m, tile_n, tm, tn; };
 static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi) {
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
   const int64_t cus = cu_count(), steps = (K + BK - 1) / BK;
   F32Shape best{};
   double best_us = 0;
-  const int edges[4][2] = {{128, 128}, {128, 64}, {64, 64}, {32, 32}};
-  for (int t = 0; t < 4; ++t) {
+  const int edges[5][2] = {{128, 128}, {128, 64}, {64, 64}, {32, 32}, {16, 16}};
+  for (int t = 0; t < 5; ++t) {
     const int m = edges[t][0], n = edges[t][1], w = epi == kEpiSwiglu && t < 3 ? n / 2 : n;   // w: stored columns of one run
     const int64_t tm = (M + m - 1) / m, tn = (out + w - 1) / w, load = (tm * tn + cus - 1) / cus;
     const double c = (double)load;
     const double step = t == 0 ? 1.25 * c : t == 1 ? (load == 1 ? 0.78 : 0.72 * c) : t == 2 ? (load == 1 ? 0.58 : 0.44 * c)
-                        : (load == 1 ? 0.27 : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
-    const double us = step * ((double)steps + (t == 0 ? 4.8 : t == 3 ? 6.0 : 4.0));
+                        : (load == 1 ? 0.29 : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
+    const double few = 1.0 + c * (0.17 * (double)((steps + kRun - 1) / kRun) + 0.45) * (epi == kEpiSwiglu ? 1.85 : 1.0);
+    const double us = t == 4 ? few : step * ((double)steps + (t == 0 ? 4.8 : t == 3 ? 6.0 : 4.0));
     if (t && us >= best_us) continue;
     best_us = us;
     best = {m, n, (int)tm, (int)tn};
@@ -552,7 +656,7 @@ static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi) {
 
 GemmShape gemm_f32_shape(int64_t M, int64_t N, int64_t K, int epi) {
   const F32Shape c = choose_f32(M, N, K, epi);
-  return {c.tile_n, c.tm * c.tn, c.tm * c.tn};
+  return {std::max(c.tile_n, 32), c.tm * c.tn, c.tm * c.tn};
 }
 
 // epi as in gemm_mfma: 0 plain (R optional), 1 rotary, 2 SwiGLU (N = 2h, aux = act), 3 SwiGLU backward (N = h, R =
@@ -574,7 +678,8 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
     if (c.tile_n == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 128, VEC>), grid, dim3(kThreads), 0, s, g);           \
     else if (c.tile_m == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 64, VEC>), grid, dim3(kThreads), 0, s, g);       \
     else if (c.tile_n == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, 64, VEC>), grid, dim3(kThreads), 0, s, g);         \
-    else hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 32, 32, VEC>), grid, dim3(kThreads), 0, s, g);                             \
+    else if (c.tile_n == 32) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 32, 32, VEC>), grid, dim3(kThreads), 0, s, g);         \
+    else hipLaunchKernelGGL((k_gemm_f32_few<OP, EPI, VEC>), grid, dim3(kThreads), 0, s, g);                                 \
   } while (0)
 #define SP_GO_V(OP, EPI) do { if (vec) SP_GO(OP, EPI, true); else SP_GO(OP, EPI, false); } while (0)
   if (op == 0 && epi == kEpiRope) SP_GO_V(0, kEpiRope);

@@ -229,3 +229,26 @@ def test_float_products_of_values_at_the_ends_of_the_range(M, N, K):
         with np.errstate(over="ignore", invalid="ignore"):
             size = np.sqrt((a.astype(np.float64) ** 2) @ (b.astype(np.float64) ** 2).T)
         assert np.all(np.abs(got[fin] - ref[fin]) <= 6e-7 * np.sqrt(K) * size[fin] + 1e-37), op
+
+
+# rows: few take tiles of 16, whose wavefronts form the runs of 64 k in turn (one run less than eight, eight, one more, several
+# rounds, a run of one step), the others tiles of 32, 64, 128 x 64 and 128
+@pytest.mark.parametrize("N,K,few,rows", [(288, 448, 33, 700), (288, 512, 64, 5000), (288, 576, 16, 700), (70, 1569, 50, 20000), (288, 1536, 64, 1024), (512, 65, 1, 9000)])
+def test_float_rows_have_the_bits_of_larger_tiles_in_tiles_of_16(N, K, few, rows):
+    a = dev(synth.normal(68, f"qa{N}{K}", (rows, K))); b = dev(synth.normal(69, f"qb{N}{K}", (N, K))); r = dev(synth.normal(70, f"qr{N}{K}", (rows, N)))
+    gu = dev(synth.normal(71, f"qg{N}{K}", (rows, 2 * N))); wgu = torch.cat([b, b.flip(0)]); bt = b.t().contiguous()
+    assert sp.gemm_shape(sp.SP_F32, 0, few, N, K)[1] == ((few + 15) // 16) * ((N + 15) // 16)   # tiles of 16
+    assert sp.gemm_shape(sp.SP_F32, 0, rows, N, K)[1] < ((rows + 15) // 16) * ((N + 15) // 16)
+    out = []
+    for n in (rows, few):
+        empty = lambda w: torch.empty((n, w), device="cuda")
+        c0, c1, up, act, dgu = empty(N), empty(N), empty(2 * N), empty(N), empty(2 * N)
+        sp.gemm(0, a[:n], b, c0, r[:n])
+        sp.gemm(1, a[:n], bt, c1)
+        sp.ffn_up_fwd(a[:n], wgu, up, act)
+        sp.ffn_down_bwd(a[:n], bt, gu[:n], dgu, empty(N))
+        out.append([x[:few].cpu().numpy() for x in (c0, c1, up, act, dgu)])
+    for name, x, y in zip(("op 0", "op 1", "gate|up", "act", "d(gate)|d(up)"), *out):
+        assert np.array_equal(x, y), (name, relerr(x, y))
+    want = a[:few].double() @ b.double().T
+    assert relerr(out[1][1], want.cpu().numpy()) < 2e-5
