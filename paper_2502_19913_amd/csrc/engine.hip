@@ -72,7 +72,7 @@ int64_t head_chunk_rows(const Dims& D, int64_t total_rows) {
 }
 
 struct Carve {
-  size_t arena, t_y, t_dy[2], t_dh[2], t_d2, t_da, t_dgu[2], t_dqkv[2], t_delta, rope, h_xn, h_rstd, h_logits, h_dxn, pool_a, pool_d,
+  size_t arena, t_y, t_dy[3], t_dh[2], t_d2, t_da, t_dgu[2], t_dqkv[2], t_delta, rope, h_xn, h_rstd, h_logits, h_dxn, pool_a, pool_d,
       loss_mb, counts, bad, dgpart, total;
   size_t arena_bytes;
 };
@@ -86,10 +86,10 @@ Carve carve(const sp_cfg& c, int n_mb_max, int n_visits_max) {
   w.arena_bytes = (size_t)n_visits_max * c.layers_per_stage * layer_saved_bytes(D, D.Nmb);
   w.arena = take(w.arena_bytes);
   w.t_y = take(Rmax * D.d * D.E);
-  // two sets of the gradients a weight-gradient product reads: it may still be running (on the side stream)
-  // while the next layer's are written
+  // two sets of the gradients that a layer's weight-gradient products read: they may still be running (on the side stream)
+  // while the next layer's are written; three of the one that the layer above writes
+  for (int p = 0; p < 3; ++p) w.t_dy[p] = take(Rmax * D.d * D.E);
   for (int p = 0; p < 2; ++p) {
-    w.t_dy[p] = take(Rmax * D.d * D.E);
     w.t_dh[p] = take(Rmax * D.d * D.E);
     w.t_dgu[p] = take(Rmax * 2 * D.h * D.E);
     w.t_dqkv[p] = take(Rmax * D.nq * D.E);
@@ -135,8 +135,7 @@ struct sp_ctx {
   // weight-gradient products run on a stream of their own, beside the chain that carries the activation
   // gradient down the layers; events order the two (ready: input written; done: input no longer read)
   hipStream_t side;
-  hipEvent_t ready[4], done[2][4], joined;
-  bool done_set[2][4];
+  hipEvent_t ready[kGrads], done[2][kGrads], joined;
   int use_side;      // 0: weight gradients run in line on the caller's stream; 1: beside it when that pays; 2: always
   Carve w;
   size_t arena_top;
@@ -218,7 +217,7 @@ int sp_create(const sp_cfg* cfg, void* hip_stream, int n_mb_max, int n_visits_ma
   c->side = nullptr;
   c->use_side = 1;
   e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
-  for (int i = 0; i < 4 && e == hipSuccess; ++i) {
+  for (int i = 0; i < kGrads && e == hipSuccess; ++i) {
     e = hipEventCreateWithFlags(&c->ready[i], hipEventDisableTiming);
     for (int p = 0; p < 2 && e == hipSuccess; ++p) e = hipEventCreateWithFlags(&c->done[p][i], hipEventDisableTiming);
   }
@@ -246,7 +245,7 @@ int sp_destroy(sp_ctx* ctx) {
   if (!ctx) return SP_OK;
   hipError_t e = hipStreamSynchronize(ctx->stream);
   (void)hipStreamSynchronize(ctx->side);
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < kGrads; ++i) {
     (void)hipEventDestroy(ctx->ready[i]);
     for (int p = 0; p < 2; ++p) (void)hipEventDestroy(ctx->done[p][i]);
   }
@@ -421,59 +420,74 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
   constexpr int64_t kSideMaxTiles = 640;
   const bool side_pays = ((R + 255) / 256) * ((D.d + 255) / 256) < kSideMaxTiles;
   hipStream_t side = ctx->use_side == 2 || (ctx->use_side == 1 && side_pays) ? ctx->side : s;
-  for (int p = 0; p < 2; ++p)
-    for (int i = 0; i < 4; ++i) ctx->done_set[p][i] = false;
-  // weight gradient k of the layer (0: down, 1: gate/up, 2: output, 3: qkv) on the side stream, once its input
-  // (just written on the main stream) is ready; `done` marks when that input may be overwritten
-  auto side_dw = [&](int k, int par, int64_t M, int64_t N, const void* A, const void* B, float* C) -> int {
-    SP_HIP(hipEventRecord(ctx->ready[k], s));
-    SP_HIP(hipStreamWaitEvent(side, ctx->ready[k], 0));
-    int r = gemm(side, dt, 2, M, N, R, A, B, C, nullptr);
+  const bool beside = side != s;
+  // A layer's four weight gradients: each is launched as soon as its input is there, or, where they are so short that the
+  // host's calls take as long as the kernels, all of them in one launch at the end of the layer.  A layer of the backward pass
+  // has 9 launches (3.4 us each on the host) besides these, and these cost it 16 more calls (75 us) one by one, 5 together.
+  // us a pass, one by one / together: 50M shape in float on 2 x 64 tokens 1750 / 1440, in bf16 on 4 x 999 2960 / 2815, in float on 4 x
+  // 1024 4930 / 5050, 500M stage in float 4960 / 5270, 1.5B stage 46290 / 47500: later and all at once they fill the gaps of the
+  // chain beside them less well.  The line lies at products of about 20 us.
+  const double grad_flops = 2.0 * (double)R * (double)D.d * (double)(D.nq + D.d + 3 * D.h);
+  const bool together = grad_flops < (dt == SP_BF16 ? 12e9 : 2.5e9);
+  int n = 0;   // layers done
+  GradItem items[kGrads];
+  // weight gradient k of the layer (0: down, 1: gate/up, 2: output, 3: qkv), once its input (just written on the main stream)
+  // is ready; `done` marks when that input may be overwritten
+  auto weight_grad = [&](int k, int64_t M, int64_t N, const void* A, const void* B, float* C) -> int {
+    items[k] = {M, N, A, B, C};
+    if (together && k < 3) return SP_OK;
+    const int e = together ? 0 : k;
+    if (beside) {
+      SP_HIP(hipEventRecord(ctx->ready[e], s));
+      SP_HIP(hipStreamWaitEvent(side, ctx->ready[e], 0));
+    }
+    int r = together ? gemm_grads(side, dt, R, items) : gemm(side, dt, 2, M, N, R, A, B, C, nullptr);
     if (r) return r;
-    SP_HIP(hipEventRecord(ctx->done[par][k], side));
-    ctx->done_set[par][k] = true;
+    if (beside) SP_HIP(hipEventRecord(ctx->done[n & 1][e], side));
     return SP_OK;
   };
-  auto wait_done = [&](int k, int par) -> int {
-    if (ctx->done_set[par][k]) SP_HIP(hipStreamWaitEvent(s, ctx->done[par][k], 0));
+  // before this layer writes what weight gradient k of the layer two above has read
+  auto wait_done = [&](int k) -> int {
+    if (beside && n >= 2 && !(together && k != 1)) SP_HIP(hipStreamWaitEvent(s, ctx->done[n & 1][together ? 0 : k], 0));
     return SP_OK;
   };
 
   gather_slots(s, dt, dact_pool, sl, D.Nmb, (int)D.d, at(ctx, ctx->w.t_dy[0]));
-  int par = 0;
-  for (int l = cfg.layers_per_stage - 1; l >= 0; --l, par ^= 1) {
+  for (int l = cfg.layers_per_stage - 1; l >= 0; --l, ++n) {
     const LayerOff& w = ctx->L.layers[(size_t)loc * cfg.layers_per_stage + l];
     const LayerSaved& ls = rec.layers[l];
-    char* dy = at(ctx, ctx->w.t_dy[par]);
-    char* dy_next = at(ctx, ctx->w.t_dy[par ^ 1]);
-    char* dh = at(ctx, ctx->w.t_dh[par]);
-    char* dgu = at(ctx, ctx->w.t_dgu[par]);
-    char* dqkv = at(ctx, ctx->w.t_dqkv[par]);
+    char* dy = at(ctx, ctx->w.t_dy[n % 3]);
+    char* dy_next = at(ctx, ctx->w.t_dy[(n + 1) % 3]);
+    char* dh = at(ctx, ctx->w.t_dh[n & 1]);
+    char* dgu = at(ctx, ctx->w.t_dgu[n & 1]);
+    char* dqkv = at(ctx, ctx->w.t_dqkv[n & 1]);
     // feed-forward: y = h + a Wd^T
-    if ((rc = side_dw(0, par, D.d, D.h, dy, ls.a, grads + w.wd))) return rc;
-    if ((rc = wait_done(1, par))) return rc;
+    if ((rc = weight_grad(0, D.d, D.h, dy, ls.a, grads + w.wd))) return rc;
+    if ((rc = wait_done(1))) return rc;   // the first write of the layer
     if ((rc = ffn_down_bwd(s, dt, R, D.h, D.d, dy, P(ctx, params, w.wd), ls.gu, dgu, da))) return rc;
-    if ((rc = side_dw(1, par, 2 * D.h, D.d, dgu, ls.hn, grads + w.wgu))) return rc;
+    if ((rc = weight_grad(1, 2 * D.h, D.d, dgu, ls.hn, grads + w.wgu))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, 2 * D.h, dgu, P(ctx, params, w.wgu), t, nullptr))) return rc;
-    if ((rc = wait_done(2, par))) return rc;
+    if ((rc = wait_done(2))) return rc;
     norm_bwd(ls.h, w.g2, ls.rstd2, dy, dh);
     // attention: h = x + o Wo^T
-    if ((rc = side_dw(2, par, D.d, D.d, dh, ls.o, grads + w.wo))) return rc;
+    if ((rc = weight_grad(2, D.d, D.d, dh, ls.o, grads + w.wo))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, D.d, dh, P(ctx, params, w.wo), t, nullptr))) return rc;
-    if ((rc = wait_done(3, par))) return rc;
+    if ((rc = wait_done(3))) return rc;
     if ((rc = attention_bwd(s, dt, Bg, (int)D.T, (int)D.H, (int)D.Hkv, (int)D.hd, ls.qkv, ls.o, ls.lse, t, dqkv, delta,
                             ctx->rope_tab)))
       return rc;
-    if ((rc = side_dw(3, par, D.nq, D.d, dqkv, ls.xn, grads + w.wqkv))) return rc;
+    if ((rc = weight_grad(3, D.nq, D.d, dqkv, ls.xn, grads + w.wqkv))) return rc;
     if ((rc = gemm(s, dt, 1, R, D.d, D.nq, dqkv, P(ctx, params, w.wqkv), t, nullptr))) return rc;
-    if ((rc = wait_done(0, par ^ 1))) return rc;   // the layer above may still read its dy
+    if ((rc = wait_done(0))) return rc;
     norm_bwd(ls.x, w.g1, ls.rstd1, dh, dy_next);
   }
-  char* dy = at(ctx, ctx->w.t_dy[par]);
+  char* dy = at(ctx, ctx->w.t_dy[n % 3]);
   rmsnorm_bwd_fold(s, &fold, (int)D.d);
   // the caller's stream continues only after every weight gradient has landed
-  SP_HIP(hipEventRecord(ctx->joined, side));
-  SP_HIP(hipStreamWaitEvent(s, ctx->joined, 0));
+  if (beside) {
+    SP_HIP(hipEventRecord(ctx->joined, side));
+    SP_HIP(hipStreamWaitEvent(s, ctx->joined, 0));
+  }
   scatter_slots(s, dt, dy, sl, D.Nmb, (int)D.d, dact_pool);
   SP_HIP(hipGetLastError());
   rec.live = false;

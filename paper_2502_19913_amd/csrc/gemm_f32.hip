@@ -339,8 +339,9 @@ __device__ __forceinline__ void feed(int steps, Fetch fetch, Put put) {
 // and multiply, the others only bring the operands of the next step to LDS, split on the way, U steps of loads in flight: a
 // SIMD holds one of either, and beside the matrix instructions of one wavefront (16 cycles each) another can issue 2.5
 // others, where one that does both gets 1.5 for nothing.
+// wg of n_wgs: the workgroup's number among those of the product
 template <int OP, int EPI, int TM, int TN, bool VEC>
-__global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f32(Args g) {
+__device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
   constexpr bool AS = OP == 2, BS = OP != 0;
   // SwiGLU in 32-tiles: a wavefront holds 16 gate columns and the 16 up columns, so the tile of B has 64 rows
   constexpr int NSEG = EPI == kEpiSwiglu && TN == 32 ? 2 : 1, TB = TN * NSEG;
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f3
   const int lane = threadIdx.x & 63, lr = lane & 15, kg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int tm, tn;
-  tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
+  tile_of(g, xcd_major(wg, n_wgs), tm, tn);
   const int m0 = tm * TM, n0 = tn * TN, K = g.K, steps = (K + BK - 1) / BK, lda = AS ? g.M : K, ldb = BS ? g.N : K;
   const int b0 = EPI == kEpiSwiglu && NSEG == 1 ? n0 / 2 : n0;   // the tile's first row (column) of B
   // memory row of the tile's row t of B (k-contiguous).  SwiGLU: a wavefront's share holds gate rows and the up rows of the
@@ -519,7 +520,7 @@ __global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f3
 // LDS operations of one wavefront are in order), the next run's loads on their way.  After every eight runs the first
 // wavefront adds them up in order, so that entries have the bits that the other tiles give them.
 template <int OP, int EPI, bool VEC>
-__global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) {
+__device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
   constexpr bool AS = OP == 2, BS = OP != 0;
   constexpr int NB = EPI == kEpiSwiglu ? 2 : 1, NW = kThreads / 64;
   typedef Share<AS, 16, 1, VEC> SA;
@@ -530,7 +531,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) {
   const int lane = threadIdx.x & 63, lr = lane & 15, kg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int tm, tn;
-  tile_of(g, xcd_major(blockIdx.x, gridDim.x), tm, tn);
+  tile_of(g, xcd_major(wg, n_wgs), tm, tn);
   const int m0 = tm * 16, n0 = tn * 16, K = g.K, steps = (K + BK - 1) / BK, runs = (steps + kRun - 1) / kRun;
   const int cols = NB == 2 ? g.N / 2 : g.N, lda = AS ? g.M : K, ldb = BS ? g.N : K;
   f32x4 sum[NB];
@@ -618,7 +619,24 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) {
   else emit<OP, EPI, VEC>(g, m, n, sum[0]);
 }
 
+template <int OP, int EPI, int TM, int TN, bool VEC>
+__global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f32(Args g) { gemm_tile<OP, EPI, TM, TN, VEC>(g, blockIdx.x, gridDim.x); }
+template <int OP, int EPI, bool VEC>
+__global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) { gemm_few<OP, EPI, VEC>(g, blockIdx.x, gridDim.x); }
+
+// the weight gradients of a layer in one launch, all in tiles of one size
+template <int TM, int TN, bool VEC>
+__global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 || TN == 16 ? 2 : 4) void k_gemm_f32_grads(GradGroup l) {
+  int i = 0;
+  while (i + 1 < kGrads && (int)blockIdx.x >= l.first[i + 1]) ++i;
+  const int wg = (int)blockIdx.x - l.first[i], n = l.first[i + 1] - l.first[i];
+  const Args g{(const float*)l.A[i], (const float*)l.B[i], nullptr, l.C[i], nullptr, l.M[i], l.N[i], l.K, l.tm[i], l.tn[i], RopeArgs{nullptr, 1, 2, 0}};
+  if constexpr (TN == 16) gemm_few<2, kEpiPlain, VEC>(g, wg, n);
+  else gemm_tile<2, kEpiPlain, TM, TN, VEC>(g, wg, n);
+}
+
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+constexpr int64_t kVecMax = 1 << 21;
 
 }  // namespace
 
@@ -632,21 +650,24 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.  32 / 16: op 0
 // 128 x 288 x 1536 16.6 / below 7.5 (the launch), 512 x 288 x 1536 16.9 / 14.2, 1024 x 288 x 1536 21 / 22, 64 x 1024 x 5632 53 / 21,
 // 512 x 768 x 288 7.7 / 8.9.
+constexpr int kEdges[5][2] = {{128, 128}, {128, 64}, {64, 64}, {32, 32}, {16, 16}};
+static double f32_us(int t, int64_t tiles, int64_t K, int epi) {
+  const int64_t cus = cu_count(), steps = (K + BK - 1) / BK, load = (tiles + cus - 1) / cus;
+  const double c = (double)load;
+  if (t == 4) return 1.0 + c * (0.17 * (double)((steps + kRun - 1) / kRun) + 0.45) * (epi == kEpiSwiglu ? 1.85 : 1.0);
+  const double step = t == 0 ? 1.25 * c : t == 1 ? (load == 1 ? 0.78 : 0.72 * c) : t == 2 ? (load == 1 ? 0.58 : 0.44 * c)
+                      : (load == 1 ? 0.29 : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
+  return step * ((double)steps + (t == 0 ? 4.8 : t == 3 ? 6.0 : 4.0));
+}
 struct F32Shape { int tile_m, tile_n, tm, tn; };
 static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi) {
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
-  const int64_t cus = cu_count(), steps = (K + BK - 1) / BK;
   F32Shape best{};
   double best_us = 0;
-  const int edges[5][2] = {{128, 128}, {128, 64}, {64, 64}, {32, 32}, {16, 16}};
   for (int t = 0; t < 5; ++t) {
-    const int m = edges[t][0], n = edges[t][1], w = epi == kEpiSwiglu && t < 3 ? n / 2 : n;   // w: stored columns of one run
-    const int64_t tm = (M + m - 1) / m, tn = (out + w - 1) / w, load = (tm * tn + cus - 1) / cus;
-    const double c = (double)load;
-    const double step = t == 0 ? 1.25 * c : t == 1 ? (load == 1 ? 0.78 : 0.72 * c) : t == 2 ? (load == 1 ? 0.58 : 0.44 * c)
-                        : (load == 1 ? 0.29 : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
-    const double few = 1.0 + c * (0.17 * (double)((steps + kRun - 1) / kRun) + 0.45) * (epi == kEpiSwiglu ? 1.85 : 1.0);
-    const double us = t == 4 ? few : step * ((double)steps + (t == 0 ? 4.8 : t == 3 ? 6.0 : 4.0));
+    const int m = kEdges[t][0], n = kEdges[t][1], w = epi == kEpiSwiglu && t < 3 ? n / 2 : n;   // w: stored columns of one run
+    const int64_t tm = (M + m - 1) / m, tn = (out + w - 1) / w;
+    const double us = f32_us(t, tm * tn, K, epi);
     if (t && us >= best_us) continue;
     best_us = us;
     best = {m, n, (int)tm, (int)tn};
@@ -668,7 +689,7 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   if (rope) epi = kEpiRope;
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
   const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0) &&
-                   std::max(std::max(M, N), K) <= 1 << 21 && (epi != kEpiSwiglu || (out + 128) * K < 1ll << 29);   // a tile's offsets fit 31 bits
+                   std::max(std::max(M, N), K) <= kVecMax && (epi != kEpiSwiglu || (out + 128) * K < 1ll << 29);   // a tile's offsets fit 31 bits
   const F32Shape c = choose_f32(M, N, K, epi);
   g.tiles_m = c.tm;
   g.tiles_n = c.tn;
@@ -689,6 +710,45 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   else if (op == 1) SP_GO_V(1, kEpiPlain);
   else SP_GO_V(2, kEpiPlain);
 #undef SP_GO_V
+#undef SP_GO
+}
+
+// One tile for all of them; entries as in gemm_f32, bit for bit.
+void gemm_f32_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]) {
+  GradGroup g{};
+  bool vec = K <= kVecMax;
+  for (const GradItem& i : items)
+    vec = vec && al16(i.A) && al16(i.B) && al16(i.C) && i.M % 4 == 0 && i.N % 4 == 0 && std::max(i.M, i.N) <= kVecMax;
+  int tile = 0;
+  double best_us = 0;
+  for (int t = 0; t < 5; ++t) {
+    int64_t tiles = 0;
+    for (const GradItem& i : items) tiles += ((i.M + kEdges[t][0] - 1) / kEdges[t][0]) * ((i.N + kEdges[t][1] - 1) / kEdges[t][1]);
+    const double us = f32_us(t, tiles, K, kEpiPlain);
+    if (t && us >= best_us) continue;
+    best_us = us;
+    tile = t;
+  }
+  for (int i = 0; i < kGrads; ++i) {
+    const GradItem& x = items[i];
+    g.A[i] = x.A; g.B[i] = x.B; g.C[i] = x.C;
+    g.M[i] = (int)x.M; g.N[i] = (int)x.N;
+    g.tm[i] = (int)((x.M + kEdges[tile][0] - 1) / kEdges[tile][0]);
+    g.tn[i] = (int)((x.N + kEdges[tile][1] - 1) / kEdges[tile][1]);
+    g.first[i + 1] = g.first[i] + g.tm[i] * g.tn[i];
+  }
+  g.K = (int)K;
+  const dim3 grid(g.first[kGrads]);
+#define SP_GO(TM, TN)                                                                                       \
+  do {                                                                                                      \
+    if (vec) hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, true>), grid, dim3(kThreads), 0, s, g);           \
+    else hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, false>), grid, dim3(kThreads), 0, s, g);              \
+  } while (0)
+  if (tile == 0) SP_GO(128, 128);
+  else if (tile == 1) SP_GO(128, 64);
+  else if (tile == 2) SP_GO(64, 64);
+  else if (tile == 3) SP_GO(32, 32);
+  else SP_GO(16, 16);
 #undef SP_GO
 }
 

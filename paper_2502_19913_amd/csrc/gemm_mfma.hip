@@ -311,11 +311,11 @@ __device__ __forceinline__ void store_tile(const char* smem, bf16* C, const bf16
   }
 }
 
+// wg of n_wgs: the workgroup's number among those of the product
 template <int OP, bool KMASK, int EPI>
-__global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__ A, const bf16* __restrict__ B,
-                                                        void* __restrict__ Cv, const bf16* __restrict__ Rr, int M,
-                                                        int N, int K, int tiles_m, int tiles_n, RopeArgs rope,
-                                                        bf16* __restrict__ aux) {
+__device__ __forceinline__ void gemm_256(const bf16* __restrict__ A, const bf16* __restrict__ B, void* __restrict__ Cv,
+                                         const bf16* __restrict__ Rr, int M, int N, int K, int tiles_m, int tiles_n,
+                                         const RopeArgs& rope, bf16* __restrict__ aux, int wg, int n_wgs) {
   constexpr int TILE = 256;
   static_assert(EPI == kEpiPlain || (EPI == kEpiSwigluBwd ? OP == 1 : OP == 0), "epilogue and product do not match");
   constexpr bool AS = OP == 2, BS = OP != 0;   // which operands are k-strided
@@ -328,25 +328,25 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__
   const int wm = wave >> 2, wn = wave & 3;
 
   // ---- the work of this workgroup: tiles of the output, or a range of the k-steps of one.
-  // OP 0/1: whole tiles id, id + gridDim.x, ...: the launch has as many workgroups as make its rounds of
-  // tiles equally full.  OP 2: one of gridDim.x / tiles equal runs of the k-steps of one tile, added to the output
+  // OP 0/1: whole tiles id, id + n_wgs, ...: the launch has as many workgroups as make its rounds of
+  // tiles equally full.  OP 2: one of n_wgs / tiles equal runs of the k-steps of one tile, added to the output
   // atomically.
   // Ids that share an XCD (id mod 8) get consecutive tiles (runs); tiles run down M first inside bands
   // of 8 tile columns so that neighbours share B panels and reuse A panels.
   const int tiles = tiles_m * tiles_n;
-  int id = blockIdx.x;
+  int id = wg;
   {
-    const int n_ids = gridDim.x, per = n_ids / 8, rem = n_ids % 8, x = id % 8;
+    const int n_ids = n_wgs, per = n_ids / 8, rem = n_ids % 8, x = id % 8;
     id = x * per + min(x, rem) + id / 8;
   }
   const int ksteps = (K + BK - 1) / BK;
-  // OP 2: gridDim.x = tiles x s; id -> run id / tiles of tile id % tiles, so that the ids that share an XCD (a
+  // OP 2: n_wgs = tiles x s; id -> run id / tiles of tile id % tiles, so that the ids that share an XCD (a
   // contiguous range) work on neighbouring tiles over the same k range and share their operand panels
-  const int s_runs = OP == 2 ? (int)gridDim.x / tiles : 1;
+  const int s_runs = OP == 2 ? n_wgs / tiles : 1;
   const int run = OP == 2 ? id / tiles : 0;
   const int ks0 = OP == 2 ? (int)((int64_t)run * ksteps / s_runs) : 0;
   const int ks1 = OP == 2 ? (int)((int64_t)(run + 1) * ksteps / s_runs) : ksteps;
-  for (int tile = OP == 2 ? id % tiles : id; tile < tiles; tile += OP == 2 ? tiles : (int)gridDim.x) {
+  for (int tile = OP == 2 ? id % tiles : id; tile < tiles; tile += OP == 2 ? tiles : n_wgs) {
   constexpr int kBand = 8;
   const int band = tile / (kBand * tiles_m);
   const int band_w = min(kBand, tiles_n - band * kBand);
@@ -569,10 +569,9 @@ struct RingOperand {
 };
 
 template <int OP, bool KMASK, int EPI, int TILE>
-__global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__ A, const bf16* __restrict__ B,
-                                                        void* __restrict__ Cv, const bf16* __restrict__ Rr, int M,
-                                                        int N, int K, int tiles_m, int tiles_n, RopeArgs rope,
-                                                        bf16* __restrict__ aux) {
+__device__ __forceinline__ void gemm_ring(const bf16* __restrict__ A, const bf16* __restrict__ B, void* __restrict__ Cv,
+                                          const bf16* __restrict__ Rr, int M, int N, int K, int tiles_m, int tiles_n,
+                                          const RopeArgs& rope, bf16* __restrict__ aux, int wg, int n_wgs) {
   static_assert(EPI == kEpiPlain || (EPI == kEpiSwigluBwd ? OP == 1 : OP == 0), "epilogue and product do not match");
   constexpr bool AS = OP == 2, BS = OP != 0;
   typedef Geo<TILE> G;
@@ -588,18 +587,18 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__
 
   // the tiles of this workgroup, numbered as in k_gemm_mfma
   const int tiles = tiles_m * tiles_n;
-  int id = blockIdx.x;
+  int id = wg;
   {
-    const int n_ids = gridDim.x, per = n_ids / 8, rem = n_ids % 8, x = id % 8;
+    const int n_ids = n_wgs, per = n_ids / 8, rem = n_ids % 8, x = id % 8;
     id = x * per + min(x, rem) + id / 8;
   }
   const int ksteps = (K + BK - 1) / BK;
-  const int s_runs = OP == 2 ? (int)gridDim.x / tiles : 1;
+  const int s_runs = OP == 2 ? n_wgs / tiles : 1;
   const int run = OP == 2 ? id / tiles : 0;
   const int ks0 = OP == 2 ? (int)((int64_t)run * ksteps / s_runs) : 0;
   const int ks1 = OP == 2 ? (int)((int64_t)(run + 1) * ksteps / s_runs) : ksteps;
   const int kb = ks0 * BK, kend = min(K, ks1 * BK), nk = ks1 - ks0;
-  for (int tile = OP == 2 ? id % tiles : id; tile < tiles; tile += OP == 2 ? tiles : (int)gridDim.x) {
+  for (int tile = OP == 2 ? id % tiles : id; tile < tiles; tile += OP == 2 ? tiles : n_wgs) {
     constexpr int kBand = 8;
     const int band = tile / (kBand * tiles_m);
     const int band_w = min(kBand, tiles_n - band * kBand);
@@ -742,6 +741,35 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__
   }
 }
 
+template <int OP, bool KMASK, int EPI>
+__global__ __launch_bounds__(kThreads) void k_gemm_mfma(const bf16* __restrict__ A, const bf16* __restrict__ B,
+                                                        void* __restrict__ Cv, const bf16* __restrict__ Rr, int M,
+                                                        int N, int K, int tiles_m, int tiles_n, RopeArgs rope,
+                                                        bf16* __restrict__ aux) {
+  gemm_256<OP, KMASK, EPI>(A, B, Cv, Rr, M, N, K, tiles_m, tiles_n, rope, aux, blockIdx.x, gridDim.x);
+}
+template <int OP, bool KMASK, int EPI, int TILE>
+__global__ __launch_bounds__(kThreads) void k_gemm_ring(const bf16* __restrict__ A, const bf16* __restrict__ B,
+                                                        void* __restrict__ Cv, const bf16* __restrict__ Rr, int M,
+                                                        int N, int K, int tiles_m, int tiles_n, RopeArgs rope,
+                                                        bf16* __restrict__ aux) {
+  gemm_ring<OP, KMASK, EPI, TILE>(A, B, Cv, Rr, M, N, K, tiles_m, tiles_n, rope, aux, blockIdx.x, gridDim.x);
+}
+
+// The weight gradients of a layer in one launch: its four products together fill the chip where one of them leaves it partly
+// idle or has to be cut into many runs.
+template <int TILE>
+__global__ __launch_bounds__(kThreads) void k_gemm_grads(GradGroup g) {
+  int i = 0;
+  while (i + 1 < kGrads && (int)blockIdx.x >= g.first[i + 1]) ++i;
+  const int wg = (int)blockIdx.x - g.first[i], n = g.first[i + 1] - g.first[i];
+  const RopeArgs none{nullptr, 1, 8, 0};
+  if constexpr (TILE == 256)
+    gemm_256<2, false, kEpiPlain>((const bf16*)g.A[i], (const bf16*)g.B[i], g.C[i], nullptr, g.M[i], g.N[i], g.K, g.tm[i], g.tn[i], none, nullptr, wg, n);
+  else
+    gemm_ring<2, false, kEpiPlain, TILE>((const bf16*)g.A[i], (const bf16*)g.B[i], g.C[i], nullptr, g.M[i], g.N[i], g.K, g.tm[i], g.tn[i], none, nullptr, wg, n);
+}
+
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // Tile, tile grid and workgroups of a launch: the least of what each choice is expected to take, in microseconds,
@@ -843,6 +871,43 @@ void gemm_mfma(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const voi
 #undef SP_LAUNCH_T
 #undef SP_LAUNCH_K
 #undef SP_LAUNCH
+}
+
+// One tile and one number of runs for all of them, by the costs of choose_shape.
+void gemm_mfma_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]) {
+  const int64_t cus = cu_count(), ksteps = (K + BK - 1) / BK;
+  GradGroup g{};
+  int tile = 0, best_runs = 0;
+  double best_us = 0;
+  for (int t : {256, 128, 64}) {
+    int64_t tiles = 0;
+    double bytes = 0;
+    for (const GradItem& i : items) {
+      tiles += ((i.M + t - 1) / t) * ((i.N + t - 1) / t);
+      bytes += 4.0 * (double)i.M * (double)i.N;
+    }
+    for (int runs = 1; runs <= 16 && (runs == 1 || ksteps / runs >= 4); ++runs) {
+      const int64_t wgs = tiles * runs, slots = t == 64 && wgs > cus ? 2 * cus : cus, rounds = (wgs + slots - 1) / slots;
+      const double step = t == 256 ? 0.85 + 0.45 * (double)wgs / (double)(rounds * cus) : t == 128 ? 0.5 : slots > cus ? 0.37 : 0.3;
+      const double us = (double)rounds * ((double)((ksteps + runs - 1) / runs) * step + (t == 256 ? 5 : t == 128 ? 4 : 3)) + runs * bytes / 1.4e6;
+      if (tile && us >= best_us) continue;
+      best_us = us;
+      tile = t;
+      best_runs = runs;
+    }
+  }
+  for (int i = 0; i < kGrads; ++i) {
+    const GradItem& x = items[i];
+    g.A[i] = x.A; g.B[i] = x.B; g.C[i] = x.C;
+    g.M[i] = (int)x.M; g.N[i] = (int)x.N;
+    g.tm[i] = (int)((x.M + tile - 1) / tile); g.tn[i] = (int)((x.N + tile - 1) / tile);
+    g.first[i + 1] = g.first[i] + g.tm[i] * g.tn[i] * best_runs;
+  }
+  g.K = (int)K;
+  const dim3 grid(g.first[kGrads]);
+  if (tile == 256) hipLaunchKernelGGL(k_gemm_grads<256>, grid, dim3(kThreads), 0, s, g);
+  else if (tile == 128) hipLaunchKernelGGL(k_gemm_grads<128>, grid, dim3(kThreads), 0, s, g);
+  else hipLaunchKernelGGL(k_gemm_grads<64>, grid, dim3(kThreads), 0, s, g);
 }
 
 bool gemm_swiglu_supported(bool bwd, int64_t R, int64_t h, int64_t d, const void* X, const void* W, const void* gu,

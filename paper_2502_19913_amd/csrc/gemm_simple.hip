@@ -94,6 +94,26 @@ int gemm(hipStream_t s, int dtype, int op, int64_t M, int64_t N, int64_t K, cons
   return SP_OK;
 }
 
+int gemm_grads(hipStream_t s, int dtype, int64_t K, const GradItem (&items)[kGrads]) {
+  bool together = K > 0;
+  double work = 0;
+  for (const GradItem& i : items) {
+    if (i.M < 1 || i.N < 1 || !i.A || !i.B || !i.C) return fail(SP_EINVAL, "gemm_grads: bad item");
+    together = together && (dtype == SP_F32 || gemm_mfma_supported(2, i.M, i.N, K, i.A, i.B, i.C, nullptr));
+    work += 2.0 * (double)i.M * (double)i.N * (double)K;
+  }
+  if (!together) {
+    for (const GradItem& i : items)
+      if (int rc = gemm(s, dtype, 2, i.M, i.N, K, i.A, i.B, i.C, nullptr)) return rc;
+    return SP_OK;
+  }
+  const int pi = prof_start(dtype == SP_F32 ? PROF_GEMM_PLAIN : PROF_GEMM_TN, s);
+  if (dtype == SP_F32) gemm_f32_grads(s, K, items);
+  else gemm_mfma_grads(s, K, items);
+  prof_stop(pi, s, work);
+  return SP_OK;
+}
+
 int gemm_rope(hipStream_t s, int dtype, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
               const RopeArgs& ra, float rope_theta) {
   if (M < 0 || N < 0 || K < 0 || ra.hd < 2 || ra.hd % 2 || ra.rot_cols % ra.hd || ra.rot_cols > N || ra.T < 1)

@@ -92,6 +92,19 @@ void cross_entropy(hipStream_t s, int dtype, void* logits, const int32_t* tgt, i
 int gemm(hipStream_t s, int dtype, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
          const void* R);
 
+// The weight gradients of a layer: C[i] (float) += A[i]^T B[i] over K rows, in one launch where the matrix-core kernels take all of them.
+constexpr int kGrads = 4;
+struct GradItem { int64_t M, N; const void *A, *B; float* C; };
+int gemm_grads(hipStream_t s, int dtype, int64_t K, const GradItem (&items)[kGrads]);
+// What such a launch needs on the device; item i has the workgroups first[i] .. first[i + 1] - 1
+struct GradGroup {
+  const void *A[kGrads], *B[kGrads];
+  float* C[kGrads];
+  int M[kGrads], N[kGrads], tm[kGrads], tn[kGrads], first[kGrads + 1], K;
+};
+void gemm_mfma_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]);
+void gemm_f32_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]);
+
 int attention_fwd(hipStream_t s, int dtype, int B, int T, int H, int Hkv, int hd, const void* qkv, void* o, float* lse);
 // rope_tab (may be null): if given, q and k in qkv are rotated vectors and dqkv is returned with respect to
 // the vectors before the rotation
