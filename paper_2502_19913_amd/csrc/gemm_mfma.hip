@@ -227,7 +227,7 @@ __device__ __forceinline__ void store_tile(const char* smem, bf16* C, const bf16
   constexpr int kCRowBytes = Geo<TILE>::kCRowBytes;
   const int hN = N / 2;
   asm volatile("" : "+v"(tid));   // keeps what follows from tid out of the registers of the loop over tiles (30 spills)
-  const bool add = OP == 0 && Rr != nullptr;
+  const bool add = OP == 0 && EPI == kEpiPlain && Rr != nullptr;
   if (EPI == kEpiSwiglu) {
     // chunk nc < TILE/16 of a staged row is 8 gate values, chunk nc + TILE/16 the up values of the same features
 #pragma unroll 4
@@ -247,26 +247,52 @@ __device__ __forceinline__ void store_tile(const char* smem, bf16* C, const bf16
         store8_stream(aux + (int64_t)grow * hN + gcol, o);
       }
     }
-  } else if (EPI == kEpiSwigluBwd) {
-#pragma unroll 4
-    for (int it = 0; it < TILE * TILE / 8 / kThreads; ++it) {
-      const int c = tid + kThreads * it;
-      const int row = c / (TILE / 8), nc = c % (TILE / 8);
-      const int grow = m0 + row, gcol = n0 + nc * 8;
-      if (grow < M && gcol < N) {
-        float d[8], g[8], u[8], og[8], ou[8];
-        unpack8(*reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16), d);
-        const int64_t at = (int64_t)grow * 2 * N + gcol;
-        load8(Rr + at, g);
-        load8(Rr + at + N, u);
+  } else if (EPI == kEpiSwigluBwd || add) {
+    // A second operand comes from memory: its loads for kBatch chunks are issued together (where a chunk is outside the matrix, of
+    // the nearest one inside), so that a thread waits for memory once or twice and not for every chunk.  Measured against one
+    // load and one wait per chunk, in us: sum with R of 8192x1024 over k = 1024 29.4 -> 27.4, over k = 2816 53.5 -> 51.8; d(gate) |
+    // d(up) of 16384x2816 over k = 1024 141.7 -> 140.5, of 2048x1408 over k = 512 12.9 -> 12.5.  Loads issued before the tile goes
+    // to its staging area gave no more and spilled (4096 cubed with R 98.3 -> 99.8).
+    constexpr int kIts = TILE * TILE / 8 / kThreads, kBatch = kIts < 8 ? kIts : 8;
+    const int64_t ld = EPI == kEpiSwigluBwd ? 2 * N : N;
+#pragma unroll 1
+    for (int it0 = 0; it0 < kIts; it0 += kBatch) {
+      uint4 r0[kBatch], r1[kBatch];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float sg = 1.0f / (1.0f + expf(-g[e]));
-          og[e] = d[e] * u[e] * sg * (1.0f + g[e] * (1.0f - sg));
-          ou[e] = d[e] * g[e] * sg;
+      for (int b = 0; b < kBatch; ++b) {
+        const int c = tid + kThreads * (it0 + b);
+        const bf16* r = Rr + min(m0 + c / (TILE / 8), M - 1) * ld + min(n0 + c % (TILE / 8) * 8, N - 8);
+        r0[b] = *reinterpret_cast<const uint4*>(r);
+        if (EPI == kEpiSwigluBwd) r1[b] = *reinterpret_cast<const uint4*>(r + N);
+      }
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) {
+        const int c = tid + kThreads * (it0 + b);
+        const int row = c / (TILE / 8), nc = c % (TILE / 8);
+        const int grow = m0 + row, gcol = n0 + nc * 8;
+        if (grow < M && gcol < N) {   // N is a multiple of 8: a chunk is inside or outside as a whole
+          float d[8], g[8];
+          unpack8(*reinterpret_cast<const uint4*>(smem + row * kCRowBytes + nc * 16), d);
+          unpack8(r0[b], g);
+          const int64_t at = grow * ld + gcol;
+          if (EPI == kEpiSwigluBwd) {
+            float u[8], og[8], ou[8];
+            unpack8(r1[b], u);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float sg = 1.0f / (1.0f + expf(-g[e]));
+              og[e] = d[e] * u[e] * sg * (1.0f + g[e] * (1.0f - sg));
+              ou[e] = d[e] * g[e] * sg;
+            }
+            store8_stream(C + at, og);
+            store8_stream(C + at + N, ou);
+          } else {
+            // the sum is formed in float from the accumulator's bf16 rounding; one more rounding on the way out
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d[e] += g[e];
+            store8_stream(C + at, d);
+          }
         }
-        store8_stream(C + at, og);
-        store8_stream(C + at + N, ou);
       }
     }
   } else
@@ -293,16 +319,6 @@ __device__ __forceinline__ void store_tile(const char* smem, bf16* C, const bf16
           x[2 * e] = a * c[e] - b * sn[e];
           x[2 * e + 1] = a * sn[e] + b * c[e];
         }
-        store8_stream(C + at, x);
-      } else if (add) {
-        // the sum is formed in float from the accumulator's bf16 rounding; one more rounding on the way out
-        float x[8], y[8];
-        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { x[2 * e] = bf16_bits_to_float(wv[e] & 0xffffu); x[2 * e + 1] = bf16_bits_to_float(wv[e] >> 16); }
-        load8(Rr + at, y);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += y[e];
         store8_stream(C + at, x);
       } else {
         store16_stream(C + at, v);

@@ -73,3 +73,15 @@ def test_feed_forward_epilogues_at_tile_edges(R, h, d):
                               np.concatenate([da * u * sg * (1 + g * (1 - sg)), da * g * sg], 1), 2)):
         lim = (n + 0.25) * 2.0 ** -8
         assert relerr(x, want) < lim and maxerr(x, want) < lim, (name, relerr(x, want), maxerr(x, want))
+
+
+@pytest.mark.parametrize("M,N,K", [(72, 136, 320), (1288, 1544, 192), (4096, 2824, 72), (2056, 1160, 328)])
+def test_a_sum_in_place_has_the_bits_of_one_beside(M, N, K):
+    """R may be the output: a thread reads a batch of its own entries of R before it stores them (tiles of every size, the last
+    row and column of tiles partly outside the matrix)."""
+    a, b = dev(synth.normal(61, f"ia{M}", (M, K))), dev(synth.normal(62, f"ib{M}", (N, K)))
+    r = dev(synth.normal(63, f"ir{M}", (M, N)))
+    c = torch.empty_like(r)
+    sp.gemm(0, a, b, c, r)
+    sp.gemm(0, a, b, r, r)
+    assert torch.equal(c, r)
