@@ -15,10 +15,11 @@
 // 32-cycle instruction leaves LDS idle most of the time; what bounds a workgroup is the chain of its tiles.  In bf16 the
 // matrix instructions are a fifth of that and vector instructions bound it (four wavefronts a SIMD, 285 a tile and wavefront of
 // the forward kernel before, 190 now): tiles lie in LDS as stored, the transposed operand comes by the LDS transpose read,
-// exponentials take half of expf's instructions, masks only stand where some key is hidden.  Heads of 48, forward | backward us, float
-// instruction and float tiles -> this: 3 x 333 positions x 6 heads 17 | 43 -> 10 | 25, 16 x 256 x 6 22 | 53 -> 13 | 31, 8 x 1024 x 16
-// 263 | 646 -> 109 | 289; the 50M shape on 3 x 333 tokens 3.60 -> 2.96 ms a pass.  (Float, of the same exponentials and masks: 8 x
-// 1024 x 16 heads of 48 312 | 891 -> 284 | 856.)  HD is the head dimension rounded up to a compiled size; columns past the real one are zeros. One wavefront per row of
+// exponentials take half of expf's instructions, masks only stand where some key is hidden.  Heads of 48, forward | backward
+// us, float instruction and float tiles -> this: 3 x 333 positions x 6 heads 17 | 43 -> 10 | 25, 16 x 256 x 6 22 | 53 -> 13 |
+// 31, 8 x 1024 x 16 263 | 646 -> 109 | 289; the 50M shape on 3 x 333 tokens 3.60 -> 2.96 ms a pass.  (Float, of the same
+// exponentials and masks: 8 x 1024 x 16 heads of 48 312 | 891 -> 284 | 856.)  HD is the head dimension rounded up to a compiled
+// size; columns past the real one are zeros.  One wavefront per row of
 // scores (the kernels these replaced) left the matrix cores idle and re-read K and V for every query.  Measured,
 // forward | backward (dQ and dK/dV), us: 6 sequences x 512 x 16 heads of 64 in float 542 -> 90 (36 TFLOP/s of the
 // causal half) | 7825 -> 269; 16 x 256 x 6 heads of 48 129 -> 33 | 1522 -> 82; 2 x 64 x 6 heads of 48, where launches

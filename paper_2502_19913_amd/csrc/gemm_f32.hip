@@ -51,8 +51,7 @@ constexpr int kThreads = 512;
 // length (4.2e-7 at K = 768, 1.0e-6 at 4096).  It takes one more set of accumulators.
 // The instruction rounds the sum of its products towards minus infinity, so that all entries are off in one direction (the mean
 // of the errors at K = 1536 is 3.5e-8 of an entry, four times what chance leaves; through a model's residual additions
-// such errors add up, not their squares).  So every second run is formed of the
-// negated A, and subtracted.  Gradients of whole models against 64 bits, float instruction / this / this without the negation:
+// such errors add up, not their squares).  So every second run is formed of the negated A, and subtracted.  Gradients of whole models against 64 bits, float instruction / this / this without the negation:
 // 50M widths, 2 x 256 tokens 6.3e-7 / 5.8e-7 / 9.0e-7, 500M widths, 2 x 128 tokens 8.3e-7 / 7.0e-7 / 12.4e-7.
 constexpr int kRun = 64 / BK;   // steps
 enum { kEpiPlain = 0, kEpiRope = 1, kEpiSwiglu = 2, kEpiSwigluBwd = 3 };   // as in the bf16 kernels
