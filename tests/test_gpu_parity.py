@@ -180,6 +180,18 @@ def test_small_bf16_row_counts_that_fill_no_round():
     check_bf16(got, ref, "ragged rows bf16")
 
 
+@pytest.mark.parametrize("base,seq_len,seqs", [(None, 3, 67), (None, 97, 3), ("c2", 7, 640)])
+def test_rotation_in_short_and_odd_sequences_bf16(base, seq_len, seqs):
+    # the product's epilogue steps from position to position by 16 (256-tiles; the last case), 32 or 64 rows, past the ends
+    # of several sequences at once where they are shorter
+    cfg = SMALL if base is None else synth.shrink(synth.CONFIGS[base], vocab=512, layers_per_stage=1)
+    cfg = dict(cfg, dtype="bf16", n_stages=2, local_stage_count=2, layers_per_stage=1, n_mb=1, seq_len=seq_len, seqs_per_mb=seqs)
+    named, tok, tgt = inputs(cfg, 41, bf16=True)
+    paths, lens = np.array([[0, 1]], np.int32), np.array([2], np.int32)
+    ref = orc.run_paths(cfg, named, paths, lens, tokens=tok, targets=tgt, dtype=np.float32)
+    check_bf16(run(cfg, named, paths, lens, tokens=tok, targets=tgt), ref, f"{seq_len} positions")
+
+
 @pytest.mark.parametrize("vocab", [8200, 40000, 70000, 131080])
 def test_head_and_loss_over_vocabulary_sizes_bf16(vocab):
     # the loss kernel holds a row of logits in the registers of 256, 512 or 1024 threads, by the row's length;
