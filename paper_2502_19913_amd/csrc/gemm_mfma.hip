@@ -328,8 +328,8 @@ __device__ __forceinline__ void store_tile(const char* smem, bf16* C, const bf16
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float p = x[2 * e], q = x[2 * e + 1];
-              x[2 * e] = p * c[e] - q * sn[e];
-              x[2 * e + 1] = p * sn[e] + q * c[e];
+              x[2 * e] = __builtin_fmaf(p, c[e], -(q * sn[e]));   // written out: which product is rounded is the compiler's
+              x[2 * e + 1] = __builtin_fmaf(q, c[e], p * sn[e]);  // choice otherwise, and bf16 results move with it
             }
             store8_stream(C + at, x);
           } else {
