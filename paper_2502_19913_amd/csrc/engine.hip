@@ -424,11 +424,17 @@ int sp_stage_bwd(sp_ctx* ctx, int stage, const void* params, void* dact_pool, co
   // A layer's four weight gradients: each is launched as soon as its input is there, or, where they are so short that the
   // host's calls take as long as the kernels, all of them in one launch at the end of the layer.  A layer of the backward pass
   // has 9 launches (3.4 us each on the host) besides these, and these cost it 16 more calls (75 us) one by one, 5 together.
-  // us a pass, one by one / together: 50M shape in float on 2 x 64 tokens 1750 / 1440, in bf16 on 4 x 999 2960 / 2815, in float on 4 x
-  // 1024 4930 / 5050, 500M stage in float 4960 / 5270, 1.5B stage 46290 / 47500: later and all at once they fill the gaps of the
-  // chain beside them less well.  The line lies at products of about 20 us.
-  const double grad_flops = 2.0 * (double)R * (double)D.d * (double)(D.nq + D.d + 3 * D.h);
-  const bool together = grad_flops < (dt == SP_BF16 ? 12e9 : 2.5e9);
+  // us for forward and backward of 4 layers, one by one / together, on either side of the lines:
+  //   bf16  50M shape 5598 rows 1312 / 1262, 6398 1395 / 1345, 8192 1622 / 1535; 500M 350 rows 1004 / 909, 450 1033 / 936, 500
+  //         1030 / 946, 1000 1241 / 1260, 2000 1703 / 1745, 4096 2252 / 2224, 12288 5032 / 5200; 1.5B 64 rows 1693 / 1643, 100 1650 /
+  //         1660, 256 1833 / 1784, 700 2435 / 2514; 7B 16 rows 3940 / 4133, 40 4110 / 4251
+  //   float 50M 1000 rows 1416 / 1390, 1200 1180 / 1159, 1400 1336 / 1300, 2000 1627 / 1647, 4096 2463 / 2517; 500M 64 rows 982 / 952,
+  //         90 1098 / 1107, 256 1665 / 1644, 512 2386 / 2416
+  // Past the lines neither way is the better one throughout (all at once they leave fewer workgroups idle at the end, but later
+  // they fill the gaps of the chain beside them less well).  The lines lie at products of about 20 us, and at outputs whose
+  // atomics take far longer than any host call.
+  const double grad_elems = (double)D.d * (double)(D.nq + D.d + 3 * D.h), grad_flops = 2.0 * (double)R * grad_elems;
+  const bool together = grad_flops < (dt == SP_BF16 ? 12e9 : 2.5e9) && grad_elems < 100e6;
   int n = 0;   // layers done
   GradItem items[kGrads];
   // weight gradient k of the layer (0: down, 1: gate/up, 2: output, 3: qkv), once its input (just written on the main stream)

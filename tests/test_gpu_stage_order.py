@@ -58,14 +58,14 @@ def captured(stream, work):
     return names, before
 
 
-# rows, width, hidden: products one by one and, of fewer operations, in one launch a layer
+# rows, width, hidden: products one by one and, of fewer operations, in one launch a layer; few operations but large outputs
 @pytest.mark.parametrize("dtype,rows,d,hidden,launches", [("bf16", 1024, 1024, 2816, 4), ("f32", 1024, 512, 1408, 4), ("bf16", 64, 256, 512, 1),
-                                                          ("f32", 128, 256, 512, 1)])
+                                                          ("f32", 128, 256, 512, 1), ("bf16", 16, 4096, 11008, 4)])
 def test_the_gradient_chain_waits_for_no_weight_gradient_too_early(dtype, rows, d, hidden, launches):
     """Beside the chain, weight gradients may fall a layer behind: what ends a layer (its last norm, which writes the gradient
     of the layer below over what the layer above had for its own) waits for the layers two and more above and for the first
     launch of the layer above, and for none of its own layer."""
-    layers = 6
+    layers = 6 if d < 4096 else 3
     cfg = dict(synth.CONFIGS["c1"], dim=d, n_heads=d // 64, n_kv_heads=d // 64, hidden=hidden, vocab=512, n_stages=2, layers_per_stage=layers,
                seq_len=rows, seqs_per_mb=1, n_mb=1, dtype=dtype, local_stage_begin=1, local_stage_count=1, has_embed=0, has_head=0)
     stream = torch.cuda.Stream()
