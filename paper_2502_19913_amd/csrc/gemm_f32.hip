@@ -250,7 +250,9 @@ struct Share {
       lds[u] = Planes<T>::at(row[u], k >> 3) + (k & 4) * 2;
     }
   }
-  // v[q]: quad q = unit * XW + column; MASK: k past the end of a k-contiguous operand become zeros
+  // v[q]: quad q = unit * XW + column.  k past the end are zeros in both operands: what a k-contiguous one holds there are the
+  // first values of its next row, and if those are not finite, zeros in the other operand alone would leave NaN in this row.
+  // MASK: there are such k (a branch per load instead stops the compiler from keeping loads in flight: 1.05 to 1.2 x).
   template <bool MASK>
   __device__ __forceinline__ void load(float (*v)[4], int k0, int K, int ld) const {
     if constexpr (VEC) {
@@ -370,36 +372,40 @@ __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
       if (s & kRun) a.template put<true>(buf(s), v);
       else a.template put<false>(buf(s), v);
     };
-    // Tiles of the same size: two wavefronts for each operand (wider loads); else all four for both.  In op 0 the operands'
-    // rows run on past the end of k: zeros in one of them do (where what the other meets there is not finite, entries are
-    // formed anew).
-    if constexpr (TM == TB) {
-      if (wave < 6) {
-        Share<AS, TM, 2, VEC> a;
-        a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
-        feed<a.Q>(steps, [&](int s, float (*v)[4]) { a.template load<false>(v, s * BK, K, lda); }, [&](int s, float (*v)[4]) { put_a(a, s, v); });
+    // Tiles of the same size: two wavefronts for each operand (wider loads); else all four for both.
+    auto bring = [&](auto mask) {
+      constexpr bool MASK = decltype(mask)::value;
+      if constexpr (TM == TB) {
+        if (wave < 6) {
+          Share<AS, TM, 2, VEC> a;
+          a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
+          feed<a.Q>(steps, [&](int s, float (*v)[4]) { a.template load<MASK>(v, s * BK, K, lda); }, [&](int s, float (*v)[4]) { put_a(a, s, v); });
+        } else {
+          Share<BS, TB, 2, VEC> b;
+          b.init(g.B, ldb, b0, g.N, K, wave - 6, lane, b_row);
+          feed<b.Q>(steps, [&](int s, float (*v)[4]) { b.template load<MASK>(v, s * BK, K, ldb); },
+                    [&](int s, float (*v)[4]) { b.template put<false>(buf(s) + Planes<TM>::kBytes, v); });
+        }
       } else {
-        Share<BS, TB, 2, VEC> b;
-        b.init(g.B, ldb, b0, g.N, K, wave - 6, lane, b_row);
-        feed<b.Q>(steps, [&](int s, float (*v)[4]) { b.template load<true>(v, s * BK, K, ldb); },
-                  [&](int s, float (*v)[4]) { b.template put<false>(buf(s) + Planes<TM>::kBytes, v); });
+        Share<AS, TM, 4, VEC> a;
+        Share<BS, TB, 4, VEC> b;
+        a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
+        b.init(g.B, ldb, b0, g.N, K, wave - 4, lane, b_row);
+        feed<a.Q + b.Q>(
+            steps,
+            [&](int s, float (*v)[4]) {
+              a.template load<MASK>(v, s * BK, K, lda);
+              b.template load<MASK>(v + a.Q, s * BK, K, ldb);
+            },
+            [&](int s, float (*v)[4]) {
+              put_a(a, s, v);
+              b.template put<false>(buf(s) + Planes<TM>::kBytes, v + a.Q);
+            });
       }
-    } else {
-      Share<AS, TM, 4, VEC> a;
-      Share<BS, TB, 4, VEC> b;
-      a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
-      b.init(g.B, ldb, b0, g.N, K, wave - 4, lane, b_row);
-      feed<a.Q + b.Q>(
-          steps,
-          [&](int s, float (*v)[4]) {
-            a.template load<false>(v, s * BK, K, lda);
-            b.template load<true>(v + a.Q, s * BK, K, ldb);
-          },
-          [&](int s, float (*v)[4]) {
-            put_a(a, s, v);
-            b.template put<false>(buf(s) + Planes<TM>::kBytes, v + a.Q);
-          });
-    }
+    };
+    constexpr bool masks = VEC && !(AS && BS);   // what a k-strided operand's end leaves, and single elements, are zeros anyway
+    if (masks && K % BK) bring(std::integral_constant<bool, masks>());
+    else bring(std::false_type());
     return;
   }
   const int wm = wave >> 1, wn = wave & 1, base_a = wm * WM, base_b = wn * WN * NSEG;
@@ -543,60 +549,66 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
 #pragma unroll
     for (int i = 0; i < NB; ++i) b[i].init(g.B, ldb, i * cols + n0, NB == 2 ? 2 * cols : cols, K, 0, lane, [&](int t) { return i * cols + min(n0 + t, cols - 1); });
     float ra[kRun][SA::Q][4], rb[kRun][NB][SB::Q][4];
-    auto load = [&](int run) {   // past the end: the last step again
-#pragma unroll
-      for (int e = 0; e < kRun; ++e) {
-        const int k0 = min(run * kRun + e, steps - 1) * BK;
-        a.template load<false>(ra[e], k0, K, lda);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) b[i].template load<true>(rb[e][i], k0, K, ldb);
-      }
-    };
     char* const mine = tiles[wave];
     const int at = Planes<16>::at(lr, kg);
-    load(wave);
-    for (int r0 = 0, par = 0; r0 < runs; r0 += NW, par ^= 1) {
-      const int run = r0 + wave;
-      if (run < runs) {
-        f32x4 acc[NB];
+    auto form = [&](auto mask) {
+      constexpr bool MASK = decltype(mask)::value;
+      auto load = [&](int run) {   // past the end: the last step again
 #pragma unroll
         for (int e = 0; e < kRun; ++e) {
-          if (run * kRun + e < steps) {
-            if (run & 1) a.template put<true>(mine, ra[e]);
-            else a.template put<false>(mine, ra[e]);
+          const int k0 = min(run * kRun + e, steps - 1) * BK;
+          a.template load<MASK>(ra[e], k0, K, lda);
 #pragma unroll
-            for (int i = 0; i < NB; ++i) b[i].template put<false>(mine + (1 + i) * kTile, rb[e][i]);
-            const Frag fa = frag<16>(mine, 0, at);
+          for (int i = 0; i < NB; ++i) b[i].template load<MASK>(rb[e][i], k0, K, ldb);
+        }
+      };
+      load(wave);
+      for (int r0 = 0, par = 0; r0 < runs; r0 += NW, par ^= 1) {
+        const int run = r0 + wave;
+        if (run < runs) {
+          f32x4 acc[NB];
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-              const Frag fb = frag<16>(mine + (1 + i) * kTile, 0, at);
+          for (int e = 0; e < kRun; ++e) {
+            if (run * kRun + e < steps) {
+              if (run & 1) a.template put<true>(mine, ra[e]);
+              else a.template put<false>(mine, ra[e]);
 #pragma unroll
-              for (int t = 0; t < kTerms; ++t) {
-                const f32x4 c = e == 0 && t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i];
-                acc[i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.p[kTermX[t]], fb.p[kTermY[t]], c, 0, 0, 0)
-                                 : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb.p[kTermX[t]], fa.p[kTermY[t]], c, 0, 0, 0);
+              for (int i = 0; i < NB; ++i) b[i].template put<false>(mine + (1 + i) * kTile, rb[e][i]);
+              const Frag fa = frag<16>(mine, 0, at);
+#pragma unroll
+              for (int i = 0; i < NB; ++i) {
+                const Frag fb = frag<16>(mine + (1 + i) * kTile, 0, at);
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t) {
+                  const f32x4 c = e == 0 && t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i];
+                  acc[i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.p[kTermX[t]], fb.p[kTermY[t]], c, 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb.p[kTermX[t]], fa.p[kTermY[t]], c, 0, 0, 0);
+                }
               }
             }
           }
+          if (run + NW < runs) load(run + NW);
+#pragma unroll
+          for (int i = 0; i < NB; ++i) found[par][wave][i][lane] = acc[i];
         }
-        if (run + NW < runs) load(run + NW);
+        __syncthreads();   // the other half of `found` is free: the first wavefront read it before it came here
+        if (wave == 0) {
+          const int n = min(NW, runs - r0);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) found[par][wave][i][lane] = acc[i];
+          for (int w = 0; w < NW; ++w)
+            if (w < n)
+#pragma unroll
+              for (int i = 0; i < NB; ++i) {
+                const f32x4 v = found[par][w][i][lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[i][e] = __builtin_fmaf(v[e], w & 1 ? -1.f : 1.f, sum[i][e]);
+              }
+        }
       }
-      __syncthreads();   // the other half of `found` is free: the first wavefront read it before it came here
-      if (wave == 0) {
-        const int n = min(NW, runs - r0);
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-          if (w < n)
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-              const f32x4 v = found[par][w][i][lane];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) sum[i][e] = __builtin_fmaf(v[e], w & 1 ? -1.f : 1.f, sum[i][e]);
-            }
-      }
-    }
+    };
+    constexpr bool masks = VEC && !(AS && BS);
+    if (masks && K % BK) form(std::integral_constant<bool, masks>());
+    else form(std::false_type());
   }
   if (wave) return;
   static_assert(NW % 2 == 0, "a wavefront's runs are all odd or all even");

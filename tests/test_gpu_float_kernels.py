@@ -252,3 +252,25 @@ def test_float_rows_have_the_bits_of_larger_tiles_in_tiles_of_16(N, K, few, rows
         assert np.array_equal(x, y), (name, relerr(x, y))
     want = a[:few].double() @ b.double().T
     assert relerr(out[1][1], want.cpu().numpy()) < 2e-5
+
+
+# a last step that is not full (16-byte access, and not), in tiles of 16, 32, 64, 128 x 64 and 128
+@pytest.mark.parametrize("M,N,K", [(33, 40, 36), (512, 768, 292), (1100, 516, 36), (1100, 515, 35), (2048, 1024, 100), (2183, 1352, 36)])
+def test_float_rows_keep_their_bits_beside_rows_that_are_not_finite(M, N, K):
+    # a row runs on into the next one past the end of k: nothing of that may reach it, not even the order of its sums
+    a = dev(synth.normal(72, f"ka{M}{K}", (M, K))); b = dev(synth.normal(73, f"kb{N}{K}", (N, K)))
+    gu = dev(synth.normal(74, f"kg{M}{N}", (M, 2 * N))); bt = b.t().contiguous(); wgu = torch.cat([b, b.flip(0)])
+    bad = torch.arange(M, device="cuda") % 3 == 1
+    out = []
+    for poison in (False, True):
+        if poison:
+            a[bad] = float("nan")
+        empty = lambda w: torch.empty((M, w), device="cuda")
+        c0, c1, up, act, dgu = empty(N), empty(N), empty(2 * N), empty(N), empty(2 * N)
+        sp.gemm(0, a, b, c0)
+        sp.gemm(1, a, bt, c1)
+        sp.ffn_up_fwd(a, wgu, up, act)
+        sp.ffn_down_bwd(a, bt, gu, dgu, empty(N))
+        out.append([x[~bad] for x in (c0, c1, up, act, dgu)])
+    for name, x, y in zip(("op 0", "op 1", "gate|up", "act", "d(gate)|d(up)"), *out):
+        assert torch.equal(x, y), name
