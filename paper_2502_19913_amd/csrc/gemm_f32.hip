@@ -191,24 +191,76 @@ __device__ __forceinline__ Frag frag(const char* lds, int base, int lane_at) {  
 constexpr int kTerms = 6;
 constexpr int kTermX[kTerms] = {2, 0, 1, 1, 0, 0}, kTermY[kTerms] = {0, 2, 1, 0, 1, 0};
 
-// The parts of a value that is not finite, or rounds past the largest bfloat16, are infinities and NaN.  Entries of a block of
-// 16 x 16 that come out as either are formed anew from the floats themselves, on the float instruction.  m, n: lane's row of A and
-// row (column) of B.
-template <int OP>
-__device__ __forceinline__ void mend(const Args& g, f32x4& v, int m, int n, int kg) {
+// The parts of a value that is not finite, or rounds past the largest bfloat16, are infinities and NaN.  Entries of the blocks of
+// 16 x 16 in `sum` that come out as either are formed anew from the floats themselves, on the float instruction and in the same
+// runs (k-slots may stand for any k: a lane takes four neighbours of every 16).  NaN stays NaN: a block whose entries all
+// have come to that is done, so that a pass through which it has spread costs about one run a block.  us, op 0 / 1 / 2, 4096 x
+// 1024 x 2816: finite 130 / 119 / 118, NaN throughout 126 / 131 / 150, NaN in the last k alone or an infinity in every row 1080 /
+// 1570 / 1820, an infinity in one row 343 / 461 / 530.  (The loads of a whole run at once, 720 / 1130 / 1470, took 25 registers
+// more, and with them a workgroup of 128 x 64.)
+// row_m(j), row_n(i): lane's row of A and row (column) of B in block (j, i).
+template <int OP, bool VEC, int NA, int NB, class RowM, class RowN>
+__device__ __forceinline__ void mend(const Args& g, f32x4 (&sum)[NA][NB], RowM row_m, RowN row_n, int kg) {
   constexpr bool AS = OP == 2, BS = OP != 0;
-  if (!__ballot(!(finite(v[0]) && finite(v[1]) && finite(v[2]) && finite(v[3])))) return;
-  const int K = g.K;
-  f32x4 c = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < K; k += 4) {
-    const bool in = k + kg < K;
-    const int kk = min(k + kg, K - 1);
-    const float a = in ? (AS ? g.A[(int64_t)kk * g.M + m] : g.A[(int64_t)m * K + kk]) : 0.f;
-    const float b = in ? (BS ? g.B[(int64_t)kk * g.N + n] : g.B[(int64_t)n * K + kk]) : 0.f;
-    c = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0);
-  }
+  uint32_t todo = 0;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = finite(v[r]) ? v[r] : c[r];
+  for (int j = 0; j < NA; ++j)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const f32x4 v = sum[j][i];
+      if (__ballot(!(finite(v[0]) && finite(v[1]) && finite(v[2]) && finite(v[3])))) todo |= 1u << (j * NB + i);
+    }
+  const int K = g.K;
+  while (todo) {
+    const int blk = __builtin_ctz(todo);
+    todo &= todo - 1;
+    const int m = row_m(blk / NB), n = row_n(blk % NB);
+    f32x4 v, c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (blk == j * NB + i) v = sum[j][i];
+    // the block's first row (column) is uniform; a lane's place in it
+    const int m_first = __builtin_amdgcn_readfirstlane(m), n_first = __builtin_amdgcn_readfirstlane(n);
+    const float* pa = g.A + (AS ? (int64_t)m_first : (int64_t)m_first * K);
+    const float* pb = g.B + (BS ? (int64_t)n_first : (int64_t)n_first * K);
+    typedef std::conditional_t<AS, uint32_t, int64_t> LA;   // 15 columns, or 15 rows
+    typedef std::conditional_t<BS, uint32_t, int64_t> LB;
+    const LA la = AS ? (LA)(m - m_first) : (LA)(m - m_first) * K;
+    const LB lb = BS ? (LB)(n - n_first) : (LB)(n - n_first) * K;
+    for (int k0 = 0; k0 < K; k0 += kRun * BK) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int h = k0; h < k0 + kRun * BK; h += 16) {
+        f32x4 a, b;
+        const int k = h + kg * 4;
+        if (AS) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[e] = k + e < K ? pa[(int64_t)(k + e) * g.M + la] : 0.f;
+        } else a = load4<VEC>(pa + la + k, K - k);
+        if (BS) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) b[e] = k + e < K ? pb[(int64_t)(k + e) * g.N + lb] : 0.f;
+        } else b = load4<VEC>(pb + lb + k, K - k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc, 0, 0, 0);
+      }
+      c += acc;
+      bool open = false;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) open = open || (!finite(v[r]) && c[r] == c[r]);
+      if (!__ballot(open)) break;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = finite(v[r]) ? v[r] : c[r];
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (blk == j * NB + i) sum[j][i] = v;
+  }
 }
 
 // The share of one of NW wavefronts in bringing an operand's tile from memory to LDS: units of a row's 4 consecutive k
@@ -486,11 +538,8 @@ __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
       for (int j = 0; j < NA; ++j) add_up(j, (steps - 1) & kRun ? -1.f : 1.f);
     else if (NA > 1) add_up(NA - 1, (steps - 1) & kRun ? -1.f : 1.f);
   }
-#pragma unroll
-  for (int j = 0; j < NA; ++j)
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-      mend<OP>(g, sum[j][i], min(m0 + base_a + j * 16 + lr, g.M - 1), BS ? min(n0 + base_b + i * 16 + lr, g.N - 1) : b_row(base_b + i * 16 + lr), kg);
+  mend<OP, VEC>(g, sum, [&](int j) { return min(m0 + base_a + j * 16 + lr, g.M - 1); },
+                [&](int i) { return BS ? min(n0 + base_b + i * 16 + lr, g.N - 1) : b_row(base_b + i * 16 + lr); }, kg);
   if (OP == 2) {
 #pragma unroll
     for (int j = 0; j < NA; ++j)
@@ -539,7 +588,8 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
   tile_of(g, xcd_major(wg, n_wgs), tm, tn);
   const int m0 = tm * 16, n0 = tn * 16, K = g.K, steps = (K + BK - 1) / BK, runs = (steps + kRun - 1) / kRun;
   const int cols = NB == 2 ? g.N / 2 : g.N, lda = AS ? g.M : K, ldb = BS ? g.N : K;
-  f32x4 sum[NB];
+  f32x4 sums[1][NB];
+  f32x4 (&sum)[NB] = sums[0];
 #pragma unroll
   for (int i = 0; i < NB; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (runs > 0) {
@@ -612,9 +662,7 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
   }
   if (wave) return;
   static_assert(NW % 2 == 0, "a wavefront's runs are all odd or all even");
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-    mend<OP>(g, sum[i], min(m0 + lr, g.M - 1), i * cols + min(n0 + lr, cols - 1), kg);
+  mend<OP, VEC>(g, sums, [&](int) { return min(m0 + lr, g.M - 1); }, [&](int i) { return i * cols + min(n0 + lr, cols - 1); }, kg);
   if (OP == 2) {
     const int n = n0 + lr;
 #pragma unroll
@@ -630,14 +678,16 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
   else emit<OP, EPI, VEC>(g, m, n, sum[0]);
 }
 
+// Wavefronts a SIMD: LDS holds one workgroup with tiles of 128, two with 128 x 64 (128 registers; with more, and one workgroup, op 2
+// 2048 x 3072 x 1024 takes 97 us for 80).
 template <int OP, int EPI, int TM, int TN, bool VEC>
-__global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 ? 2 : 4) void k_gemm_f32(Args g) { gemm_tile<OP, EPI, TM, TN, VEC>(g, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(kThreads, TM * TN > (VEC ? 128 : 64) * 64 ? 2 : 4) void k_gemm_f32(Args g) { gemm_tile<OP, EPI, TM, TN, VEC>(g, blockIdx.x, gridDim.x); }
 template <int OP, int EPI, bool VEC>
 __global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) { gemm_few<OP, EPI, VEC>(g, blockIdx.x, gridDim.x); }
 
 // the weight gradients of a layer in one launch, all in tiles of one size
 template <int TM, int TN, bool VEC>
-__global__ __launch_bounds__(kThreads, TM * TN > 64 * 64 || TN == 16 ? 2 : 4) void k_gemm_f32_grads(GradGroup l) {
+__global__ __launch_bounds__(kThreads, TM * TN > (VEC ? 128 : 64) * 64 || TN == 16 ? 2 : 4) void k_gemm_f32_grads(GradGroup l) {
   int i = 0;
   while (i + 1 < kGrads && (int)blockIdx.x >= l.first[i + 1]) ++i;
   const int wg = (int)blockIdx.x - l.first[i], n = l.first[i + 1] - l.first[i];

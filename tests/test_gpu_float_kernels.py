@@ -274,3 +274,38 @@ def test_float_rows_keep_their_bits_beside_rows_that_are_not_finite(M, N, K):
         out.append([x[~bad] for x in (c0, c1, up, act, dgu)])
     for name, x, y in zip(("op 0", "op 1", "gate|up", "act", "d(gate)|d(up)"), *out):
         assert torch.equal(x, y), name
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 40, 4096), (1030, 1100, 3072), (2048, 2048, 2051)])
+def test_float_products_formed_anew_lose_no_more_than_others(M, N, K):
+    # a factor that rounds past the largest bfloat16 has no finite parts, and all its row's entries are formed again from the
+    # floats: in runs of 64 k too (bound: test_float_products_lose_little_over_long_reductions)
+    a = synth.normal(75, f"ma{M}{K}", (M, K)); b = synth.normal(76, f"mb{N}{K}", (N, K))
+    a[M // 2:, K // 3] = 3.4e38; b[:, K // 3] *= np.float32(1e-38)
+    want = a.astype(np.float64) @ b.astype(np.float64).T
+    for op in (0, 1, 2):
+        c = torch.zeros((M, N), device="cuda")
+        sp.gemm(op, dev(a.T if op == 2 else a), dev(b if op == 0 else b.T), c)
+        err = relerr(c[M // 2:].cpu().numpy(), want[M // 2:])
+        assert err < 3.6e-8 * np.sqrt(16 + K / 64), (op, err)
+
+
+@pytest.mark.parametrize("op", [0, 1, 2])
+def test_float_products_of_nan_take_little_longer_than_others(op):
+    # a pass that has diverged is NaN throughout: such entries are settled by the first run of k, at a few per cent of a product
+    # (1.1 to 1.3 times the time of a finite one; 12 to 18 times when every entry took the whole reduction); four leaves room
+    M, N, K = 4096, 1024, 2816
+    a = dev(synth.normal(77, "na", (M, K) if op < 2 else (K, M))); b = dev(synth.normal(78, "nb", (N, K) if op == 0 else (K, N)))
+    c = torch.zeros((M, N), device="cuda")
+    best = []
+    for x in (a, torch.full_like(a, float("nan"))):
+        took = []
+        for _ in range(6):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            sp.gemm(op, x, b, c)
+            t[1].record()
+            torch.cuda.synchronize()
+            took.append(t[0].elapsed_time(t[1]))
+        best.append(min(took))
+    assert torch.isnan(c).all() and best[1] < 4 * best[0], best
