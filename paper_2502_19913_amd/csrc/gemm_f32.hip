@@ -569,9 +569,16 @@ __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
   }
 }
 
+// Lanes of one wavefront exchange values through LDS, whose operations of one wavefront are in order: no instruction, but the
+// compiler, which keeps the order of one lane's accesses only, has to leave them on their sides of this.
+__device__ __forceinline__ void exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // For products too small to fill the chip, where the time is one chain of latencies: tiles of 16 x 16 (SwiGLU: rows x
 // features), eight wavefronts that each form whole runs of 64 k, in turn, from loads and splits of their own (no barrier:
-// LDS operations of one wavefront are in order), the next run's loads on their way.  After every eight runs the first
+// exchange() above), the next run's loads on their way.  After every eight runs the first
 // wavefront adds them up in order, so that entries have the bits that the other tiles give them.
 template <int OP, int EPI, bool VEC>
 __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
@@ -624,15 +631,19 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
               else a.template put<false>(mine, ra[e]);
 #pragma unroll
               for (int i = 0; i < NB; ++i) b[i].template put<false>(mine + (1 + i) * kTile, rb[e][i]);
+              exchange();
               const Frag fa = frag<16>(mine, 0, at);
+              Frag fb[NB];
+#pragma unroll
+              for (int i = 0; i < NB; ++i) fb[i] = frag<16>(mine + (1 + i) * kTile, 0, at);
+              exchange();   // the next step's values may follow
 #pragma unroll
               for (int i = 0; i < NB; ++i) {
-                const Frag fb = frag<16>(mine + (1 + i) * kTile, 0, at);
 #pragma unroll
                 for (int t = 0; t < kTerms; ++t) {
                   const f32x4 c = e == 0 && t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i];
-                  acc[i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.p[kTermX[t]], fb.p[kTermY[t]], c, 0, 0, 0)
-                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb.p[kTermX[t]], fa.p[kTermY[t]], c, 0, 0, 0);
+                  acc[i] = OP == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.p[kTermX[t]], fb[i].p[kTermY[t]], c, 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[i].p[kTermX[t]], fa.p[kTermY[t]], c, 0, 0, 0);
                 }
               }
             }
