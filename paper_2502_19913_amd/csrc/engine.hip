@@ -657,7 +657,7 @@ int sp_gemm_shape(int dtype, int op, int M, int N, int K, int epilogue, int32_t*
       (epilogue && op != (epilogue == 3 ? 1 : 0)) || (epilogue == 2 && N % 2))
     return fail(SP_EINVAL, "gemm_shape: bad op, shape or epilogue");
   GemmShape s{0, 0, 0};
-  if (dtype == SP_F32) s = gemm_f32_shape(M, N, K, epilogue);
+  if (dtype == SP_F32) s = gemm_f32_shape(op, M, N, K, epilogue);
   else if (epilogue >= 2 && gemm_swiglu_supported(epilogue == 3, M, epilogue == 3 ? N : N / 2, K, nullptr, nullptr, nullptr, nullptr))
     s = gemm_mfma_shape(op, M, N, K, epilogue);
   else if (gemm_mfma_supported(op, M, N, K, nullptr, nullptr, nullptr, nullptr)) s = gemm_mfma_shape(op, M, N, K, epilogue >= 2 ? 0 : epilogue);

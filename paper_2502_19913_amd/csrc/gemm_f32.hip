@@ -263,19 +263,27 @@ __device__ __forceinline__ void mend(const Args& g, f32x4 (&sum)[NA][NB], RowM r
   }
 }
 
+// How a product's operands are reached.  kAligned: pointers and widths are multiples of 16 bytes / 4.  kUnaligned: buffer loads
+// need 4-byte alignment only, so all is loaded alike; what crosses the end of the matrix is loaded again one by one.  kFar: a
+// tile reaches further than 31 bits (gemm_f32_far): one by one from pointers.
+// us, one by one from pointers (as all that are not aligned were; float instruction before that) / this: op 0 1024 x 1023 x 1021 58
+// (41) / 21, 4096 x 2050 x 515 152 (186) / 78, op 1 2048 x 287 x 289 20 (16) / 9.2, op 2 1024 x 1023 x 1021 70 (48) / 24, 999 x 1024 x
+// 5632 474 (234) / 89 (aligned, 1024: 88).
+enum { kFar = 0, kUnaligned = 1, kAligned = 2 };
+
 // The share of one of NW wavefronts in bringing an operand's tile from memory to LDS: units of a row's 4 consecutive k
 // (k-contiguous) or of 4 k of XW neighbouring columns (k-strided).
-// VEC: buffer loads from a descriptor that starts at the step, so that a lane's offsets are the same for all steps and k past
-// the end of a k-strided operand reads as zeros.  Otherwise element by element.  Rows (columns) past the edge are read as
-// the last one (VEC, k-strided: as what follows); nothing of them is stored.
-template <bool KS, int T, int NW, bool VEC>
+// Buffer loads from a descriptor that starts at the step, so that a lane's offsets are the same for all steps and k past
+// the end of a k-strided operand reads as zeros.  Rows (columns) past the edge are read as the last one (k-strided: as
+// what follows); nothing of them is stored.
+template <bool KS, int T, int NW, int ACC>
 struct Share {
   static constexpr int Q = T / (8 * NW);                          // quads of 4 k
   static constexpr int XW = KS ? (Q < 4 ? Q : 4) : 1, NU = Q / XW;
-  const char* base;      // VEC: the first byte that the tile can reach, and how many follow it
+  const char* base;      // the first byte that the tile can reach, and how many follow it
   int64_t left;
   uint32_t off[NU];
-  const float* p[NU];    // not VEC: a unit's row or first column, and where its other columns are
+  const float* p[NU];    // kFar: a unit's row or first column, and where its other columns are
   int dx[NU][3], row[NU], lds[NU], k;
   template <class RowOf>
   __device__ __forceinline__ void init(const float* X, int ld, int x0, int cols, int K, int wave, int lane, RowOf row_of) {
@@ -302,15 +310,21 @@ struct Share {
       lds[u] = Planes<T>::at(row[u], k >> 3) + (k & 4) * 2;
     }
   }
-  // v[q]: quad q = unit * XW + column.  k past the end are zeros in both operands: what a k-contiguous one holds there are the
-  // first values of its next row, and if those are not finite, zeros in the other operand alone would leave NaN in this row.
-  // MASK: there are such k (a branch per load instead stops the compiler from keeping loads in flight: 1.05 to 1.2 x).
-  template <bool MASK>
+  // v[q]: quad q = unit * XW + column
   __device__ __forceinline__ void load(float (*v)[4], int k0, int K, int ld) const {
-    if constexpr (VEC) {
-      const int64_t skip = (int64_t)k0 * (KS ? ld : 1) * 4, rest = left - skip;
-      const rsrc_t rs = make_rsrc(base + skip, (uint32_t)(rest > 0x7fffffff ? 0x7fffffff : rest));
-      const uint32_t dead = MASK && !KS && k0 + k >= K ? 0x80000000u : 0u;   // a quad is inside or outside as a whole
+    if constexpr (ACC == kFar) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int c = 0; c < XW; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int at = min(k0 + k + e, K - 1);
+            const float x = KS ? p[u][(int64_t)at * ld + (c ? dx[u][c ? c - 1 : 0] : 0)] : p[u][at];
+            v[u * XW + c][e] = k0 + k + e < K ? x : 0.f;
+          }
+    } else {
+      const rsrc_t rs = make_rsrc(base + (int64_t)k0 * (KS ? ld : 1) * 4, bytes(k0, ld));
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
         if constexpr (KS) {
@@ -329,22 +343,52 @@ struct Share {
             }
           }
         } else {
-          const f32x4 x = __builtin_bit_cast(f32x4, buffer_load16(rs, MASK ? off[u] | dead : off[u]));
+          const f32x4 x = __builtin_bit_cast(f32x4, buffer_load16(rs, off[u]));
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[u][e] = x[e];
         }
       }
-    } else {
+    }
+  }
+  __device__ __forceinline__ uint32_t bytes(int k0, int ld) const {   // from step k0 to the end of the matrix, as the descriptor holds it
+    const int64_t rest = left - (int64_t)k0 * (KS ? ld : 1) * 4;
+    return (uint32_t)(rest > 0x7fffffff ? 0x7fffffff : rest);
+  }
+  // is there something to finish in step k0 or before it (a load of four from the third row before the last may cross the end: rows
+  // of one float)
+  static __device__ __forceinline__ bool unfinished(int k0, int K) { return ACC != kFar && k0 + BK + (ACC == kUnaligned ? 3 : 0) > K; }
+  // What load() brought of the last steps, made right before it is used (a choice at the load instead keeps the compiler from
+  // leaving loads in flight: 1.05 to 1.2 x).  A load of several floats that crosses the end of the matrix: one by one.  k past the
+  // end become zeros, in both operands: what a k-contiguous one holds there are the first values of its next row, and if those
+  // are not finite, zeros in the other operand alone would leave NaN in this row.
+  __device__ __forceinline__ void finish(float (*v)[4], int k0, int K, int ld) const {
+    if (!unfinished(k0, K)) return;
+    if constexpr (ACC == kUnaligned && (!KS || XW > 1)) {
+      const uint32_t end = bytes(k0, ld);
+      bool crosses = false;
 #pragma unroll
       for (int u = 0; u < NU; ++u)
 #pragma unroll
-        for (int c = 0; c < XW; ++c)
+        for (int e = 0; e < (KS ? 4 : 1); ++e) {
+          const uint32_t o = off[u] + (uint32_t)e * (uint32_t)ld * 4u;
+          crosses = crosses || (o < end && o + (KS ? XW : 4) * 4 > end);
+        }
+      if (__ballot(crosses)) {
+        const rsrc_t rs = make_rsrc(base + (int64_t)k0 * (KS ? ld : 1) * 4, end);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int at = min(k0 + k + e, K - 1);
-            const float x = KS ? p[u][(int64_t)at * ld + (c ? dx[u][c ? c - 1 : 0] : 0)] : p[u][at];
-            v[u * XW + c][e] = k0 + k + e < K ? x : 0.f;
-          }
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+          for (int c = 0; c < XW; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              v[u * XW + c][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(off[u] + (KS ? (uint32_t)e * (uint32_t)ld + c : e) * 4u), 0, 0));
+      }
+    }
+    if (!KS) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = k0 + k + e < K ? v[u][e] : 0.f;
     }
   }
   template <bool NEG>   // negated (a modifier of the split's instructions)
@@ -361,9 +405,9 @@ struct Share {
 };
 
 // The feeding wavefronts' work: a step per barrier into the buffer that the multiplying ones have left; loads U steps ahead.
-// fetch(step, quads) and put(step, quads): all of the wavefront's quads of a step.
-template <int Q, class Fetch, class Put>
-__device__ __forceinline__ void feed(int steps, Fetch fetch, Put put) {
+// fetch(step, quads) and put(step, quads): all of the wavefront's quads of a step; finish(step, quads) before it in the last two.
+template <int Q, class Fetch, class Finish, class Put>
+__device__ __forceinline__ void feed(int steps, Fetch fetch, Finish finish, Put put) {
   constexpr int U = Q > 6 ? 2 : Q > 4 ? 3 : Q > 3 ? 4 : 6;
   float raw[U][Q][4];
   auto load = [&](int s, int u) {   // past the last step the last one again
@@ -373,19 +417,22 @@ __device__ __forceinline__ void feed(int steps, Fetch fetch, Put put) {
 #pragma unroll
   for (int u = 0; u < U; ++u) load(u, u);
   int s = 0;
-  for (; s + U <= steps; s += U)
+  for (; s + U + 2 <= steps; s += U)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       put(s + u, raw[u]);
       load(s + u + U, u);
       __syncthreads();
     }
+  for (; s < steps; s += U)
 #pragma unroll
-  for (int u = 0; u < U - 1; ++u)   // the rest is on its way
-    if (s + u < steps) {
-      put(s + u, raw[u]);
-      __syncthreads();
-    }
+    for (int u = 0; u < U; ++u)
+      if (s + u < steps) {
+        finish(s + u, raw[u]);
+        put(s + u, raw[u]);
+        load(s + u + U, u);
+        __syncthreads();
+      }
 }
 
 // Tiles of TM x TN, eight wavefronts, a barrier per step.  The first four (a share of TM / 2 x TN / 2 each) only read fragments
@@ -393,7 +440,7 @@ __device__ __forceinline__ void feed(int steps, Fetch fetch, Put put) {
 // SIMD holds one of either, and beside the matrix instructions of one wavefront (16 cycles each) another can issue 2.5
 // others, where one that does both gets 1.5 for nothing.
 // wg of n_wgs: the workgroup's number among those of the product
-template <int OP, int EPI, int TM, int TN, bool VEC>
+template <int OP, int EPI, int TM, int TN, int ACC>
 __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
   constexpr bool AS = OP == 2, BS = OP != 0;
   // SwiGLU in 32-tiles: a wavefront holds 16 gate columns and the 16 up columns, so the tile of B has 64 rows
@@ -424,40 +471,40 @@ __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
       if (s & kRun) a.template put<true>(buf(s), v);
       else a.template put<false>(buf(s), v);
     };
+    auto put_b = [&](const auto& b, int s, float (*v)[4]) { b.template put<false>(buf(s) + Planes<TM>::kBytes, v); };
     // Tiles of the same size: two wavefronts for each operand (wider loads); else all four for both.
-    auto bring = [&](auto mask) {
-      constexpr bool MASK = decltype(mask)::value;
-      if constexpr (TM == TB) {
-        if (wave < 6) {
-          Share<AS, TM, 2, VEC> a;
-          a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
-          feed<a.Q>(steps, [&](int s, float (*v)[4]) { a.template load<MASK>(v, s * BK, K, lda); }, [&](int s, float (*v)[4]) { put_a(a, s, v); });
-        } else {
-          Share<BS, TB, 2, VEC> b;
-          b.init(g.B, ldb, b0, g.N, K, wave - 6, lane, b_row);
-          feed<b.Q>(steps, [&](int s, float (*v)[4]) { b.template load<MASK>(v, s * BK, K, ldb); },
-                    [&](int s, float (*v)[4]) { b.template put<false>(buf(s) + Planes<TM>::kBytes, v); });
-        }
-      } else {
-        Share<AS, TM, 4, VEC> a;
-        Share<BS, TB, 4, VEC> b;
+    if constexpr (TM == TB) {
+      if (wave < 6) {
+        Share<AS, TM, 2, ACC> a;
         a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
-        b.init(g.B, ldb, b0, g.N, K, wave - 4, lane, b_row);
-        feed<a.Q + b.Q>(
-            steps,
-            [&](int s, float (*v)[4]) {
-              a.template load<MASK>(v, s * BK, K, lda);
-              b.template load<MASK>(v + a.Q, s * BK, K, ldb);
-            },
-            [&](int s, float (*v)[4]) {
-              put_a(a, s, v);
-              b.template put<false>(buf(s) + Planes<TM>::kBytes, v + a.Q);
-            });
+        feed<a.Q>(steps, [&](int s, float (*v)[4]) { a.load(v, s * BK, K, lda); }, [&](int s, float (*v)[4]) { a.finish(v, s * BK, K, lda); },
+                  [&](int s, float (*v)[4]) { put_a(a, s, v); });
+      } else {
+        Share<BS, TB, 2, ACC> b;
+        b.init(g.B, ldb, b0, g.N, K, wave - 6, lane, b_row);
+        feed<b.Q>(steps, [&](int s, float (*v)[4]) { b.load(v, s * BK, K, ldb); }, [&](int s, float (*v)[4]) { b.finish(v, s * BK, K, ldb); },
+                  [&](int s, float (*v)[4]) { put_b(b, s, v); });
       }
-    };
-    constexpr bool masks = VEC && !(AS && BS);   // what a k-strided operand's end leaves, and single elements, are zeros anyway
-    if (masks && K % BK) bring(std::integral_constant<bool, masks>());
-    else bring(std::false_type());
+    } else {
+      Share<AS, TM, 4, ACC> a;
+      Share<BS, TB, 4, ACC> b;
+      a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
+      b.init(g.B, ldb, b0, g.N, K, wave - 4, lane, b_row);
+      feed<a.Q + b.Q>(
+          steps,
+          [&](int s, float (*v)[4]) {
+            a.load(v, s * BK, K, lda);
+            b.load(v + a.Q, s * BK, K, ldb);
+          },
+          [&](int s, float (*v)[4]) {
+            a.finish(v, s * BK, K, lda);
+            b.finish(v + a.Q, s * BK, K, ldb);
+          },
+          [&](int s, float (*v)[4]) {
+            put_a(a, s, v);
+            put_b(b, s, v + a.Q);
+          });
+    }
     return;
   }
   const int wm = wave >> 1, wn = wave & 1, base_a = wm * WM, base_b = wn * WN * NSEG;
@@ -538,7 +585,7 @@ __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
       for (int j = 0; j < NA; ++j) add_up(j, (steps - 1) & kRun ? -1.f : 1.f);
     else if (NA > 1) add_up(NA - 1, (steps - 1) & kRun ? -1.f : 1.f);
   }
-  mend<OP, VEC>(g, sum, [&](int j) { return min(m0 + base_a + j * 16 + lr, g.M - 1); },
+  mend<OP, ACC == kAligned>(g, sum, [&](int j) { return min(m0 + base_a + j * 16 + lr, g.M - 1); },
                 [&](int i) { return BS ? min(n0 + base_b + i * 16 + lr, g.N - 1) : b_row(base_b + i * 16 + lr); }, kg);
   if (OP == 2) {
 #pragma unroll
@@ -561,10 +608,10 @@ __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
     if (EPI == kEpiSwiglu) {
       const int f0 = b0 + wn * (NSEG == 2 ? 16 : WN / 2);   // the share's first feature
 #pragma unroll
-      for (int i = 0; i < NB / 2; ++i) emit_swiglu<VEC>(g, m, f0 + i * 16 + kg * 4, sum[j][i], sum[j][i + NB / 2]);
+      for (int i = 0; i < NB / 2; ++i) emit_swiglu<ACC == kAligned>(g, m, f0 + i * 16 + kg * 4, sum[j][i], sum[j][i + NB / 2]);
     } else {
 #pragma unroll
-      for (int i = 0; i < NB; ++i) emit<OP, EPI, VEC>(g, m, n0 + base_b + i * 16 + kg * 4, sum[j][i]);
+      for (int i = 0; i < NB; ++i) emit<OP, EPI, ACC == kAligned>(g, m, n0 + base_b + i * 16 + kg * 4, sum[j][i]);
     }
   }
 }
@@ -580,12 +627,12 @@ __device__ __forceinline__ void exchange() {
 // features), eight wavefronts that each form whole runs of 64 k, in turn, from loads and splits of their own (no barrier:
 // exchange() above), the next run's loads on their way.  After every eight runs the first
 // wavefront adds them up in order, so that entries have the bits that the other tiles give them.
-template <int OP, int EPI, bool VEC>
+template <int OP, int EPI, int ACC>
 __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
   constexpr bool AS = OP == 2, BS = OP != 0;
   constexpr int NB = EPI == kEpiSwiglu ? 2 : 1, NW = kThreads / 64;
-  typedef Share<AS, 16, 1, VEC> SA;
-  typedef Share<BS, 16, 1, VEC> SB;
+  typedef Share<AS, 16, 1, ACC> SA;
+  typedef Share<BS, 16, 1, ACC> SB;
   constexpr int kTile = Planes<16>::kBytes;
   __shared__ __attribute__((aligned(16))) char tiles[NW][(1 + NB) * kTile];
   __shared__ __attribute__((aligned(16))) f32x4 found[2][NW][NB][64];
@@ -608,22 +655,29 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
     float ra[kRun][SA::Q][4], rb[kRun][NB][SB::Q][4];
     char* const mine = tiles[wave];
     const int at = Planes<16>::at(lr, kg);
-    auto form = [&](auto mask) {
-      constexpr bool MASK = decltype(mask)::value;
-      auto load = [&](int run) {   // past the end: the last step again
+    auto load = [&](int run) {   // past the end: the last step again
 #pragma unroll
-        for (int e = 0; e < kRun; ++e) {
-          const int k0 = min(run * kRun + e, steps - 1) * BK;
-          a.template load<MASK>(ra[e], k0, K, lda);
+      for (int e = 0; e < kRun; ++e) {
+        const int k0 = min(run * kRun + e, steps - 1) * BK;
+        a.load(ra[e], k0, K, lda);
 #pragma unroll
-          for (int i = 0; i < NB; ++i) b[i].template load<MASK>(rb[e][i], k0, K, ldb);
-        }
-      };
+        for (int i = 0; i < NB; ++i) b[i].load(rb[e][i], k0, K, ldb);
+      }
+    };
+    auto form = [&](auto ends) {   // ends: the last step has something to finish (a branch for it takes 1.07 x)
       load(wave);
       for (int r0 = 0, par = 0; r0 < runs; r0 += NW, par ^= 1) {
         const int run = r0 + wave;
         if (run < runs) {
           f32x4 acc[NB];
+          if (decltype(ends)::value && a.unfinished((run + 1) * kRun * BK - BK, K))
+#pragma unroll
+            for (int e = 0; e < kRun; ++e)
+              if (run * kRun + e < steps) {
+                a.finish(ra[e], (run * kRun + e) * BK, K, lda);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) b[i].finish(rb[e][i], (run * kRun + e) * BK, K, ldb);
+              }
 #pragma unroll
           for (int e = 0; e < kRun; ++e) {
             if (run * kRun + e < steps) {
@@ -667,13 +721,12 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
         }
       }
     };
-    constexpr bool masks = VEC && !(AS && BS);
-    if (masks && K % BK) form(std::integral_constant<bool, masks>());
+    if (a.unfinished((steps - 1) * BK, K)) form(std::true_type());
     else form(std::false_type());
   }
   if (wave) return;
   static_assert(NW % 2 == 0, "a wavefront's runs are all odd or all even");
-  mend<OP, VEC>(g, sums, [&](int) { return min(m0 + lr, g.M - 1); }, [&](int i) { return i * cols + min(n0 + lr, cols - 1); }, kg);
+  mend<OP, ACC == kAligned>(g, sums, [&](int) { return min(m0 + lr, g.M - 1); }, [&](int i) { return i * cols + min(n0 + lr, cols - 1); }, kg);
   if (OP == 2) {
     const int n = n0 + lr;
 #pragma unroll
@@ -685,30 +738,29 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
   }
   const int m = m0 + lr, n = n0 + kg * 4;
   if (m >= g.M) return;
-  if (EPI == kEpiSwiglu) emit_swiglu<VEC>(g, m, n, sum[0], sum[NB - 1]);
-  else emit<OP, EPI, VEC>(g, m, n, sum[0]);
+  if (EPI == kEpiSwiglu) emit_swiglu<ACC == kAligned>(g, m, n, sum[0], sum[NB - 1]);
+  else emit<OP, EPI, ACC == kAligned>(g, m, n, sum[0]);
 }
 
 // Wavefronts a SIMD: LDS holds one workgroup with tiles of 128, two with 128 x 64 (128 registers; with more, and one workgroup, op 2
 // 2048 x 3072 x 1024 takes 97 us for 80).
-template <int OP, int EPI, int TM, int TN, bool VEC>
-__global__ __launch_bounds__(kThreads, TM * TN > (VEC ? 128 : 64) * 64 ? 2 : 4) void k_gemm_f32(Args g) { gemm_tile<OP, EPI, TM, TN, VEC>(g, blockIdx.x, gridDim.x); }
-template <int OP, int EPI, bool VEC>
-__global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) { gemm_few<OP, EPI, VEC>(g, blockIdx.x, gridDim.x); }
+template <int OP, int EPI, int TM, int TN, int ACC>
+__global__ __launch_bounds__(kThreads, TM * TN > 128 * 64 ? 2 : 4) void k_gemm_f32(Args g) { gemm_tile<OP, EPI, TM, TN, ACC>(g, blockIdx.x, gridDim.x); }
+template <int OP, int EPI, int ACC>
+__global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) { gemm_few<OP, EPI, ACC>(g, blockIdx.x, gridDim.x); }
 
 // the weight gradients of a layer in one launch, all in tiles of one size
-template <int TM, int TN, bool VEC>
-__global__ __launch_bounds__(kThreads, TM * TN > (VEC ? 128 : 64) * 64 || TN == 16 ? 2 : 4) void k_gemm_f32_grads(GradGroup l) {
+template <int TM, int TN, int ACC>
+__global__ __launch_bounds__(kThreads, TM * TN > 128 * 64 || TN == 16 ? 2 : 4) void k_gemm_f32_grads(GradGroup l) {
   int i = 0;
   while (i + 1 < kGrads && (int)blockIdx.x >= l.first[i + 1]) ++i;
   const int wg = (int)blockIdx.x - l.first[i], n = l.first[i + 1] - l.first[i];
   const Args g{(const float*)l.A[i], (const float*)l.B[i], nullptr, l.C[i], nullptr, l.M[i], l.N[i], l.K, l.tm[i], l.tn[i], RopeArgs{nullptr, 1, 2, 0}};
-  if constexpr (TN == 16) gemm_few<2, kEpiPlain, VEC>(g, wg, n);
-  else gemm_tile<2, kEpiPlain, TM, TN, VEC>(g, wg, n);
+  if constexpr (TN == 16) gemm_few<2, kEpiPlain, ACC>(g, wg, n);
+  else gemm_tile<2, kEpiPlain, TM, TN, ACC>(g, wg, n);
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-constexpr int64_t kVecMax = 1 << 21;
 
 }  // namespace
 
@@ -732,24 +784,31 @@ static double f32_us(int t, int64_t tiles, int64_t K, int epi) {
   return step * ((double)steps + (t == 0 ? 4.8 : t == 3 ? 6.0 : 4.0));
 }
 struct F32Shape { int tile_m, tile_n, tm, tn; };
-static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi) {
+static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi, bool far) {   // far: tiles of 64 only
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
   F32Shape best{};
   double best_us = 0;
-  for (int t = 0; t < 5; ++t) {
+  for (int t = far ? 2 : 0; t < (far ? 3 : 5); ++t) {
     const int m = kEdges[t][0], n = kEdges[t][1], w = epi == kEpiSwiglu && t < 3 ? n / 2 : n;   // w: stored columns of one run
     const int64_t tm = (M + m - 1) / m, tn = (out + w - 1) / w;
     const double us = f32_us(t, tm * tn, K, epi);
-    if (t && us >= best_us) continue;
+    if (best.tm && us >= best_us) continue;
     best_us = us;
     best = {m, n, (int)tm, (int)tn};
   }
   return best;
 }
 
-GemmShape gemm_f32_shape(int64_t M, int64_t N, int64_t K, int epi) {
-  const F32Shape c = choose_f32(M, N, K, epi);
+GemmShape gemm_f32_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
+  const F32Shape c = choose_f32(M, N, K, epi, gemm_f32_far(op, M, N, K, epi));
   return {std::max(c.tile_n, 32), c.tm * c.tn, c.tm * c.tn};
+}
+
+// A tile of some operand reaches further than 31 bits: 127 rows of K, 31 rows of a k-strided one's width, all up rows from the gate
+// rows on.
+bool gemm_f32_far(int op, int64_t M, int64_t N, int64_t K, int epi) {
+  constexpr int64_t kRow = 1 << 22, kWidth = 1 << 24;
+  return op == 0 ? K > kRow || (epi == kEpiSwiglu && (N / 2 + 128) * K >= 1ll << 29) : op == 1 ? K > kRow || N > kWidth : M > kWidth || N > kWidth;
 }
 
 // epi as in gemm_mfma: 0 plain (R optional), 1 rotary, 2 SwiGLU (N = 2h, aux = act), 3 SwiGLU backward (N = h, R =
@@ -760,21 +819,26 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
          rope ? *rope : RopeArgs{nullptr, 1, 2, 0}};
   if (rope) epi = kEpiRope;
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
-  const bool vec = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0) &&
-                   std::max(std::max(M, N), K) <= kVecMax && (epi != kEpiSwiglu || (out + 128) * K < 1ll << 29);   // a tile's offsets fit 31 bits
-  const F32Shape c = choose_f32(M, N, K, epi);
+  const bool aligned = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0);
+  const bool far = gemm_f32_far(op, M, N, K, epi);
+  const F32Shape c = choose_f32(M, N, K, epi, far);
   g.tiles_m = c.tm;
   g.tiles_n = c.tn;
   const dim3 grid((unsigned)(c.tm * c.tn));
-#define SP_GO(OP, EPI, VEC)                                                                                             \
+#define SP_GO(OP, EPI, ACC)                                                                                             \
   do {                                                                                                                  \
-    if (c.tile_n == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 128, VEC>), grid, dim3(kThreads), 0, s, g);           \
-    else if (c.tile_m == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 64, VEC>), grid, dim3(kThreads), 0, s, g);       \
-    else if (c.tile_n == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, 64, VEC>), grid, dim3(kThreads), 0, s, g);         \
-    else if (c.tile_n == 32) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 32, 32, VEC>), grid, dim3(kThreads), 0, s, g);         \
-    else hipLaunchKernelGGL((k_gemm_f32_few<OP, EPI, VEC>), grid, dim3(kThreads), 0, s, g);                                 \
+    if (c.tile_n == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 128, ACC>), grid, dim3(kThreads), 0, s, g);           \
+    else if (c.tile_m == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 64, ACC>), grid, dim3(kThreads), 0, s, g);       \
+    else if (c.tile_n == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, 64, ACC>), grid, dim3(kThreads), 0, s, g);         \
+    else if (c.tile_n == 32) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 32, 32, ACC>), grid, dim3(kThreads), 0, s, g);         \
+    else hipLaunchKernelGGL((k_gemm_f32_few<OP, EPI, ACC>), grid, dim3(kThreads), 0, s, g);                                 \
   } while (0)
-#define SP_GO_V(OP, EPI) do { if (vec) SP_GO(OP, EPI, true); else SP_GO(OP, EPI, false); } while (0)
+#define SP_GO_V(OP, EPI)                                                                                                \
+  do {                                                                                                                  \
+    if (far) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, 64, kFar>), grid, dim3(kThreads), 0, s, g);                    \
+    else if (aligned) SP_GO(OP, EPI, kAligned);                                                                         \
+    else SP_GO(OP, EPI, kUnaligned);                                                                                    \
+  } while (0)
   if (op == 0 && epi == kEpiRope) SP_GO_V(0, kEpiRope);
   else if (op == 0 && epi == kEpiSwiglu) SP_GO_V(0, kEpiSwiglu);
   else if (op == 0) SP_GO_V(0, kEpiPlain);
@@ -788,9 +852,8 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
 // One tile for all of them; entries as in gemm_f32, bit for bit.
 void gemm_f32_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]) {
   GradGroup g{};
-  bool vec = K <= kVecMax;
-  for (const GradItem& i : items)
-    vec = vec && al16(i.A) && al16(i.B) && al16(i.C) && i.M % 4 == 0 && i.N % 4 == 0 && std::max(i.M, i.N) <= kVecMax;
+  bool aligned = true;
+  for (const GradItem& i : items) aligned = aligned && al16(i.A) && al16(i.B) && al16(i.C) && i.M % 4 == 0 && i.N % 4 == 0;
   int tile = 0;
   double best_us = 0;
   for (int t = 0; t < 5; ++t) {
@@ -813,8 +876,8 @@ void gemm_f32_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]) {
   const dim3 grid(g.first[kGrads]);
 #define SP_GO(TM, TN)                                                                                       \
   do {                                                                                                      \
-    if (vec) hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, true>), grid, dim3(kThreads), 0, s, g);           \
-    else hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, false>), grid, dim3(kThreads), 0, s, g);              \
+    if (aligned) hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, kAligned>), grid, dim3(kThreads), 0, s, g);   \
+    else hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, kUnaligned>), grid, dim3(kThreads), 0, s, g);         \
   } while (0)
   if (tile == 0) SP_GO(128, 128);
   else if (tile == 1) SP_GO(128, 64);

@@ -99,7 +99,7 @@ int gemm_grads(hipStream_t s, int dtype, int64_t K, const GradItem (&items)[kGra
   double work = 0;
   for (const GradItem& i : items) {
     if (i.M < 1 || i.N < 1 || !i.A || !i.B || !i.C) return fail(SP_EINVAL, "gemm_grads: bad item");
-    together = together && (dtype == SP_F32 || gemm_mfma_supported(2, i.M, i.N, K, i.A, i.B, i.C, nullptr));
+    together = together && (dtype == SP_F32 ? !gemm_f32_far(2, i.M, i.N, K, 0) : gemm_mfma_supported(2, i.M, i.N, K, i.A, i.B, i.C, nullptr));
     work += 2.0 * (double)i.M * (double)i.N * (double)K;
   }
   if (!together) {

@@ -290,22 +290,88 @@ def test_float_products_formed_anew_lose_no_more_than_others(M, N, K):
         assert err < 3.6e-8 * np.sqrt(16 + K / 64), (op, err)
 
 
+def least_ms(*works):
+    """The least of six timings of each."""
+    best = []
+    for work in works:
+        took = []
+        for _ in range(6):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            work()
+            t[1].record()
+            torch.cuda.synchronize()
+            took.append(t[0].elapsed_time(t[1]))
+        best.append(min(took))
+    return best
+
+
 @pytest.mark.parametrize("op", [0, 1, 2])
 def test_float_products_of_nan_take_little_longer_than_others(op):
     # a pass that has diverged is NaN throughout: such entries are settled by the first run of k, at a few per cent of a product
     # (1.1 to 1.3 times the time of a finite one; 12 to 18 times when every entry took the whole reduction); four leaves room
     M, N, K = 4096, 1024, 2816
     a = dev(synth.normal(77, "na", (M, K) if op < 2 else (K, M))); b = dev(synth.normal(78, "nb", (N, K) if op == 0 else (K, N)))
-    c = torch.zeros((M, N), device="cuda")
-    best = []
-    for x in (a, torch.full_like(a, float("nan"))):
-        took = []
-        for _ in range(6):
-            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            t[0].record()
-            sp.gemm(op, x, b, c)
-            t[1].record()
-            torch.cuda.synchronize()
-            took.append(t[0].elapsed_time(t[1]))
-        best.append(min(took))
+    c = torch.zeros((M, N), device="cuda"); nan = torch.full_like(a, float("nan"))
+    best = least_ms(lambda: sp.gemm(op, a, b, c), lambda: sp.gemm(op, nan, b, c))
     assert torch.isnan(c).all() and best[1] < 4 * best[0], best
+
+
+# strided widths of one to five columns (a load of four reaches past the row), reductions that end with, before and after a step,
+# in tiles of 16 and larger; pointers off by 4, 8 and 12 bytes; rows so long that a tile of theirs passes 31 bits
+@pytest.mark.parametrize("M,N,K,off", [(20000, 1, 64, 0), (20000, 2, 65, 1), (3, 9000, 96, 2), (5000, 5, 33, 3), (1, 2, 99, 1), (1030, 513, 64, 1),
+                                       (2048, 1026, 160, 2), (2049, 2050, 97, 3), (9, 130, 224, 1), (2, 3, (1 << 22) + 5, 0)])
+def test_float_products_at_any_alignment(M, N, K, off):
+    a = synth.normal(79, f"ga{M}{N}", (M, K)); b = synth.normal(80, f"gb{M}{N}", (N, K)); r = synth.normal(81, f"gr{M}{N}", (M, N))
+    guard = 64
+
+    def put(x):   # `off` floats into its buffer, with NaN on both sides
+        buf = torch.full((x.size + off + guard,), float("nan"), device="cuda")
+        buf[off:off + x.size] = dev(x).view(-1)
+        return buf[off:off + x.size].view(*x.shape)
+    want = a.astype(np.float64) @ b.astype(np.float64).T
+    for op, ref in ((0, want + r), (1, want), (2, want + r)):
+        if op == 2 and K > 1 << 22:
+            continue
+        c = put(r)
+        if op == 0:
+            sp.gemm(0, put(a), put(b), c, put(r))
+        else:
+            sp.gemm(op, put(a if op == 1 else np.ascontiguousarray(a.T)), put(np.ascontiguousarray(b.T)), c)
+        got = c.cpu().numpy()
+        assert relerr(got, ref) < 2e-5 and maxerr(got, ref) < 2e-5, (op, relerr(got, ref), maxerr(got, ref))
+
+
+def test_float_products_of_far_operands():
+    # k-strided widths past 2^24: no buffer load reaches the tile's last rows
+    torch.manual_seed(82)
+    W = (1 << 24) + 3
+    a = torch.randn(W, 33, device="cuda"); b = torch.randn(2, 33, device="cuda")
+    want = a @ b.t()
+    at = a.t().contiguous()
+    c = torch.zeros((W, 2), device="cuda")
+    sp.gemm(2, at, b.t().contiguous(), c)
+    assert float((c - want).norm() / want.norm()) < 1e-5
+    c = torch.zeros((2, W), device="cuda")
+    sp.gemm(1, b, at, c)
+    assert float((c.t() - want).norm() / want.norm()) < 1e-5
+    h, d, R = 2, (1 << 22) + 8, 3       # a SwiGLU tile
+    hn = torch.randn(R, d, device="cuda"); w = torch.randn(2 * h, d, device="cuda") / d ** 0.5
+    gu, act = torch.empty(R, 2 * h, device="cuda"), torch.empty(R, h, device="cuda")
+    sp.ffn_up_fwd(hn, w, gu, act)
+    ref = (hn.double() @ w.double().t())
+    lim = 3.6e-8 * (16 + d / 64) ** 0.5   # as in test_float_products_lose_little_over_long_reductions: 9.2e-6
+    assert float((gu - ref).norm() / ref.norm()) < lim
+    # two factors, and silu at most doubles the relative error of values of order one
+    assert float((act - torch.nn.functional.silu(ref[:, :h]) * ref[:, h:]).norm() / act.norm()) < 4 * lim
+
+
+def test_float_weight_gradients_of_odd_widths_take_no_longer_than_of_even_ones():
+    # 999 columns leave rows unaligned: 5.4 times the time of 1024 when they were loaded one by one, 1.0 times now
+    K, N = 5632, 1024
+    works = []
+    for M in (1024, 999):
+        a, b, c = torch.randn(K, M, device="cuda"), torch.randn(K, N, device="cuda"), torch.zeros(M, N, device="cuda")
+        works.append(lambda a=a, b=b, c=c: sp.gemm(2, a, b, c))
+    even, odd = least_ms(*works)
+    assert odd < 2 * even, (odd, even)
