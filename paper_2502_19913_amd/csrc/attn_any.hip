@@ -15,9 +15,9 @@
 // 32-cycle instruction leaves LDS idle most of the time; what bounds a workgroup is the chain of its tiles.  In bf16 the
 // matrix instructions are a fifth of that and vector instructions bound it (four wavefronts a SIMD, 285 a tile and wavefront of
 // the forward kernel before, 190 now): tiles lie in LDS as stored, the transposed operand comes by the LDS transpose read,
-// exponentials take half of expf's instructions, masks only stand where some key is hidden.  Heads of 48, forward | backward
-// us, float instruction and float tiles -> this: 3 x 333 positions x 6 heads 17 | 43 -> 10 | 25, 16 x 256 x 6 22 | 53 -> 13 |
-// 31, 8 x 1024 x 16 263 | 646 -> 109 | 289; the 50M shape on 3 x 333 tokens 3.60 -> 2.96 ms a pass.  (Float, of the same
+// exponentials take two thirds of expf's instructions, masks only stand where some key is hidden.  Heads of 48, forward | backward
+// us, float instruction and float tiles -> this: 3 x 333 positions x 6 heads 17 | 43 -> 10 | 25, 16 x 256 x 6 22 | 53 -> 12 |
+// 31, 8 x 1024 x 16 263 | 646 -> 106 | 287; the 50M shape on 3 x 333 tokens 3.60 -> 2.96 ms a pass.  (Float, of the same
 // exponentials and masks: 8 x 1024 x 16 heads of 48 312 | 891 -> 284 | 856.)  HD is the head dimension rounded up to a compiled
 // size; columns past the real one are zeros.  One wavefront per row of
 // scores (the kernels these replaced) left the matrix cores idle and re-read K and V for every query.  Measured,
@@ -54,12 +54,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 __device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-// exp(x) for x at most a few units above zero: x log2(e) in two parts, the second (the first's rounding and the constant's) at
-// first order, so that large arguments lose nothing; half the instructions of expf, which also looks after overflow.
+// exp(x): 2^n times 2^f of x log2(e), f formed from two parts of the constant; two thirds of expf's instructions (which also looks after
+// overflow), and as that one the subnormal results, which the instruction alone returns as zero.  n ends at -200, where nothing is
+// left of a float, so that f is a number for all x but infinities, and -inf for -inf.
 __device__ __forceinline__ float exp_(float x) {
-  constexpr float kL = 1.44269502f, kLl = 1.92596299e-8f, kLn2 = 0.693147182f;   // log2(e) and what is left of it; ln 2
-  const float hi = x * kL, lo = __builtin_fmaf(x, kLl, __builtin_fmaf(x, kL, -hi)), e = __builtin_amdgcn_exp2f(hi);
-  return hi > -__FLT_MAX__ ? __builtin_fmaf(e, lo * kLn2, e) : e;   // at -inf there is no second part
+  constexpr float kL = 1.44269502f, kLl = 1.92596299e-8f;   // log2(e) and what is left of it
+  const float n = fmaxf(rintf(x * kL), -200.f), f = __builtin_fmaf(x, kLl, __builtin_fmaf(x, kL, -n));
+  return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
 
 // What differs between the two storage types.  Quad: four values of a row as they travel and lie in LDS (LD values a row).
@@ -69,7 +70,7 @@ __device__ __forceinline__ float exp_(float x) {
 //           group kg holds those of rows 4 kg .. 4 kg + 3 of either half (p0, p1).
 // Probabilities and score gradients are floats in either type.  bf16 storage takes the bf16 instruction for both: stored
 // operands are used as they are, their products are exact and the sums float, and a probability is the sum of three
-// bfloat16s, exactly: three instructions over 32 rows (48 cycles) instead of eight float ones (256).
+// bfloat16s, exactly (one below 2^-110 to 2^-134): three instructions over 32 rows (48 cycles) instead of eight float ones (256).
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 template <class T> struct Stored {

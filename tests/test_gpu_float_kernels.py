@@ -375,3 +375,34 @@ def test_float_weight_gradients_of_odd_widths_take_no_longer_than_of_even_ones()
         works.append(lambda a=a, b=b, c=c: sp.gemm(2, a, b, c))
     even, odd = least_ms(*works)
     assert odd < 2 * even, (odd, even)
+
+
+@pytest.mark.parametrize("late", [True, False])
+@pytest.mark.parametrize("dtype,hd", [("f32", 16), ("f32", 48), ("f32", 80), ("f32", 128), ("bf16", 16), ("bf16", 48), ("bf16", 80)])
+def test_attention_weights_below_the_smallest_normal_float(dtype, hd, late):
+    """Weights of e^-90 that meet values of 1e30.  late: the largest score (key 70) is met after sums have been formed, which are
+    scaled down by as much.  Scores carry 90 * 2^-24 times a few, a float weight at most 2^-150 of 2^-130: 1e-4 leaves a factor of
+    three.  In bf16 a weight is multiplied to 2^-134 (1/16 of this one), and results round to 2^-9."""
+    T, top = 100, 70 if late else 0
+    rnd = round_bf16 if dtype == "bf16" else (lambda a: a.astype(np.float32))
+    q, k, v, do = (np.zeros((T, hd)) for _ in range(4))
+    q[:, 0] = 20
+    k[:, 0] = -4.5 * np.sqrt(hd); k[top] = 0
+    v[1, 2] = 1e30                                  # forward: a row that sees key `top` has e^-90 of this
+    qkv = rnd(np.concatenate([q, k, v], 1))
+    tol = 1e-4 if dtype == "f32" else 1 / 16 + 2.0 ** -8
+    close = lambda x, want: np.all(np.abs(x - want) <= tol * np.abs(want))
+    parts = lambda: [np.ascontiguousarray(qkv[:, i * hd:(i + 1) * hd]).reshape(T, 1, hd).astype(np.float64) for i in range(3)]
+    want = orc.attention_fwd(*parts(), 1, T).reshape(T, hd)
+    assert 0 < want[80, 2] < 1e-8
+    got, _ = attention(qkv, np.zeros((T, hd)), dtype, 1, T, 1, 1, hd)
+    assert close(got, want), (got[[1, 69, 70, 99], 2], want[[1, 69, 70, 99], 2])
+    v[:] = 0; v[:, 3] = 1; v[top] = 0
+    qkv = rnd(np.concatenate([q, k, v], 1))
+    do[80, 3] = 1e30
+    do = rnd(do)
+    grads = orc.attention_bwd(do.reshape(T, 1, hd).astype(np.float64), *parts(), 1, T)
+    want = np.concatenate([g.reshape(T, hd) for g in grads], 1)
+    assert 0 < abs(want[5, 2 * hd + 3]) < 1e-8 and 0 < abs(want[5, hd]) < 1e-8 and 0 < abs(want[80, 0]) < 1e-5
+    got = attention(qkv, do, dtype, 1, T, 1, 1, hd)[1].reshape(T, -1)
+    assert close(got, want), [(got[at], want[at]) for at in ((5, 2 * hd + 3), (5, hd), (80, 0))]
