@@ -265,8 +265,8 @@ int sp_gemm(void* hip_stream, int dtype, int op, int M, int N, int K, const void
 
 /* Measurement aid (host only): how a product of 16-byte aligned operands is divided on the current device.  epilogue: 0
  * none, 1 rotation, 2 SwiGLU (op 0 with N = 2h), 3 SwiGLU gradient (op 1 with N = h).  shape (host int32[3]): edge of the
- * tiles (of 128 x 64 the shorter, 32 also for tiles of 16; 0: the plain kernel), their number, workgroups (fewer than tiles: each takes several in turn; op 2 more:
- * runs of the reduction). */
+ * tiles (of 128 x 64 the shorter; 0: the plain kernel), their number, workgroups (fewer than tiles: each takes several in turn;
+ * op 2 more: runs of the reduction). */
 int sp_gemm_shape(int dtype, int op, int M, int N, int K, int epilogue, int32_t* shape);
 
 /* The two feed-forward steps whose pointwise part rides in a matrix product's epilogue (the SwiGLU block of the

@@ -31,7 +31,6 @@
 // Every entry is summed in one order (runs of 64 k), with the same instructions, whatever the tile: that follows the
 // number of rows, and a microbatch's rows must not depend on how many microbatches share its group; a weight gradient is
 // added with one atomic per entry and launch, so that it repeats to the bit.
-#include <algorithm>
 #include <type_traits>
 
 #include "devutil.h"
@@ -801,7 +800,7 @@ static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi, bool far) {
 
 GemmShape gemm_f32_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
   const F32Shape c = choose_f32(M, N, K, epi, gemm_f32_far(op, M, N, K, epi));
-  return {std::max(c.tile_n, 32), c.tm * c.tn, c.tm * c.tn};
+  return {c.tile_n, c.tm * c.tn, c.tm * c.tn};
 }
 
 // A tile of some operand reaches further than 31 bits: 127 rows of K, 31 rows of a k-strided one's width, all up rows from the gate

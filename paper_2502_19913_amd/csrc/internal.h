@@ -119,7 +119,7 @@ int cu_count();   // compute units of the current device
 struct GemmShape { int tile, tiles, workgroups; };
 GemmShape gemm_mfma_shape(int op, int64_t M, int64_t N, int64_t K, int epi);
 bool gemm_f32_far(int op, int64_t M, int64_t N, int64_t K, int epi);   // not for gemm_f32_grads
-GemmShape gemm_f32_shape(int op, int64_t M, int64_t N, int64_t K, int epi);   // 128 x 64 counts as 64, 16 as 32
+GemmShape gemm_f32_shape(int op, int64_t M, int64_t N, int64_t K, int epi);   // of 128 x 64 the shorter edge
 // building blocks the dispatchers choose between
 void gemm_simple(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C, const void* R);
 // float, any shape; rope / epi / aux as for gemm_mfma

@@ -17,15 +17,16 @@ def dev(a):
 
 # A float sum of K products of unit normals carries a relative rounding error of about sqrt(K) 2^-24 or less: 2e-6 at
 # K = 1100.  The bounds allow ten times that over the tensor, and over the largest entry.
-PRODUCTS = [  # M, N, K: 32-tiles and one entry; remainders in every dimension that are no multiple of 4 (element-wise
-    # access); 64-tiles; a reduction of one step, of one group past a step, and of many
+PRODUCTS = [  # M, N, K: 16-tiles and one entry; remainders in every dimension that are no multiple of 4 (unaligned
+    # access); 64- and 128 x 64-tiles; a reduction of one step, of one group past a step, and of many
     (1, 1, 1), (33, 31, 17), (70, 50, 35), (130, 66, 300), (1100, 515, 33), (1030, 1100, 515), (2048, 2052, 36),
     (2049, 2047, 65), (516, 260, 1100), (36, 68, 4100),
 ]
-# 128-tiles (the last two: of op 2 as well), with and without remainders that are no multiple of 4; 64-tiles of op 2; the
-# small kernel one step short of, at and past its eight steps in flight.  tests/test_host.py checks this against the dispatch.
+# 128-tiles, with and without remainders that are no multiple of 4; 16-tiles of reductions that end around a step; 32-tiles of one step
+# and a part, of a run and a part, and of many, and aligned 64-tiles.  tests/test_host.py checks this against the dispatch.
 PRODUCTS += [(2048, 2048, 36), (2183, 1351, 33), (2047, 2045, 67), (4096, 2048, 36), (4095, 2047, 33),
-             (40, 36, 224), (40, 36, 256), (39, 35, 287), (40, 36, 292), (40, 36, 321)]
+             (40, 36, 224), (40, 36, 256), (39, 35, 287), (40, 36, 292), (40, 36, 321),
+             (516, 772, 36), (515, 771, 35), (600, 700, 100), (513, 770, 97), (512, 768, 292), (1100, 516, 36)]
 
 
 @pytest.mark.parametrize("M,N,K", PRODUCTS)
@@ -237,8 +238,7 @@ def test_float_products_of_values_at_the_ends_of_the_range(M, N, K):
 def test_float_rows_have_the_bits_of_larger_tiles_in_tiles_of_16(N, K, few, rows):
     a = dev(synth.normal(68, f"qa{N}{K}", (rows, K))); b = dev(synth.normal(69, f"qb{N}{K}", (N, K))); r = dev(synth.normal(70, f"qr{N}{K}", (rows, N)))
     gu = dev(synth.normal(71, f"qg{N}{K}", (rows, 2 * N))); wgu = torch.cat([b, b.flip(0)]); bt = b.t().contiguous()
-    assert sp.gemm_shape(sp.SP_F32, 0, few, N, K)[1] == ((few + 15) // 16) * ((N + 15) // 16)   # tiles of 16
-    assert sp.gemm_shape(sp.SP_F32, 0, rows, N, K)[1] < ((rows + 15) // 16) * ((N + 15) // 16)
+    assert sp.gemm_shape(sp.SP_F32, 0, few, N, K)[0] == 16 and sp.gemm_shape(sp.SP_F32, 0, rows, N, K)[0] > 16
     out = []
     for n in (rows, few):
         empty = lambda w: torch.empty((n, w), device="cuda")

@@ -186,8 +186,16 @@ def test_the_product_tests_reach_every_tile():
         assert {1, 2, 4, 5, 17} <= {g[5] for g in got if g[:3] == (op, 0, 64)}
     for op in (0, 1):
         assert {3, 4, 5, 6} <= {g[5] for g in got if g[:3] == (op, 0, 128)}
-    f32 = {(op, sp.gemm_shape(sp.SP_F32, op, *c)[0], any(x % 4 for x in c)) for c in flt.PRODUCTS for op in (0, 1, 2)}
-    assert {(op, t, odd) for op in (0, 1, 2) for t in (32, 64, 128) for odd in (False, True)} <= f32, f32
-    ffn = {(op, sp.gemm_shape(sp.SP_F32, op, R, n * h, d, e)[0], h % 4 + d % 4 > 0) for R, h, d in ops.FFN_SHAPES for op, n, e in ((0, 2, 2), (1, 1, 3))}
-    assert {(op, t, odd) for op in (0, 1) for t in (32, 64, 128) for odd in (False, True)} <= ffn, ffn
+
+    def float_tile(op, M, N, K, epi=0):   # rows, columns: 64 columns go with 128 rows or 64, which their number tells
+        n, count, _ = sp.gemm_shape(sp.SP_F32, op, M, N, K, epi)
+        across = -(-N // n) if epi != 2 else -(-(N // 2) // (n // 2 if n >= 64 else n))   # stored columns of gate, and as many of up
+        fits = [m for m in ((128, 64) if n == 64 else (n,)) if -(-M // m) * across == count]
+        assert len(fits) == 1, (op, M, N, K, epi, n, count)
+        return fits[0], n
+    edges = [(16, 16), (32, 32), (64, 64), (128, 64), (128, 128)]
+    f32 = {(op, float_tile(op, *c), any(x % 4 for x in c)) for c in flt.PRODUCTS for op in (0, 1, 2)}
+    assert {(op, t, odd) for op in (0, 1, 2) for t in edges for odd in (False, True)} <= f32, f32
+    ffn = {(op, float_tile(op, R, n * h, d, e), h % 4 + d % 4 > 0) for R, h, d in ops.FFN_SHAPES for op, n, e in ((0, 2, 2), (1, 1, 3))}
+    assert {(op, t, odd) for op in (0, 1) for t in edges for odd in (False, True)} <= ffn, ffn
     assert any(sp.gemm_shape(sp.SP_BF16, op, 65, 50, 36)[0] == 0 for op in (0, 1))
