@@ -50,8 +50,9 @@ constexpr int kThreads = 512;
 // length (4.2e-7 at K = 768, 1.0e-6 at 4096).  It takes one more set of accumulators.
 // The instruction rounds the sum of its products towards minus infinity, so that all entries are off in one direction (the mean
 // of the errors at K = 1536 is 3.5e-8 of an entry, four times what chance leaves; through a model's residual additions
-// such errors add up, not their squares).  So every second run is formed of the negated A, and subtracted.  Gradients of whole models against 64 bits, float instruction / this / this without the negation:
-// 50M widths, 2 x 256 tokens 6.3e-7 / 5.8e-7 / 9.0e-7, 500M widths, 2 x 128 tokens 8.3e-7 / 7.0e-7 / 12.4e-7.
+// such errors add up, not their squares).  So every second run is formed of the negated A, and subtracted.  Gradients of whole models
+// against 64 bits, float instruction / this / this without the negation: 50M widths, 2 x 256 tokens 6.3e-7 / 5.8e-7 / 9.0e-7, 500M
+// widths, 2 x 128 tokens 8.3e-7 / 7.0e-7 / 12.4e-7.
 constexpr int kRun = 64 / BK;   // steps
 enum { kEpiPlain = 0, kEpiRope = 1, kEpiSwiglu = 2, kEpiSwigluBwd = 3 };   // as in the bf16 kernels
 
@@ -171,8 +172,9 @@ __device__ __forceinline__ Split split4(float a, float b, float c, float d) {
 
 // An operand's tile of T rows (columns of a k-strided operand) x BK in LDS: three planes [T][BK] of parts, 64 bytes a row,
 // unpadded.  Row r lies at position r / 4 + (r % 4) T / 4 and its 16-byte chunks are permuted by r % 4, so that the 16 rows of
-// a fragment read, the 4 k x columns that half a wavefront of a k-strided operand writes, and the four rows of 32 k of half
-// a wavefront of the other kind each fall in all 64 banks.
+// a fragment read and the four rows of 32 k that half a wavefront writes of a k-contiguous operand each fall in all 64 banks (no
+// conflict is counted in op 0).  The 4 k x columns that it writes of a k-strided one do not: 4 conflict cycles a store of 512 bytes,
+// as many as it takes without them, are counted in ops 1 (B) and 2 (A and B).
 template <int T>
 struct Planes {
   static constexpr int kPlane = T * BK * 2, kBytes = 3 * kPlane;
@@ -766,9 +768,9 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // Tile and its grid for a product: the least of (steps + ends) x time of a step of the CU with the most tiles.  Times are fits
 // (us, op 0 to 2 within 5 %): a 128-tile 1.25; 128 x 64 0.78 alone on its CU, 0.72 each of several; a 64-tile 0.58 alone, 0.88
 // two, 0.44 each of more; a 32-tile 0.29, 0.36 two, 0.52 three, 0.18 each of more (SwiGLU, with its 64 rows of B, 1.6 x).
-// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps.  A 16-tile of k_gemm_f32_few: 0.17 a run and 0.45 (SwiGLU 1.85 x), 1 once.  A product is not cut along k over workgroups: their sums would be
-// added in the order in which they end, and neither would a microbatch's rows have the same bits alone and in a group, nor two
-// passes of the mode that gradients are checked in agree.  us by tile, 128 / 128 x 64 / 64 / 32: op 0 1024 x 1024 x 1024 39 /
+// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps.  A 16-tile of k_gemm_f32_few: 0.17 a run and 0.45 (SwiGLU 1.85 x),
+// 1 once.  A product is not cut along k over workgroups: their sums would be added in the order in which they end, and neither would a
+// microbatch's rows have the same bits alone and in a group, nor two passes of the mode that gradients are checked in agree.  us by tile, 128 / 128 x 64 / 64 / 32: op 0 1024 x 1024 x 1024 39 /
 // 29 / 22 / 28, 2048 x 1024 x 5632 188 / 143 / 157 / 236, 3072 x 1024 x 1024 42 / 46 / 46 / 66, 4096 x 768 x 288 17 / 18 / 17 / 23,
 // 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.  32 / 16: op 0
 // 128 x 288 x 1536 16.6 / below 7.5 (the launch), 512 x 288 x 1536 16.9 / 14.2, 1024 x 288 x 1536 21 / 22, 64 x 1024 x 5632 53 / 21,
