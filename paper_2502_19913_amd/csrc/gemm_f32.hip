@@ -768,31 +768,36 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // Tile and its grid for a product: the least of (steps + ends) x time of a step of the CU with the most tiles.  Times are fits
 // (us, op 0 to 2 within 5 %): a 128-tile 1.25; 128 x 64 0.78 alone on its CU, 0.72 each of several; a 64-tile 0.58 alone, 0.88
 // two, 0.44 each of more; a 32-tile 0.29, 0.36 two, 0.52 three, 0.18 each of more (SwiGLU, with its 64 rows of B, 1.6 x).
-// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps.  A 16-tile of k_gemm_f32_few: 0.17 a run and 0.45 (SwiGLU 1.85 x),
-// 1 once.  A product is not cut along k over workgroups: their sums would be added in the order in which they end, and neither would a
-// microbatch's rows have the same bits alone and in a group, nor two passes of the mode that gradients are checked in agree.  us by tile, 128 / 128 x 64 / 64 / 32: op 0 1024 x 1024 x 1024 39 /
-// 29 / 22 / 28, 2048 x 1024 x 5632 188 / 143 / 157 / 236, 3072 x 1024 x 1024 42 / 46 / 46 / 66, 4096 x 768 x 288 17 / 18 / 17 / 23,
+// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps; in op 2, whose large tiles have many atomics to themselves, as 6, 5, 4 and 6;
+// with the SwiGLU gradient, whose loads and arithmetic a large tile has alone on its CU, as 12, 8, 5 and 6.  A 16-tile of
+// k_gemm_f32_few: 0.17 a run (op 2, whose loads take 64 bytes of a row, 0.23) and 0.45 (SwiGLU 1.85 x), 1 once.  With one set for all,
+// op 2 828 x 152 x 3768 took 47 us in tiles of 16 (39 in tiles of 32), the gradient 3728 x 2352 over k = 48 41 us in 128 x 64 (33 in 64);
+// over 1500 sizes 119 choices differ, 0.75 to 1.06 times the time, the median 0.90.
+// A product is not cut along k over workgroups: their sums would be added in the order in which they end, and neither would a
+// microbatch's rows have the same bits alone and in a group, nor two passes of the mode that gradients are checked in agree.
+// us by tile, 128 / 128 x 64 / 64 / 32: op 0 1024 x 1024 x 1024 39 / 29 / 22 / 28, 2048 x 1024 x 5632 188 / 143 / 157 / 236, 3072 x 1024 x 1024 42 / 46 / 46 / 66, 4096 x 768 x 288 17 / 18 / 17 / 23,
 // 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.  32 / 16: op 0
 // 128 x 288 x 1536 16.6 / below 7.5 (the launch), 512 x 288 x 1536 16.9 / 14.2, 1024 x 288 x 1536 21 / 22, 64 x 1024 x 5632 53 / 21,
 // 512 x 768 x 288 7.7 / 8.9.
 constexpr int kEdges[5][2] = {{128, 128}, {128, 64}, {64, 64}, {32, 32}, {16, 16}};
-static double f32_us(int t, int64_t tiles, int64_t K, int epi) {
+static double f32_us(int op, int t, int64_t tiles, int64_t K, int epi) {
   const int64_t cus = cu_count(), steps = (K + BK - 1) / BK, load = (tiles + cus - 1) / cus;
   const double c = (double)load;
-  if (t == 4) return 1.0 + c * (0.17 * (double)((steps + kRun - 1) / kRun) + 0.45) * (epi == kEpiSwiglu ? 1.85 : 1.0);
+  if (t == 4) return 1.0 + c * ((op == 2 ? 0.23 : 0.17) * (double)((steps + kRun - 1) / kRun) + 0.45) * (epi == kEpiSwiglu ? 1.85 : 1.0);
   const double step = t == 0 ? 1.25 * c : t == 1 ? (load == 1 ? 0.78 : 0.72 * c) : t == 2 ? (load == 1 ? 0.58 : 0.44 * c)
                       : (load == 1 ? 0.29 : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
-  return step * ((double)steps + (t == 0 ? 4.8 : t == 3 ? 6.0 : 4.0));
+  constexpr double kEnds[3][4] = {{4.8, 4, 4, 6}, {6, 5, 4, 6}, {12, 8, 5, 6}};
+  return step * ((double)steps + kEnds[epi == kEpiSwigluBwd ? 2 : op == 2 ? 1 : 0][t]);
 }
 struct F32Shape { int tile_m, tile_n, tm, tn; };
-static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi, bool far) {   // far: tiles of 64 only
+static F32Shape choose_f32(int op, int64_t M, int64_t N, int64_t K, int epi, bool far) {   // far: tiles of 64 only
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
   F32Shape best{};
   double best_us = 0;
   for (int t = far ? 2 : 0; t < (far ? 3 : 5); ++t) {
     const int m = kEdges[t][0], n = kEdges[t][1], w = epi == kEpiSwiglu && t < 3 ? n / 2 : n;   // w: stored columns of one run
     const int64_t tm = (M + m - 1) / m, tn = (out + w - 1) / w;
-    const double us = f32_us(t, tm * tn, K, epi);
+    const double us = f32_us(op, t, tm * tn, K, epi);
     if (best.tm && us >= best_us) continue;
     best_us = us;
     best = {m, n, (int)tm, (int)tn};
@@ -801,7 +806,7 @@ static F32Shape choose_f32(int64_t M, int64_t N, int64_t K, int epi, bool far) {
 }
 
 GemmShape gemm_f32_shape(int op, int64_t M, int64_t N, int64_t K, int epi) {
-  const F32Shape c = choose_f32(M, N, K, epi, gemm_f32_far(op, M, N, K, epi));
+  const F32Shape c = choose_f32(op, M, N, K, epi, gemm_f32_far(op, M, N, K, epi));
   return {c.tile_n, c.tm * c.tn, c.tm * c.tn};
 }
 
@@ -822,7 +827,7 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
   const bool aligned = al16(A) && al16(B) && al16(C) && al16(R) && al16(aux) && out % 4 == 0 && (op == 2 ? M % 4 == 0 : K % 4 == 0);
   const bool far = gemm_f32_far(op, M, N, K, epi);
-  const F32Shape c = choose_f32(M, N, K, epi, far);
+  const F32Shape c = choose_f32(op, M, N, K, epi, far);
   g.tiles_m = c.tm;
   g.tiles_n = c.tn;
   const dim3 grid((unsigned)(c.tm * c.tn));
@@ -860,7 +865,7 @@ void gemm_f32_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]) {
   for (int t = 0; t < 5; ++t) {
     int64_t tiles = 0;
     for (const GradItem& i : items) tiles += ((i.M + kEdges[t][0] - 1) / kEdges[t][0]) * ((i.N + kEdges[t][1] - 1) / kEdges[t][1]);
-    const double us = f32_us(t, tiles, K, kEpiPlain);
+    const double us = f32_us(2, t, tiles, K, kEpiPlain);
     if (t && us >= best_us) continue;
     best_us = us;
     tile = t;

@@ -23,10 +23,10 @@ PRODUCTS = [  # M, N, K: 16-tiles and one entry; remainders in every dimension t
     (2049, 2047, 65), (516, 260, 1100), (36, 68, 4100),
 ]
 # 128-tiles, with and without remainders that are no multiple of 4; 16-tiles of reductions that end around a step; 32-tiles of one step
-# and a part, of a run and a part, and of many, and aligned 64-tiles.  tests/test_host.py checks this against the dispatch.
+# and a part, of a run and a part, and of many, at most two a compute unit and (the last two) more; aligned 64- and 128 x 64-tiles.  tests/test_host.py checks this against the dispatch.
 PRODUCTS += [(2048, 2048, 36), (2183, 1351, 33), (2047, 2045, 67), (4096, 2048, 36), (4095, 2047, 33),
              (40, 36, 224), (40, 36, 256), (39, 35, 287), (40, 36, 292), (40, 36, 321),
-             (516, 772, 36), (515, 771, 35), (600, 700, 100), (513, 770, 97), (512, 768, 292), (1100, 516, 36)]
+             (516, 772, 36), (515, 771, 35), (600, 700, 100), (513, 770, 97), (512, 768, 292), (1100, 516, 36), (1600, 768, 132), (772, 772, 520), (775, 773, 519)]
 
 
 @pytest.mark.parametrize("M,N,K", PRODUCTS)
@@ -206,7 +206,7 @@ def test_float_products_lose_little_over_long_reductions(op, M, N, K):
 
 
 # 64-tiles alone on their CUs and 128 x 64-tiles, one step and a run and a half; with and without remainders; the smallest
-@pytest.mark.parametrize("M,N,K", [(1024, 1024, 96), (1023, 1021, 97), (2048, 1024, 32), (2048, 1024, 96), (2047, 1023, 95), (5, 3, 2), (36, 32, 33)])
+@pytest.mark.parametrize("M,N,K", [(1024, 1024, 96), (1023, 1021, 97), (2048, 1024, 32), (2048, 1024, 96), (2047, 1023, 95), (5, 3, 2), (36, 32, 33), (1600, 768, 132)])
 def test_float_products_of_values_at_the_ends_of_the_range(M, N, K):
     # operands are split into bfloat16 parts: values that have none, that round past the largest one, and that are so
     # small that products vanish give what float products of them give, and reach no other row or column
@@ -255,7 +255,7 @@ def test_float_rows_have_the_bits_of_larger_tiles_in_tiles_of_16(N, K, few, rows
 
 
 # a last step that is not full (16-byte access, and not), in tiles of 16, 32, 64, 128 x 64 and 128
-@pytest.mark.parametrize("M,N,K", [(33, 40, 36), (512, 768, 292), (1100, 516, 36), (1100, 515, 35), (2048, 1024, 100), (2183, 1352, 36)])
+@pytest.mark.parametrize("M,N,K", [(33, 40, 36), (512, 768, 292), (1100, 516, 36), (1100, 515, 35), (2048, 1024, 100), (2183, 1352, 36), (2183, 1352, 260)])
 def test_float_rows_keep_their_bits_beside_rows_that_are_not_finite(M, N, K):
     # a row runs on into the next one past the end of k: nothing of that may reach it, not even the order of its sums
     a = dev(synth.normal(72, f"ka{M}{K}", (M, K))); b = dev(synth.normal(73, f"kb{N}{K}", (N, K)))

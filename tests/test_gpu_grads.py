@@ -23,8 +23,8 @@ class Item(C.Structure):   # GradItem
 @pytest.mark.parametrize("dtype,d,h,nq,rows,tile", [
     ("f32", 32, 64, 80, 33, (16, 16)), ("f32", 64, 128, 160, 320, (16, 16)), ("f32", 31, 67, 81, 99, (16, 16)),
     ("f32", 136, 272, 392, 100, (32, 32)), ("f32", 137, 271, 393, 65, (32, 32)), ("f32", 200, 600, 584, 200, (64, 64)),
-    ("f32", 201, 601, 583, 97, (64, 64)), ("f32", 264, 792, 776, 100, (128, 64)), ("f32", 263, 793, 775, 35, (128, 64)),
-    ("f32", 776, 1552, 2312, 72, (128, 128)), ("f32", 775, 1553, 2311, 33, (128, 128)),
+    ("f32", 201, 601, 583, 97, (64, 64)), ("f32", 264, 792, 776, 100, (128, 64)), ("f32", 263, 793, 775, 97, (128, 64)),
+    ("f32", 544, 1088, 1616, 132, (128, 128)), ("f32", 543, 1087, 1615, 65, (128, 128)),
     ("bf16", 32, 64, 80, 33, (64,)), ("bf16", 64, 128, 160, 1000, (64,)), ("bf16", 392, 1176, 1160, 200, (128,)),
     ("bf16", 264, 792, 776, 2000, (128,)), ("bf16", 520, 1560, 1544, 100, (256,)), ("bf16", 520, 1560, 1544, 4100, (256,)),
 ])

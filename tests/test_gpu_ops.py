@@ -116,6 +116,7 @@ FFN_SHAPES = [  # R, h, d: tiles of 256 (h % 128 == 0) and of 128 (h % 64 == 0),
     (4096, 2816, 1024), (300, 192, 72), (5000, 1152, 520), (77, 96, 40), (2560, 5632, 128), (3000, 5632, 200), (45, 50, 36),
     (1100, 515, 33), (2183, 1351, 33), (1543, 1003, 33), (2048, 2048, 36),   # float tiles of 64 and 128, remainders that are no multiple of 4
     (257, 515, 292), (257, 516, 292), (257, 515, 33), (257, 516, 36), (1000, 516, 36), (99, 101, 70),   # of 16, 32, 64 and 128 x 64
+    (2183, 1351, 257), (1223, 2443, 641), (772, 772, 520), (775, 773, 519),   # the gradient's of 128 x 64 and 128, with remainders, and more than 512 of 32
 ]
 
 
