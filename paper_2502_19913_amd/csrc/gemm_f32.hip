@@ -440,8 +440,14 @@ __device__ __forceinline__ void feed(int steps, Fetch fetch, Finish finish, Put 
 // and multiply, the others only bring the operands of the next step to LDS, split on the way, U steps of loads in flight: a
 // SIMD holds one of either, and beside the matrix instructions of one wavefront (16 cycles each) another can issue 2.5
 // others, where one that does both gets 1.5 for nothing.
+// FEED of them bring operands.  What a 32-tile takes alone on its CU is the chain of a feeding wavefront's instructions (70 a step), and
+// eight that have half of it each are faster while two such workgroups are all that a CU gets (three of four feeding ones fit): op 2
+// 828 x 152 x 3768 (130 tiles) 38 -> 29 us, by tiles a CU (op 0 / 1 / 2) one 0.79 / 0.81 / 0.78 times, two 0.91 / 0.94 / 0.90, three 1.05 /
+// 1.06 / 1.02.
+constexpr int kFeed = 4, kFeedFew = 8;
+template <int TN, int FEED> constexpr int kTileThreads = TN == 16 ? kThreads : 64 * (4 + FEED);
 // wg of n_wgs: the workgroup's number among those of the product
-template <int OP, int EPI, int TM, int TN, int ACC>
+template <int OP, int EPI, int TM, int TN, int ACC, int FEED>
 __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
   constexpr bool AS = OP == 2, BS = OP != 0;
   // SwiGLU in 32-tiles: a wavefront holds 16 gate columns and the 16 up columns, so the tile of B has 64 rows
@@ -473,16 +479,17 @@ __device__ __forceinline__ void gemm_tile(const Args& g, int wg, int n_wgs) {
       else a.template put<false>(buf(s), v);
     };
     auto put_b = [&](const auto& b, int s, float (*v)[4]) { b.template put<false>(buf(s) + Planes<TM>::kBytes, v); };
-    // Tiles of the same size: two wavefronts for each operand (wider loads); else all four for both.
+    // Tiles of the same size: half of the wavefronts for each operand (wider loads); else all for both.
+    constexpr int NW = FEED / 2;
     if constexpr (TM == TB) {
-      if (wave < 6) {
-        Share<AS, TM, 2, ACC> a;
+      if (wave < 4 + NW) {
+        Share<AS, TM, NW, ACC> a;
         a.init(g.A, lda, m0, g.M, K, wave - 4, lane, a_row);
         feed<a.Q>(steps, [&](int s, float (*v)[4]) { a.load(v, s * BK, K, lda); }, [&](int s, float (*v)[4]) { a.finish(v, s * BK, K, lda); },
                   [&](int s, float (*v)[4]) { put_a(a, s, v); });
       } else {
-        Share<BS, TB, 2, ACC> b;
-        b.init(g.B, ldb, b0, g.N, K, wave - 6, lane, b_row);
+        Share<BS, TB, NW, ACC> b;
+        b.init(g.B, ldb, b0, g.N, K, wave - 4 - NW, lane, b_row);
         feed<b.Q>(steps, [&](int s, float (*v)[4]) { b.load(v, s * BK, K, ldb); }, [&](int s, float (*v)[4]) { b.finish(v, s * BK, K, ldb); },
                   [&](int s, float (*v)[4]) { put_b(b, s, v); });
       }
@@ -745,20 +752,23 @@ __device__ __forceinline__ void gemm_few(const Args& g, int wg, int n_wgs) {
 
 // Wavefronts a SIMD: LDS holds one workgroup with tiles of 128, two with 128 x 64 (128 registers; with more, and one workgroup, op 2
 // 2048 x 3072 x 1024 takes 97 us for 80).
-template <int OP, int EPI, int TM, int TN, int ACC>
-__global__ __launch_bounds__(kThreads, TM * TN > 128 * 64 ? 2 : 4) void k_gemm_f32(Args g) { gemm_tile<OP, EPI, TM, TN, ACC>(g, blockIdx.x, gridDim.x); }
+constexpr int waves_of(int tm, int tn, int feed) { return tm * tn > 128 * 64 || tn == 16 ? 2 : feed == kFeedFew ? 6 : 4; }
+template <int OP, int EPI, int TM, int TN, int ACC, int FEED = kFeed>
+__global__ __launch_bounds__((kTileThreads<TN, FEED>), waves_of(TM, TN, FEED)) void k_gemm_f32(Args g) {
+  gemm_tile<OP, EPI, TM, TN, ACC, FEED>(g, blockIdx.x, gridDim.x);
+}
 template <int OP, int EPI, int ACC>
 __global__ __launch_bounds__(kThreads, 2) void k_gemm_f32_few(Args g) { gemm_few<OP, EPI, ACC>(g, blockIdx.x, gridDim.x); }
 
 // the weight gradients of a layer in one launch, all in tiles of one size
-template <int TM, int TN, int ACC>
-__global__ __launch_bounds__(kThreads, TM * TN > 128 * 64 || TN == 16 ? 2 : 4) void k_gemm_f32_grads(GradGroup l) {
+template <int TM, int TN, int ACC, int FEED = kFeed>
+__global__ __launch_bounds__((kTileThreads<TN, FEED>), waves_of(TM, TN, FEED)) void k_gemm_f32_grads(GradGroup l) {
   int i = 0;
   while (i + 1 < kGrads && (int)blockIdx.x >= l.first[i + 1]) ++i;
   const int wg = (int)blockIdx.x - l.first[i], n = l.first[i + 1] - l.first[i];
   const Args g{(const float*)l.A[i], (const float*)l.B[i], nullptr, l.C[i], nullptr, l.M[i], l.N[i], l.K, l.tm[i], l.tn[i], RopeArgs{nullptr, 1, 2, 0}};
   if constexpr (TN == 16) gemm_few<2, kEpiPlain, ACC>(g, wg, n);
-  else gemm_tile<2, kEpiPlain, TM, TN, ACC>(g, wg, n);
+  else gemm_tile<2, kEpiPlain, TM, TN, ACC, FEED>(g, wg, n);
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -767,28 +777,31 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // Tile and its grid for a product: the least of (steps + ends) x time of a step of the CU with the most tiles.  Times are fits
 // (us, op 0 to 2 within 5 %): a 128-tile 1.25; 128 x 64 0.78 alone on its CU, 0.72 each of several; a 64-tile 0.58 alone, 0.88
-// two, 0.44 each of more; a 32-tile 0.29, 0.36 two, 0.52 three, 0.18 each of more (SwiGLU, with its 64 rows of B, 1.6 x).
-// What starts and ends a tile counts as 4.8, 4, 4 and 6 steps; in op 2, whose large tiles have many atomics to themselves, as 6, 5, 4 and 6;
-// with the SwiGLU gradient, whose loads and arithmetic a large tile has alone on its CU, as 12, 8, 5 and 6.  A 16-tile of
-// k_gemm_f32_few: 0.17 a run (op 2, whose loads take 64 bytes of a row, 0.23) and 0.45 (SwiGLU 1.85 x), 1 once.  With one set for all,
-// op 2 828 x 152 x 3768 took 47 us in tiles of 16 (39 in tiles of 32), the gradient 3728 x 2352 over k = 48 41 us in 128 x 64 (33 in 64);
-// over 1500 sizes 119 choices differ, 0.75 to 1.06 times the time, the median 0.90.
+// two, 0.44 each of more; a 32-tile 0.23 (SwiGLU, with four feeding wavefronts and 64 rows of B, 0.46), 0.36 two, 0.52 three, 0.18 each of
+// more (SwiGLU 1.6 x).  What starts and ends a tile counts as 4.8, 4, 4 and 6 steps (10 of 0.23); in op 2, whose large tiles have many atomics to
+// themselves, as 6, 5, 4 and 6; with the SwiGLU gradient, whose loads and arithmetic a large tile has alone on its CU, as 12, 8, 5 and
+// 6.  A 16-tile of k_gemm_f32_few: 0.17 a run (op 2, whose loads take 64 bytes of a row, 0.23) and 0.45 (SwiGLU 1.85 x), 1 once.  With
+// one set of ends and runs for all, op 2 828 x 152 x 3768 went to tiles of 16 (47 us, 39 in tiles of 32 with four feeding wavefronts),
+// the gradient 3728 x 2352 over k = 48 to 128 x 64 (41 us, 33 in 64); over 1500 sizes 119 choices differed, 0.75 to 1.06 times the
+// time, the median 0.90.
 // A product is not cut along k over workgroups: their sums would be added in the order in which they end, and neither would a
 // microbatch's rows have the same bits alone and in a group, nor two passes of the mode that gradients are checked in agree.
-// us by tile, 128 / 128 x 64 / 64 / 32: op 0 1024 x 1024 x 1024 39 / 29 / 22 / 28, 2048 x 1024 x 5632 188 / 143 / 157 / 236, 3072 x 1024 x 1024 42 / 46 / 46 / 66, 4096 x 768 x 288 17 / 18 / 17 / 23,
-// 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.  32 / 16: op 0
-// 128 x 288 x 1536 16.6 / below 7.5 (the launch), 512 x 288 x 1536 16.9 / 14.2, 1024 x 288 x 1536 21 / 22, 64 x 1024 x 5632 53 / 21,
-// 512 x 768 x 288 7.7 / 8.9.
+// us by tile, 128 / 128 x 64 / 64 / 32 (four feeding wavefronts): op 0 1024 x 1024 x 1024 39 / 29 / 22 / 28, 2048 x 1024 x 5632 188 / 143 / 157 /
+// 236, 3072 x 1024 x 1024 42 / 46 / 46 / 66, 4096 x 768 x 288 17 / 18 / 17 / 23, 1024 x 288 x 1536 55 / 39 / 27 / 20, op 2 5632 x 1024 x 2048
+// 164 / 147 / 166 / 253, 288 x 768 x 4096 139 / 105 / 64 / 38.  32 / 16: op 0 128 x 288 x 1536 16.6 / below 7.5 (the launch), 512 x 288 x 1536
+// 16.9 / 14.2, 1024 x 288 x 1536 21 / 22, 64 x 1024 x 5632 53 / 21, 512 x 768 x 288 7.7 / 8.9.
 constexpr int kEdges[5][2] = {{128, 128}, {128, 64}, {64, 64}, {32, 32}, {16, 16}};
 static double f32_us(int op, int t, int64_t tiles, int64_t K, int epi) {
   const int64_t cus = cu_count(), steps = (K + BK - 1) / BK, load = (tiles + cus - 1) / cus;
   const double c = (double)load;
   if (t == 4) return 1.0 + c * ((op == 2 ? 0.23 : 0.17) * (double)((steps + kRun - 1) / kRun) + 0.45) * (epi == kEpiSwiglu ? 1.85 : 1.0);
   const double step = t == 0 ? 1.25 * c : t == 1 ? (load == 1 ? 0.78 : 0.72 * c) : t == 2 ? (load == 1 ? 0.58 : 0.44 * c)
-                      : (load == 1 ? 0.29 : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
+                      : (load == 1 ? (epi == kEpiSwiglu ? 0.29 : 0.23) : load == 2 ? 0.36 : load == 3 ? 0.52 : 0.18 * c) * (epi == kEpiSwiglu ? 1.6 : 1.0);
   constexpr double kEnds[3][4] = {{4.8, 4, 4, 6}, {6, 5, 4, 6}, {12, 8, 5, 6}};
+  if (t == 3 && load == 1 && epi != kEpiSwiglu) return step * ((double)steps + 10.0);
   return step * ((double)steps + kEnds[epi == kEpiSwigluBwd ? 2 : op == 2 ? 1 : 0][t]);
 }
+static bool feed_few(int64_t tiles, int epi) { return tiles <= 2 * (int64_t)cu_count() && epi != kEpiSwiglu; }   // see gemm_tile
 struct F32Shape { int tile_m, tile_n, tm, tn; };
 static F32Shape choose_f32(int op, int64_t M, int64_t N, int64_t K, int epi, bool far) {   // far: tiles of 64 only
   const int64_t out = epi == kEpiSwiglu ? N / 2 : N;   // width of one stored run of columns
@@ -831,12 +844,15 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   g.tiles_m = c.tm;
   g.tiles_n = c.tn;
   const dim3 grid((unsigned)(c.tm * c.tn));
+#define SP_GO_32(OP, EPI, ACC, FEED) \
+  hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 32, 32, ACC, FEED>), grid, dim3(kTileThreads<32, FEED>), 0, s, g)
 #define SP_GO(OP, EPI, ACC)                                                                                             \
   do {                                                                                                                  \
     if (c.tile_n == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 128, ACC>), grid, dim3(kThreads), 0, s, g);           \
     else if (c.tile_m == 128) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 128, 64, ACC>), grid, dim3(kThreads), 0, s, g);       \
     else if (c.tile_n == 64) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 64, 64, ACC>), grid, dim3(kThreads), 0, s, g);         \
-    else if (c.tile_n == 32) hipLaunchKernelGGL((k_gemm_f32<OP, EPI, 32, 32, ACC>), grid, dim3(kThreads), 0, s, g);         \
+    else if (c.tile_n == 32 && feed_few(c.tm * c.tn, EPI)) SP_GO_32(OP, EPI, ACC, (EPI == kEpiSwiglu ? kFeed : kFeedFew));  \
+    else if (c.tile_n == 32) SP_GO_32(OP, EPI, ACC, kFeed);                                                                 \
     else hipLaunchKernelGGL((k_gemm_f32_few<OP, EPI, ACC>), grid, dim3(kThreads), 0, s, g);                                 \
   } while (0)
 #define SP_GO_V(OP, EPI)                                                                                                \
@@ -853,6 +869,7 @@ void gemm_f32(hipStream_t s, int op, int64_t M, int64_t N, int64_t K, const void
   else SP_GO_V(2, kEpiPlain);
 #undef SP_GO_V
 #undef SP_GO
+#undef SP_GO_32
 }
 
 // One tile for all of them; entries as in gemm_f32, bit for bit.
@@ -880,16 +897,17 @@ void gemm_f32_grads(hipStream_t s, int64_t K, const GradItem (&items)[kGrads]) {
   }
   g.K = (int)K;
   const dim3 grid(g.first[kGrads]);
-#define SP_GO(TM, TN)                                                                                       \
-  do {                                                                                                      \
-    if (aligned) hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, kAligned>), grid, dim3(kThreads), 0, s, g);   \
-    else hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, kUnaligned>), grid, dim3(kThreads), 0, s, g);         \
+#define SP_GO(TM, TN, FEED)                                                                                                                      \
+  do {                                                                                                                                           \
+    if (aligned) hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, kAligned, FEED>), grid, dim3(kTileThreads<TN, FEED>), 0, s, g);                    \
+    else hipLaunchKernelGGL((k_gemm_f32_grads<TM, TN, kUnaligned, FEED>), grid, dim3(kTileThreads<TN, FEED>), 0, s, g);                          \
   } while (0)
-  if (tile == 0) SP_GO(128, 128);
-  else if (tile == 1) SP_GO(128, 64);
-  else if (tile == 2) SP_GO(64, 64);
-  else if (tile == 3) SP_GO(32, 32);
-  else SP_GO(16, 16);
+  if (tile == 0) SP_GO(128, 128, kFeed);
+  else if (tile == 1) SP_GO(128, 64, kFeed);
+  else if (tile == 2) SP_GO(64, 64, kFeed);
+  else if (tile == 3 && feed_few(g.first[kGrads], kEpiPlain)) SP_GO(32, 32, kFeedFew);
+  else if (tile == 3) SP_GO(32, 32, kFeed);
+  else SP_GO(16, 16, kFeed);
 #undef SP_GO
 }
 

@@ -198,4 +198,9 @@ def test_the_product_tests_reach_every_tile():
     assert {(op, t, odd) for op in (0, 1, 2) for t in edges for odd in (False, True)} <= f32, f32
     ffn = {(op, float_tile(op, R, n * h, d, e), h % 4 + d % 4 > 0) for R, h, d in ops.FFN_SHAPES for op, n, e in ((0, 2, 2), (1, 1, 3))}
     assert {(op, t, odd) for op in (0, 1) for t in edges for odd in (False, True)} <= ffn, ffn
+    few = lambda op, M, N, K, epi=0: float_tile(op, M, N, K, epi) == (32, 32) and sp.gemm_shape(sp.SP_F32, op, M, N, K, epi)[1] <= 512
+    many = lambda op, M, N, K, epi=0: float_tile(op, M, N, K, epi) == (32, 32) and not few(op, M, N, K, epi)
+    for fits in (few, many):   # 32-tiles by how many share a compute unit
+        assert {(op, odd) for op in (0, 1, 2) for odd in (False, True)} <= {(op, any(x % 4 for x in c)) for c in flt.PRODUCTS for op in (0, 1, 2) if fits(op, *c)}
+        assert {False, True} <= {h % 4 + d % 4 > 0 for R, h, d in ops.FFN_SHAPES if fits(1, R, h, d, 3)}
     assert any(sp.gemm_shape(sp.SP_BF16, op, 65, 50, 36)[0] == 0 for op in (0, 1))
