@@ -442,7 +442,7 @@ __device__ __forceinline__ void feed(int steps, Fetch fetch, Finish finish, Put 
 // others, where one that does both gets 1.5 for nothing.
 // FEED of them bring operands.  What a 32-tile takes alone on its CU is the chain of a feeding wavefront's instructions (70 a step), and
 // eight that have half of it each are faster while two such workgroups are all that a CU gets (three of four feeding ones fit): op 2
-// 828 x 152 x 3768 (130 tiles) 38 -> 29 us, by tiles a CU (op 0 / 1 / 2) one 0.79 / 0.81 / 0.78 times, two 0.91 / 0.94 / 0.90, three 1.05 /
+// 828 x 152 x 3768 (130 tiles) 39 -> 31 us, 288 x 768 x 4096 (216) 42 -> 32, by tiles a CU (op 0 / 1 / 2) one 0.79 / 0.81 / 0.78 times, two 0.91 / 0.94 / 0.90, three 1.05 /
 // 1.06 / 1.02.
 constexpr int kFeed = 4, kFeedFew = 8;
 template <int TN, int FEED> constexpr int kTileThreads = TN == 16 ? kThreads : 64 * (4 + FEED);
