@@ -436,7 +436,7 @@ __device__ __forceinline__ void feed(int steps, Fetch fetch, Finish finish, Put 
       }
 }
 
-// Tiles of TM x TN, eight wavefronts, a barrier per step.  The first four (a share of TM / 2 x TN / 2 each) only read fragments
+// Tiles of TM x TN, eight wavefronts (or twelve), a barrier per step.  The first four (a share of TM / 2 x TN / 2 each) only read fragments
 // and multiply, the others only bring the operands of the next step to LDS, split on the way, U steps of loads in flight: a
 // SIMD holds one of either, and beside the matrix instructions of one wavefront (16 cycles each) another can issue 2.5
 // others, where one that does both gets 1.5 for nothing.

@@ -19,10 +19,12 @@ class Item(C.Structure):   # GradItem
 
 
 # width, hidden, width of q|k|v, rows; edges of the tiles that the launch takes.  float: widths with and without remainders (unaligned
-# rows), a step and a part of one, whole and half runs of 64 k.  bf16: one run of the reduction a tile and several.
+# rows), a step and a part of one, whole and half runs of 64 k; 32-tiles at more than two and at most two a compute
+# unit.  bf16: one run of the reduction a tile and several.
 @pytest.mark.parametrize("dtype,d,h,nq,rows,tile", [
     ("f32", 32, 64, 80, 33, (16, 16)), ("f32", 64, 128, 160, 320, (16, 16)), ("f32", 31, 67, 81, 99, (16, 16)),
-    ("f32", 136, 272, 392, 100, (32, 32)), ("f32", 137, 271, 393, 65, (32, 32)), ("f32", 200, 600, 584, 200, (64, 64)),
+    ("f32", 228, 456, 456, 420, (32, 32)), ("f32", 227, 457, 455, 421, (32, 32)), ("f32", 136, 272, 392, 100, (32, 32)),
+    ("f32", 137, 271, 393, 65, (32, 32)), ("f32", 200, 600, 584, 200, (64, 64)),
     ("f32", 201, 601, 583, 97, (64, 64)), ("f32", 264, 792, 776, 100, (128, 64)), ("f32", 263, 793, 775, 97, (128, 64)),
     ("f32", 544, 1088, 1616, 132, (128, 128)), ("f32", 543, 1087, 1615, 65, (128, 128)),
     ("bf16", 32, 64, 80, 33, (64,)), ("bf16", 64, 128, 160, 1000, (64,)), ("bf16", 392, 1176, 1160, 200, (128,)),
